@@ -446,136 +446,257 @@ __global__ void bin_big_kernel(const ViewConst *__restrict__ views, const TriSet
 
 // ----------------------------------------------------------------------------- raster
 
-// A triangle as the tile raster tests it: each edge function in plane form,
-// E_e(px, py) = a px + b py + c with a = -dy, b = dx, c = dy xa - dx ya for
-// the directed edge a -> b opposite vertex e.  With fixed-point coordinates
-// below 2^23 and differences below 2^24 every term and every partial sum is
-// an integer below 2^49, so float64 holds the coefficients and evaluates
-// E_e exactly with two fused multiply-adds: the same value, and the same
-// inside / top-left / depth results, as the 64-bit integer form.  a and b
-// (below 2^24) are kept as int32 to keep the LDS record small.
+// A triangle as the raster tests it: the edge functions of edges 1 and 2 in
+// plane form, E_e(px, py) = a px + b py + c with a = -dy, b = dx,
+// c = dy xa - dx ya for the directed edge a -> b opposite vertex e, and
+// E_0 = A - E_1 - E_2 (the three sub-triangles' doubled areas sum to A at
+// every point).  With fixed-point coordinates below 2^23 and differences
+// below 2^24 every term and every partial sum is an integer below 2^50, so
+// float64 holds the coefficients and evaluates the functions exactly: the
+// same value, and the same inside / top-left / depth results, as the 64-bit
+// integer form.  The constants hold E_e - 1 for edges that are neither top
+// nor left: E_e is an integer, so "E_e > 0, or E_e = 0 on a top or left edge"
+// is "not negative" for the stored form, and one sign test decides all three.
+// The constants are relative to an origin in whole pixels (a tile's first).
 struct RasterTri {
-    double c[3];
-    int a[3], b[3];
+    double c1, c2, A;       // E_1, E_2 at the origin and the doubled area, less their edges' 1 or 0
+    int a1, b1, a2, b2;
     float z0, dz1, dz2;     // z0, z1 - z0, z2 - z0
-    float rA;           // correctly rounded float32 1 / A
-    unsigned short bx0, by0, bx1, by1;
+    float rA;               // correctly rounded float32 1 / A
     unsigned tri;
-    int top_left;       // bit e: edge e is a top or left edge
+    unsigned box;           // x0 | x1 << 5 | y0 << 10 | y1 << 15 (samples of its tile) | tile << 20 | edge bits << 24
 };
+static_assert(sizeof(RasterTri) == 64, "RasterTri is four 16-byte LDS words");
+constexpr unsigned kTL1 = 1u << 24, kTL2 = 1u << 25;       // edge 1 / 2 is a top or left edge
 
 __device__ __forceinline__ bool top_left(int xa, int ya, int xb, int yb) {
     const int dx = xb - xa, dy = yb - ya;
     return dy < 0 || (dy == 0 && dx > 0);
 }
 
-__device__ __forceinline__ RasterTri load_raster_tri(const TriSetup &s, unsigned local) {
+// The record of triangle s relative to pixel (ox, oy); box holds the edge bits only.
+__device__ __forceinline__ RasterTri load_raster_tri(const TriSetup &s, unsigned local, int ox, int oy) {
     RasterTri r;
-    r.top_left = 0;
-#pragma unroll
-    for (int e = 0; e < 3; ++e) {
-        const int ia = (e + 1) % 3, ib = (e + 2) % 3;
-        const int xa = s.X[ia], ya = s.Y[ia], dx = s.X[ib] - xa, dy = s.Y[ib] - ya;
-        r.a[e] = -dy;
-        r.b[e] = dx;
-        r.c[e] = (double)((long long)dy * xa - (long long)dx * ya);
-        r.top_left |= top_left(xa, ya, s.X[ib], s.Y[ib]) ? 1 << e : 0;
-    }
+    const double px = (double)(ox * kSub), py = (double)(oy * kSub);
+    const bool tl0 = top_left(s.X[1], s.Y[1], s.X[2], s.Y[2]), tl1 = top_left(s.X[2], s.Y[2], s.X[0], s.Y[0]),
+               tl2 = top_left(s.X[0], s.Y[0], s.X[1], s.Y[1]);
+    r.a1 = s.Y[2] - s.Y[0];
+    r.b1 = s.X[0] - s.X[2];
+    r.a2 = s.Y[0] - s.Y[1];
+    r.b2 = s.X[1] - s.X[0];
+    const double t0 = tl0 ? 0.0 : 1.0, t1 = tl1 ? 0.0 : 1.0, t2 = tl2 ? 0.0 : 1.0;
+    // E_1 = a1 (px - X2) + b1 (py - Y2), E_2 = a2 (px - X0) + b2 (py - Y0)
+    r.c1 = fma((double)r.a1, px - (double)s.X[2], fma((double)r.b1, py - (double)s.Y[2], -t1));
+    r.c2 = fma((double)r.a2, px - (double)s.X[0], fma((double)r.b2, py - (double)s.Y[0], -t2));
+    r.A = (double)s.A - ((t0 + t1) + t2);
     r.z0 = s.z[0];
     r.dz1 = s.z[1] - s.z[0];
     r.dz2 = s.z[2] - s.z[0];
     r.rA = 1.0f / (float)(double)s.A;
-    r.bx0 = s.bx0; r.by0 = s.by0; r.bx1 = s.bx1; r.by1 = s.by1;
     r.tri = local;
+    r.box = (tl1 ? kTL1 : 0u) | (tl2 ? kTL2 : 0u);
     return r;
 }
 
-// Key of triangle r at pixel (i, j), or kBgKey when not covered.
-__device__ __forceinline__ unsigned long long sample_key(const RasterTri &r, int i, int j) {
-    if (i < r.bx0 || i > r.bx1 || j < r.by0 || j > r.by1) return kBgKey;
-    const double px = (double)(i * kSub + kSub / 2), py = (double)(j * kSub + kSub / 2);
-    const double e0 = fma((double)r.a[0], px, fma((double)r.b[0], py, r.c[0]));
-    const double e1 = fma((double)r.a[1], px, fma((double)r.b[1], py, r.c[1]));
-    const double e2 = fma((double)r.a[2], px, fma((double)r.b[2], py, r.c[2]));
-    const bool in0 = e0 > 0.0 || (e0 == 0.0 && (r.top_left & 1));
-    const bool in1 = e1 > 0.0 || (e1 == 0.0 && (r.top_left & 2));
-    const bool in2 = e2 > 0.0 || (e2 == 0.0 && (r.top_left & 4));
-    if (!(in0 && in1 && in2)) return kBgKey;
+// Key of triangle r at a sample with edge functions (e1, e2) in the stored
+// form, or kBgKey when not covered.
+__device__ __forceinline__ unsigned long long edge_key(const RasterTri &r, double e1, double e2) {
+    const double e0 = (r.A - e1) - e2;
+    // exact sums of integers are never -0, so the sign bits are the test
+    if ((__double2hiint(e0) | __double2hiint(e1) | __double2hiint(e2)) < 0) return kBgKey;
     // b_e = f32(E_e) * (1 / A): one reciprocal per triangle, one product per sample
-    const float b1 = (float)e1 * r.rA;
-    const float b2 = (float)e2 * r.rA;
+    const float b1 = (float)(e1 + ((r.box & kTL1) ? 0.0 : 1.0)) * r.rA;
+    const float b2 = (float)(e2 + ((r.box & kTL2) ? 0.0 : 1.0)) * r.rA;
     const float z = (r.z0 + b1 * r.dz1) + b2 * r.dz2;
     if (!(z >= 0.0f && z <= 1.0f)) return kBgKey;
     const unsigned bits = __float_as_uint(z) & 0x7FFFFFFFu;
     return ((unsigned long long)bits << 32) | r.tri;
 }
 
+// ... at pixel (x, y) from the record's origin.
+__device__ __forceinline__ unsigned long long pixel_key(const RasterTri &r, double px, double py) {
+    return edge_key(r, fma((double)r.a1, px, fma((double)r.b1, py, r.c1)),
+                    fma((double)r.a2, px, fma((double)r.b2, py, r.c2)));
+}
+__device__ __forceinline__ double sample_pos(int i) { return (double)(i * kSub + kSub / 2); }
+
+// False when the triangle misses every sample of the box [x0, x1] x [y0, y1]:
+// some edge function is negative at the box's best corner.
+__device__ __forceinline__ bool touches(const RasterTri &r, int x0, int x1, int y0, int y1) {
+    const double pl = sample_pos(x0), pr = sample_pos(x1), pt = sample_pos(y0), pb = sample_pos(y1);
+    const int a0 = -(r.a1 + r.a2), b0 = -(r.b1 + r.b2);
+    const double c0 = (r.A - r.c1) - r.c2;
+    const double m0 = fma((double)a0, a0 > 0 ? pr : pl, fma((double)b0, b0 > 0 ? pb : pt, c0));
+    const double m1 = fma((double)r.a1, r.a1 > 0 ? pr : pl, fma((double)r.b1, r.b1 > 0 ? pb : pt, r.c1));
+    const double m2 = fma((double)r.a2, r.a2 > 0 ? pr : pl, fma((double)r.b2, r.b2 > 0 ? pb : pt, r.c2));
+    return (__double2hiint(m0) | __double2hiint(m1) | __double2hiint(m2)) >= 0;
+}
+
+// One workgroup rasterizes a group of kGroup consecutive tiles of the global
+// tile list, whose bins are one contiguous range of entries.  The range
+// streams through the workgroup's lanes, an entry a lane: the lane reads the
+// triangle's record and clips its bounding box to its tile.  A triangle with
+// few samples there is tested by its lane alone, sample by sample, stepping
+// the edge functions; the others go to a list in LDS that the four waves
+// share, 64 samples of a triangle at a time.  Both take the minimum of the
+// samples' keys in LDS, so neither the order of the entries nor the split
+// matters.  What bounds it: the records' loads and the tests.  A mesh of
+// pixel-sized triangles keeps every lane on a triangle of its own (the
+// wave-wide test alone uses 64 lanes on the four samples of a 2 x 2 box), a
+// crowded tile is shared by four waves, and a group of nearly empty tiles
+// waits for one chain of loads instead of one per tile.  Against one wave per
+// tile testing its bin an entry at a time: 64 scenes at 512^2 388 -> 266 us,
+// 8 x 1024^2 maps and 16 views of a 99k-triangle sphere 432 -> 136, four
+// scenes at 200^2 (hundreds of entries a tile) 133 -> 23.  Groups of 4 or 16
+// tiles: 338 and 313 us on the 64 scenes.
 constexpr int kRasterThreads = 256;
 
-// One workgroup per tile; each thread owns T*T/256 (or one) pixels and keeps
-// the minimum key in registers while the tile's bin streams through LDS.
+template <int T>
+struct RasterShape {
+    static constexpr int kGroup = T == 8 ? 8 : T == 16 ? 2 : 1;     // tiles per workgroup
+    static constexpr int kPix = kGroup * T * T;
+};
+
 template <int T>
 __global__ __launch_bounds__(kRasterThreads) void raster_kernel(
-    const ViewConst *__restrict__ views, const int *__restrict__ tile_view, const TriSetup *__restrict__ setup,
-    const unsigned *__restrict__ tile_start, const unsigned *__restrict__ bins,
+    const ViewConst *__restrict__ views, const int *__restrict__ tile_view, int ntiles,
+    const TriSetup *__restrict__ setup, const unsigned *__restrict__ tile_start, const unsigned *__restrict__ bins,
     unsigned long long *__restrict__ keys) {
-    constexpr int NPIX = T * T;
-    constexpr int NT = NPIX < kRasterThreads ? NPIX : kRasterThreads;
-    constexpr int PPT = NPIX / NT;
-    __shared__ RasterTri tris[NT];
-    const int gt = xcd_remap((int)blockIdx.x, (int)gridDim.x);
-    const int view = tile_view[gt];
-    const ViewConst &v = views[view];
-    const int lt = gt - v.tile_off;
-    const int tx = lt % v.tiles_x, ty = lt / v.tiles_x;
-    const int tid = threadIdx.x;
-    if (tid >= NT) return;
-    int pi[PPT], pj[PPT];
-    unsigned long long best[PPT];
+    using RS = RasterShape<T>;
+    constexpr int G = RS::kGroup;
+    struct TileInfo {
+        long long pix;           // key index of the tile's first sample
+        int x0, y0, W, H, setup_off;
+    };
+    __shared__ unsigned long long best[RS::kPix];
+    __shared__ TileInfo info[G];
+    __shared__ __align__(16) RasterTri wide[kRasterThreads];
+    __shared__ unsigned nwide;
+    const int g0 = xcd_remap((int)blockIdx.x, (int)gridDim.x) * G;
+    const int ng = min(G, ntiles - g0);
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    unsigned ts[G + 1];
 #pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        const int l = tid + k * NT;
-        pi[k] = tx * T + (l % T);
-        pj[k] = ty * T + (l / T);
-        best[k] = kBgKey;
+    for (int k = 0; k <= G; ++k) ts[k] = tile_start[min(g0 + k, ntiles)];
+    // the first entry's record is requested before anything waits
+    unsigned e = ts[0] + (unsigned)tid;
+    unsigned si = 0;
+    TriSetup st;
+    if (e < ts[G]) {
+        si = bins[e];
+        st = setup[si];
     }
-    const unsigned b0 = tile_start[gt], b1 = tile_start[gt + 1];
-    for (unsigned c = b0; c < b1; c += NT) {
-        const unsigned n = min((unsigned)NT, b1 - c);
-        __syncthreads();
-        if ((unsigned)tid < n) {
-            const unsigned si = bins[c + tid];
-            tris[tid] = load_raster_tri(setup[si], si - (unsigned)v.setup_off);
-        }
-        __syncthreads();
-        // four entries per step: their independent edge-function / depth
-        // chains interleave, which hides latency at a given occupancy
-        unsigned q = 0;
-        for (; q + 4 <= n; q += 4) {
-            const RasterTri &r0 = tris[q], &r1 = tris[q + 1], &r2 = tris[q + 2], &r3 = tris[q + 3];
-#pragma unroll
-            for (int k = 0; k < PPT; ++k) {
-                const unsigned long long k0 = sample_key(r0, pi[k], pj[k]);
-                const unsigned long long k1 = sample_key(r1, pi[k], pj[k]);
-                const unsigned long long k2 = sample_key(r2, pi[k], pj[k]);
-                const unsigned long long k3 = sample_key(r3, pi[k], pj[k]);
-                const unsigned long long a01 = k0 < k1 ? k0 : k1, a23 = k2 < k3 ? k2 : k3;
-                const unsigned long long a = a01 < a23 ? a01 : a23;
-                best[k] = a < best[k] ? a : best[k];
-            }
-        }
-        for (; q < n; ++q) {
-            const RasterTri &r = tris[q];
-#pragma unroll
-            for (int k = 0; k < PPT; ++k) {
-                const unsigned long long key = sample_key(r, pi[k], pj[k]);
-                best[k] = key < best[k] ? key : best[k];
-            }
-        }
+    if (tid < ng) {
+        const ViewConst &v = views[tile_view[g0 + tid]];
+        const int lt = g0 + tid - v.tile_off;
+        TileInfo ti;
+        ti.x0 = (lt % v.tiles_x) * T;
+        ti.y0 = (lt / v.tiles_x) * T;
+        ti.W = v.W;
+        ti.H = v.H;
+        ti.pix = v.pix_off + (long long)ti.y0 * v.W + ti.x0;
+        ti.setup_off = v.setup_off;
+        info[tid] = ti;
     }
 #pragma unroll
-    for (int k = 0; k < PPT; ++k)
-        if (pi[k] < v.W && pj[k] < v.H) keys[v.pix_off + (long long)pj[k] * v.W + pi[k]] = best[k];
+    for (int q = tid; q < RS::kPix; q += kRasterThreads) best[q] = kBgKey;
+    if (tid == 0) nwide = 0u;
+    __syncthreads();
+    for (unsigned c = ts[0]; c < ts[G]; c += kRasterThreads) {          // uniform
+        RasterTri r;
+        int area = 0, x0 = 0, x1 = 0, y0 = 0, y1 = 0, k = 0;
+        if (e < ts[G]) {
+#pragma unroll
+            for (int q = 1; q < G; ++q) k += e >= ts[q] ? 1 : 0;
+            const int ox = info[k].x0, oy = info[k].y0;
+            r = load_raster_tri(st, si - (unsigned)info[k].setup_off, ox, oy);
+            x0 = max((int)st.bx0 - ox, 0);
+            x1 = min((int)st.bx1 - ox, T - 1);
+            y0 = max((int)st.by0 - oy, 0);
+            y1 = min((int)st.by1 - oy, T - 1);
+            area = touches(r, x0, x1, y0, y1) ? (x1 - x0 + 1) * (y1 - y0 + 1) : 0;
+            r.box |= (unsigned)x0 | (unsigned)x1 << 5 | (unsigned)y0 << 10 | (unsigned)y1 << 15 | (unsigned)k << 20;
+        }
+        // largest box that a lane tests alone: each step up costs the wave
+        // that many more samples and saves one wave-wide test per triangle
+        const int n0 = __popcll(__ballot(area > 0)), n16 = __popcll(__ballot(area > 16)),
+                  n32 = __popcll(__ballot(area > 32)), n64 = __popcll(__ballot(area > 64));
+        const int most = n16 - n64 > 48 ? 64 : n16 - n32 > 16 ? 32 : n0 - n16 > 8 ? 16 : 0;
+        const bool own = area > 0 && area <= most, shared = area > most;
+        const unsigned long long m = __ballot(shared);
+        if (m) {
+            unsigned at = 0;
+            if (lane == 0) at = atomicAdd(&nwide, (unsigned)__popcll(m));
+            at = (unsigned)__builtin_amdgcn_readfirstlane((int)at);
+            if (shared) wide[at + __popcll(m & ((1ull << lane) - 1ull))] = r;
+        }
+        if (own) {
+            unsigned long long *row = best + k * (T * T) + y0 * T;
+            const double px = sample_pos(x0), py = sample_pos(y0);
+            double r1 = fma((double)r.a1, px, fma((double)r.b1, py, r.c1));
+            double r2 = fma((double)r.a2, px, fma((double)r.b2, py, r.c2));
+            const double ax1 = (double)(r.a1 * kSub), ax2 = (double)(r.a2 * kSub);
+            const double by1 = (double)r.b1 * kSub, by2 = (double)r.b2 * kSub;
+            double e1 = r1, e2 = r2;
+            int x = x0;
+            for (int q = 0; q < area; ++q) {
+                const unsigned long long key = edge_key(r, e1, e2);
+                if (key != kBgKey) atomicMin(row + x, key);
+                e1 += ax1;
+                e2 += ax2;
+                if (++x > x1) {
+                    x = x0;
+                    row += T;
+                    r1 += by1;
+                    r2 += by2;
+                    e1 = r1;
+                    e2 = r2;
+                }
+            }
+        }
+        __syncthreads();
+        const int n = (int)nwide;
+        for (int j = tid >> 6; j < n; j += kRasterThreads / 64) {
+            const RasterTri w = wide[j];
+            const int wx0 = w.box & 31, wx1 = (w.box >> 5) & 31, wy0 = (w.box >> 10) & 31, wy1 = (w.box >> 15) & 31;
+            unsigned long long *tb = best + ((w.box >> 20) & 15) * (T * T);
+            // the tile's 8 x 8 blocks that the bounding box touches
+            if constexpr (T == 8) {
+                const int lx = lane & 7, ly = lane >> 3;
+                if (lx >= wx0 && lx <= wx1 && ly >= wy0 && ly <= wy1) {
+                    const unsigned long long key = pixel_key(w, sample_pos(lx), sample_pos(ly));
+                    if (key != kBgKey) atomicMin(&tb[lane], key);
+                }
+                continue;
+            }
+            for (int by = wy0 >> 3; by <= wy1 >> 3; ++by)
+                for (int bx = wx0 >> 3; bx <= wx1 >> 3; ++bx) {
+                    const int lx = bx * 8 + (lane & 7), ly = by * 8 + (lane >> 3);
+                    if (lx < wx0 || lx > wx1 || ly < wy0 || ly > wy1) continue;
+                    const unsigned long long key = pixel_key(w, sample_pos(lx), sample_pos(ly));
+                    if (key != kBgKey) atomicMin(&tb[ly * T + lx], key);
+                }
+        }
+        __syncthreads();
+        if (c + kRasterThreads < ts[G]) {
+            if (tid == 0) nwide = 0u;
+            e += kRasterThreads;
+            if (e < ts[G]) {
+                si = bins[e];
+                st = setup[si];
+            }
+            __syncthreads();
+        }
+    }
+    // store the group as rows of its tiles side by side
+#pragma unroll
+    for (int q = tid; q < RS::kPix; q += kRasterThreads) {
+        const int row = q / (G * T), col = q % (G * T), k = col / T, lx = col % T;
+        if (k >= ng) continue;
+        const TileInfo &ti = info[k];
+        if (ti.x0 + lx < ti.W && ti.y0 + row < ti.H)
+            keys[ti.pix + (long long)row * ti.W + lx] = best[k * (T * T) + row * T + lx];
+    }
 }
 
 // Triangles that did not fit the bins: one workgroup per listed triangle at
@@ -590,13 +711,13 @@ __global__ void overflow_raster_kernel(const ViewConst *__restrict__ views, cons
         const unsigned si = list[o];
         const TriSetup &s = setup[si];
         const ViewConst &v = views[s.pad2[0]];
-        const RasterTri r = load_raster_tri(s, si - (unsigned)v.setup_off);
-        const int w = r.bx1 - r.bx0 + 1, h = r.by1 - r.by0 + 1;
+        const RasterTri r = load_raster_tri(s, si - (unsigned)v.setup_off, 0, 0);
+        const int w = s.bx1 - s.bx0 + 1, h = s.by1 - s.by0 + 1;
         if (w <= 0 || h <= 0) continue;
         const long long npix = (long long)w * h;
         for (long long q = threadIdx.x; q < npix; q += blockDim.x) {
-            const int i = r.bx0 + (int)(q % w), j = r.by0 + (int)(q / w);
-            const unsigned long long key = sample_key(r, i, j);
+            const int i = s.bx0 + (int)(q % w), j = s.by0 + (int)(q / w);
+            const unsigned long long key = pixel_key(r, sample_pos(i), sample_pos(j));
             if (key != kBgKey) atomicMin(&keys[v.pix_off + (long long)j * v.W + i], key);
         }
     }
@@ -668,17 +789,15 @@ hipError_t launch_raster(const ViewConst *views, const int *tile_view, int ntile
                          const unsigned *tile_start, const unsigned *bins, const unsigned *overflow_list,
                          const DevCounters *counters_ro, DevCounters *counters, unsigned long long *keys,
                          hipStream_t s) {
+#define DSM_RASTER(TT)                                                                                              \
+    hipLaunchKernelGGL(raster_kernel<TT>, dim3((ntiles + RasterShape<TT>::kGroup - 1) / RasterShape<TT>::kGroup),  \
+                       dim3(kRasterThreads), 0, s, views, tile_view, ntiles, setup, tile_start, bins, keys)
     if (ntiles > 0) {
-        if (tile == 8)
-            hipLaunchKernelGGL(raster_kernel<8>, dim3(ntiles), dim3(64), 0, s, views, tile_view, setup, tile_start,
-                               bins, keys);
-        else if (tile == 16)
-            hipLaunchKernelGGL(raster_kernel<16>, dim3(ntiles), dim3(256), 0, s, views, tile_view, setup, tile_start,
-                               bins, keys);
-        else
-            hipLaunchKernelGGL(raster_kernel<32>, dim3(ntiles), dim3(256), 0, s, views, tile_view, setup, tile_start,
-                               bins, keys);
+        if (tile == 8) DSM_RASTER(8);
+        else if (tile == 16) DSM_RASTER(16);
+        else DSM_RASTER(32);
     }
+#undef DSM_RASTER
     hipLaunchKernelGGL(overflow_raster_kernel, dim3(512), dim3(256), 0, s, views, setup, overflow_list, counters,
                        keys);
     return hipGetLastError();
