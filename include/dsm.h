@@ -343,8 +343,8 @@ typedef enum {
     DSM_STAGE_SETUP = 0,        /* zero fills, light frames, transform, triangle setup, silhouette masks */
     DSM_STAGE_BIN,              /* (triangle, tile) pair scan and tile binning */
     DSM_STAGE_RASTER,           /* tile raster of every light and camera view (a2-a3, a7) */
-    DSM_STAGE_RESOLVE,          /* light-view moment resolve (z, z^2) */
-    DSM_STAGE_LIGHT_AA,         /* light-view edge smoothing */
+    DSM_STAGE_RESOLVE,          /* light-view moment resolve (z, z^2) and edge smoothing, one launch */
+    DSM_STAGE_LIGHT_AA,         /* no work of its own (runs in the resolve's launch) */
     DSM_STAGE_FILTER,           /* moment filter G (Alg. 1) */
     DSM_STAGE_LOOKUP,           /* Chebyshev visibility + Lambert shading (Alg. 2) */
     DSM_STAGE_CAMERA_AA,        /* camera-view edge smoothing */

@@ -43,22 +43,17 @@ __device__ __forceinline__ void clip_f64(const float *M, const float *p, double 
                                      (double)M[4 * r + 3];
 }
 
-// Evaluate the pair (self sample s, neighbour sample n).  Returns false when
-// the pair is not smoothed.  keys: this view's key array base.
+// Evaluate the pair (self sample s, neighbour sample n) whose front triangle
+// is t (self_is_front: the self sample's).  Returns false when the pair is not
+// smoothed.
 template <bool WANT_GRAD>
 __device__ __forceinline__ bool aa_eval(const ViewConst &v, const TriSetup *__restrict__ setup,
                                         const int *__restrict__ faces, const unsigned char *__restrict__ silm,
-                                        const float *__restrict__ verts, unsigned long long ks,
-                                        unsigned long long kn, int is, int js, int in_, int jn, bool horiz,
-                                        bool &self_is_front, AAPair &out) {
-    const unsigned ts = (unsigned)ks, tn = (unsigned)kn;
-    if (ts == tn) return false;
-    self_is_front = ks < kn;
-    const unsigned t = self_is_front ? ts : tn;
+                                        const float *__restrict__ verts, unsigned t, bool self_is_front, int is,
+                                        int js, int in_, int jn, bool horiz, AAPair &out) {
     const int fi = self_is_front ? is : in_, fj = self_is_front ? js : jn;
     const int oi = self_is_front ? in_ : is, oj = self_is_front ? jn : js;
     const unsigned sm = silm[v.setup_off + t];
-    if (sm == 0) return false;                       // no silhouette edge to cross
     const TriSetup &S = setup[v.setup_off + t];
     // the triangle's three vertex indices, loaded with its setup record so
     // that the vertex fetch below is the only load that waits on the edge choice
@@ -169,57 +164,220 @@ __device__ __forceinline__ AANeighbours aa_neighbours(const ViewConst &v, const 
     return n;
 }
 
-// Sample of thread t of workgroup b (256 threads) in a W x H view.  When
-// the view is a whole number of 32 x 8 regions, each workgroup takes one
-// region and each wave one 8 x 8 tile of it, so that a silhouette touches
-// fewer waves than with row segments of 64 samples (a wave with one
-// candidate pair waits for the pair tests' loads on all of its lanes);
-// otherwise samples run in row order.  Either way the workgroups cover the
-// view's W * H samples exactly once.
-__device__ __forceinline__ int aa_sample_index(int b, int t, int W, int H) {
-    if ((W & 31) == 0 && (H & 7) == 0) {
-        const int rx = b % (W >> 5), ry = b / (W >> 5);
-        const int w = t >> 6, l = t & 63;
-        return (ry * 8 + (l >> 3)) * W + rx * 32 + w * 8 + (l & 7);
-    }
-    return b * 256 + t;
-}
+// Smoothing of a region of kAaW x kAaH samples by one wave: a lane owns a
+// column of kAaH samples.  Every pair of neighbours with at least one sample
+// in the region has a slot: the pair of columns c - 1 and c of row r (c = 0..64)
+// at r * 65 + c, the pair of rows r - 1 and r of column c (r = 0..4) at
+// 260 + r * 64 + c; its sample a is the left or upper one, b the other.
+//
+// A pair is a candidate when its triangles differ and the front one has a
+// silhouette edge in this view.  Candidates are rare and cost three dependent
+// loads and some 200 instructions, many in float64.  They are therefore
+// listed and evaluated a pair a lane, each pair once for both of its samples
+// (a pair across a region's border once in each region), and the result goes
+// to the pair's slot, so a sample adds its pairs' terms in the order
+// -x, +x, -y, +y whichever lane evaluated them.  The keys of a column are
+// loaded once (six per four samples; the horizontal neighbours' keys come
+// from the lanes beside), the silhouette bytes once per pair.
+constexpr int kAaW = 64, kAaH = 4;
+constexpr int kAaRow = kAaW + 1, kAaVert = kAaH * kAaRow, kAaSlots = kAaVert + (kAaH + 1) * kAaW;
 
-// Samples listed for the second pass of the smoothing kernels.  The list is
-// cut into segments, each with its own counter, so that the appends of
-// different workgroups do not contend for one address: workgroup b of the
-// first pass (b counted over the whole grid) appends to segment
-// b % kAaSegments, which holds every sample of the workgroups that map to
-// it and so cannot overflow.  The second pass runs one workgroup per
-// segment.
-constexpr int kAaSegments = 4096;
+constexpr unsigned char kAaB = 1, kAaA = 2, kAaCand = 4;    // b receives, a receives, candidate
 
-struct AaList {
-    uint2 *items;
-    unsigned *counts;        // kAaSegments counters, zero before the first pass
-    unsigned nseg, segcap;   // segments in use, items per segment
+struct AARegion {
+    unsigned short item[kAaSlots];     // listed slots
+    unsigned char state[kAaSlots];
+    float w[kAaSlots];                 // blend weights
 };
 
-__host__ __device__ inline AaList aa_list_for(uint2 *items, unsigned *counts, long long blocks) {
-    AaList l;
-    l.items = items;
-    l.counts = counts;
-    l.nseg = (unsigned)(blocks < kAaSegments ? blocks : kAaSegments);
-    l.segcap = l.nseg ? (unsigned)(((blocks + l.nseg - 1) / l.nseg) * 256) : 0u;
-    return l;
+__host__ __device__ __forceinline__ int aa_regions(int W, int H) {
+    return ((W + kAaW - 1) / kAaW) * ((H + kAaH - 1) / kAaH);
 }
 
-// Append the active lanes' items to the segment of this workgroup (one
-// atomic per wave).  lin: the workgroup's index over the whole grid.
-__device__ __forceinline__ void wave_append(bool mine, uint2 item, const AaList &l, long long lin) {
-    const unsigned long long m = __ballot(mine);
-    if (m == 0ull) return;
-    const unsigned seg = (unsigned)(lin % l.nseg);
-    const int lane = (int)(threadIdx.x & 63), leader = __ffsll(m) - 1;
-    unsigned first = 0;
-    if (lane == leader) first = atomicAdd(l.counts + seg, (unsigned)__popcll(m));
-    first = (unsigned)__shfl((int)first, leader, 64);
-    if (mine) l.items[(size_t)seg * l.segcap + first + (unsigned)__popcll(m & ((1ull << lane) - 1ull))] = item;
+__device__ __forceinline__ unsigned long long shfl_key(unsigned long long k, int src) {
+    const unsigned lo = (unsigned)__shfl((int)(unsigned)k, src, 64), hi = (unsigned)__shfl((int)(unsigned)(k >> 32), src, 64);
+    return (unsigned long long)hi << 32 | lo;
+}
+
+// Keys of the region's column i = i0 + lane: k[r] of row j0 - 1 + r, and of
+// the sample beside the region's edge columns (lane 0: left, lane 63: right)
+// in rows j0 .. j0 + 3.
+struct AAKeys {
+    unsigned long long k[kAaH + 2], side[kAaH];
+    bool ok[kAaH + 2], side_ok[kAaH];
+};
+
+__device__ __forceinline__ AAKeys aa_keys(const unsigned long long *__restrict__ kv, int W, int H, int i0, int j0,
+                                          int lane) {
+    AAKeys r;
+    const int i = i0 + lane, is = lane == 0 ? i - 1 : i + 1;
+    const bool col = i < W, edge = (lane == 0 && i > 0) || (lane == 63 && is < W);
+#pragma unroll
+    for (int q = 0; q < kAaH + 2; ++q) {
+        const int j = j0 - 1 + q;
+        r.ok[q] = col && j >= 0 && j < H;
+        r.k[q] = r.ok[q] ? kv[j * W + i] : kBgKey;
+    }
+#pragma unroll
+    for (int q = 0; q < kAaH; ++q) {
+        r.side_ok[q] = edge && r.ok[q + 1];
+        r.side[q] = r.side_ok[q] ? kv[(j0 + q) * W + is] : kBgKey;
+    }
+    return r;
+}
+
+// List the region's candidate pairs; returns their number (uniform).  When
+// it is not zero, state[] holds kAaCand for candidates and 0 elsewhere.  All
+// lanes of the (one-wave) workgroup call.
+__device__ __forceinline__ int aa_list(AARegion &g, const AAKeys &k, const unsigned char *__restrict__ sil, int lane) {
+    // left pair and (lane 63) right pair of each row, upper pair of each row and of the row below
+    unsigned front[2 * kAaH + kAaH + 1];
+    bool differ[2 * kAaH + kAaH + 1];
+    bool any = false;
+#pragma unroll
+    for (int q = 0; q < kAaH; ++q) {
+        const unsigned long long up = shfl_key(k.k[q + 1], lane - 1);
+        const bool up_ok = __shfl((int)k.ok[q + 1], lane - 1, 64) != 0;
+        const unsigned long long l = lane == 0 ? k.side[q] : up, s = k.k[q + 1], r = k.side[q];
+        differ[q] = (lane == 0 ? k.side_ok[q] : up_ok) && k.ok[q + 1] && (unsigned)l != (unsigned)s;
+        front[q] = (unsigned)(l < s ? l : s);
+        differ[kAaH + q] = lane == 63 && k.side_ok[q] && (unsigned)r != (unsigned)s;
+        front[kAaH + q] = (unsigned)(r < s ? r : s);
+    }
+#pragma unroll
+    for (int q = 0; q <= kAaH; ++q) {
+        const unsigned long long l = k.k[q], s = k.k[q + 1];
+        differ[2 * kAaH + q] = k.ok[q] && k.ok[q + 1] && (unsigned)l != (unsigned)s;
+        front[2 * kAaH + q] = (unsigned)(l < s ? l : s);
+    }
+#pragma unroll
+    for (int q = 0; q < 3 * kAaH + 1; ++q) any = any || differ[q];
+    if (__ballot(any) == 0ull) return 0;     // one triangle (most of a ground plane): no silhouette byte is needed
+    unsigned char sb[3 * kAaH + 1];
+#pragma unroll
+    for (int q = 0; q < 3 * kAaH + 1; ++q) sb[q] = differ[q] ? sil[front[q]] : (unsigned char)0;
+    bool cand = false;
+#pragma unroll
+    for (int q = 0; q < 3 * kAaH + 1; ++q) cand = cand || sb[q] != 0;
+    if (__ballot(cand) == 0ull) return 0;
+    unsigned *z = (unsigned *)g.state;
+    for (int q = lane; q < kAaSlots / 4; q += 64) z[q] = 0u;
+    __syncthreads();
+    int n = 0;
+    const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int q = 0; q < 3 * kAaH + 1; ++q) {
+        const unsigned long long m = __ballot(sb[q] != 0);
+        if (sb[q] != 0) {
+            const int slot = q < kAaH ? q * kAaRow + lane
+                             : q < 2 * kAaH ? (q - kAaH) * kAaRow + kAaW : kAaVert + (q - 2 * kAaH) * kAaW + lane;
+            g.item[n + __popcll(m & below)] = (unsigned short)slot;
+            g.state[slot] = kAaCand;
+        }
+        n += __popcll(m);
+    }
+    __syncthreads();
+    return n;
+}
+static_assert(kAaSlots % 4 == 0, "state is cleared in words");
+
+// Samples a and b of a slot, relative to the region's first sample.
+struct AASlot {
+    int ia, ja, ib, jb;
+    bool horiz;
+};
+__device__ __forceinline__ AASlot aa_slot(int slot) {
+    AASlot s;
+    s.horiz = slot < kAaVert;
+    if (s.horiz) {
+        s.jb = slot / kAaRow;
+        s.ib = slot - s.jb * kAaRow;
+        s.ia = s.ib - 1;
+        s.ja = s.jb;
+    } else {
+        s.jb = (slot - kAaVert) >> 6;
+        s.ib = (slot - kAaVert) & 63;
+        s.ia = s.ib;
+        s.ja = s.jb - 1;
+    }
+    return s;
+}
+__device__ __forceinline__ bool aa_inside(int i, int j) { return i >= 0 && i < kAaW && j >= 0 && j < kAaH; }
+
+// The four slots of sample (lane, row) in the order -x, +x, -y, +y, and the
+// state bit that says the sample receives.
+__device__ __forceinline__ int aa_slot_of(int lane, int row, int d) {
+    return d < 2 ? row * kAaRow + lane + d : kAaVert + (row + d - 2) * kAaW + lane;
+}
+__device__ __forceinline__ constexpr unsigned char aa_self_bit(int d) { return d & 1 ? kAaA : kAaB; }
+
+// Which sample of the pair receives: its state bit.
+__device__ __forceinline__ unsigned char aa_receiver(const AAPair &pr, bool a_is_front) {
+    return (pr.recv == 1) == a_is_front ? kAaB : kAaA;
+}
+
+// The candidate pairs of a workgroup's samples, compacted so that they can be
+// evaluated a pair a lane.  Few samples of a wave have one, and a pair costs
+// three dependent loads and some 200 instructions, many in float64: evaluated
+// in place, direction by direction, every wave with a single candidate pays
+// for all of its lanes four times.  Each wave lists its own pairs (sample of
+// the workgroup << 2 | direction) and one barrier publishes the lists; the
+// pair's result goes to the slot of that name, so a sample adds its pairs'
+// terms in the order of directions whatever lane evaluated them.
+template <int NT>
+struct AAPairs {
+    static constexpr int NW = NT / 64;
+    unsigned short item[NT * 4];
+    unsigned cnt[NW];
+    float w[NT * 4];               // blend weight, by slot
+    unsigned char state[NT * 4];   // 0: not smoothed, 1: the sample receives, 2: it gives
+};
+
+template <int NT>
+__device__ __forceinline__ void aa_pairs_list(AAPairs<NT> &l, int tid, const bool (&cand)[4]) {
+    const int lane = tid & 63, w = tid >> 6;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    unsigned at = 0;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const unsigned long long m = __ballot(cand[d]);
+        if (cand[d]) l.item[w * 256 + at + __popcll(m & below)] = (unsigned short)(tid << 2 | d);
+        at += (unsigned)__popcll(m);
+    }
+    if (lane == 0) l.cnt[w] = at;
+}
+
+template <int NT>
+__device__ __forceinline__ unsigned aa_pairs_total(const AAPairs<NT> &l) {
+    unsigned n = 0;
+#pragma unroll
+    for (int w = 0; w < AAPairs<NT>::NW; ++w) n += l.cnt[w];
+    return n;
+}
+
+// Slot (sample << 2 | direction) of the e-th listed pair.
+template <int NT>
+__device__ __forceinline__ unsigned aa_pairs_item(const AAPairs<NT> &l, unsigned e) {
+    unsigned base = 0;
+#pragma unroll
+    for (int w = 0; w < AAPairs<NT>::NW - 1; ++w)
+        if (e >= l.cnt[w] && base == (unsigned)w * 256u) {
+            e -= l.cnt[w];
+            base += 256u;
+        }
+    return l.item[base + e];
+}
+
+// Renders of one camera share its keys, so a thread of the camera smoothing
+// (and of its adjoint) evaluates its sample's pairs once and applies them to
+// a chunk of the camera's renders.  The chunk is the whole list unless that
+// leaves the GPU under kAaFillBlocks workgroups, where a single camera with
+// many renders would be a serial loop on an idle chip.
+constexpr int kAaFillBlocks = 2048;
+inline int aa_render_chunk(int max_renders, long long blocks) {
+    int chunk = max_renders;
+    while (chunk > 1 && blocks * ((max_renders + chunk - 1) / chunk) < kAaFillBlocks) chunk = (chunk + 1) / 2;
+    return chunk;
 }
 
 }  // namespace dsm

@@ -122,20 +122,21 @@ __global__ void zero_kernel(unsigned *p, size_t n) {
 // which an affine map turns back: f = f' + zc, f^2 = f^2' + zc (2 f' + zc),
 // or for exponential maps f = f' e^{c zc}, f^2 = f^2' e^{2 c zc}.  Filtered
 // maps are stored (m1, m2) interleaved per texel with side S + 2P (the face
-// at offset P); the others are planar with side S.
-__global__ void light_maps_out_kernel(const float *src, int S, int sp, int P, bool interleaved, const float *zc_p,
+// at offset P), smoothed maps planar with side S, unsmoothed maps as f alone
+// (which: as in dsm_get_light_maps).
+__global__ void light_maps_out_kernel(const float *src, int S, int sp, int P, int which, const float *zc_p,
                                       float warp_c, float *out) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= S * S) return;
     const float zc = *zc_p;
     float a, b;
-    if (interleaved) {
+    if (which == 2) {
         const long long q = 2 * ((long long)(t / S + P) * sp + (t % S + P));
         a = src[q];
         b = src[q + 1];
     } else {
         a = src[t];
-        b = src[(long long)S * S + t];
+        b = which == 0 ? a * a : src[(long long)S * S + t];
     }
     if (warp_c > 0.f) {
         const float e = expf(warp_c * zc);
@@ -364,6 +365,7 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
         part_light += (long long)v.tiles_x * v.tiles_y;
         v.part_gm_off = (int)part_gm;
         part_gm += (v.nverts + 255) / 256;
+        p->max_light_regions = std::max(p->max_light_regions, aa_regions(x.resolution, x.resolution));
         p->max_light_texels = std::max(p->max_light_texels, x.resolution * x.resolution);
         p->max_light_tiles = std::max(p->max_light_tiles, v.tiles_x * v.tiles_y);
         p->views_h[l] = v;
@@ -409,6 +411,7 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
         for (int i = 0; i < 16; ++i) v.M[i] = (float)M[i];
         p->max_cam_pix = std::max(p->max_cam_pix, x.width * x.height);
         p->max_cam_tiles = std::max(p->max_cam_tiles, v.tiles_x * v.tiles_y);
+        p->max_cam_regions = std::max(p->max_cam_regions, aa_regions(x.width, x.height));
         p->views_h[L + c] = v;
     }
     long long img = 0;
@@ -494,7 +497,7 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
     p->sv_setup = o; o = align_up(o + sizeof(TriSetup) * (size_t)tri);
     p->sv_sil = o; o = align_up(o + (size_t)tri);
     p->sv_tv = o; o = align_up(o + sizeof(TriVerts) * (size_t)std::max<long long>(Ft, 1));
-    p->sv_F0 = o; o = align_up(o + 4 * (size_t)maps);
+    p->sv_F0 = o; o = align_up(o + 2 * (size_t)maps);      // f alone: f^2 is its square
     p->sv_M = o; o = align_up(o + 4 * (size_t)fmaps);
     p->sv_img0 = o; o = align_up(o + 4 * (size_t)img);
     p->sv_pair_off = o; o = align_up(o + 4 * ((size_t)tri + 1));
@@ -508,19 +511,12 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
     // scratch layout
     o = 0;
     p->sc_tile_cnt = o; o = align_up(o + 4 * ((size_t)tiles + 1));
-    p->sc_aa_count = o; o = align_up(o + 4 * (size_t)kAaSegments);      // light smoothing list counters
     p->sc_zero_fwd_end = o;
     p->sc_pair_cnt = o; o = align_up(o + 4 * ((size_t)tri + 1));
     p->sc_scan = o; o = align_up(o + 4 * (size_t)std::max(scan_scratch_words((int)tri), scan_scratch_words((int)tiles)) + 64);
     p->sc_facing = o; o = align_up(o + (size_t)tri + 1);
     p->sc_pair_slot = o; o = align_up(o + 4 * (size_t)p->capacity);    // each pair's slot in its tile's bin
     p->sc_big_bin = o; o = align_up(o + 4 * ((size_t)tri + 1));       // triangles binned a workgroup each
-    // light-map samples whose smoothing has candidate pairs: the segmented list of the light smoothing
-    // grid (launch_aa_forward cuts it the same way)
-    {
-        const AaList ll = aa_list_for(nullptr, nullptr, (long long)((p->max_light_texels + 255) / 256) * L);
-        p->sc_aa_list = o; o = align_up(o + 8 * (size_t)ll.nseg * ll.segcap + 8);
-    }
     p->sc_F1 = o; o = align_up(o + 4 * (size_t)(maps + padmaps));
     p->sc_fwd_end = o;                 // the forward touches nothing past this
     p->sc_pair_flag = o; o = align_up(o + (size_t)p->capacity);
@@ -557,6 +553,7 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
         for (int r = 0; r < R; ++r)
             if (d->renders[r].camera == c) cam_list.push_back(r);
         cam_off[c + 1] = (int)cam_list.size();
+        p->max_cam_renders = std::max(p->max_cam_renders, cam_off[c + 1] - cam_off[c]);
     }
     std::vector<int> sv_off(B + 1, 0), sv_list;
     for (int b = 0; b < B; ++b) {
@@ -683,8 +680,6 @@ dsm_status enqueue_forward(dsm_plan *p, const float *verts, const float *lparams
     DevCounters *cnt = at<DevCounters>(saved, p->sv_counters);
     unsigned *tile_cnt = at<unsigned>(scratch, p->sc_tile_cnt);
     unsigned *pair_slot = at<unsigned>(scratch, p->sc_pair_slot);
-    uint2 *aa_list = at<uint2>(scratch, p->sc_aa_list);
-    unsigned *aa_count = at<unsigned>(scratch, p->sc_aa_count);
     unsigned *pair_cnt = at<unsigned>(scratch, p->sc_pair_cnt);
     unsigned *pair_off = at<unsigned>(saved, p->sv_pair_off);
     unsigned *scan = at<unsigned>(scratch, p->sc_scan);
@@ -723,10 +718,9 @@ dsm_status enqueue_forward(dsm_plan *p, const float *verts, const float *lparams
     DSM_TRY(launch_raster(p->views_d, p->tile_view_d, p->ntiles, p->tile, setup, tile_start, bins, overflow, cnt, cnt,
                           keys, s));
     DSM_MARK(DSM_STAGE_RESOLVE);
-    DSM_TRY(launch_resolve(p->views_d, p->L, p->max_light_texels, tv, keys, F0, s));
-    DSM_MARK(DSM_STAGE_LIGHT_AA);
-    DSM_TRY(launch_aa_forward(true, p->views_d, p->renders_d, p->L, p->max_light_texels, setup, p->faces_d, silm,
-                              verts, keys, F0, F1, 2, aa_list, aa_count, aa_flag, s));
+    DSM_TRY(launch_light_moments(p->views_d, p->L, p->max_light_regions, tv, setup, p->faces_d, silm, verts, keys, F0,
+                                 F1, aa_flag, s));
+    DSM_MARK(DSM_STAGE_LIGHT_AA);       // runs with the resolve
     DSM_MARK(DSM_STAGE_FILTER);
     if (p->has_cube) DSM_TRY(launch_cube_pad(p->views_d, p->L, p->max_cube_padded, p->cube_taps_d, F1, s));
     for (const auto &g : p->blur_groups)
@@ -735,8 +729,9 @@ dsm_status enqueue_forward(dsm_plan *p, const float *verts, const float *lparams
     DSM_TRY(launch_lookup(p->views_d, p->renders_d, p->R, p->max_cam_pix, p->render_lights_d, tv, albedo, keys, Mm,
                           img0, p->C, s));
     DSM_MARK(DSM_STAGE_CAMERA_AA);
-    DSM_TRY(launch_aa_forward(false, p->views_d, p->renders_d, p->R, p->max_cam_pix, setup, p->faces_d, silm,
-                              verts, keys, img0, images, p->C, nullptr, nullptr, aa_flag, s));
+    DSM_TRY(launch_aa_camera(p->views_d, p->L, p->Cm, p->max_cam_regions, p->max_cam_renders, p->renders_d,
+                             p->cam_renders_off_d, p->cam_renders_d, setup, p->faces_d, silm, verts, keys, img0, images,
+                             p->C, aa_flag, s));
     return DSM_OK;
 }
 
@@ -780,8 +775,9 @@ dsm_status enqueue_backward(dsm_plan *p, const float *verts, const float *lparam
                                 s));
     DSM_TRY(launch_overflow_rows_zero(overflow, cnt, gtri, s));
     DSM_MARK(DSM_STAGE_CAMERA_AA_ADJ);
-    DSM_TRY(launch_aa_camera_backward(p->views_d, p->renders_d, p->R, p->max_cam_pix, setup, p->faces_d, silm,
-                                      verts, keys, aa_flag, img0, gimg, gimg0, gclip, p->C, s));
+    DSM_TRY(launch_aa_camera_backward(p->views_d, p->L, p->Cm, p->max_cam_regions, p->max_cam_renders, p->renders_d,
+                                      p->cam_renders_off_d, p->cam_renders_d, setup, p->faces_d, silm, verts, keys,
+                                      aa_flag, img0, gimg, gimg0, gclip, p->C, s));
     DSM_MARK(DSM_STAGE_LOOKUP_ADJ);
     DSM_TRY(launch_lookup_backward(p->tile, p->views_d, p->L, p->Cm, p->max_cam_tiles, p->max_lights_per_render,
                                    p->renders_d, p->cam_renders_off_d, p->cam_renders_d, p->render_lights_d,
@@ -974,10 +970,11 @@ extern "C" dsm_status dsm_get_light_maps(const dsm_plan *p, const void *saved, c
     const void *src = which == 1 ? scratch : saved;
     if (!saved) return DSM_ERR_INVALID_ARG;       // holds the light's reference depth
     const bool il = which == 2;
+    const size_t first = (size_t)(il ? v.fmap_off : which == 0 ? v.map_off / 2 : v.map_off);
     // filtered maps: the face itself, without the texels sampled from cube neighbours
     hipLaunchKernelGGL(light_maps_out_kernel, dim3((v.W * v.W + 255) / 256), dim3(256), 0, (hipStream_t)stream,
-                       at<float>(src, base + 4 * (size_t)(il ? v.fmap_off : v.map_off)), v.W,
-                       il ? v.W + 2 * v.fpad : v.W, il ? v.fpad : 0, il, at<float>(saved, p->sv_zc + 4 * (size_t)light), v.warp_c, out);
+                       at<float>(src, base + 4 * first), v.W,
+                       il ? v.W + 2 * v.fpad : v.W, il ? v.fpad : 0, which, at<float>(saved, p->sv_zc + 4 * (size_t)light), v.warp_c, out);
     DSM_TRY(hipGetLastError());
     return DSM_OK;
 }

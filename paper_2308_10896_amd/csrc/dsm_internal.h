@@ -307,12 +307,15 @@ hipError_t launch_cube_pad(const ViewConst *views, int L, int max_padded, const 
                            hipStream_t s);
 hipError_t launch_cube_pad_transpose(const ViewConst *views, int L, int max_texels, int max_ring,
                                      const CubeTap *taps, float *gF1, hipStream_t s);
-hipError_t launch_resolve(const ViewConst *views, int L, int max_texels, const TriVerts *tv,
-                          const unsigned long long *keys, float *F0, hipStream_t s);
-hipError_t launch_aa_forward(bool light, const ViewConst *views, const RenderConst *renders, int n, int max_pix,
-                             const TriSetup *setup, const int *faces, const unsigned char *silm, const float *verts,
-                             const unsigned long long *keys, const float *src, float *dst, int C, uint2 *list,
-                             unsigned *count, unsigned char *aa_flag, hipStream_t s);
+hipError_t launch_light_moments(const ViewConst *views, int L, int max_regions, const TriVerts *tv,
+                                const TriSetup *setup, const int *faces, const unsigned char *silm, const float *verts,
+                                const unsigned long long *keys, float *F0, float *F1, unsigned char *aa_flag,
+                                hipStream_t s);
+hipError_t launch_aa_camera(const ViewConst *views, int L, int Cm, int max_regions, int max_renders,
+                            const RenderConst *renders, const int *cam_renders_off, const int *cam_renders,
+                            const TriSetup *setup, const int *faces, const unsigned char *silm, const float *verts,
+                            const unsigned long long *keys, const float *src, float *dst, int C,
+                            unsigned char *aa_flag, hipStream_t s);
 hipError_t launch_lookup(const ViewConst *views, const RenderConst *renders, int R, int max_pix,
                          const int *render_lights, const TriVerts *tv, const float *albedo,
                          const unsigned long long *keys, const float *maps, float *img0, int C, hipStream_t s);
@@ -320,7 +323,8 @@ hipError_t launch_tri_verts(const int *scene_vert_off, const int *scene_face_off
                             const int *faces, const float *verts, const float *albedo, int C, TriVerts *tv,
                             hipStream_t s);
 // backward
-hipError_t launch_aa_camera_backward(const ViewConst *views, const RenderConst *renders, int R, int max_pix,
+hipError_t launch_aa_camera_backward(const ViewConst *views, int L, int Cm, int max_regions, int max_renders,
+                                     const RenderConst *renders, const int *cam_renders_off, const int *cam_renders,
                                      const TriSetup *setup, const int *faces, const unsigned char *silm, const float *verts,
                                      const unsigned long long *keys, const unsigned char *aa_flag, const float *img0,
                                      const float *gimg, float *gimg0, float4 *gclip, int C, hipStream_t s);

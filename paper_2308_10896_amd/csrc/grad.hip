@@ -49,16 +49,6 @@ __device__ __forceinline__ void scatter_by_key(bool active, int key, const float
     }
 }
 
-// Wave-sum N values and add them at dst (lane 0).  All 64 lanes must call.
-template <int N>
-__device__ __forceinline__ void wave_add(const float (&val)[N], float *dst) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        const float s = wave_sum(val[i]);
-        if ((threadIdx.x & 63) == 0) atomic_add_f32(dst + i, s);
-    }
-}
-
 // Reciprocal (about one ulp) for gradient terms and for the shading values
 // the adjoints recompute exactly as the forward kernels form them (the map
 // position, which picks the bilinear cell, among them: both passes take that
@@ -106,87 +96,174 @@ __device__ __forceinline__ void bary_backward(const BaryFull &b, float px, float
     out[6] = ga2x; out[7] = ga2y; out[8] = -fmaf(px, ga2x, py * ga2y);
 }
 
+// ----------------------------------------------------------------------------- silhouette edge terms
+
+// A silhouette pair's gradient: six terms for the clip coordinates (x, y, w)
+// of its edge's two vertices.
+struct EdgeTerm {
+    bool has;
+    int va, vb;
+    float g[6];
+};
+
+__device__ __forceinline__ void edge_set(EdgeTerm &t, const AAPair &pr, double galpha) {
+    galpha *= pr.recv == 1 ? 1.0 : -1.0;      // w = alpha - 1/2 or 1/2 - alpha
+    t.has = true;
+    t.va = pr.va;
+    t.vb = pr.vb;
+    t.g[0] = (float)(galpha * pr.dax);
+    t.g[1] = (float)(galpha * pr.day);
+    t.g[2] = (float)(galpha * pr.daw);
+    t.g[3] = (float)(galpha * pr.dbx);
+    t.g[4] = (float)(galpha * pr.dby);
+    t.g[5] = (float)(galpha * pr.dbw);
+}
+
+// Add the lanes' terms.  Lanes with the same edge are summed in the
+// wave first and added with one atomic a term: float atomics run at the
+// memory side, where the hundreds of samples along a large object's outline
+// would queue on the same two vertices.  All 64 lanes must call.
+__device__ __forceinline__ void edge_add(EdgeTerm &t, float4 *__restrict__ gclip) {
+    const int lane = (int)(threadIdx.x & 63);
+    unsigned long long pending = __ballot(t.has);
+    while (pending) {
+        const int leader = __ffsll(pending) - 1;
+        const int va = __builtin_amdgcn_readlane(t.va, leader), vb = __builtin_amdgcn_readlane(t.vb, leader);
+        const bool mine = t.has && t.va == va && t.vb == vb;
+        const unsigned long long m = __ballot(mine);
+        pending &= ~m;
+        if (__popcll(m) < 3) continue;                   // these lanes add their own below
+        float v[6];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) v[k] = mine ? t.g[k] : 0.f;
+        const float s = wave_sum_multi(v);               // lane 2k: the group's total of term k
+        const int k = lane >> 1;
+        if ((lane & 1) == 0 && k < 6) {
+            float *p = (float *)(gclip + (k < 3 ? va : vb));
+            const int c = k < 3 ? k : k - 3;
+            atomic_add_f32(p + (c == 2 ? 3 : c), s);
+        }
+        t.has = t.has && !mine;
+    }
+    if (t.has) {
+        float4 *ga = gclip + t.va, *gb = gclip + t.vb;
+        atomic_add_f32(&ga->x, t.g[0]);
+        atomic_add_f32(&ga->y, t.g[1]);
+        atomic_add_f32(&ga->w, t.g[2]);
+        atomic_add_f32(&gb->x, t.g[3]);
+        atomic_add_f32(&gb->y, t.g[4]);
+        atomic_add_f32(&gb->w, t.g[5]);
+    }
+}
+
 // ----------------------------------------------------------------------------- camera smoothing^T
 
+// A wave per 64 x 4 region for a chunk of the camera's renders: as in the
+// forward, the pairs are evaluated once, a pair a lane.  A pair across a
+// region's border is evaluated in both; the region of its receiving sample
+// adds the edge's terms.  64 512^2 images 188 -> 120 us; a 1920 x 1080 image
+// with long outlines 260 -> 32 and a 256^2 one 46 -> 10, where the atomics of
+// all samples of an outline met on its two vertices.
 template <int C>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void aa_camera_backward_kernel(
-    const ViewConst *__restrict__ views, const RenderConst *__restrict__ renders, const TriSetup *__restrict__ setup,
-    const int *__restrict__ faces, const unsigned char *__restrict__ silm, const float *__restrict__ verts,
-    const unsigned long long *__restrict__ keys, const unsigned char *__restrict__ aa_flag,
-    const float *__restrict__ img0, const float *__restrict__ gimg,
+__global__ __launch_bounds__(64) void aa_camera_backward_kernel(
+    const ViewConst *__restrict__ views, int L, const RenderConst *__restrict__ renders,
+    const int *__restrict__ cam_renders_off, const int *__restrict__ cam_renders, int chunk,
+    const TriSetup *__restrict__ setup, const int *__restrict__ faces, const unsigned char *__restrict__ silm,
+    const float *__restrict__ verts, const unsigned long long *__restrict__ keys,
+    const unsigned char *__restrict__ aa_flag, const float *__restrict__ img0, const float *__restrict__ gimg,
     float *__restrict__ gimg0, float4 *__restrict__ gclip) {
+    __shared__ AARegion g;
     const Blk blk = xcd_block2();
-    const RenderConst &R = renders[blk.y];
-    const ViewConst &v = views[R.camera_view];
+    const ViewConst &v = views[L + blk.y];
     const int W = v.W, H = v.H;
-    const int p = aa_sample_index(blk.x, (int)threadIdx.x, W, H);
-    if (blk.x * 256 >= W * H || p >= W * H) return;
-    const float *c0 = img0 + R.img_off;
-    const float *g = gimg + R.img_off;
-    float acc[3] = {0.f, 0.f, 0.f};
+    if (blk.x >= aa_regions(W, H)) return;
+    const int r0 = cam_renders_off[blk.y] + (int)blockIdx.z * chunk, r1 = min(r0 + chunk, cam_renders_off[blk.y + 1]);
+    if (r0 >= r1) return;
+    const int lane = (int)threadIdx.x, rxn = (W + kAaW - 1) / kAaW;
+    const int i0 = (blk.x % rxn) * kAaW, j0 = (blk.x / rxn) * kAaH, i = i0 + lane;
+    long long base = renders[cam_renders[r0]].img_off;
+    float gself[kAaH][C];
+    bool flagged = false;
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
-        if (c < C) acc[c] = g[(long long)p * C + c];
-    const float gself[3] = {acc[0], acc[1], acc[2]};
-    // samples the forward found without candidate pairs pass the gradient through
-    if (v.antialias && v.nfaces > 0 && aa_flag[v.pix_off + p]) {
-        const int i = p % W, j = p / W;
-        const unsigned long long *kv = keys + v.pix_off;
-        const unsigned long long ks = kv[p];
-        const int di[4] = {-1, 1, 0, 0}, dj[4] = {0, 0, -1, 1};
-        const AANeighbours nb = aa_neighbours(v, kv, silm, ks, i, j);
-        // image values and upstream gradients of this sample and the
-        // candidate neighbours, fetched before the pair tests so that they
-        // arrive with the triangle records
-        const bool any = nb.cand[0] || nb.cand[1] || nb.cand[2] || nb.cand[3];
-        float cself[3], cn[4][3], gn[4][3];
+    for (int q = 0; q < kAaH; ++q) {
+        const bool live = i < W && j0 + q < H;
+        const long long p = (long long)(j0 + q) * W + i;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) cself[c] = (any && c < C) ? c0[(long long)p * C + c] : 0.f;
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const bool ld = nb.cand[d] && c < C;
-                cn[d][c] = ld ? c0[(long long)nb.q[d] * C + c] : 0.f;
-                gn[d][c] = ld ? g[(long long)nb.q[d] * C + c] : 0.f;
-            }
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            if (!nb.cand[d]) continue;
-            const int in_ = i + di[d], jn = j + dj[d];
-            const unsigned long long kn = nb.kn[d];
-            bool self_front;
-            AAPair pr;
-            if (!aa_eval<true>(v, setup, faces, silm, verts, ks, kn, i, j, in_, jn, d < 2, self_front, pr)) continue;
-            const bool self_recv = (pr.recv == 1) != self_front;
-            if (self_recv) {
-                double galpha = 0;
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    if (c >= C) continue;
-                    const float gs = gself[c];
-                    acc[c] -= pr.w * gs;
-                    galpha += (double)gs * (cn[d][c] - cself[c]);
-                }
-                galpha *= pr.recv == 1 ? 1.0 : -1.0;      // w = alpha - 1/2 or 1/2 - alpha
-                float4 *ga = gclip + v.clip_off + pr.va;
-                float4 *gb = gclip + v.clip_off + pr.vb;
-                atomic_add_f32(&ga->x, (float)(galpha * pr.dax));
-                atomic_add_f32(&ga->y, (float)(galpha * pr.day));
-                atomic_add_f32(&ga->w, (float)(galpha * pr.daw));
-                atomic_add_f32(&gb->x, (float)(galpha * pr.dbx));
-                atomic_add_f32(&gb->y, (float)(galpha * pr.dby));
-                atomic_add_f32(&gb->w, (float)(galpha * pr.dbw));
-            } else {
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    if (c < C) acc[c] += pr.w * gn[d][c];
-            }
-        }
+        for (int c = 0; c < C; ++c) gself[q][c] = live ? gimg[base + p * C + c] : 0.f;
+        // samples the forward found without candidate pairs pass the gradient through
+        flagged = flagged || (live && v.antialias && v.nfaces > 0 && aa_flag[v.pix_off + p]);
     }
+    int n = 0;
+    if (__ballot(flagged) != 0ull) {
+        const unsigned long long *kv = keys + v.pix_off;
+        n = aa_list(g, aa_keys(kv, W, H, i0, j0, lane), silm + v.setup_off, lane);
+        for (int e0 = 0; e0 < n; e0 += 64) {      // uniform
+            const int e = e0 + lane;
+            EdgeTerm t;
+            t.has = false;
+            t.va = t.vb = 0;
+            if (e < n) {
+                const int slot = g.item[e];
+                const AASlot s = aa_slot(slot);
+                const long long pa = (long long)(j0 + s.ja) * W + i0 + s.ia, pb = (long long)(j0 + s.jb) * W + i0 + s.ib;
+                const unsigned long long ka = kv[pa], kb = kv[pb];
+                const bool front = ka < kb;
+                AAPair pr{};
+                if (aa_eval<true>(v, setup, faces, silm, verts, front ? (unsigned)ka : (unsigned)kb, front, i0 + s.ia,
+                                  j0 + s.ja, i0 + s.ib, j0 + s.jb, s.horiz, pr)) {
+                    const unsigned char recv = aa_receiver(pr, front);
+                    g.state[slot] = kAaCand | recv;
+                    g.w[slot] = pr.w;
+                    const bool ra = recv == kAaA;
+                    if (ra ? aa_inside(s.ia, s.ja) : aa_inside(s.ib, s.jb)) {
+                        const long long ps = ra ? pa : pb, pn = ra ? pb : pa;
+                        double galpha = 0;
+                        for (int r = r0; r < r1; ++r) {
+                            const long long b = renders[cam_renders[r]].img_off;
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
-        if (c < C) gimg0[R.img_off + (long long)p * C + c] = acc[c];
+                            for (int c = 0; c < C; ++c)
+                                galpha += (double)gimg[b + ps * C + c] * (img0[b + pn * C + c] - img0[b + ps * C + c]);
+                        }
+                        edge_set(t, pr, galpha);
+                    }
+                }
+            }
+            edge_add(t, gclip + v.clip_off);
+        }
+        __syncthreads();
+    }
+    for (int r = r0;;) {
+#pragma unroll
+        for (int q = 0; q < kAaH; ++q) {
+            if (!(i < W && j0 + q < H)) continue;
+            const long long p = (long long)(j0 + q) * W + i;
+            float acc[C];
+#pragma unroll
+            for (int c = 0; c < C; ++c) acc[c] = gself[q][c];
+            if (n)
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const int slot = aa_slot_of(lane, q, d);
+                    const unsigned st = g.state[slot];
+                    if (!(st & (kAaA | kAaB))) continue;
+                    const float w = g.w[slot];
+                    const long long pn = p + (d == 0 ? -1 : d == 1 ? 1 : d == 2 ? -W : W);
+#pragma unroll
+                    for (int c = 0; c < C; ++c)
+                        if (st & aa_self_bit(d)) acc[c] -= w * gself[q][c];
+                        else acc[c] += w * gimg[base + pn * C + c];
+                }
+#pragma unroll
+            for (int c = 0; c < C; ++c) gimg0[base + p * C + c] = acc[c];
+        }
+        if (++r >= r1) break;
+        base = renders[cam_renders[r]].img_off;
+#pragma unroll
+        for (int q = 0; q < kAaH; ++q)
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                gself[q][c] = i < W && j0 + q < H ? gimg[base + ((long long)(j0 + q) * W + i) * C + c] : 0.f;
+    }
 }
 
 // ----------------------------------------------------------------------------- reduction by (triangle, tile)
@@ -958,8 +1035,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void l
     if (!kWavePairs) head = bin_head(gt, (int)threadIdx.x, tile_start, bins, bin_pair);
     const int tx = lt % l.tiles_x, ty = lt / l.tiles_x;
     const unsigned long long *kv = keys + l.pix_off;
-    const float *f0a = F0 + l.map_off, *f0b = F0 + l.map_off + plane;
+    const float *f0a = F0 + l.map_off / 2;      // f; f^2 is its square
     const float *ga = gF1 + l.map_off, *gbp = gF1 + l.map_off + plane;
+    __shared__ AAPairs<TS::NT> pairs;
     float accl[6] = {0, 0, 0, 0, 0, 0};
     int key[TS::PPT];
     bool act[TS::PPT], matched[TS::PPT];
@@ -976,43 +1054,64 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void l
 #pragma unroll
         for (int q = 0; q < 18; ++q) val[k][q] = 0.f;
         float g0 = in ? ga[pp] : 0.f, g1 = in ? gbp[pp] : 0.f;
-        // texels the forward found without candidate pairs skip the smoothing terms
-        if (in && l.antialias && l.nfaces > 0 && aa_flag[l.pix_off + pp]) {
-            const float gs0 = g0, gs1 = g1;
-            const int di[4] = {-1, 1, 0, 0}, dj[4] = {0, 0, -1, 1};
-            // the four neighbour keys, then their silhouette bytes, each batch
-            // loaded together; a candidate neighbour's map values and
-            // gradients are requested with its triangle's records
-            const AANeighbours nb = aa_neighbours(l, kv, silm, ks, i, j);
-            const bool any = nb.cand[0] || nb.cand[1] || nb.cand[2] || nb.cand[3];
-            const float fs0 = any ? f0a[pp] : 0.f, fs1 = any ? f0b[pp] : 0.f;
+        if (l.antialias && l.nfaces > 0) {                       // uniform
+            bool cand[4] = {false, false, false, false};
+            // texels the forward found without candidate pairs skip the smoothing terms
+            const bool flagged = in && aa_flag[l.pix_off + pp];
+            const int tid = (int)threadIdx.x;
+            unsigned n = 0;
+            if (TS::NW > 1 || __ballot(flagged) != 0ull) {
+                if (flagged) {
+                    const AANeighbours nb = aa_neighbours(l, kv, silm, ks, i, j);
 #pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                if (!nb.cand[d]) continue;
-                const int q = nb.q[d];
-                const float fn0 = f0a[q], fn1 = f0b[q], gn0 = ga[q], gn1 = gbp[q];
-                const int in_ = i + di[d], jn = j + dj[d];
-                const unsigned long long kn = nb.kn[d];
-                bool self_front;
-                AAPair pr;
-                if (!aa_eval<true>(l, setup, faces, silm, verts, ks, kn, i, j, in_, jn, d < 2, self_front, pr)) continue;
-                const bool self_recv = (pr.recv == 1) != self_front;
-                if (self_recv) {
-                    g0 -= pr.w * gs0;
-                    g1 -= pr.w * gs1;
-                    double galpha = (double)gs0 * (fn0 - fs0) + (double)gs1 * (fn1 - fs1);
-                    galpha *= pr.recv == 1 ? 1.0 : -1.0;
-                    float4 *gpa = gclip + l.clip_off + pr.va;
-                    float4 *gpb = gclip + l.clip_off + pr.vb;
-                    atomic_add_f32(&gpa->x, (float)(galpha * pr.dax));
-                    atomic_add_f32(&gpa->y, (float)(galpha * pr.day));
-                    atomic_add_f32(&gpa->w, (float)(galpha * pr.daw));
-                    atomic_add_f32(&gpb->x, (float)(galpha * pr.dbx));
-                    atomic_add_f32(&gpb->y, (float)(galpha * pr.dby));
-                    atomic_add_f32(&gpb->w, (float)(galpha * pr.dbw));
-                } else {
-                    g0 += pr.w * gn0;
-                    g1 += pr.w * gn1;
+                    for (int d = 0; d < 4; ++d) cand[d] = nb.cand[d];
+                }
+                if (k > 0) __syncthreads();
+                aa_pairs_list(pairs, tid, cand);
+                __syncthreads();
+                n = aa_pairs_total(pairs);
+                for (unsigned e0 = (unsigned)(tid & ~63); e0 < n; e0 += TS::NT) {      // uniform in the wave
+                    const unsigned e = e0 + (unsigned)(tid & 63);
+                    EdgeTerm t;
+                    t.has = false;
+                    t.va = t.vb = 0;
+                    if (e < n) {
+                        const unsigned slot = aa_pairs_item(pairs, e);
+                        const int d = slot & 3, u = (int)(slot >> 2) + k * TS::NT;
+                        const int is = tx * T + (u % T), js = ty * T + (u / T);
+                        const int in_ = is + (d == 0 ? -1 : d == 1 ? 1 : 0), jn = js + (d == 2 ? -1 : d == 3 ? 1 : 0);
+                        const int ps = js * S + is, pn = jn * S + in_;
+                        const unsigned long long kp = kv[ps], kn = kv[pn];
+                        const float fs0 = f0a[ps], fs1 = fs0 * fs0, fn0 = f0a[pn], fn1 = fn0 * fn0, gs0 = ga[ps],
+                                    gs1 = gbp[ps];
+                        const bool front = kp < kn;
+                        AAPair pr{};
+                        const bool ok = aa_eval<true>(l, setup, faces, silm, verts, front ? (unsigned)kp : (unsigned)kn,
+                                                      front, is, js, in_, jn, d < 2, pr);
+                        const bool self_recv = (pr.recv == 1) != front;
+                        pairs.state[slot] = !ok ? 0 : self_recv ? 1 : 2;
+                        pairs.w[slot] = pr.w;
+                        if (ok && self_recv) edge_set(t, pr, (double)gs0 * (fn0 - fs0) + (double)gs1 * (fn1 - fs1));
+                    }
+                    edge_add(t, gclip + l.clip_off);
+                }
+            }
+            if (n) {
+                __syncthreads();
+                const float gs0 = g0, gs1 = g1;
+                const int q[4] = {pp - 1, pp + 1, pp - S, pp + S};
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    if (!cand[d]) continue;
+                    const int st = pairs.state[tid << 2 | d];
+                    const float w = pairs.w[tid << 2 | d];
+                    if (st == 1) {
+                        g0 -= w * gs0;
+                        g1 -= w * gs1;
+                    } else if (st == 2) {
+                        g0 += w * ga[q[d]];
+                        g1 += w * gbp[q[d]];
+                    }
                 }
             }
         }
@@ -1421,18 +1520,20 @@ __global__ __launch_bounds__(256) void pose_backward_kernel(const int *__restric
 
 // ----------------------------------------------------------------------------- launchers
 
-hipError_t launch_aa_camera_backward(const ViewConst *views, const RenderConst *renders, int R, int max_pix,
+hipError_t launch_aa_camera_backward(const ViewConst *views, int L, int Cm, int max_regions, int max_renders,
+                                     const RenderConst *renders, const int *cam_renders_off, const int *cam_renders,
                                      const TriSetup *setup, const int *faces, const unsigned char *silm, const float *verts,
                                      const unsigned long long *keys, const unsigned char *aa_flag, const float *img0,
                                      const float *gimg, float *gimg0, float4 *gclip, int C, hipStream_t s) {
-    if (R == 0) return hipSuccess;
-    const dim3 grid((max_pix + 255) / 256, R);
-    if (C == 1)
-        hipLaunchKernelGGL(aa_camera_backward_kernel<1>, grid, dim3(256), 0, s, views, renders, setup, faces, silm,
-                           verts, keys, aa_flag, img0, gimg, gimg0, gclip);
-    else
-        hipLaunchKernelGGL(aa_camera_backward_kernel<3>, grid, dim3(256), 0, s, views, renders, setup, faces, silm,
-                           verts, keys, aa_flag, img0, gimg, gimg0, gclip);
+    if (Cm == 0 || max_renders == 0) return hipSuccess;
+    const int chunk = aa_render_chunk(max_renders, (long long)max_regions * Cm);
+    const dim3 grid(max_regions, Cm, (max_renders + chunk - 1) / chunk);
+#define DSM_AACB(CC)                                                                                                 \
+    hipLaunchKernelGGL(aa_camera_backward_kernel<CC>, grid, dim3(64), 0, s, views, L, renders, cam_renders_off,     \
+                       cam_renders, chunk, setup, faces, silm, verts, keys, aa_flag, img0, gimg, gimg0, gclip)
+    if (C == 1) DSM_AACB(1);
+    else DSM_AACB(3);
+#undef DSM_AACB
     return hipGetLastError();
 }
 

@@ -21,6 +21,7 @@ struct dsm_plan {
     long long key_count = 0, map_floats = 0, image_floats = 0;
     int blur_tiles = 0, blur_rmax = 0, max_pose_verts = 0;
     int max_light_tiles = 0, max_cam_tiles = 0, max_lights_per_render = 0;
+    int max_cam_regions = 0, max_light_regions = 0, max_cam_renders = 0;   // smoothing regions; renders of one camera
     int max_scene_verts = 0, max_scene_faces = 0;
 
     std::vector<dsm::ViewConst> views_h;
@@ -69,7 +70,7 @@ struct dsm_plan {
     // layout of the caller's scratch buffer (byte offsets): temporaries of
     // one call, nothing carried from a forward to its backward
     size_t sc_pair_cnt = 0, sc_scan = 0, sc_tile_cnt = 0, sc_facing = 0, sc_big_bin = 0,
-           sc_pair_slot = 0, sc_aa_list = 0, sc_aa_count = 0, sc_pair_flag = 0, sc_F1 = 0, sc_fwd_end = 0, sc_gimg0 = 0, sc_gM = 0, sc_gF1 = 0,
+           sc_pair_slot = 0, sc_pair_flag = 0, sc_F1 = 0, sc_fwd_end = 0, sc_gimg0 = 0, sc_gM = 0, sc_gF1 = 0,
            sc_gclip = 0, sc_glight = 0, sc_zero_fwd_end = 0, sc_bigcount = 0, sc_zero_rec = 0, sc_zero_bwd_end = 0,
            sc_pair_sums = 0, sc_gtri = 0, sc_biglist = 0, sc_part_light = 0, sc_part_gm = 0, sc_part_render = 0, sc_jac = 0,
            scratch_bytes = 0;

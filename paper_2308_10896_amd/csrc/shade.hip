@@ -64,281 +64,200 @@ __device__ __forceinline__ float light_depth(const ViewConst &l, float x, float 
     return d * __builtin_amdgcn_rcpf(l.zfar) - l.zc;
 }
 
-// ----------------------------------------------------------------------------- resolve
+// ----------------------------------------------------------------------------- light moments
 
-// Texels per thread of the resolve (256 apart): their keys, then their face
-// records, in flight together (the chain key -> record -> store is the
-// kernel's latency; 80 -> 62 -> 55 us for 1, 2, 4 on 64 512^2 maps).
-constexpr int kResolvePerThread = 4;
-
-__global__ __launch_bounds__(256) void resolve_kernel(const ViewConst *__restrict__ views,
-                                                      const TriVerts *__restrict__ tv,
-                                                      const unsigned long long *__restrict__ keys,
-                                                      float *__restrict__ F0) {
-    constexpr int PPT = kResolvePerThread;
-    const ViewConst &l = views[blockIdx.y];
-    const int S = l.W, P = S * S;
-    const int t0 = blockIdx.x * (256 * PPT) + (int)threadIdx.x;
-    if (t0 >= P) return;
-    unsigned long long key[PPT];
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        const int t = t0 + 256 * k;
-        key[k] = t < P ? keys[l.pix_off + t] : kBgKey;
+// f of a light-map texel (i, j) with the given key: z - zc of the nearest
+// triangle's point, or exp(c (z - zc)) for exponential maps.
+__device__ __forceinline__ float texel_moment(const ViewConst &l, const TriVerts &r, unsigned long long key, int i,
+                                              int j) {
+    const int S = l.W;
+    float z = 1.0f - l.zc;          // background: the far plane
+    if (key != kBgKey) {
+        const float v0[3] = {r.a.x, r.a.y, r.a.z}, v1[3] = {r.a.w, r.b.x, r.b.y}, v2[3] = {r.b.z, r.b.w, r.c.x};
+        const float px = ndc_centre(i, S), py = -ndc_centre(j, S);
+        const float4 c0 = clip_of(l.M, v0[0], v0[1], v0[2]), c1 = clip_of(l.M, v1[0], v1[1], v1[2]),
+                     c2 = clip_of(l.M, v2[0], v2[1], v2[2]);
+        const Bary b = persp_bary_rcp(c0, c1, c2, px, py);
+        const float x = (b.b0 * v0[0] + b.b1 * v1[0]) + b.b2 * v2[0];
+        const float y = (b.b0 * v0[1] + b.b1 * v1[1]) + b.b2 * v2[1];
+        const float zz = (b.b0 * v0[2] + b.b1 * v1[2]) + b.b2 * v2[2];
+        z = light_depth(l, x, y, zz);
     }
-    TriVerts r[PPT];
-#pragma unroll
-    for (int k = 0; k < PPT; ++k)
-        if (key[k] != kBgKey) r[k] = tv[l.face_off + (int)(unsigned)key[k]];
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        const int t = t0 + 256 * k;
-        if (t >= P) break;
-        float z = 1.0f - l.zc;          // background: the far plane
-        if (key[k] != kBgKey) {
-            const float v0[3] = {r[k].a.x, r[k].a.y, r[k].a.z}, v1[3] = {r[k].a.w, r[k].b.x, r[k].b.y},
-                        v2[3] = {r[k].b.z, r[k].b.w, r[k].c.x};
-            const int i = t % S, j = t / S;
-            const float px = ndc_centre(i, S), py = -ndc_centre(j, S);
-            const float4 c0 = clip_of(l.M, v0[0], v0[1], v0[2]), c1 = clip_of(l.M, v1[0], v1[1], v1[2]),
-                         c2 = clip_of(l.M, v2[0], v2[1], v2[2]);
-            const Bary b = persp_bary_rcp(c0, c1, c2, px, py);
-            const float x = (b.b0 * v0[0] + b.b1 * v1[0]) + b.b2 * v2[0];
-            const float y = (b.b0 * v0[1] + b.b1 * v1[1]) + b.b2 * v2[1];
-            const float zz = (b.b0 * v0[2] + b.b1 * v1[2]) + b.b2 * v2[2];
-            z = light_depth(l, x, y, zz);
-        }
-        if (l.warp_c > 0.f) z = expf(l.warp_c * z);     // exponential maps
-        F0[l.map_off + t] = z;
-        F0[l.map_off + (long long)P + t] = z * z;
-    }
+    return l.warp_c > 0.f ? expf(l.warp_c * z) : z;     // exponential maps
 }
 
-// ----------------------------------------------------------------------------- smoothing forward
-
-// Light maps: planar 2-channel; grid.y = light view.  Camera images:
-// interleaved C channels; grid.y = render (view = that render's camera).
-// C is a template parameter so that the per-channel values stay in registers.
-//
-// Light maps: two passes.  A sample changes only through a pair whose front
-// triangle has a silhouette edge (a candidate, AANeighbours), which is rare
-// in a shadow map, while testing a candidate waits for three more dependent
-// loads (the triangle's record, then its vertices).  The first pass therefore copies every
-// sample without candidates and lists the others (AaList, one atomic per
-// wave on one of many counters); the second pass evaluates only the listed
-// samples, so no wave of the first waits for them.
-
-// The smoothed value of sample p (all of its candidate pairs evaluated).
-template <bool LIGHT, int C>
-__device__ __forceinline__ void aa_forward_sample(const ViewConst &v, long long base, const TriSetup *__restrict__ setup,
-                                                  const int *__restrict__ faces, const unsigned char *__restrict__ silm,
-                                                  const float *__restrict__ verts,
-                                                  const unsigned long long *__restrict__ kv,
-                                                  const float *__restrict__ src, float *__restrict__ dst, int p) {
-    const int W = v.W;
-    const long long cstride = LIGHT ? (long long)W * v.H : 1;
-    const int pstride = LIGHT ? 1 : C;
-    const int i = p % W, j = p / W;
-    const unsigned long long ks = kv[p];
-    float acc[3] = {0.f, 0.f, 0.f};
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-        if (c < C) acc[c] = src[base + (long long)p * pstride + c * cstride];
-    const float self[3] = {acc[0], acc[1], acc[2]};
-    const int di[4] = {-1, 1, 0, 0}, dj[4] = {0, 0, -1, 1};
-    const AANeighbours nb = aa_neighbours(v, kv, silm, ks, i, j);
-    // values of the candidate neighbours, fetched before the pair tests
-    // so that they arrive with the triangle records
-    float nv[4][3];
-#pragma unroll
-    for (int d = 0; d < 4; ++d)
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-            nv[d][c] = (nb.cand[d] && c < C) ? src[base + (long long)nb.q[d] * pstride + c * cstride] : 0.f;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        if (!nb.cand[d]) continue;
-        const int in_ = i + di[d], jn = j + dj[d];
-        const unsigned long long kn = nb.kn[d];
-        bool self_front;
-        AAPair pr;
-        if (!aa_eval<false>(v, setup, faces, silm, verts, ks, kn, i, j, in_, jn, d < 2, self_front, pr)) continue;
-        const bool self_recv = (pr.recv == 1) != self_front;   // receiver: other when recv==1
-        if (!self_recv) continue;
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-            if (c < C) acc[c] += pr.w * (nv[d][c] - self[c]);
-    }
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-        if (c < C) dst[base + (long long)p * pstride + c * cstride] = acc[c];
-}
-
-// First pass: copy samples without candidates, list the others.  Each
-// thread takes kAaFirstPassPerThread samples 256 apart, with all of their
-// neighbour keys in flight together and one wave vote on whether any
-// silhouette byte is needed; list segments are assigned per 256-sample
-// chunk (chunk index gxv * row + column), as if each chunk were a
-// workgroup, so the list sizing does not depend on it.  Samples run in row
-// order: this pass streams, and has no candidate tests to concentrate.
-constexpr int kAaFirstPassPerThread = 2;
-
-template <bool LIGHT, int C>
-__global__ __launch_bounds__(256) void aa_forward_kernel(const ViewConst *__restrict__ views,
-                                                         const RenderConst *__restrict__ renders,
-                                                         const unsigned char *__restrict__ silm,
-                                                         const unsigned long long *__restrict__ keys,
-                                                         const float *__restrict__ src, float *__restrict__ dst,
-                                                         AaList list, unsigned char *__restrict__ flag, int gxv) {
-    constexpr int PPT = kAaFirstPassPerThread;
+// Moment resolve and edge smoothing of the light maps: a wave per 64 x 4
+// region, four texels a lane with their keys, then their face records, in
+// flight together.  F0 keeps f alone (f^2 is its square); F1 takes the
+// smoothed (f, f^2).  A pair's giving sample outside the region is resolved
+// again from its key.  Bytes a texel: 8 (key) + 4 (F0) + 8 (F1) + 1 (flag),
+// where a resolve, a copying pass and a list pass moved 41; 64 512^2 maps
+// 212 -> 134 us (vector issue and the record gathers; the bytes take 70),
+// three 2048^2 maps 177 -> 106.
+__global__ __launch_bounds__(64) void light_moments_kernel(const ViewConst *__restrict__ views,
+                                                           const TriVerts *__restrict__ tv,
+                                                           const TriSetup *__restrict__ setup,
+                                                           const int *__restrict__ faces,
+                                                           const unsigned char *__restrict__ silm,
+                                                           const float *__restrict__ verts,
+                                                           const unsigned long long *__restrict__ keys,
+                                                           float *__restrict__ F0, float *__restrict__ F1,
+                                                           unsigned char *__restrict__ flag) {
+    constexpr int ZW = kAaW + 2;
+    __shared__ AARegion g;
+    __shared__ float zs[(kAaH + 2) * ZW];       // f of the region and, where a pair needs it, of its border
     const Blk blk = xcd_block2();
-    const ViewConst &v = LIGHT ? views[blk.y] : views[renders[blk.y].camera_view];
-    const int W = v.W, H = v.H, P = W * H;
-    const int p0 = blk.x * (256 * PPT) + (int)threadIdx.x;
-    if (p0 >= P) return;
-    int ps[PPT];
-    bool live[PPT];
+    const ViewConst &l = views[blk.y];
+    const int S = l.W;
+    if (blk.x >= aa_regions(S, S)) return;
+    const int lane = (int)threadIdx.x, rxn = (S + kAaW - 1) / kAaW;
+    const int i0 = (blk.x % rxn) * kAaW, j0 = (blk.x / rxn) * kAaH, i = i0 + lane;
+    const unsigned long long *kv = keys + l.pix_off;
+    const AAKeys k = aa_keys(kv, S, S, i0, j0, lane);
+    TriVerts r[kAaH];
 #pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        ps[k] = p0 + 256 * k;
-        live[k] = ps[k] < P;
+    for (int q = 0; q < kAaH; ++q)
+        if (k.k[q + 1] != kBgKey) r[q] = tv[l.face_off + (int)(unsigned)k.k[q + 1]];
+    float z[kAaH];
+    float *f0 = F0 + l.map_off / 2;
+#pragma unroll
+    for (int q = 0; q < kAaH; ++q) {
+        z[q] = texel_moment(l, r[q], k.k[q + 1], i, j0 + q);
+        if (k.ok[q + 1]) f0[(j0 + q) * S + i] = z[q];
     }
-    const long long base = LIGHT ? v.map_off : renders[blk.y].img_off;
-    const long long cstride = LIGHT ? (long long)P : 1;
-    const int pstride = LIGHT ? 1 : C;
-    const unsigned long long *kv = keys + v.pix_off;
-    float val[PPT][3];
+    const int n = l.antialias && l.nfaces > 0 ? aa_list(g, k, silm + l.setup_off, lane) : 0;
+    if (n) {
 #pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        const int p = ps[k];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) val[k][c] = (live[k] && c < C) ? src[base + (long long)p * pstride + c * cstride] : 0.f;
-    }
-    bool cand[PPT];
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) cand[k] = false;
-    if (v.antialias && v.nfaces > 0) {
-        // every neighbour key of every sample first, then the differing pairs
-        unsigned long long ks[PPT], kn[PPT][4];
-        bool differ[PPT][4];
-        bool any = false;
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            const int p = live[k] ? ps[k] : ps[0];
-            const int i = p % W, j = p / W;
-            ks[k] = kv[p];
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const int in_ = i + (d == 0 ? -1 : d == 1 ? 1 : 0), jn = j + (d == 2 ? -1 : d == 3 ? 1 : 0);
-                const bool inb = in_ >= 0 && in_ < W && jn >= 0 && jn < H;
-                kn[k][d] = kv[inb ? jn * W + in_ : p];
-                differ[k][d] = inb;
+        for (int q = 0; q < kAaH; ++q) zs[(q + 1) * ZW + lane + 1] = z[q];
+        __syncthreads();
+        for (int e = lane; e < n; e += 64) {
+            const int slot = g.item[e];
+            const AASlot s = aa_slot(slot);
+            const unsigned long long ka = kv[(j0 + s.ja) * S + i0 + s.ia], kb = kv[(j0 + s.jb) * S + i0 + s.ib];
+            const bool front = ka < kb;
+            AAPair pr{};
+            if (!aa_eval<false>(l, setup, faces, silm, verts, front ? (unsigned)ka : (unsigned)kb, front, i0 + s.ia,
+                                j0 + s.ja, i0 + s.ib, j0 + s.jb, s.horiz, pr))
+                continue;
+            const unsigned char recv = aa_receiver(pr, front);
+            g.state[slot] = kAaCand | recv;
+            g.w[slot] = pr.w;
+            const int gi = recv == kAaA ? s.ib : s.ia, gj = recv == kAaA ? s.jb : s.ja;
+            if (!aa_inside(gi, gj)) {
+                const unsigned long long kg = recv == kAaA ? kb : ka;
+                TriVerts t{};
+                if (kg != kBgKey) t = tv[l.face_off + (int)(unsigned)kg];
+                zs[(gj + 1) * ZW + gi + 1] = texel_moment(l, t, kg, i0 + gi, j0 + gj);
             }
         }
+        __syncthreads();
+    }
+    const long long plane = (long long)S * S;
 #pragma unroll
-        for (int k = 0; k < PPT; ++k)
+    for (int q = 0; q < kAaH; ++q) {
+        if (!k.ok[q + 1]) continue;
+        const int p = (j0 + q) * S + i;
+        const float f = z[q], ff = f * f;
+        float a0 = f, a1 = ff;
+        unsigned any = 0;
+        if (n)
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
-                differ[k][d] = live[k] && differ[k][d] && (unsigned)kn[k][d] != (unsigned)ks[k];
-                any = any || differ[k][d];
+                const int slot = aa_slot_of(lane, q, d);
+                const unsigned st = g.state[slot];
+                any |= st;
+                if (!(st & aa_self_bit(d))) continue;
+                const float fn = zs[(q + 1 + (d == 2 ? -1 : d == 3 ? 1 : 0)) * ZW + lane + 1 +
+                                    (d == 0 ? -1 : d == 1 ? 1 : 0)];
+                a0 += g.w[slot] * (fn - f);
+                a1 += g.w[slot] * (fn * fn - ff);
             }
-        if (__ballot(any) != 0ull) {
+        F1[l.map_off + p] = a0;
+        F1[l.map_off + plane + p] = a1;
+        flag[l.pix_off + p] = any ? 1 : 0;       // for the adjoint: this sample has candidate pairs
+    }
+}
+
+// ----------------------------------------------------------------------------- camera smoothing
+
+// Edge smoothing of the camera images, a wave per 64 x 4 region, for a chunk
+// of the camera's renders: the pairs depend on the keys alone, so they are
+// evaluated once for all of them.  Latency of the pairs' loads bounds it; 64
+// 512^2 images 121 -> 79 us against four pair tests per thread in place, 16
+// cameras with 8 renders each 211 -> 96.
+template <int C>
+__global__ __launch_bounds__(64) void aa_camera_forward_kernel(
+    const ViewConst *__restrict__ views, int L, const RenderConst *__restrict__ renders,
+    const int *__restrict__ cam_renders_off, const int *__restrict__ cam_renders, int chunk,
+    const TriSetup *__restrict__ setup, const int *__restrict__ faces, const unsigned char *__restrict__ silm,
+    const float *__restrict__ verts, const unsigned long long *__restrict__ keys, const float *__restrict__ src,
+    float *__restrict__ dst, unsigned char *__restrict__ flag) {
+    __shared__ AARegion g;
+    const Blk blk = xcd_block2();
+    const ViewConst &v = views[L + blk.y];
+    const int W = v.W, H = v.H;
+    if (blk.x >= aa_regions(W, H)) return;
+    const int r0 = cam_renders_off[blk.y] + (int)blockIdx.z * chunk, r1 = min(r0 + chunk, cam_renders_off[blk.y + 1]);
+    if (r0 >= r1) return;
+    const int lane = (int)threadIdx.x, rxn = (W + kAaW - 1) / kAaW;
+    const int i0 = (blk.x % rxn) * kAaW, j0 = (blk.x / rxn) * kAaH, i = i0 + lane;
+    long long base = renders[cam_renders[r0]].img_off;
+    float self[kAaH][C];
 #pragma unroll
-            for (int k = 0; k < PPT; ++k)
+    for (int q = 0; q < kAaH; ++q)
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            self[q][c] = i < W && j0 + q < H ? src[base + ((long long)(j0 + q) * W + i) * C + c] : 0.f;
+    int n = 0;
+    if (v.antialias && v.nfaces > 0) {                          // uniform
+        const unsigned long long *kv = keys + v.pix_off;
+        n = aa_list(g, aa_keys(kv, W, H, i0, j0, lane), silm + v.setup_off, lane);
+        for (int e = lane; e < n; e += 64) {
+            const int slot = g.item[e];
+            const AASlot s = aa_slot(slot);
+            const unsigned long long ka = kv[(j0 + s.ja) * W + i0 + s.ia], kb = kv[(j0 + s.jb) * W + i0 + s.ib];
+            const bool front = ka < kb;
+            AAPair pr{};
+            if (!aa_eval<false>(v, setup, faces, silm, verts, front ? (unsigned)ka : (unsigned)kb, front, i0 + s.ia,
+                                j0 + s.ja, i0 + s.ib, j0 + s.jb, s.horiz, pr))
+                continue;
+            g.state[slot] = kAaCand | aa_receiver(pr, front);
+            g.w[slot] = pr.w;
+        }
+        __syncthreads();
+    }
+    for (int r = r0;;) {
+#pragma unroll
+        for (int q = 0; q < kAaH; ++q) {
+            if (!(i < W && j0 + q < H)) continue;
+            const long long p = (long long)(j0 + q) * W + i;
+            float acc[C];
+#pragma unroll
+            for (int c = 0; c < C; ++c) acc[c] = self[q][c];
+            unsigned any = 0;
+            if (n)
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
-                    const unsigned front = ks[k] < kn[k][d] ? (unsigned)ks[k] : (unsigned)kn[k][d];
-                    const unsigned char sil = differ[k][d] ? silm[v.setup_off + front] : (unsigned char)0;
-                    cand[k] = cand[k] || (differ[k][d] && sil != 0);
+                    const int slot = aa_slot_of(lane, q, d);
+                    const unsigned st = g.state[slot];
+                    any |= st;
+                    if (!(st & aa_self_bit(d))) continue;
+                    const float w = g.w[slot];
+                    const long long pn = p + (d == 0 ? -1 : d == 1 ? 1 : d == 2 ? -W : W);
+#pragma unroll
+                    for (int c = 0; c < C; ++c) acc[c] += w * (src[base + pn * C + c] - self[q][c]);
                 }
+#pragma unroll
+            for (int c = 0; c < C; ++c) dst[base + p * C + c] = acc[c];
+            if (r == r0 && blockIdx.z == 0) flag[v.pix_off + p] = any ? 1 : 0;      // for the adjoint
         }
-    }
+        if (++r >= r1) break;
+        base = renders[cam_renders[r]].img_off;
 #pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        const int p = ps[k];
-        if (live[k]) flag[v.pix_off + p] = cand[k] ? 1 : 0;
-        wave_append(cand[k], make_uint2((unsigned)blk.y, (unsigned)p), list,
-                    (long long)blk.y * gxv + (long long)blk.x * PPT + k);
-        if (live[k] && !cand[k]) {
+        for (int q = 0; q < kAaH; ++q)
 #pragma unroll
-            for (int c = 0; c < 3; ++c)
-                if (c < C) dst[base + (long long)p * pstride + c * cstride] = val[k][c];
-        }
-    }
-}
-
-// One pass over every sample (camera images: their candidates are too
-// frequent for a second pass to pay off).
-template <bool LIGHT, int C>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void aa_forward_direct_kernel(const ViewConst *__restrict__ views, const RenderConst *__restrict__ renders,
-                                  const TriSetup *__restrict__ setup, const int *__restrict__ faces,
-                                  const unsigned char *__restrict__ silm, const float *__restrict__ verts,
-                                  const unsigned long long *__restrict__ keys, const float *__restrict__ src,
-                                  float *__restrict__ dst,
-                                  unsigned char *__restrict__ flag) {
-    const Blk blk = xcd_block2();
-    const ViewConst &v = LIGHT ? views[blk.y] : views[renders[blk.y].camera_view];
-    const int W = v.W, H = v.H;
-    const int p = aa_sample_index(blk.x, (int)threadIdx.x, W, H);
-    if (blk.x * 256 >= W * H || p >= W * H) return;
-    const long long base = LIGHT ? v.map_off : renders[blk.y].img_off;
-    const long long cstride = LIGHT ? (long long)W * H : 1;
-    const int pstride = LIGHT ? 1 : C;
-    const int i = p % W, j = p / W;
-    const unsigned long long *kv = keys + v.pix_off;
-    const unsigned long long ks = kv[p];
-    float acc[3] = {0.f, 0.f, 0.f};
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-        if (c < C) acc[c] = src[base + (long long)p * pstride + c * cstride];
-    const float self[3] = {acc[0], acc[1], acc[2]};
-    const int di[4] = {-1, 1, 0, 0}, dj[4] = {0, 0, -1, 1};
-    bool any = false;
-    if (v.antialias && v.nfaces > 0) {
-        const AANeighbours nb = aa_neighbours(v, kv, silm, ks, i, j);
-        any = nb.cand[0] || nb.cand[1] || nb.cand[2] || nb.cand[3];
-        // values of the candidate neighbours, fetched before the pair tests
-        // so that they arrive with the triangle records
-        float nv[4][3];
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-                nv[d][c] = (nb.cand[d] && c < C) ? src[base + (long long)nb.q[d] * pstride + c * cstride] : 0.f;
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            if (!nb.cand[d]) continue;
-            const int in_ = i + di[d], jn = j + dj[d];
-            const unsigned long long kn = nb.kn[d];
-            bool self_front;
-            AAPair pr;
-            if (!aa_eval<false>(v, setup, faces, silm, verts, ks, kn, i, j, in_, jn, d < 2, self_front, pr)) continue;
-            const bool self_recv = (pr.recv == 1) != self_front;   // receiver: other when recv==1
-            if (!self_recv) continue;
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-                if (c < C) acc[c] += pr.w * (nv[d][c] - self[c]);
-        }
-    }
-    flag[v.pix_off + p] = any ? 1 : 0;      // for the adjoint: this sample has candidate pairs
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-        if (c < C) dst[base + (long long)p * pstride + c * cstride] = acc[c];
-}
-
-// Second pass: one workgroup per list segment.
-template <bool LIGHT, int C>
-__global__ __launch_bounds__(256) void aa_forward_list_kernel(
-    const ViewConst *__restrict__ views, const RenderConst *__restrict__ renders, const TriSetup *__restrict__ setup,
-    const int *__restrict__ faces, const unsigned char *__restrict__ silm, const float *__restrict__ verts,
-    const unsigned long long *__restrict__ keys, const float *__restrict__ src, float *__restrict__ dst,
-    AaList list) {
-    const unsigned seg = blockIdx.x, n = list.counts[seg];
-    for (unsigned e = threadIdx.x; e < n; e += blockDim.x) {
-        const uint2 it = list.items[(size_t)seg * list.segcap + e];
-        const ViewConst &v = LIGHT ? views[it.x] : views[renders[it.x].camera_view];
-        const long long base = LIGHT ? v.map_off : renders[it.x].img_off;
-        aa_forward_sample<LIGHT, C>(v, base, setup, faces, silm, verts, keys + v.pix_off, src, dst, (int)it.y);
+            for (int c = 0; c < C; ++c)
+                self[q][c] = i < W && j0 + q < H ? src[base + ((long long)(j0 + q) * W + i) * C + c] : 0.f;
     }
 }
 
@@ -493,41 +412,30 @@ __global__ __launch_bounds__(256) void lookup_kernel(const ViewConst *__restrict
 
 // ----------------------------------------------------------------------------- launchers
 
-hipError_t launch_resolve(const ViewConst *views, int L, int max_texels, const TriVerts *tv,
-                          const unsigned long long *keys, float *F0, hipStream_t s) {
+hipError_t launch_light_moments(const ViewConst *views, int L, int max_regions, const TriVerts *tv,
+                                const TriSetup *setup, const int *faces, const unsigned char *silm, const float *verts,
+                                const unsigned long long *keys, float *F0, float *F1, unsigned char *aa_flag,
+                                hipStream_t s) {
     if (L == 0) return hipSuccess;
-    hipLaunchKernelGGL(resolve_kernel, dim3((max_texels + 256 * kResolvePerThread - 1) / (256 * kResolvePerThread), L),
-                       dim3(256), 0, s, views, tv, keys, F0);
+    hipLaunchKernelGGL(light_moments_kernel, dim3(max_regions, L), dim3(64), 0, s, views, tv, setup, faces, silm, verts,
+                       keys, F0, F1, aa_flag);
     return hipGetLastError();
 }
 
-hipError_t launch_aa_forward(bool light, const ViewConst *views, const RenderConst *renders, int n, int max_pix,
-                             const TriSetup *setup, const int *faces, const unsigned char *silm, const float *verts,
-                             const unsigned long long *keys, const float *src, float *dst, int C, uint2 *list,
-                             unsigned *counts, unsigned char *aa_flag, hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    const dim3 grid((max_pix + 255) / 256, n);
-    const AaList l = aa_list_for(list, counts, (long long)grid.x * grid.y);
-    constexpr int P1 = kAaFirstPassPerThread;
-    const dim3 grid1((max_pix + 256 * P1 - 1) / (256 * P1), n);
-#define DSM_AAF(LL, CC)                                                                                          \
-    do {                                                                                                         \
-        hipLaunchKernelGGL((aa_forward_kernel<LL, CC>), grid1, dim3(256), 0, s, views, renders, silm, keys, src, \
-                           dst, l, aa_flag, (int)grid.x);                                                        \
-        hipLaunchKernelGGL((aa_forward_list_kernel<LL, CC>), dim3(l.nseg), dim3(256), 0, s, views, renders,      \
-                           setup, faces, silm, verts, keys, src, dst, l);                                        \
-    } while (0)
-    // light maps in two passes (a sample with candidate pairs is rare there); camera images in one
-    if (light) {
-        DSM_AAF(true, 2);
-    } else if (C == 1) {
-        hipLaunchKernelGGL((aa_forward_direct_kernel<false, 1>), grid, dim3(256), 0, s, views, renders, setup, faces,
-                           silm, verts, keys, src, dst, aa_flag);
-    } else {
-        hipLaunchKernelGGL((aa_forward_direct_kernel<false, 3>), grid, dim3(256), 0, s, views, renders, setup, faces,
-                           silm, verts, keys, src, dst, aa_flag);
-    }
-#undef DSM_AAF
+hipError_t launch_aa_camera(const ViewConst *views, int L, int Cm, int max_regions, int max_renders,
+                            const RenderConst *renders, const int *cam_renders_off, const int *cam_renders,
+                            const TriSetup *setup, const int *faces, const unsigned char *silm, const float *verts,
+                            const unsigned long long *keys, const float *src, float *dst, int C,
+                            unsigned char *aa_flag, hipStream_t s) {
+    if (Cm == 0 || max_renders == 0) return hipSuccess;
+    const int chunk = aa_render_chunk(max_renders, (long long)max_regions * Cm);
+    const dim3 grid(max_regions, Cm, (max_renders + chunk - 1) / chunk);
+#define DSM_AAC(CC)                                                                                                 \
+    hipLaunchKernelGGL(aa_camera_forward_kernel<CC>, grid, dim3(64), 0, s, views, L, renders, cam_renders_off,     \
+                       cam_renders, chunk, setup, faces, silm, verts, keys, src, dst, aa_flag)
+    if (C == 1) DSM_AAC(1);
+    else DSM_AAC(3);
+#undef DSM_AAC
     return hipGetLastError();
 }
 
