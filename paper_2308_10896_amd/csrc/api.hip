@@ -493,7 +493,6 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
     p->sv_counters = o; o = align_up(o + sizeof(DevCounters));
     p->sv_zero_end = o;
     p->sv_keys = o; o = align_up(o + 8 * (size_t)pix);
-    p->sv_clip = o; o = align_up(o + 16 * (size_t)clip);
     p->sv_setup = o; o = align_up(o + sizeof(TriSetup) * (size_t)tri);
     p->sv_sil = o; o = align_up(o + (size_t)tri);
     p->sv_tv = o; o = align_up(o + sizeof(TriVerts) * (size_t)std::max<long long>(Ft, 1));
@@ -501,10 +500,14 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
     p->sv_M = o; o = align_up(o + 4 * (size_t)fmaps);
     p->sv_img0 = o; o = align_up(o + 4 * (size_t)img);
     p->sv_pair_off = o; o = align_up(o + 4 * ((size_t)tri + 1));
-    p->sv_tile_start = o; o = align_up(o + 4 * ((size_t)tiles + 1));
+    p->sv_tile_start = o; o = align_up(o + 4 * ((size_t)tiles + (size_t)tiles / kScanBlock + 2));
     p->sv_bins = o; o = align_up(o + 4 * (size_t)p->capacity);
-    p->sv_bin_pair = o; o = align_up(o + 4 * (size_t)p->capacity);
+    // the backward walks the bins of 16 x 16 and 32 x 32 tiles only
+    p->sv_bin_pair = o; o = align_up(o + (tile_size == 8 ? 0 : 4 * (size_t)p->capacity));
     p->sv_overflow = o; o = align_up(o + 4 * ((size_t)tri + 1));
+    p->item_cap = (unsigned)std::min<long long>(tri + p->capacity / kLargeChunk, 0x7fffffff);
+    p->sv_large = o; o = align_up(o + 4 * ((size_t)tri + 1));        // triangles of many tiles and their items
+    p->sv_items = o; o = align_up(o + 8 * ((size_t)p->item_cap + 1));
     p->sv_zc = o; o = align_up(o + 4 * (size_t)std::max(L, 1));
     p->sv_aa_flag = o; o = align_up(o + (size_t)pix);        // per sample: it has candidate smoothing pairs
     p->saved_bytes = std::max<size_t>(o, kAlign);
@@ -512,11 +515,10 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
     o = 0;
     p->sc_tile_cnt = o; o = align_up(o + 4 * ((size_t)tiles + 1));
     p->sc_zero_fwd_end = o;
-    p->sc_pair_cnt = o; o = align_up(o + 4 * ((size_t)tri + 1));
-    p->sc_scan = o; o = align_up(o + 4 * (size_t)std::max(scan_scratch_words((int)tri), scan_scratch_words((int)tiles)) + 64);
+    p->sc_pair_local = o; o = align_up(o + 4 * ((size_t)tri + 1));
+    p->sc_block_total = o; o = align_up(o + 4 * ((size_t)tri / kTriRun + (size_t)p->nviews + 2));
     p->sc_facing = o; o = align_up(o + (size_t)tri + 1);
     p->sc_pair_slot = o; o = align_up(o + 4 * (size_t)p->capacity);    // each pair's slot in its tile's bin
-    p->sc_big_bin = o; o = align_up(o + 4 * ((size_t)tri + 1));       // triangles binned a workgroup each
     p->sc_F1 = o; o = align_up(o + 4 * (size_t)(maps + padmaps));
     p->sc_fwd_end = o;                 // the forward touches nothing past this
     p->sc_pair_flag = o; o = align_up(o + (size_t)p->capacity);
@@ -537,6 +539,19 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
     p->sc_part_render = o; o = align_up(o + 4 * (size_t)(part_render + 1));
     p->scratch_bytes = o;
 
+    // runs of triangles for the triangle passes
+    std::vector<TriBlock> tri_blocks;
+    {
+        std::vector<char> seen(B, 0);
+        for (int v = 0; v < p->nviews; ++v) {
+            ViewConst &x = p->views_h[v];
+            x.write_tv = seen[x.scene] ? 0 : 1;
+            seen[x.scene] = 1;
+            x.tri_block = (int)tri_blocks.size();
+            for (int f = 0; f < x.nfaces; f += kTriRun) tri_blocks.push_back(TriBlock{v, f});
+        }
+        p->tri_blocks = (int)tri_blocks.size();
+    }
     // device uploads
     std::vector<int> adj(3 * (size_t)Ft, -1);
     for (int b = 0; b < B; ++b)
@@ -598,6 +613,7 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
     if (st == DSM_OK) st = upload(&p->render_lights_d, p->render_lights_h.data(), p->render_lights_h.size());
     if (st == DSM_OK) st = upload(&p->faces_d, d->faces, 3 * (size_t)Ft);
     if (st == DSM_OK) st = upload(&p->adj_d, adj.data(), adj.size());
+    if (st == DSM_OK) st = upload(&p->tri_blocks_d, tri_blocks.data(), tri_blocks.size());
     if (st == DSM_OK) st = upload(&p->tile_view_d, tile_view.data(), tile_view.size());
     if (st == DSM_OK) st = upload(&p->blur_jobs_d, p->blur_jobs_h.data(), p->blur_jobs_h.size());
     if (st == DSM_OK && !p->cube_taps_h.empty())
@@ -617,7 +633,7 @@ extern "C" void dsm_plan_destroy(dsm_plan *p) {
     if (!p) return;
     if (p->graph_exec) (void)hipGraphExecDestroy(p->graph_exec);
     if (p->graph) (void)hipGraphDestroy(p->graph);
-    void *bufs[] = {p->views_d, p->light_cams_d, p->renders_d, p->render_lights_d, p->faces_d, p->adj_d,
+    void *bufs[] = {p->views_d, p->tri_blocks_d, p->light_cams_d, p->renders_d, p->render_lights_d, p->faces_d, p->adj_d,
                     p->tile_view_d, p->blur_jobs_d, p->cube_taps_d, p->scene_vert_off_d, p->pose_counts_d, p->pose_centers_d,
                     p->cam_renders_off_d, p->cam_renders_d, p->scene_views_off_d, p->scene_views_d, p->vc_off_d,
                     p->vc_list_d, p->light_renders_off_d, p->light_renders_d, p->scene_face_off_d};
@@ -680,17 +696,17 @@ dsm_status enqueue_forward(dsm_plan *p, const float *verts, const float *lparams
     DevCounters *cnt = at<DevCounters>(saved, p->sv_counters);
     unsigned *tile_cnt = at<unsigned>(scratch, p->sc_tile_cnt);
     unsigned *pair_slot = at<unsigned>(scratch, p->sc_pair_slot);
-    unsigned *pair_cnt = at<unsigned>(scratch, p->sc_pair_cnt);
+    unsigned *pair_local = at<unsigned>(scratch, p->sc_pair_local);
+    unsigned *block_total = at<unsigned>(scratch, p->sc_block_total);
     unsigned *pair_off = at<unsigned>(saved, p->sv_pair_off);
-    unsigned *scan = at<unsigned>(scratch, p->sc_scan);
+    const LargeLists large{at<unsigned>(saved, p->sv_large), at<uint2>(saved, p->sv_items), p->item_cap};
     unsigned *tile_start = at<unsigned>(saved, p->sv_tile_start);
     unsigned *bins = at<unsigned>(saved, p->sv_bins);
-    unsigned *bin_pair = at<unsigned>(saved, p->sv_bin_pair);
+    unsigned *bin_pair = p->tile == 8 ? nullptr : at<unsigned>(saved, p->sv_bin_pair);
     unsigned *overflow = at<unsigned>(saved, p->sv_overflow);
     float *F1 = at<float>(scratch, p->sc_F1);
     unsigned long long *keys = at<unsigned long long>(saved, p->sv_keys);
     unsigned char *aa_flag = at<unsigned char>(saved, p->sv_aa_flag);
-    float4 *clip = at<float4>(saved, p->sv_clip);
     TriSetup *setup = at<TriSetup>(saved, p->sv_setup);
     unsigned char *silm = at<unsigned char>(saved, p->sv_sil);
     TriVerts *tv = at<TriVerts>(saved, p->sv_tv);
@@ -702,21 +718,16 @@ dsm_status enqueue_forward(dsm_plan *p, const float *verts, const float *lparams
     // with the light frames, the counters (saved) and the tile counts (scratch) are cleared
     DSM_TRY(launch_light_frames(p->views_d, p->light_cams_d, lparams, p->L, nullptr, at<float>(saved, p->sv_zc), saved,
                                 p->sv_zero_end, scratch, p->sc_zero_fwd_end, s));
-    DSM_TRY(launch_transform(p->views_d, p->nviews, p->max_verts, verts, clip, s));
-    DSM_TRY(launch_tri_verts(p->scene_vert_off_d, p->scene_face_off_d, p->B, p->max_scene_faces, p->faces_d, verts,
-                             albedo, p->C, tv, s));
     signed char *facing8 = at<signed char>(scratch, p->sc_facing);
-    DSM_TRY(launch_setup(p->views_d, p->nviews, p->max_faces, p->faces_d, clip, setup, facing8, pair_cnt, p->tile,
-                         cnt, s));
-    DSM_TRY(launch_silhouettes(p->views_d, p->nviews, p->max_faces, p->adj_d, facing8, silm, s));
+    DSM_TRY(launch_setup(p->views_d, p->tri_blocks_d, p->tri_blocks, p->faces_d, verts, albedo, p->C,
+                         tv, setup, facing8, pair_local, block_total, large, p->tile, cnt, s));
     DSM_MARK(DSM_STAGE_BIN);
-    DSM_TRY(launch_scan(pair_cnt, pair_off, scan, p->ntri, s));
-    DSM_TRY(launch_binning(p->views_d, setup, pair_off, p->ntri, p->capacity, p->tile, tile_cnt, tile_start,
-                           pair_slot, scan, p->ntiles, bins, bin_pair, overflow, at<unsigned>(scratch, p->sc_big_bin), cnt,
-                           s));
+    DSM_TRY(launch_binning(p->views_d, p->tri_blocks_d, p->tri_blocks, setup, p->adj_d, facing8, silm,
+                           pair_local, block_total, pair_off, p->ntri, p->capacity, p->tile, tile_cnt, tile_start,
+                           pair_slot, p->ntiles, bins, bin_pair, overflow, large, cnt, keys, p->key_count, s));
     DSM_MARK(DSM_STAGE_RASTER);
-    DSM_TRY(launch_raster(p->views_d, p->tile_view_d, p->ntiles, p->tile, setup, tile_start, bins, overflow, cnt, cnt,
-                          keys, s));
+    DSM_TRY(launch_raster(p->views_d, p->tile_view_d, p->ntiles, p->tile, setup, tile_start, bins, overflow, cnt, keys,
+                          s));
     DSM_MARK(DSM_STAGE_RESOLVE);
     DSM_TRY(launch_light_moments(p->views_d, p->L, p->max_light_regions, tv, setup, p->faces_d, silm, verts, keys, F0,
                                  F1, aa_flag, s));
@@ -740,7 +751,6 @@ dsm_status enqueue_backward(dsm_plan *p, const float *verts, const float *lparam
                             float *galbedo, hipStream_t s, const StageMarks *marks = nullptr) {
     const unsigned long long *keys = at<unsigned long long>(saved, p->sv_keys);
     const unsigned char *aa_flag = at<unsigned char>(saved, p->sv_aa_flag);
-    const float4 *clip = at<float4>(saved, p->sv_clip);
     const TriSetup *setup = at<TriSetup>(saved, p->sv_setup);
     const unsigned char *silm = at<unsigned char>(saved, p->sv_sil);
     const TriVerts *tv = at<TriVerts>(saved, p->sv_tv);

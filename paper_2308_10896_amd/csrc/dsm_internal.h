@@ -50,7 +50,19 @@ struct ViewConst {
                         // | its edge << 3 | (indices along the edge reversed) << 5
     int ring_off;       // cube faces: first CubeTap of this face's padding (4 P S entries)
     float zc;           // light views: reference depth; maps hold moments of z - zc (see light_depth)
+    int write_tv;       // first view of its scene: its setup writes the scene's TriVerts records
+    int tri_block;      // first TriBlock of this view
 };
+
+// A run of triangles of one view, a workgroup's share of the triangle passes.
+struct TriBlock {
+    int view, first;
+};
+// Up to this many workgroups, each one of a triangle pass sums the totals of
+// those before it, and the large triangles' workgroups hold all totals in LDS.
+constexpr int kTriRun = 256, kMaxTriBlocks = 1024;
+// Tiles per workgroup of the tile scan.
+constexpr int kScanShift = 11, kScanBlock = 1 << kScanShift;
 
 // One padded texel of a cube face beyond one of its edges: the bilinear
 // sample of the neighbouring face g along the direction the padded texel
@@ -137,9 +149,38 @@ struct DevCounters {
     unsigned long long overflow;
     unsigned long long bad_indices;
     unsigned int overflow_list_len;
-    unsigned int big_bin_len;        // triangles binned a workgroup each
-    unsigned int pad[6];
+    unsigned int large_len, item_len; // listed large triangles and their items (LargeLists)
+    unsigned int bin_cursor;         // running total of the tile scan
+    unsigned int pad[4];
 };
+
+// Triangles of more than kBigBin tiles, and their pairs in items (triangle,
+// first pair within it) of kLargeChunk.  item_cap holds every item whose pairs
+// can fit the bins; with more pairs than that the items may be incomplete.
+constexpr unsigned kBigBin = 32, kLargeChunk = 512;
+constexpr int kLargeBlocks = 512;      // workgroups that take the items
+struct LargeLists {
+    unsigned *list;
+    uint2 *items;
+    unsigned item_cap;
+};
+
+// f(t, q0, n) for workgroup b's share of the items, n the triangle's pairs
+// (count(t)).  With incomplete items every workgroup walks the triangles and
+// takes its chunks of each.
+template <class Count, class F>
+__device__ __forceinline__ void for_large_items(const LargeLists &l, const DevCounters *counters, int b, int nb,
+                                                Count count, F f) {
+    const unsigned nitems = counters->item_len, nlist = counters->large_len;
+    if (nitems <= l.item_cap) {
+        for (unsigned o = (unsigned)b; o < nitems; o += (unsigned)nb) f(l.items[o].x, l.items[o].y, count(l.items[o].x));
+        return;
+    }
+    for (unsigned o = 0; o < nlist; ++o) {
+        const unsigned t = l.list[o], n = count(t);
+        for (unsigned k = ((unsigned)b + o) % (unsigned)nb; k * kLargeChunk < n; k += (unsigned)nb) f(t, k * kLargeChunk, n);
+    }
+}
 
 // ----------------------------------------------------------------------------- helpers
 
@@ -224,6 +265,14 @@ __device__ __forceinline__ int wave_max(int v) {
     return max(max(r0, r1), max(r2, r3));
 }
 
+// Order the LDS accesses of a wave's lanes before and after (the hardware
+// keeps them in order; this keeps the compiler from carrying a value across).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Workgroups are dispatched to the 8 XCDs round-robin by linear id, and each
 // XCD has its own L2.  These renumber a grid so that each XCD takes a
 // contiguous range of work items: neighbouring tiles and rows, which share
@@ -285,24 +334,20 @@ constexpr int kJac = 66;
 // Also clears bytes1 at z1 and bytes2 at z2 (multiples of 4) in the same launch.
 hipError_t launch_light_frames(ViewConst *views, const CamStatic *cams, const float *params, int L, float *jac,
                                float *zc_out, void *z1, size_t bytes1, void *z2, size_t bytes2, hipStream_t s);
-hipError_t launch_transform(const ViewConst *views, int nviews, int max_verts, const float *verts, float4 *clip,
-                            hipStream_t s);
-hipError_t launch_silhouettes(const ViewConst *views, int nviews, int max_faces, const int *adj,
-                              const signed char *facing8, unsigned char *silm, hipStream_t s);
-hipError_t launch_setup(const ViewConst *views, int nviews, int max_faces, const int *faces, const float4 *clip,
-                        TriSetup *setup, signed char *facing8, unsigned *pair_count, int tile, DevCounters *counters,
-                        hipStream_t s);
-int scan_scratch_words(int n);
-hipError_t launch_scan(const unsigned *in, unsigned *out, unsigned *scratch, int n, hipStream_t s);
-hipError_t launch_binning(const ViewConst *views, const TriSetup *setup, const unsigned *pair_off, int ntri,
-                          unsigned capacity, int tile, unsigned *tile_count, unsigned *tile_start,
-                          unsigned *pair_slot, unsigned *scan_scratch, int ntiles, unsigned *bins,
-                          unsigned *bin_pair, unsigned *overflow_list, unsigned *big_list, DevCounters *counters,
+hipError_t launch_setup(const ViewConst *views, const TriBlock *blocks, int nblocks, const int *faces,
+                        const float *verts, const float *albedo, int C, TriVerts *tv, TriSetup *setup,
+                        signed char *facing8, unsigned *pair_local, unsigned *block_total, const LargeLists &large,
+                        int tile, DevCounters *counters, hipStream_t s);
+hipError_t launch_binning(const ViewConst *views, const TriBlock *blocks, int nblocks, const TriSetup *setup,
+                          const int *adj, const signed char *facing8, unsigned char *silm, const unsigned *pair_local,
+                          unsigned *block_total, unsigned *pair_off, int ntri, unsigned capacity, int tile,
+                          unsigned *tile_count, unsigned *tile_start, unsigned *pair_slot, int ntiles, unsigned *bins,
+                          unsigned *bin_pair, unsigned *overflow_list, const LargeLists &large,
+                          DevCounters *counters, unsigned long long *keys, long long nkeys,
                           hipStream_t s);
 hipError_t launch_raster(const ViewConst *views, const int *tile_view, int ntiles, int tile, const TriSetup *setup,
                          const unsigned *tile_start, const unsigned *bins, const unsigned *overflow_list,
-                         const DevCounters *counters_ro, DevCounters *counters, unsigned long long *keys,
-                         hipStream_t s);
+                         DevCounters *counters, unsigned long long *keys, hipStream_t s);
 hipError_t launch_cube_pad(const ViewConst *views, int L, int max_padded, const CubeTap *taps, float *F1,
                            hipStream_t s);
 hipError_t launch_cube_pad_transpose(const ViewConst *views, int L, int max_texels, int max_ring,
@@ -319,9 +364,6 @@ hipError_t launch_aa_camera(const ViewConst *views, int L, int Cm, int max_regio
 hipError_t launch_lookup(const ViewConst *views, const RenderConst *renders, int R, int max_pix,
                          const int *render_lights, const TriVerts *tv, const float *albedo,
                          const unsigned long long *keys, const float *maps, float *img0, int C, hipStream_t s);
-hipError_t launch_tri_verts(const int *scene_vert_off, const int *scene_face_off, int B, int max_faces,
-                            const int *faces, const float *verts, const float *albedo, int C, TriVerts *tv,
-                            hipStream_t s);
 // backward
 hipError_t launch_aa_camera_backward(const ViewConst *views, int L, int Cm, int max_regions, int max_renders,
                                      const RenderConst *renders, const int *cam_renders_off, const int *cam_renders,

@@ -350,8 +350,9 @@ __device__ __forceinline__ BinHead bin_head(int gt, int tid, const unsigned *__r
                                             const unsigned *__restrict__ bins,
                                             const unsigned *__restrict__ bin_pair) {
     BinHead h;
-    h.b0 = tile_start[gt];
-    h.b1 = tile_start[gt + 1];
+    const int at = gt + (gt >> kScanShift);          // the tile scan keeps an end per kScanBlock tiles
+    h.b0 = tile_start[at];
+    h.b1 = tile_start[at + 1];
     const unsigned c = h.b1 > h.b0 ? min(h.b0 + (unsigned)tid, h.b1 - 1) : 0u;
     h.si = bins[c];
     h.pair = bin_pair[c];

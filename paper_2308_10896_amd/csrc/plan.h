@@ -15,7 +15,7 @@ struct dsm_plan {
     long long V_total = 0, F_total = 0;
     int tile = 16;
     int bin_scale = 8;
-    unsigned capacity = 0;
+    unsigned capacity = 0, item_cap = 0;
     int ntri = 0, ntiles = 0, nclip = 0;
     int max_verts = 0, max_faces = 0, max_light_texels = 0, max_cam_pix = 0;
     long long key_count = 0, map_floats = 0, image_floats = 0;
@@ -47,6 +47,8 @@ struct dsm_plan {
     int *faces_d = nullptr;
     int *adj_d = nullptr;
     int *tile_view_d = nullptr;
+    dsm::TriBlock *tri_blocks_d = nullptr;
+    int tri_blocks = 0;
     dsm::BlurJob *blur_jobs_d = nullptr;
     dsm::CubeTap *cube_taps_d = nullptr;
     int *scene_vert_off_d = nullptr;    // [B+1]
@@ -64,12 +66,12 @@ struct dsm_plan {
 
     // layout of the caller's saved buffer (byte offsets): everything the
     // forward writes and the backward reads, the binning state included
-    size_t sv_counters = 0, sv_zero_end = 0, sv_keys = 0, sv_clip = 0, sv_setup = 0, sv_sil = 0, sv_tv = 0, sv_F0 = 0,
-           sv_M = 0, sv_img0 = 0, sv_pair_off = 0, sv_tile_start = 0, sv_bins = 0, sv_bin_pair = 0, sv_overflow = 0, sv_zc = 0, sv_aa_flag = 0,
+    size_t sv_counters = 0, sv_zero_end = 0, sv_keys = 0, sv_setup = 0, sv_sil = 0, sv_tv = 0, sv_F0 = 0,
+           sv_M = 0, sv_img0 = 0, sv_pair_off = 0, sv_tile_start = 0, sv_bins = 0, sv_bin_pair = 0, sv_overflow = 0, sv_large = 0, sv_items = 0, sv_zc = 0, sv_aa_flag = 0,
            saved_bytes = 0;
     // layout of the caller's scratch buffer (byte offsets): temporaries of
     // one call, nothing carried from a forward to its backward
-    size_t sc_pair_cnt = 0, sc_scan = 0, sc_tile_cnt = 0, sc_facing = 0, sc_big_bin = 0,
+    size_t sc_pair_local = 0, sc_block_total = 0, sc_tile_cnt = 0, sc_facing = 0,
            sc_pair_slot = 0, sc_pair_flag = 0, sc_F1 = 0, sc_fwd_end = 0, sc_gimg0 = 0, sc_gM = 0, sc_gF1 = 0,
            sc_gclip = 0, sc_glight = 0, sc_zero_fwd_end = 0, sc_bigcount = 0, sc_zero_rec = 0, sc_zero_bwd_end = 0,
            sc_pair_sums = 0, sc_gtri = 0, sc_biglist = 0, sc_part_light = 0, sc_part_gm = 0, sc_part_render = 0, sc_jac = 0,

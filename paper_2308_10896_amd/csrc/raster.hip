@@ -78,371 +78,559 @@ __global__ void light_frames_kernel(ViewConst *views, const CamStatic *cams, con
     if (jac) light_jacobian(cams[l], params + 3 * l, jac + (size_t)kJac * l);
 }
 
-// ----------------------------------------------------------------------------- transform
-
-__global__ void transform_kernel(const ViewConst *__restrict__ views, const float *__restrict__ verts,
-                                 float4 *__restrict__ clip) {
-    const ViewConst &v = views[blockIdx.y];
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= v.nverts) return;
-    const float *p = verts + 3 * (size_t)(v.vert_off + i);
-    const float x = p[0], y = p[1], z = p[2];
-    clip[v.clip_off + i] = clip_of(v.M, x, y, z);
-}
-
-// One TriVerts record per face: the corners' world positions gathered once,
-// so that per-pixel passes fetch one record instead of face -> vertices.
-__global__ void tri_verts_kernel(const int *__restrict__ scene_vert_off, const int *__restrict__ scene_face_off,
-                                 const int *__restrict__ faces, const float *__restrict__ verts,
-                                 const float *__restrict__ albedo, int C, TriVerts *__restrict__ tv) {
-    const int b = blockIdx.y;
-    const int f = scene_face_off[b] + blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= scene_face_off[b + 1]) return;
-    const float *v0 = verts + 3 * (size_t)(scene_vert_off[b] + faces[3 * (size_t)f]);
-    const float *v1 = verts + 3 * (size_t)(scene_vert_off[b] + faces[3 * (size_t)f + 1]);
-    const float *v2 = verts + 3 * (size_t)(scene_vert_off[b] + faces[3 * (size_t)f + 2]);
-    TriVerts r;
-    r.a = make_float4(v0[0], v0[1], v0[2], v1[0]);
-    r.b = make_float4(v1[1], v1[2], v2[0], v2[1]);
-    // the face's albedo rides in the record's spare words: the lookups read it
-    // with the corners instead of with a load of its own
-    const float *rho = albedo + (size_t)f * C;
-    r.c = make_float4(v2[2], rho[0], C > 1 ? rho[1] : 0.f, C > 2 ? rho[2] : 0.f);
-    tv[f] = r;
-}
-
-hipError_t launch_tri_verts(const int *scene_vert_off, const int *scene_face_off, int B, int max_faces,
-                            const int *faces, const float *verts, const float *albedo, int C, TriVerts *tv,
-                            hipStream_t s) {
-    if (B == 0 || max_faces == 0) return hipSuccess;
-    hipLaunchKernelGGL(tri_verts_kernel, dim3((max_faces + 255) / 256, B), dim3(256), 0, s, scene_vert_off,
-                       scene_face_off, faces, verts, albedo, C, tv);
-    return hipGetLastError();
-}
-
 // ----------------------------------------------------------------------------- setup
 
 __device__ __forceinline__ int floor_div256(int a) { return a >= 0 ? (a >> 8) : -((-a + 255) >> 8); }
 
-__global__ void setup_kernel(const ViewConst *__restrict__ views, const int *__restrict__ faces,
-                             const float4 *__restrict__ clip, TriSetup *__restrict__ setup,
-                             signed char *__restrict__ facing8, unsigned *__restrict__ pair_count, int tile,
-                             DevCounters *counters) {
-    const int view = blockIdx.y;
-    const ViewConst &v = views[view];
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= v.nfaces) return;
-    const int *f = faces + 3 * (size_t)(v.face_off + t);
-    int idx[3] = {f[0], f[1], f[2]};
-    bool bad = false;
-    for (int k = 0; k < 3; ++k)
-        if (idx[k] < 0 || idx[k] >= v.nverts) { bad = true; idx[k] = 0; }
-    int X[3], Y[3];
-    float z[3];
-    bool ok = !bad;
-    const float hw = 0.5f * (float)v.W, hh = 0.5f * (float)v.H;
-    for (int k = 0; k < 3; ++k) {
-        const float4 c = clip[v.clip_off + idx[k]];
-        const float nx = c.x / c.w, ny = c.y / c.w, nz = c.z / c.w;
-        const float sx = (nx + 1.0f) * hw;
-        const float sy = (1.0f - ny) * hh;
-        const bool okv = (c.w > 0.0f) && (nz >= -1.0f) && (fabsf(sx) < kGuard) && (fabsf(sy) < kGuard);
-        ok = ok && okv;
-        X[k] = okv ? (int)rintf(sx * 256.0f) : 0;
-        Y[k] = okv ? (int)rintf(sy * 256.0f) : 0;
-        z[k] = 0.5f * nz + 0.5f;
-    }
-    long long A = (long long)(X[1] - X[0]) * (Y[2] - Y[0]) - (long long)(Y[1] - Y[0]) * (X[2] - X[0]);
-    const bool swapped = A < 0;
-    if (swapped) {
-        int ti = X[1]; X[1] = X[2]; X[2] = ti;
-        ti = Y[1]; Y[1] = Y[2]; Y[2] = ti;
-        float tz = z[1]; z[1] = z[2]; z[2] = tz;
-        A = -A;
-    }
-    const bool valid = ok && A > 0;
-    TriSetup s;
-    s.A = A;
-    for (int k = 0; k < 3; ++k) { s.X[k] = X[k]; s.Y[k] = Y[k]; s.z[k] = z[k]; }
-    s.facing = valid ? (swapped ? -1 : 1) : 0;
-    s.swapped = swapped ? 1 : 0;
-    s.sil = 0;
-    s.pad1 = 0;
-    s.pad2[0] = view;
-    s.pad2[1] = 0;
-    unsigned npairs = 0;
-    int i0 = 1, i1 = 0, j0 = 1, j1 = 0;
-    if (valid) {
-        const int mnx = min(X[0], min(X[1], X[2])), mxx = max(X[0], max(X[1], X[2]));
-        const int mny = min(Y[0], min(Y[1], Y[2])), mxy = max(Y[0], max(Y[1], Y[2]));
-        // pixel centres 256 i + 128 inside [mnx, mxx]
-        i0 = max(floor_div256(mnx - 128 + 255), 0);
-        i1 = min(floor_div256(mxx - 128), v.W - 1);
-        j0 = max(floor_div256(mny - 128 + 255), 0);
-        j1 = min(floor_div256(mxy - 128), v.H - 1);
-        if (i0 <= i1 && j0 <= j1) npairs = (unsigned)((i1 / tile - i0 / tile + 1) * (j1 / tile - j0 / tile + 1));
-    }
-    if (!(i0 <= i1 && j0 <= j1)) { i0 = 1; i1 = 0; j0 = 1; j1 = 0; }
-    s.bx0 = (unsigned short)i0;
-    s.bx1 = (unsigned short)i1;
-    s.by0 = (unsigned short)j0;
-    s.by1 = (unsigned short)j1;
-    setup[v.setup_off + t] = s;
-    facing8[v.setup_off + t] = s.facing;
-    pair_count[v.setup_off + t] = npairs;
-    const unsigned long long nc = __popcll(__ballot(!ok && !bad));
-    const unsigned long long nb = __popcll(__ballot(bad));
-    if ((threadIdx.x & 63) == __ffsll((unsigned long long)__ballot(1)) - 1) {
-        if (nc) atomicAdd(&counters->culled, nc);
-        if (nb) atomicAdd(&counters->bad_indices, nb);
-    }
-}
+// Workgroups of the triangle passes (setup, bin count, bin fill) take runs of
+// kTriRun triangles of one view (TriBlock, in the order of the per-(view,
+// triangle) arrays), a triangle a thread.
+constexpr int kTriThreads = kTriRun;
 
-// Silhouette mask per (view, triangle): oriented edge e is a silhouette when
-// no triangle or more than one other triangle shares it, or when the
-// neighbour across it faces the other way in this view.
-__global__ void silhouette_kernel(const ViewConst *__restrict__ views, const int *__restrict__ adj,
-                                  const signed char *__restrict__ facing8, unsigned char *__restrict__ silm) {
-    const ViewConst &v = views[blockIdx.y];
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= v.nfaces) return;
-    const int facing = facing8[v.setup_off + t];
-    if (facing == 0) {
-        silm[v.setup_off + t] = 0;
-        return;
-    }
-    const bool sw = facing < 0;        // second and third vertex were exchanged
-    unsigned mask = 0;
-    for (int e = 0; e < 3; ++e) {
-        const int a = (e + 1) % 3, b = (e + 2) % 3;
-        const int oa = sw ? (a == 0 ? 0 : 3 - a) : a, ob = sw ? (b == 0 ? 0 : 3 - b) : b;
-        const int nb = adj[3 * (size_t)(v.face_off + t) + (3 - oa - ob)];
-        if (nb < 0 || facing8[v.setup_off + nb] != facing) mask |= 1u << e;
-    }
-    silm[v.setup_off + t] = (unsigned char)mask;
-}
-
-// ----------------------------------------------------------------------------- scan (exclusive, uint32)
-
-constexpr int kScanThreads = 256;
-constexpr int kScanPer = 8;
-constexpr int kScanBlock = kScanThreads * kScanPer;
-
-__device__ __forceinline__ unsigned block_exclusive_scan(unsigned v, unsigned *total) {
-    __shared__ unsigned wsum[kScanThreads / 64];
+// Exclusive scan over the workgroup's PPT * 256 values, value k of thread tid
+// at position k * 256 + tid; *total: their sum.  Uniform call.
+template <int PPT>
+__device__ __forceinline__ void tri_block_scan(const unsigned (&v)[PPT], unsigned (&out)[PPT], unsigned *total) {
+    constexpr int NW = kTriThreads / 64;
+    __shared__ unsigned sum[PPT][NW];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    unsigned x = v;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const unsigned y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
+    for (int k = 0; k < PPT; ++k) {
+        unsigned x = v[k];
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) sum[k][wid] = x;
+        out[k] = x - v[k];
     }
-    if (lane == 63) wsum[wid] = x;
     __syncthreads();
-    unsigned base = 0, all = 0;
-    for (int w = 0; w < kScanThreads / 64; ++w) {
-        if (w < wid) base += wsum[w];
-        all += wsum[w];
-    }
-    __syncthreads();
+    unsigned all = 0;
+#pragma unroll
+    for (int k = 0; k < PPT; ++k)
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            if (w == wid) out[k] += all;
+            all += sum[k][w];
+        }
     *total = all;
-    return base + x - v;
 }
 
-__global__ __launch_bounds__(kScanThreads) void scan_blocks_kernel(const unsigned *in, unsigned *out,
-                                                                   unsigned *block_sums, int n) {
-    const long long base = (long long)blockIdx.x * kScanBlock + threadIdx.x * kScanPer;
-    unsigned vals[kScanPer];
-    unsigned sum = 0;
+// Tiles of the pixel box [x0, x1] x [y0, y1] (empty: x1 < x0).
+struct TileBox {
+    int tx0, ty0, ntx;
+    unsigned n;
+};
+__device__ __forceinline__ TileBox tile_box(int x0, int x1, int y0, int y1, int shift) {
+    TileBox b;
+    b.tx0 = x0 >> shift;
+    b.ty0 = y0 >> shift;
+    b.ntx = (x1 >> shift) - b.tx0 + 1;
+    b.n = x0 <= x1 && y0 <= y1 ? (unsigned)(b.ntx * ((y1 >> shift) - b.ty0 + 1)) : 0u;
+    return b;
+}
+__device__ __forceinline__ TileBox tile_box(const TriSetup &s, int shift) {
+    return tile_box(s.bx0, s.bx1, s.by0, s.by1, shift);
+}
+
+// Triangles with at most kBigBin tiles are binned by their wave.  The setup
+// lists the larger ones (large_list) and cuts them into items of kLargeChunk
+// pairs, a workgroup's work each, so that a ground polygon's 65,536 tiles are
+// 64 workgroups' work and not one's.  The items fit unless the pairs exceed
+// the bin capacity; then the passes walk large_list instead (for_large_items).
+__device__ __forceinline__ void list_large(unsigned t, unsigned n, const LargeLists &l, DevCounters *counters) {
+    l.list[atomicAdd(&counters->large_len, 1u)] = t;
+    const unsigned k = (n + kLargeChunk - 1) / kLargeChunk;
+    const unsigned at = atomicAdd(&counters->item_len, k);
+    for (unsigned q = 0; q < k && at + q < l.item_cap; ++q) l.items[at + q] = make_uint2(t, q * kLargeChunk);
+}
+
+// Per (view, triangle): the corners' clip coordinates (in the fixed order of
+// clip_of), the fixed-point record, the facing byte and the number of tiles,
+// scanned within the workgroup (pair_local, block totals).  The first view of
+// each scene also writes the faces' TriVerts records: world positions and
+// albedo gathered once, so that per-pixel passes fetch one record.  Bound by
+// the latency of the index -> vertex loads.
+__global__ __launch_bounds__(kTriThreads) void setup_kernel(
+    const ViewConst *__restrict__ views, const TriBlock *__restrict__ blocks, const int *__restrict__ faces,
+    const float *__restrict__ verts, const float *__restrict__ albedo, int C, TriVerts *__restrict__ tv,
+    TriSetup *__restrict__ setup, signed char *__restrict__ facing8, unsigned *__restrict__ pair_local,
+    unsigned *__restrict__ block_total, LargeLists large, int shift, DevCounters *counters) {
+    const TriBlock blk = blocks[blockIdx.x];
+    const ViewConst &v = views[blk.view];
+    const float hw = 0.5f * (float)v.W, hh = 0.5f * (float)v.H;
+    const int t = blk.first + (int)threadIdx.x;
+    unsigned npairs[1] = {0u}, nculled = 0, nbad = 0;
+    if (t < v.nfaces) {
+        const int *f = faces + 3 * (size_t)(v.face_off + t);
+        int idx[3] = {f[0], f[1], f[2]};
+        bool bad = false;
 #pragma unroll
-    for (int k = 0; k < kScanPer; ++k) {
-        vals[k] = (base + k < n) ? in[base + k] : 0u;
-        sum += vals[k];
-    }
-    unsigned total;
-    unsigned off = block_exclusive_scan(sum, &total);
+        for (int k = 0; k < 3; ++k)
+            if (idx[k] < 0 || idx[k] >= v.nverts) { bad = true; idx[k] = 0; }
+        float p[3][3];
 #pragma unroll
-    for (int k = 0; k < kScanPer; ++k) {
-        if (base + k < n) out[base + k] = off;
-        off += vals[k];
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) p[k][c] = verts[3 * (size_t)(v.vert_off + idx[k]) + c];
+        if (v.write_tv) {
+            TriVerts r;
+            const float *rho = albedo + (size_t)(v.face_off + t) * C;
+            r.a = make_float4(p[0][0], p[0][1], p[0][2], p[1][0]);
+            r.b = make_float4(p[1][1], p[1][2], p[2][0], p[2][1]);
+            r.c = make_float4(p[2][2], rho[0], C > 1 ? rho[1] : 0.f, C > 2 ? rho[2] : 0.f);
+            tv[v.face_off + t] = r;
+        }
+        int X[3], Y[3];
+        float z[3];
+        bool ok = !bad;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const float4 c = clip_of(v.M, p[k][0], p[k][1], p[k][2]);
+            const float nx = c.x / c.w, ny = c.y / c.w, nz = c.z / c.w;
+            const float sx = (nx + 1.0f) * hw;
+            const float sy = (1.0f - ny) * hh;
+            const bool okv = (c.w > 0.0f) && (nz >= -1.0f) && (fabsf(sx) < kGuard) && (fabsf(sy) < kGuard);
+            ok = ok && okv;
+            X[k] = okv ? (int)rintf(sx * 256.0f) : 0;
+            Y[k] = okv ? (int)rintf(sy * 256.0f) : 0;
+            z[k] = 0.5f * nz + 0.5f;
+        }
+        long long A = (long long)(X[1] - X[0]) * (Y[2] - Y[0]) - (long long)(Y[1] - Y[0]) * (X[2] - X[0]);
+        const bool swapped = A < 0;
+        if (swapped) {
+            int ti = X[1]; X[1] = X[2]; X[2] = ti;
+            ti = Y[1]; Y[1] = Y[2]; Y[2] = ti;
+            float tz = z[1]; z[1] = z[2]; z[2] = tz;
+            A = -A;
+        }
+        const bool valid = ok && A > 0;
+        TriSetup s;
+        s.A = A;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) { s.X[k] = X[k]; s.Y[k] = Y[k]; s.z[k] = z[k]; }
+        s.facing = valid ? (swapped ? -1 : 1) : 0;
+        s.swapped = swapped ? 1 : 0;
+        s.sil = 0;
+        s.pad1 = 0;
+        s.pad2[0] = blk.view;
+        s.pad2[1] = 0;
+        int i0 = 1, i1 = 0, j0 = 1, j1 = 0;
+        if (valid) {
+            const int mnx = min(X[0], min(X[1], X[2])), mxx = max(X[0], max(X[1], X[2]));
+            const int mny = min(Y[0], min(Y[1], Y[2])), mxy = max(Y[0], max(Y[1], Y[2]));
+            // pixel centres 256 i + 128 inside [mnx, mxx]
+            i0 = max(floor_div256(mnx - 128 + 255), 0);
+            i1 = min(floor_div256(mxx - 128), v.W - 1);
+            j0 = max(floor_div256(mny - 128 + 255), 0);
+            j1 = min(floor_div256(mxy - 128), v.H - 1);
+        }
+        if (!(i0 <= i1 && j0 <= j1)) { i0 = 1; i1 = 0; j0 = 1; j1 = 0; }
+        s.bx0 = (unsigned short)i0;
+        s.bx1 = (unsigned short)i1;
+        s.by0 = (unsigned short)j0;
+        s.by1 = (unsigned short)j1;
+        setup[v.setup_off + t] = s;
+        facing8[v.setup_off + t] = s.facing;
+        npairs[0] = tile_box(i0, i1, j0, j1, shift).n;
+        if (npairs[0] > kBigBin) list_large((unsigned)(v.setup_off + t), npairs[0], large, counters);
+        nculled += !ok && !bad ? 1u : 0u;
+        nbad += bad ? 1u : 0u;
     }
-    if (threadIdx.x == 0) block_sums[blockIdx.x] = total;
-}
-
-// One workgroup per scan block: its offset is the sum of the block sums
-// before it (nb <= kScanBlock, so each thread adds at most kScanPer of
-// them), added to the block's kScanBlock outputs.  The last block also
-// writes the grand total to out[n]; with n = 0 one workgroup writes 0.
-__global__ __launch_bounds__(kScanThreads) void scan_add_kernel(unsigned *out, const unsigned *block_sums, int n,
-                                                                int nb) {
-    const int b = blockIdx.x;
-    unsigned part = 0;
-    for (int k = threadIdx.x; k < b; k += kScanThreads) part += block_sums[k];
-    unsigned off;
-    block_exclusive_scan(part, &off);
-    const long long base = (long long)b * kScanBlock;
-    for (int k = threadIdx.x; k < kScanBlock; k += kScanThreads)
-        if (base + k < n) out[base + k] += off;
-    if (threadIdx.x == 0) {
-        if (nb == 0) out[0] = 0u;
-        else if (b == nb - 1) out[n] = off + block_sums[b];
+    unsigned off[1], total;
+    tri_block_scan(npairs, off, &total);
+    if (t < v.nfaces) pair_local[v.setup_off + t] = off[0];
+    if (threadIdx.x == 0) block_total[blockIdx.x] = total;
+    if (__ballot(nculled + nbad != 0)) {
+        if (nculled) atomicAdd(&counters->culled, (unsigned long long)nculled);
+        if (nbad) atomicAdd(&counters->bad_indices, (unsigned long long)nbad);
     }
-}
-
-// Exclusive scan of n values in place-capable form: out[0..n] (out[n] = total).
-// scratch: at least scan_scratch_words(n) words.
-int scan_scratch_words(int n) { return (n + kScanBlock - 1) / kScanBlock + 1; }
-
-hipError_t launch_scan(const unsigned *in, unsigned *out, unsigned *scratch, int n, hipStream_t s) {
-    const int nb = (n + kScanBlock - 1) / kScanBlock;
-    if (nb > kScanBlock) return hipErrorInvalidValue;
-    if (nb > 0) hipLaunchKernelGGL(scan_blocks_kernel, dim3(nb), dim3(kScanThreads), 0, s, in, out, scratch, n);
-    hipLaunchKernelGGL(scan_add_kernel, dim3(nb > 0 ? nb : 1), dim3(kScanThreads), 0, s, out, scratch, n, nb);
-    return hipGetLastError();
 }
 
 // ----------------------------------------------------------------------------- binning
 
 // Pairs of triangle i are the tiles of its bounding box in row-major order,
-// numbered pair_off[i] .. pair_off[i+1]-1.  FILL = false counts pairs per
-// tile and records each pair's slot in its tile (pair_slot, indexed by
-// pair); FILL = true scatters (triangle, pair) to tile_start[tile] + slot,
-// with no atomics.  Pairs q0, q0 + step, ... of the triangle are handled by
-// the calling thread.
-template <bool FILL>
-__device__ __forceinline__ void bin_pairs(const ViewConst *__restrict__ views, const TriSetup &s, int i, unsigned a,
-                                          unsigned b, int tile, unsigned q0, unsigned step,
-                                          unsigned *__restrict__ tile_count, unsigned *__restrict__ pair_slot,
-                                          const unsigned *__restrict__ tile_start, unsigned *__restrict__ bins,
-                                          unsigned *__restrict__ bin_pair) {
-    const ViewConst &v = views[s.pad2[0]];
-    const int tx0 = s.bx0 / tile, tx1 = s.bx1 / tile, ty0 = s.by0 / tile;
-    const int ntx = tx1 - tx0 + 1;
-    for (unsigned q = q0; q < b - a; q += step) {
-        const int tx = tx0 + (int)(q % ntx), ty = ty0 + (int)(q / ntx);
-        const int gt = v.tile_off + ty * v.tiles_x + tx;
-        if (!FILL) {
-            pair_slot[a + q] = atomicAdd(&tile_count[gt], 1u);
-        } else {
-            const unsigned pos = tile_start[gt] + pair_slot[a + q];
-            bins[pos] = (unsigned)i;
-            bin_pair[pos] = a + q;
-        }
-    }
-}
+// numbered pair_off[i] .. pair_off[i+1]-1.  The count pass counts pairs per
+// tile and records each pair's slot in its tile (pair_slot, by pair); the
+// fill pass scatters the triangle (and, where the backward walks bins, the
+// pair) to tile start + slot, with no atomics.  Triangles whose pair range
+// does not fit the bin capacity go to the overflow path instead (decided per
+// triangle, so never split).
 
-// Add each active lane's 1 to cnt[g], one atomic per distinct g in the wave
-// (neighbouring triangles of a mesh mostly share tiles), and return the
-// lane's slot: the old count plus its rank among the lanes with the same g.
-// All leaders' atomics are issued together, so the wave waits for one round
-// trip.  Uniform call (all 64 lanes).
-__device__ __forceinline__ unsigned wave_aggregated_slot(bool has, int g, unsigned *__restrict__ cnt) {
+// Tile starts are scanned in blocks of kScanBlock tiles whose bases come from
+// a running total, so every block keeps its own end: the start of tile t is
+// at t + (t >> kScanShift), its end one further.
+__device__ __forceinline__ int tile_start_at(int t) { return t + (t >> kScanShift); }
+
+// One counter atomic per distinct g in the wave (neighbouring triangles of a
+// mesh mostly share tiles): size lanes hold the leader's g, which adds size to
+// the counter; a lane's slot is the old count plus its rank.  A round per
+// distinct g is a serial chain, so after kSlotRounds the remaining lanes add
+// their own 1, as all do where few triangles (share = false) hold the step's
+// pairs: their tiles are distinct.  Uniform call (all 64 lanes).
+constexpr int kSlotRounds = 24;
+struct WaveSlot {
+    int leader;
+    unsigned rank, size;     // size: leaders only, else 0
+};
+__device__ __forceinline__ WaveSlot wave_slot(bool has, int g, bool share) {
     const int lane = (int)(threadIdx.x & 63);
-    unsigned long long pending = __ballot(has);
-    int leader_of = lane;
-    unsigned rank = 0, size = 0;
-    while (pending) {
+    unsigned long long pending = share ? __ballot(has) : 0ull;
+    WaveSlot s{lane, 0u, has ? 1u : 0u};
+    for (int k = 0; pending && k < kSlotRounds; ++k) {
         const int leader = __ffsll(pending) - 1;
         const int gg = __builtin_amdgcn_readlane(g, leader);
         const bool mine = has && g == gg;
         const unsigned long long m = __ballot(mine);
         pending &= ~m;
         if (mine) {
-            leader_of = leader;
-            rank = (unsigned)__popcll(m & ((1ull << lane) - 1ull));
-            if (lane == leader) size = (unsigned)__popcll(m);
+            s.leader = leader;
+            s.rank = (unsigned)__popcll(m & ((1ull << lane) - 1ull));
+            s.size = lane == leader ? (unsigned)__popcll(m) : 0u;
         }
     }
-    unsigned base = 0;
-    if (size) base = atomicAdd(&cnt[g], size);
-    base = (unsigned)__shfl((int)base, leader_of, 64);
-    return base + rank;
+    return s;
 }
 
-// Triangles with at most kBigBin pairs: one thread each.  Larger ones are
-// listed (count pass) and handled a workgroup each, by bin_big_kernel in the
-// count pass and by the fill pass's workgroups past nsmall.
-// Triangles whose pair range does not fit the bin capacity go to the
-// overflow path instead (decided per triangle, so never split).
-constexpr unsigned kBigBin = 32;
+// The pairs of a wave's 64 triangles (cnt each, at most kBigBin), flattened:
+// kPairSteps * 64 pairs a round in pair order, a pair a lane and step, so that
+// a round's loads and atomics are in flight together.  A step's owners come
+// from one bit mask of the triangles that start in it.  f(n, box, q, has) is
+// called once a round by all lanes: n steps with the triangle's box, the pair
+// within the triangle, whether the lane has a pair, and how many triangles
+// start in the step.
+struct BinItem {
+    int tile0, ntx;          // first tile of the box in the global tile list, box width
+    unsigned first, a, tri;  // first flat pair, first pair, setup index
+};
+constexpr int kPairSteps = 4;
+struct BinWave {
+    BinItem item[64];
+    unsigned long long mask[kPairSteps];
+};
 
-template <bool FILL>
-__global__ void bin_small_kernel(const ViewConst *__restrict__ views, const TriSetup *__restrict__ setup,
-                                 const unsigned *__restrict__ pair_off, int ntri, unsigned capacity, int tile,
-                                 unsigned *__restrict__ tile_count, unsigned *__restrict__ pair_slot,
-                                 const unsigned *__restrict__ tile_start, unsigned *__restrict__ bins,
-                                 unsigned *__restrict__ bin_pair, unsigned *__restrict__ big_list,
-                                 unsigned *__restrict__ overflow_list, DevCounters *counters, int nsmall) {
-    if (FILL && (int)blockIdx.x >= nsmall) {
-        // workgroups past the triangles' own: the listed large triangles, a
-        // workgroup each (their list is complete after the count pass)
-        const unsigned n = counters->big_bin_len;
-        for (unsigned o = blockIdx.x - nsmall; o < n; o += gridDim.x - nsmall) {
-            const int t = (int)big_list[o];
-            bin_pairs<true>(views, setup[t], t, pair_off[t], pair_off[t + 1], tile, threadIdx.x, blockDim.x, tile_count,
-                            pair_slot, tile_start, bins, bin_pair);
+template <class F>
+__device__ __forceinline__ void for_wave_pairs(BinWave &w, unsigned cnt, BinItem it, F f) {
+    const int lane = (int)(threadIdx.x & 63);
+    unsigned x = cnt;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    const unsigned total = (unsigned)__builtin_amdgcn_readlane((int)x, 63);
+    it.first = x - cnt;
+    const unsigned long long some = __ballot(cnt > 0);
+    const int place = __popcll(some & ((1ull << lane) - 1ull));
+    if (cnt > 0) w.item[place] = it;
+    int before = 0;                                   // triangles that started in earlier steps
+    for (unsigned c = 0; c < total; c += 64 * kPairSteps) {
+        wave_sync();
+        if (lane < kPairSteps) w.mask[lane] = 0ull;
+        wave_sync();
+        const unsigned at = it.first - c;
+        if (cnt > 0 && it.first >= c && at < 64 * kPairSteps) atomicOr(&w.mask[at >> 6], 1ull << (at & 63));
+        wave_sync();
+        BinItem b[kPairSteps];
+        unsigned q[kPairSteps];
+        bool has[kPairSteps];
+        int starts[kPairSteps];
+        const int n = (int)min((total - c + 63) / 64, (unsigned)kPairSteps);
+#pragma unroll
+        for (int u = 0; u < kPairSteps; ++u) {
+            const unsigned p = c + 64 * u + (unsigned)lane;
+            has[u] = p < total;
+            starts[u] = 0;
+            if (u < n) {                              // uniform
+                const unsigned long long m = w.mask[u];
+                b[u] = w.item[has[u] ? before + __popcll(m & (~0ull >> (63 - lane))) - 1 : 0];
+                q[u] = p - b[u].first;
+                starts[u] = __popcll(m);
+                before += starts[u];
+            }
         }
+        f(n, b, q, has, starts);
+    }
+    wave_sync();
+}
+
+// q / n for q < 2^12, 1 <= n: the product with the hardware reciprocal is off
+// by under 2^-10, the quotient's distance from a whole number at least 1 / 2n.
+__device__ __forceinline__ unsigned small_div(unsigned q, int n) {
+    return (unsigned)(((float)q + 0.5f) * __builtin_amdgcn_rcpf((float)n));
+}
+
+// Pairs [q0, q1), at most kLargeChunk, of one large triangle by the whole
+// workgroup, every pair's load or atomic in flight together.
+template <bool FILL>
+__device__ __forceinline__ void bin_range(const ViewConst &v, const TriSetup &s, unsigned tri, unsigned a, unsigned q0,
+                                          unsigned q1, int shift, unsigned *__restrict__ tile_count,
+                                          unsigned *__restrict__ pair_slot, const unsigned *__restrict__ tile_start,
+                                          unsigned *__restrict__ bins, unsigned *__restrict__ bin_pair) {
+    constexpr int PER = kLargeChunk / kTriThreads;
+    const TileBox b = tile_box(s, shift);
+    int gt[PER];
+    unsigned slot[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const unsigned q = q0 + (unsigned)(k * kTriThreads) + threadIdx.x;
+        gt[k] = v.tile_off + (b.ty0 + (int)(q / b.ntx)) * v.tiles_x + b.tx0 + (int)(q % b.ntx);
+        slot[k] = 0u;
+        if (q < q1) slot[k] = FILL ? tile_start[tile_start_at(gt[k])] + pair_slot[a + q] : atomicAdd(&tile_count[gt[k]], 1u);
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const unsigned q = q0 + (unsigned)(k * kTriThreads) + threadIdx.x;
+        if (q >= q1) break;
+        if (!FILL) {
+            pair_slot[a + q] = slot[k];
+        } else {
+            bins[slot[k]] = tri;
+            if (bin_pair) bin_pair[slot[k]] = a + q;
+        }
+    }
+}
+
+// Workgroups past the triangles' own: the listed large triangles.
+// off(t): first pair of triangle t.
+template <bool FILL, class Off>
+__device__ __forceinline__ void bin_large(const ViewConst *__restrict__ views, const TriSetup *__restrict__ setup,
+                                          unsigned capacity, int shift, int b, unsigned *__restrict__ tile_count,
+                                          unsigned *__restrict__ pair_slot, const unsigned *__restrict__ tile_start,
+                                          unsigned *__restrict__ bins, unsigned *__restrict__ bin_pair,
+                                          const LargeLists &large, const DevCounters *counters, Off off) {
+    for_large_items(large, counters, b, kLargeBlocks, [&](unsigned t) { return tile_box(setup[t], shift).n; },
+                    [&](unsigned t, unsigned q0, unsigned n) {
+                        const unsigned a = off(t);
+                        if (a + n > capacity || a + n < a) return;          // overflow path
+                        const TriSetup &s = setup[t];
+                        bin_range<FILL>(views[s.pad2[0]], s, t, a, q0, min(q0 + kLargeChunk, n), shift, tile_count,
+                                        pair_slot, tile_start, bins, bin_pair);
+                    });
+}
+
+// Silhouette mask of (view, triangle): oriented edge e is a silhouette when
+// no triangle or more than one other triangle shares it, or when the
+// neighbour across it faces the other way in this view.
+__device__ __forceinline__ unsigned char silhouette_mask(const int *__restrict__ adj,
+                                                         const signed char *__restrict__ facing_view, int t,
+                                                         size_t face) {
+    const int facing = facing_view[t];
+    if (facing == 0) return 0;
+    const bool sw = facing < 0;        // second and third vertex were exchanged
+    const int nb[3] = {adj[3 * face], adj[3 * face + 1], adj[3 * face + 2]};
+    unsigned mask = 0;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+        const int a = (e + 1) % 3, b = (e + 2) % 3;
+        const int oa = sw ? (a == 0 ? 0 : 3 - a) : a, ob = sw ? (b == 0 ? 0 : 3 - b) : b;
+        const int o = 3 - oa - ob, n = o == 0 ? nb[0] : o == 1 ? nb[1] : nb[2];
+        if (n < 0 || facing_view[n] != facing) mask |= 1u << e;
+    }
+    return (unsigned char)mask;
+}
+
+// Totals of the triangle passes' workgroups scanned in place by one workgroup,
+// for plans with more than kMaxTriBlocks of them.
+__global__ __launch_bounds__(kTriThreads) void block_prefix_kernel(unsigned *__restrict__ total, int n) {
+    __shared__ unsigned carry;
+    const int tid = (int)threadIdx.x;
+    if (tid == 0) carry = 0;
+    for (int c = 0; c < n; c += 16 * kTriThreads) {
+        unsigned v[16], o[16], sum;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = c + k * kTriThreads + tid < n ? total[c + k * kTriThreads + tid] : 0u;
+        tri_block_scan(v, o, &sum);
+        const unsigned base = carry;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (c + k * kTriThreads + tid < n) total[c + k * kTriThreads + tid] = base + o[k];
+        if (tid == 0) {
+            carry = base + sum;
+            if (c + 16 * kTriThreads >= n) total[n] = base + sum;
+        }
+        __syncthreads();
+    }
+}
+
+// Count pass.  A triangle's first pair is its offset in its workgroup plus the
+// totals of the workgroups before, which every workgroup sums itself (or finds
+// scanned, past kMaxTriBlocks of them).  The silhouette masks ride along: they need every
+// facing byte, as this pass needs every total.  Bound by the latency of the
+// tile counters' atomics.
+__global__ __launch_bounds__(kTriThreads) void bin_count_kernel(
+    const ViewConst *__restrict__ views, const TriBlock *__restrict__ blocks, int nblocks,
+    const TriSetup *__restrict__ setup, const int *__restrict__ adj, const signed char *__restrict__ facing8,
+    unsigned char *__restrict__ silm, const unsigned *__restrict__ pair_local,
+    const unsigned *__restrict__ block_total, bool scanned, unsigned *__restrict__ pair_off, unsigned capacity, int shift,
+    int ntri,
+    unsigned *__restrict__ tile_count, unsigned *__restrict__ pair_slot, LargeLists large,
+    unsigned *__restrict__ overflow_list, DevCounters *counters) {
+    __shared__ BinWave wave[kTriThreads / 64];
+    const int tid = (int)threadIdx.x;
+    if ((int)blockIdx.x >= nblocks) {
+        if (counters->large_len == 0) return;
+        // the workgroup's own prefix of all totals, one entry per TriBlock
+        __shared__ unsigned prefix[kMaxTriBlocks];
+        __shared__ unsigned carry;
+        if (tid == 0) carry = 0;
+        for (int c = 0; c < nblocks && !scanned; c += kTriThreads) {
+            const unsigned v[1] = {c + tid < nblocks ? block_total[c + tid] : 0u};
+            unsigned o[1], total;
+            tri_block_scan(v, o, &total);
+            const unsigned base = carry;
+            __syncthreads();
+            if (c + tid < nblocks) prefix[c + tid] = base + o[0];
+            if (tid == 0) carry = base + total;
+            __syncthreads();
+        }
+        bin_large<false>(views, setup, capacity, shift, (int)blockIdx.x - nblocks, tile_count, pair_slot, nullptr,
+                         nullptr, nullptr, large, counters, [&](unsigned t) {
+                             const ViewConst &v = views[setup[t].pad2[0]];
+                             const int k = v.tri_block + (int)(t - v.setup_off) / kTriRun;
+                             return pair_local[t] + (scanned ? block_total[k] : prefix[k]);
+                         });
         return;
     }
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (!FILL && i == 0) counters->pairs = pair_off[ntri];   // total pairs, for the plan's statistics
-    unsigned a = 0, b = 0;
-    if (i < ntri) {
-        a = pair_off[i];
-        b = pair_off[i + 1];
-        if (b > capacity) {                                // overflow path (listed by the count pass)
-            if (!FILL && b > a) overflow_list[atomicAdd(&counters->overflow_list_len, 1u)] = (unsigned)i;
-            b = a;
-        }
-        if (b - a > kBigBin) {
-            if (!FILL) big_list[atomicAdd(&counters->big_bin_len, 1u)] = (unsigned)i;
-            b = a;
-        }
+    const TriBlock blk = blocks[blockIdx.x];
+    const ViewConst &v = views[blk.view];
+    __shared__ unsigned part[kTriThreads / 64];
+    unsigned sum = 0;
+    if (!scanned)
+        for (int k = tid; k < (int)blockIdx.x; k += kTriThreads) sum += block_total[k];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if ((tid & 63) == 0) part[tid >> 6] = sum;
+    __syncthreads();
+    const unsigned base = scanned ? block_total[blockIdx.x] : (part[0] + part[1]) + (part[2] + part[3]);
+    if ((int)blockIdx.x == nblocks - 1 && tid == 0) {
+        const unsigned total = scanned ? block_total[nblocks] : base + block_total[blockIdx.x];
+        pair_off[ntri] = total;
+        counters->pairs = total;       // for the plan's statistics
     }
-    const unsigned cnt = b - a;
-    if (__ballot(cnt > 0) == 0) return;                    // whole wave idle
-    TriSetup st{};
-    int tx0 = 0, ty0 = 0, ntx = 1, toff = 0, tiles_x = 0;
-    if (cnt > 0) {
-        st = setup[i];
-        const ViewConst &v = views[st.pad2[0]];
-        tx0 = st.bx0 / tile;
-        ty0 = st.by0 / tile;
-        ntx = st.bx1 / tile - tx0 + 1;
-        toff = v.tile_off;
-        tiles_x = v.tiles_x;
-    }
-    if (!FILL) {
-        for (unsigned q = 0; __ballot(q < cnt) != 0; ++q) {   // uniform loop: the wave's largest count
-            const bool has = q < cnt;
-            const int gt = has ? toff + (ty0 + (int)(q / ntx)) * tiles_x + tx0 + (int)(q % ntx) : 0;
-            const unsigned slot = wave_aggregated_slot(has, gt, tile_count);
-            if (has) pair_slot[a + q] = slot;
+    const int t = blk.first + tid;
+    unsigned cnt = 0;
+    BinItem it{};
+    if (t < v.nfaces) {
+        const int si = v.setup_off + t;
+        const TileBox b = tile_box(setup[si], shift);
+        it.a = pair_local[si] + base;
+        it.ntx = b.ntx;
+        it.tile0 = v.tile_off + b.ty0 * v.tiles_x + b.tx0;
+        pair_off[si] = it.a;
+        const unsigned end = it.a + b.n;
+        if (end > capacity) {                                // overflow path
+            if (b.n) overflow_list[atomicAdd(&counters->overflow_list_len, 1u)] = (unsigned)si;
+        } else if (b.n <= kBigBin) {
+            cnt = b.n;
         }
-    } else {
-        for (unsigned q = 0; q < cnt; ++q) {
-            const int gt = toff + (ty0 + (int)(q / ntx)) * tiles_x + tx0 + (int)(q % ntx);
-            const unsigned pos = tile_start[gt] + pair_slot[a + q];
-            bins[pos] = (unsigned)i;
-            bin_pair[pos] = a + q;
-        }
+        silm[si] = silhouette_mask(adj, facing8 + v.setup_off, t, (size_t)(v.face_off + t));
     }
+    for_wave_pairs(wave[tid >> 6], cnt, it,
+                   [&](int n, const BinItem (&b)[kPairSteps], const unsigned (&q)[kPairSteps],
+                       const bool (&has)[kPairSteps], const int (&starts)[kPairSteps]) {
+                       WaveSlot s[kPairSteps];
+                       unsigned base[kPairSteps];
+#pragma unroll
+                       for (int u = 0; u < kPairSteps; ++u) {
+                           base[u] = 0u;
+                           if (u >= n) continue;
+                           const unsigned r = small_div(q[u], b[u].ntx);
+                           const int gt = has[u] ? b[u].tile0 + (int)r * v.tiles_x + (int)(q[u] - r * (unsigned)b[u].ntx) : 0;
+                           s[u] = wave_slot(has[u], gt, starts[u] > 8);
+                           if (s[u].size) base[u] = atomicAdd(&tile_count[gt], s[u].size);
+                       }
+#pragma unroll
+                       for (int u = 0; u < kPairSteps; ++u)
+                           if (u < n) {
+                               const unsigned slot = (unsigned)__shfl((int)base[u], s[u].leader, 64) + s[u].rank;
+                               if (has[u]) pair_slot[b[u].a + q[u]] = slot;
+                           }
+                   });
 }
 
-template <bool FILL>
-__global__ void bin_big_kernel(const ViewConst *__restrict__ views, const TriSetup *__restrict__ setup,
-                               const unsigned *__restrict__ pair_off, int tile, unsigned *__restrict__ tile_count,
-                               unsigned *__restrict__ pair_slot, const unsigned *__restrict__ tile_start,
-                               unsigned *__restrict__ bins, unsigned *__restrict__ bin_pair,
-                               const unsigned *__restrict__ big_list, const DevCounters *counters) {
-    const unsigned n = counters->big_bin_len;
-    for (unsigned o = blockIdx.x; o < n; o += gridDim.x) {
-        const int i = (int)big_list[o];
-        bin_pairs<FILL>(views, setup[i], i, pair_off[i], pair_off[i + 1], tile, threadIdx.x, blockDim.x, tile_count,
-                        pair_slot, tile_start, bins, bin_pair);
+// Fill pass.  With overflowed triangles, the workgroups also clear the keys,
+// which the raster then minimizes into (raster_kernel).
+__global__ __launch_bounds__(kTriThreads) void bin_fill_kernel(
+    const ViewConst *__restrict__ views, const TriBlock *__restrict__ blocks, int nblocks,
+    const TriSetup *__restrict__ setup, const unsigned *__restrict__ pair_off, unsigned capacity, int shift,
+    unsigned *__restrict__ pair_slot, const unsigned *__restrict__ tile_start, unsigned *__restrict__ bins,
+    unsigned *__restrict__ bin_pair, LargeLists large, const DevCounters *counters,
+    unsigned long long *__restrict__ keys, long long nkeys) {
+    __shared__ BinWave wave[kTriThreads / 64];
+    const int tid = (int)threadIdx.x;
+    if (counters->overflow_list_len)
+        for (long long i = (long long)blockIdx.x * kTriThreads + tid; i < nkeys; i += (long long)gridDim.x * kTriThreads)
+            keys[i] = kBgKey;
+    if ((int)blockIdx.x >= nblocks) {
+        bin_large<true>(views, setup, capacity, shift, (int)blockIdx.x - nblocks, nullptr, pair_slot, tile_start, bins,
+                        bin_pair, large, counters, [&](unsigned t) { return pair_off[t]; });
+        return;
     }
+    const TriBlock blk = blocks[blockIdx.x];
+    const ViewConst &v = views[blk.view];
+    const int t = blk.first + tid;
+    unsigned cnt = 0;
+    BinItem it{};
+    if (t < v.nfaces) {
+        const int si = v.setup_off + t;
+        const TileBox b = tile_box(setup[si], shift);
+        it.a = pair_off[si];
+        it.ntx = b.ntx;
+        it.tile0 = v.tile_off + b.ty0 * v.tiles_x + b.tx0;
+        it.tri = (unsigned)si;
+        if (it.a + b.n <= capacity && b.n <= kBigBin) cnt = b.n;
+    }
+    for_wave_pairs(wave[tid >> 6], cnt, it,
+                   [&](int n, const BinItem (&b)[kPairSteps], const unsigned (&q)[kPairSteps],
+                       const bool (&has)[kPairSteps], const int (&starts)[kPairSteps]) {
+                       unsigned pos[kPairSteps];
+#pragma unroll
+                       for (int u = 0; u < kPairSteps; ++u) {
+                           pos[u] = 0u;
+                           if (u >= n || !has[u]) continue;
+                           const unsigned r = small_div(q[u], b[u].ntx);
+                           const int gt = b[u].tile0 + (int)r * v.tiles_x + (int)(q[u] - r * (unsigned)b[u].ntx);
+                           pos[u] = tile_start[tile_start_at(gt)] + pair_slot[b[u].a + q[u]];
+                       }
+#pragma unroll
+                       for (int u = 0; u < kPairSteps; ++u)
+                           if (u < n && has[u]) {
+                               bins[pos[u]] = b[u].tri;
+                               if (bin_pair) bin_pair[pos[u]] = b[u].a + q[u];
+                           }
+                   });
 }
 
+// Tile starts: a workgroup scans kScanBlock tiles' counts and takes its base
+// from the running total, so one launch does all of them (which block comes
+// first in the bins does not matter).
+__global__ __launch_bounds__(kTriThreads) void tile_scan_kernel(const unsigned *__restrict__ count,
+                                                                unsigned *__restrict__ start, int ntiles,
+                                                                DevCounters *counters) {
+    constexpr int PER = kScanBlock / kTriThreads;
+    const int t0 = blockIdx.x * kScanBlock;
+    unsigned v[PER], off[PER], total;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int t = t0 + k * kTriThreads + (int)threadIdx.x;
+        v[k] = t < ntiles ? count[t] : 0u;
+    }
+    tri_block_scan(v, off, &total);
+    __shared__ unsigned base;
+    if (threadIdx.x == 0) {
+        base = atomicAdd(&counters->bin_cursor, total);
+        start[tile_start_at(t0) + min(kScanBlock, ntiles - t0)] = base + total;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int t = t0 + k * kTriThreads + (int)threadIdx.x;
+        if (t < ntiles) start[tile_start_at(t)] = base + off[k];
+    }
+}
 
 // ----------------------------------------------------------------------------- raster
 
@@ -532,6 +720,32 @@ __device__ __forceinline__ bool touches(const RasterTri &r, int x0, int x1, int 
     return (__double2hiint(m0) | __double2hiint(m1) | __double2hiint(m2)) >= 0;
 }
 
+// Triangles that did not fit the bins: workgroup b of kOverflowBlocks takes
+// every kOverflowBlocks-th of the list, with an atomic minimum per covered
+// sample.  They run in the tile groups' launch; their keys and the groups'
+// meet in the same atomic minimum.  The first thread also adds the list's
+// length to the overflow count.
+constexpr int kOverflowBlocks = 512;
+__device__ __forceinline__ void overflow_raster(const ViewConst *__restrict__ views, const TriSetup *__restrict__ setup,
+                                                const unsigned *__restrict__ list, unsigned n, unsigned b,
+                                                DevCounters *counters, unsigned long long *__restrict__ keys) {
+    if (n && b == 0 && threadIdx.x == 0) counters->overflow += n;
+    for (unsigned o = b; o < n; o += kOverflowBlocks) {
+        const unsigned si = list[o];
+        const TriSetup &s = setup[si];
+        const ViewConst &v = views[s.pad2[0]];
+        const RasterTri r = load_raster_tri(s, si - (unsigned)v.setup_off, 0, 0);
+        const int w = s.bx1 - s.bx0 + 1, h = s.by1 - s.by0 + 1;
+        if (w <= 0 || h <= 0) continue;
+        const long long npix = (long long)w * h;
+        for (long long q = threadIdx.x; q < npix; q += blockDim.x) {
+            const int i = s.bx0 + (int)(q % w), j = s.by0 + (int)(q / w);
+            const unsigned long long key = pixel_key(r, sample_pos(i), sample_pos(j));
+            if (key != kBgKey) atomicMin(&keys[v.pix_off + (long long)j * v.W + i], key);
+        }
+    }
+}
+
 // One workgroup rasterizes a group of kGroup consecutive tiles of the global
 // tile list, whose bins are one contiguous range of entries.  The range
 // streams through the workgroup's lanes, an entry a lane: the lane reads the
@@ -561,9 +775,15 @@ template <int T>
 __global__ __launch_bounds__(kRasterThreads) void raster_kernel(
     const ViewConst *__restrict__ views, const int *__restrict__ tile_view, int ntiles,
     const TriSetup *__restrict__ setup, const unsigned *__restrict__ tile_start, const unsigned *__restrict__ bins,
-    unsigned long long *__restrict__ keys) {
+    unsigned long long *__restrict__ keys, const unsigned *__restrict__ overflow_list, DevCounters *counters,
+    int ngroups) {
     using RS = RasterShape<T>;
     constexpr int G = RS::kGroup;
+    const unsigned nover = counters->overflow_list_len;
+    if ((int)blockIdx.x >= ngroups) {
+        overflow_raster(views, setup, overflow_list, nover, (unsigned)((int)blockIdx.x - ngroups), counters, keys);
+        return;
+    }
     struct TileInfo {
         long long pix;           // key index of the tile's first sample
         int x0, y0, W, H, setup_off;
@@ -572,12 +792,12 @@ __global__ __launch_bounds__(kRasterThreads) void raster_kernel(
     __shared__ TileInfo info[G];
     __shared__ __align__(16) RasterTri wide[kRasterThreads];
     __shared__ unsigned nwide;
-    const int g0 = xcd_remap((int)blockIdx.x, (int)gridDim.x) * G;
+    const int g0 = xcd_remap((int)blockIdx.x, ngroups) * G;
     const int ng = min(G, ntiles - g0);
     const int tid = (int)threadIdx.x, lane = tid & 63;
     unsigned ts[G + 1];
 #pragma unroll
-    for (int k = 0; k <= G; ++k) ts[k] = tile_start[min(g0 + k, ntiles)];
+    for (int k = 0; k <= G; ++k) ts[k] = tile_start[tile_start_at(g0) + min(k, ng)];     // kScanBlock is whole groups
     // the first entry's record is requested before anything waits
     unsigned e = ts[0] + (unsigned)tid;
     unsigned si = 0;
@@ -694,32 +914,11 @@ __global__ __launch_bounds__(kRasterThreads) void raster_kernel(
         const int row = q / (G * T), col = q % (G * T), k = col / T, lx = col % T;
         if (k >= ng) continue;
         const TileInfo &ti = info[k];
-        if (ti.x0 + lx < ti.W && ti.y0 + row < ti.H)
-            keys[ti.pix + (long long)row * ti.W + lx] = best[k * (T * T) + row * T + lx];
-    }
-}
-
-// Triangles that did not fit the bins: one workgroup per listed triangle at
-// a time, atomic minimum over its bounding box.  The first thread also adds
-// the list's length to the overflow count.
-__global__ void overflow_raster_kernel(const ViewConst *__restrict__ views, const TriSetup *__restrict__ setup,
-                                       const unsigned *__restrict__ list, DevCounters *counters,
-                                       unsigned long long *__restrict__ keys) {
-    const unsigned n = counters->overflow_list_len;
-    if (blockIdx.x == 0 && threadIdx.x == 0) counters->overflow += n;
-    for (unsigned o = blockIdx.x; o < n; o += gridDim.x) {
-        const unsigned si = list[o];
-        const TriSetup &s = setup[si];
-        const ViewConst &v = views[s.pad2[0]];
-        const RasterTri r = load_raster_tri(s, si - (unsigned)v.setup_off, 0, 0);
-        const int w = s.bx1 - s.bx0 + 1, h = s.by1 - s.by0 + 1;
-        if (w <= 0 || h <= 0) continue;
-        const long long npix = (long long)w * h;
-        for (long long q = threadIdx.x; q < npix; q += blockDim.x) {
-            const int i = s.bx0 + (int)(q % w), j = s.by0 + (int)(q / w);
-            const unsigned long long key = pixel_key(r, sample_pos(i), sample_pos(j));
-            if (key != kBgKey) atomicMin(&keys[v.pix_off + (long long)j * v.W + i], key);
-        }
+        if (!(ti.x0 + lx < ti.W && ti.y0 + row < ti.H)) continue;
+        unsigned long long *key = keys + ti.pix + (long long)row * ti.W + lx;
+        const unsigned long long m = best[k * (T * T) + row * T + lx];
+        if (nover == 0) *key = m;
+        else if (m != kBgKey) atomicMin(key, m);       // with the overflowed triangles; the fill pass cleared the keys
     }
 }
 
@@ -736,70 +935,56 @@ hipError_t launch_light_frames(ViewConst *views, const CamStatic *cams, const fl
     return hipGetLastError();
 }
 
-hipError_t launch_transform(const ViewConst *views, int nviews, int max_verts, const float *verts, float4 *clip,
-                            hipStream_t s) {
-    if (nviews == 0 || max_verts == 0) return hipSuccess;
-    hipLaunchKernelGGL(transform_kernel, dim3((max_verts + 255) / 256, nviews), dim3(256), 0, s, views, verts, clip);
+hipError_t launch_setup(const ViewConst *views, const TriBlock *blocks, int nblocks, const int *faces,
+                        const float *verts, const float *albedo, int C, TriVerts *tv, TriSetup *setup,
+                        signed char *facing8, unsigned *pair_local, unsigned *block_total, const LargeLists &large,
+                        int tile, DevCounters *counters, hipStream_t s) {
+    if (nblocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(setup_kernel, dim3(nblocks), dim3(kTriThreads), 0, s, views, blocks, faces, verts, albedo, C, tv,
+                       setup, facing8, pair_local, block_total, large, __builtin_ctz(tile), counters);
     return hipGetLastError();
 }
 
-hipError_t launch_silhouettes(const ViewConst *views, int nviews, int max_faces, const int *adj,
-                              const signed char *facing8, unsigned char *silm, hipStream_t s) {
-    if (nviews == 0 || max_faces == 0) return hipSuccess;
-    hipLaunchKernelGGL(silhouette_kernel, dim3((max_faces + 255) / 256, nviews), dim3(256), 0, s, views, adj, facing8, silm);
-    return hipGetLastError();
-}
-
-hipError_t launch_setup(const ViewConst *views, int nviews, int max_faces, const int *faces, const float4 *clip,
-                        TriSetup *setup, signed char *facing8, unsigned *pair_count, int tile, DevCounters *counters,
-                        hipStream_t s) {
-    if (nviews == 0 || max_faces == 0) return hipSuccess;
-    hipLaunchKernelGGL(setup_kernel, dim3((max_faces + 255) / 256, nviews), dim3(256), 0, s, views, faces, clip,
-                       setup, facing8, pair_count, tile, counters);
-    return hipGetLastError();
-}
-
-hipError_t launch_binning(const ViewConst *views, const TriSetup *setup, const unsigned *pair_off, int ntri,
-                          unsigned capacity, int tile, unsigned *tile_count, unsigned *tile_start,
-                          unsigned *pair_slot, unsigned *scan_scratch, int ntiles, unsigned *bins,
-                          unsigned *bin_pair, unsigned *overflow_list, unsigned *big_list, DevCounters *counters,
+hipError_t launch_binning(const ViewConst *views, const TriBlock *blocks, int nblocks, const TriSetup *setup,
+                          const int *adj, const signed char *facing8, unsigned char *silm, const unsigned *pair_local,
+                          unsigned *block_total, unsigned *pair_off, int ntri, unsigned capacity, int tile,
+                          unsigned *tile_count, unsigned *tile_start, unsigned *pair_slot, int ntiles, unsigned *bins,
+                          unsigned *bin_pair, unsigned *overflow_list, const LargeLists &large,
+                          DevCounters *counters, unsigned long long *keys, long long nkeys,
                           hipStream_t s) {
-    const dim3 tgrid((ntri + 255) / 256);
-    const dim3 bgrid(1024);
-    if (ntri > 0) {
-        hipLaunchKernelGGL(bin_small_kernel<false>, tgrid, dim3(256), 0, s, views, setup, pair_off, ntri, capacity, tile,
-                           tile_count, pair_slot, (const unsigned *)nullptr, (unsigned *)nullptr, (unsigned *)nullptr,
-                           big_list, overflow_list, counters, (int)tgrid.x);
-        hipLaunchKernelGGL(bin_big_kernel<false>, bgrid, dim3(256), 0, s, views, setup, pair_off, tile, tile_count,
-                           pair_slot, (const unsigned *)nullptr, (unsigned *)nullptr, (unsigned *)nullptr,
-                           (const unsigned *)big_list, (const DevCounters *)counters);
-    }
-    hipError_t e = launch_scan(tile_count, tile_start, scan_scratch, ntiles, s);
-    if (e != hipSuccess) return e;
-    if (ntri > 0) {
-        // the fill pass and the large triangles' fill in one launch (bgrid.x extra workgroups)
-        hipLaunchKernelGGL(bin_small_kernel<true>, dim3(tgrid.x + bgrid.x), dim3(256), 0, s, views, setup, pair_off,
-                           ntri, capacity, tile, (unsigned *)nullptr, pair_slot, (const unsigned *)tile_start, bins,
-                           bin_pair, big_list, overflow_list, counters, (int)tgrid.x);
-    }
+    if (ntri > kScanBlock * kScanBlock || ntiles > kScanBlock * kScanBlock) return hipErrorInvalidValue;
+    const bool scanned = nblocks > kMaxTriBlocks;
+    if (scanned) hipLaunchKernelGGL(block_prefix_kernel, dim3(1), dim3(kTriThreads), 0, s, block_total, nblocks);
+    const dim3 grid(nblocks + kLargeBlocks);
+    const int shift = __builtin_ctz(tile);
+    if (nblocks > 0)
+        hipLaunchKernelGGL(bin_count_kernel, grid, dim3(kTriThreads), 0, s, views, blocks, nblocks, setup, adj, facing8,
+                           silm, pair_local, block_total, scanned, pair_off, capacity, shift, ntri, tile_count,
+                           pair_slot, large, overflow_list, counters);
+    if (ntiles > 0)
+        hipLaunchKernelGGL(tile_scan_kernel, dim3((ntiles + kScanBlock - 1) / kScanBlock), dim3(kTriThreads), 0, s,
+                           tile_count, tile_start, ntiles, counters);
+    if (nblocks > 0)
+        hipLaunchKernelGGL(bin_fill_kernel, grid, dim3(kTriThreads), 0, s, views, blocks, nblocks, setup, pair_off,
+                           capacity, shift, pair_slot, tile_start, bins, bin_pair, large, counters, keys,
+                           nkeys);
     return hipGetLastError();
 }
 
 hipError_t launch_raster(const ViewConst *views, const int *tile_view, int ntiles, int tile, const TriSetup *setup,
                          const unsigned *tile_start, const unsigned *bins, const unsigned *overflow_list,
-                         const DevCounters *counters_ro, DevCounters *counters, unsigned long long *keys,
-                         hipStream_t s) {
+                         DevCounters *counters, unsigned long long *keys, hipStream_t s) {
+    if (ntiles == 0) return hipSuccess;
 #define DSM_RASTER(TT)                                                                                              \
-    hipLaunchKernelGGL(raster_kernel<TT>, dim3((ntiles + RasterShape<TT>::kGroup - 1) / RasterShape<TT>::kGroup),  \
-                       dim3(kRasterThreads), 0, s, views, tile_view, ntiles, setup, tile_start, bins, keys)
-    if (ntiles > 0) {
-        if (tile == 8) DSM_RASTER(8);
-        else if (tile == 16) DSM_RASTER(16);
-        else DSM_RASTER(32);
-    }
+    do {                                                                                                            \
+        const int groups = (ntiles + RasterShape<TT>::kGroup - 1) / RasterShape<TT>::kGroup;                       \
+        hipLaunchKernelGGL(raster_kernel<TT>, dim3(groups + kOverflowBlocks), dim3(kRasterThreads), 0, s, views,   \
+                           tile_view, ntiles, setup, tile_start, bins, keys, overflow_list, counters, groups);     \
+    } while (0)
+    if (tile == 8) DSM_RASTER(8);
+    else if (tile == 16) DSM_RASTER(16);
+    else DSM_RASTER(32);
 #undef DSM_RASTER
-    hipLaunchKernelGGL(overflow_raster_kernel, dim3(512), dim3(256), 0, s, views, setup, overflow_list, counters,
-                       keys);
     return hipGetLastError();
 }
 

@@ -1,0 +1,64 @@
+"""Binning of triangles with many tiles: cut into items that workgroups share,
+at the sizes where the handling changes (32 tiles; one and several items), with
+more pairs than the bins hold (the items may then be incomplete and the passes
+walk the triangles), and with more workgroups than one scan of their totals
+(many small views).  Keys bit-exact against the oracle."""
+import numpy as np
+import pytest
+
+import scenegen as sg
+from parity_helpers import check_gradients, gpu_run, loss_grad, oracle_run
+
+pytestmark = pytest.mark.gpu
+
+
+def _planes(res, w, h):
+    """Stacked quads from a few tiles to the whole view, over a small cube."""
+    parts = [sg.quad(half, 0.02 * k) for k, half in enumerate((2.0, 1.3, 0.7, 0.33, 0.2, 0.1))]
+    v, f = sg.merge(parts + [sg.cube((0.3, 0.6, 0.1), 0.2)])
+    b = sg.config0()
+    b.scenes = [sg.Scene(verts=v, faces=f, albedo=np.full((len(f), 1), 0.8, np.float32))]
+    b.lights[0].resolution = res
+    b.cameras[0].width, b.cameras[0].height = w, h
+    return b
+
+
+def _keys_equal(g, o):
+    for v, (kg, ko) in enumerate(zip(g['keys'], o['keys'])):
+        assert np.array_equal(kg, ko), f'view {v}: {int((kg != ko).sum())} keys differ'
+
+
+@pytest.mark.parametrize('tile,bins', [(8, 0), (8, 1), (16, 0), (8, 2)])
+def test_large_triangles(tile, bins):
+    b = _planes(400, 333, 250)
+    o = oracle_run(b)
+    g = gpu_run(b, tile_size=tile, bin_scale=bins)
+    _keys_equal(g, o)
+    if bins == 0:
+        assert g['stats']['overflow'] == 0
+    if bins == 1:
+        assert g['stats']['overflow'] > 0
+
+
+def test_large_triangle_gradients():
+    b = _planes(400, 333, 250)
+    o = oracle_run(b)
+    check_gradients(b, loss_grad(b, o['images']), o)
+
+
+def test_more_workgroups_than_totals_summed_directly():
+    """600 one-cube scenes: 1200 views, a triangle workgroup each."""
+    one = sg.config0()
+    one.lights[0].resolution = 24
+    one.cameras[0].width = one.cameras[0].height = 24
+    many = sg.Batch('many', [], [], [], [], channels=1)
+    for i in range(600):
+        many.scenes.append(one.scenes[0])
+        many.lights.append(sg.Light(**{**one.lights[0].__dict__, 'scene': i}))
+        many.cameras.append(sg.Camera(**{**one.cameras[0].__dict__, 'scene': i}))
+        many.renders.append(sg.Render(i, [i]))
+    a, m = gpu_run(one), gpu_run(many)
+    for i in range(600):
+        assert np.array_equal(m['keys'][i], a['keys'][0]) and np.array_equal(m['keys'][600 + i], a['keys'][1])
+        assert np.array_equal(m['images'][i], a['images'][0])
+    assert m['stats']['pairs'] == 600 * a['stats']['pairs']
