@@ -364,7 +364,7 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
         v.part_off = (int)part_light;
         part_light += (long long)v.tiles_x * v.tiles_y;
         v.part_gm_off = (int)part_gm;
-        part_gm += (v.nverts + 255) / 256;
+        part_gm += (v.nverts + 63) / 64;
         p->max_light_regions = std::max(p->max_light_regions, aa_regions(x.resolution, x.resolution));
         p->max_light_texels = std::max(p->max_light_texels, x.resolution * x.resolution);
         p->max_light_tiles = std::max(p->max_light_tiles, v.tiles_x * v.tiles_y);
@@ -447,7 +447,6 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
         delete p;
         return DSM_ERR_INVALID_ARG;
     }
-    // pair rows are addressed with 32-bit offsets (pair * 21 + value)
     p->capacity = (unsigned)std::min<long long>((long long)bin_capacity_scale * (tri + tiles) / 4,
                                                 (long long)(0xFFFFFFFFu / 21u));
 
@@ -508,6 +507,7 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
     p->item_cap = (unsigned)std::min<long long>(tri + p->capacity / kLargeChunk, 0x7fffffff);
     p->sv_large = o; o = align_up(o + 4 * ((size_t)tri + 1));        // triangles of many tiles and their items
     p->sv_items = o; o = align_up(o + 8 * ((size_t)p->item_cap + 1));
+    p->sv_medium = o; o = align_up(o + 4 * ((size_t)tri + 1));
     p->sv_zc = o; o = align_up(o + 4 * (size_t)std::max(L, 1));
     p->sv_aa_flag = o; o = align_up(o + (size_t)pix);        // per sample: it has candidate smoothing pairs
     p->saved_bytes = std::max<size_t>(o, kAlign);
@@ -521,18 +521,17 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
     p->sc_pair_slot = o; o = align_up(o + 4 * (size_t)p->capacity);    // each pair's slot in its tile's bin
     p->sc_F1 = o; o = align_up(o + 4 * (size_t)(maps + padmaps));
     p->sc_fwd_end = o;                 // the forward touches nothing past this
-    p->sc_pair_flag = o; o = align_up(o + (size_t)p->capacity);
+    p->sc_pair_flag = o; o = align_up(o + (size_t)p->capacity + 4);      // read four bytes at a time
     p->sc_gimg0 = o; o = align_up(o + 4 * (size_t)img);
-    p->sc_bigcount = o; o = align_up(o + 64);
+    p->sc_done = o; o = align_up(o + 4 * (size_t)std::max(L, 1));       // the light-gradient sum's finished workgroups
     p->sc_zero_rec = o; o = align_up(o + 32);          // an all-zero corner record for the vertex gather
     p->sc_gM = o; o = align_up(o + 4 * (size_t)fmaps);
     p->sc_gclip = o; o = align_up(o + 16 * (size_t)clip);
     p->sc_zero_bwd_end = o;
     p->sc_glight = o; o = align_up(o + 4 * 3 * (size_t)kGlightBlocks * (size_t)std::max(L, 1));
     p->sc_gF1 = o; o = align_up(o + 4 * (size_t)(maps + padmaps));
-    p->sc_pair_sums = o; o = align_up(o + 4 * 21 * (size_t)p->capacity);
-    p->sc_gtri = o; o = align_up(o + 4 * 24 * ((size_t)tri + 1));       // three 8-float corner records per triangle
-    p->sc_biglist = o; o = align_up(o + 4 * ((size_t)tri + 1));
+    p->sc_pair_sums = o; o = align_up(o + 4 * 24 * (size_t)p->capacity);   // three 8-float corner records per pair
+    p->sc_gtri = o; o = align_up(o + 4 * 24 * ((size_t)tri + 1));          // ... per triangle (overflowed or large)
     p->sc_part_light = o; o = align_up(o + 4 * 3 * (size_t)(part_light + 1));
     p->sc_part_gm = o; o = align_up(o + 4 * 3 * (size_t)(part_gm + 1));
     p->sc_jac = o; o = align_up(o + 4 * (size_t)kJac * (size_t)std::max(L, 1));
@@ -575,6 +574,7 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
         for (int v = 0; v < p->nviews; ++v)
             if (p->views_h[v].scene == b) sv_list.push_back(v);
         sv_off[b + 1] = (int)sv_list.size();
+        p->max_scene_views = std::max(p->max_scene_views, sv_off[b + 1] - sv_off[b]);
     }
     std::vector<int> vc_off(Vt + 1, 0), vc_list(3 * (size_t)Ft);
     for (int b = 0; b < B; ++b)
@@ -699,7 +699,8 @@ dsm_status enqueue_forward(dsm_plan *p, const float *verts, const float *lparams
     unsigned *pair_local = at<unsigned>(scratch, p->sc_pair_local);
     unsigned *block_total = at<unsigned>(scratch, p->sc_block_total);
     unsigned *pair_off = at<unsigned>(saved, p->sv_pair_off);
-    const LargeLists large{at<unsigned>(saved, p->sv_large), at<uint2>(saved, p->sv_items), p->item_cap};
+    const LargeLists large{at<unsigned>(saved, p->sv_large), at<uint2>(saved, p->sv_items), p->item_cap,
+                           at<unsigned>(saved, p->sv_medium)};
     unsigned *tile_start = at<unsigned>(saved, p->sv_tile_start);
     unsigned *bins = at<unsigned>(saved, p->sv_bins);
     unsigned *bin_pair = p->tile == 8 ? nullptr : at<unsigned>(saved, p->sv_bin_pair);
@@ -717,7 +718,7 @@ dsm_status enqueue_forward(dsm_plan *p, const float *verts, const float *lparams
     DSM_MARK(DSM_STAGE_SETUP);
     // with the light frames, the counters (saved) and the tile counts (scratch) are cleared
     DSM_TRY(launch_light_frames(p->views_d, p->light_cams_d, lparams, p->L, nullptr, at<float>(saved, p->sv_zc), saved,
-                                p->sv_zero_end, scratch, p->sc_zero_fwd_end, s));
+                                p->sv_zero_end, scratch, p->sc_zero_fwd_end, ClearRows{}, s));
     signed char *facing8 = at<signed char>(scratch, p->sc_facing);
     DSM_TRY(launch_setup(p->views_d, p->tri_blocks_d, p->tri_blocks, p->faces_d, verts, albedo, p->C,
                          tv, setup, facing8, pair_local, block_total, large, p->tile, cnt, s));
@@ -765,25 +766,27 @@ dsm_status enqueue_backward(dsm_plan *p, const float *verts, const float *lparam
     unsigned char *pair_flag = at<unsigned char>(scratch, p->sc_pair_flag);
     const unsigned *overflow = at<unsigned>(saved, p->sv_overflow);
     float *gimg0 = at<float>(scratch, p->sc_gimg0);
-    unsigned *big_count = at<unsigned>(scratch, p->sc_bigcount);
     float *gM = at<float>(scratch, p->sc_gM);
     float4 *gclip = at<float4>(scratch, p->sc_gclip);
     float *gF1 = at<float>(scratch, p->sc_gF1);
     float *pair_sums = at<float>(scratch, p->sc_pair_sums);
     float *gtri = at<float>(scratch, p->sc_gtri);
-    unsigned *big_list = at<unsigned>(scratch, p->sc_biglist);
     float *part_light = at<float>(scratch, p->sc_part_light);
     float *part_gm = at<float>(scratch, p->sc_part_gm);
     float *part_render = at<float>(scratch, p->sc_part_render);
     float *jac = at<float>(scratch, p->sc_jac);
 
     DSM_MARK(DSM_STAGE_BWD_SETUP);
-    // with the light frames and their Jacobian: big count, zero corner record, gM, silhouette
-    // gclip; and the pair flags (the 8x8 tile walks set only the flags of pairs that got a sum)
-    DSM_TRY(launch_light_frames(p->views_d, p->light_cams_d, lparams, p->L, jac, nullptr, big_count,
-                                p->sc_zero_bwd_end - p->sc_bigcount, pair_flag, ((size_t)p->capacity + 3) & ~(size_t)3,
-                                s));
-    DSM_TRY(launch_overflow_rows_zero(overflow, cnt, gtri, s));
+    // with the light frames and their Jacobian: the light sum's counters, the zero corner record, gM and the
+    // silhouette gclip; the pair flags (the 8x8 tile walks set only the flags of pairs that got a sum); and the
+    // rows that atomics add to (overflowed and large triangles)
+    const LargeLists large{at<unsigned>(const_cast<void *>(saved), p->sv_large),
+                           at<uint2>(const_cast<void *>(saved), p->sv_items), p->item_cap,
+                           at<unsigned>(const_cast<void *>(saved), p->sv_medium)};
+    const ClearRows rows{gtri, overflow, large.list, &cnt->overflow_list_len, &cnt->large_len};
+    DSM_TRY(launch_light_frames(p->views_d, p->light_cams_d, lparams, p->L, jac, nullptr, at<void>(scratch, p->sc_done),
+                                p->sc_zero_bwd_end - p->sc_done, pair_flag, ((size_t)p->capacity + 3) & ~(size_t)3,
+                                rows, s));
     DSM_MARK(DSM_STAGE_CAMERA_AA_ADJ);
     DSM_TRY(launch_aa_camera_backward(p->views_d, p->L, p->Cm, p->max_cam_regions, p->max_cam_renders, p->renders_d,
                                       p->cam_renders_off_d, p->cam_renders_d, setup, p->faces_d, silm, verts, keys,
@@ -805,14 +808,15 @@ dsm_status enqueue_backward(dsm_plan *p, const float *verts, const float *lparam
                                   tv, keys, aa_flag, F0, gF1, gclip, tile_start, bins, bin_pair, pair_flag, pair_sums,
                                   gtri, part_light, jac, pair_off, p->capacity, s));
     DSM_MARK(DSM_STAGE_VERTEX_GRAD);
-    DSM_TRY(launch_vertex_gradients(p->views_d, p->L, p->B, p->max_scene_verts, p->max_scene_faces, p->ntri,
-                                    p->capacity, p->scene_vert_off_d, p->scene_face_off_d, p->scene_views_off_d,
-                                    p->scene_views_d, p->vc_off_d, p->vc_list_d, pair_off, pair_flag, pair_sums, gtri,
-                                    at<float>(scratch, p->sc_zero_rec), big_list,
-                                    big_count, verts, gclip, gverts, part_gm, galbedo, p->C, jac, s));
+    DSM_TRY(launch_vertex_gradients(p->views_d, p->L, p->B, p->max_scene_verts, p->max_scene_faces, p->max_scene_views,
+                                    p->ntri, p->capacity, setup, large, cnt, p->scene_vert_off_d, p->scene_face_off_d,
+                                    p->scene_views_off_d, p->scene_views_d, p->vc_off_d, p->vc_list_d, pair_off,
+                                    pair_flag, pair_sums, gtri, at<float>(scratch, p->sc_zero_rec), verts, gclip, gverts,
+                                    part_gm, galbedo, p->C, jac, s));
     DSM_MARK(DSM_STAGE_LIGHT_GRAD);
     DSM_TRY(launch_glight_reduce(p->views_d, p->L, p->renders_d, p->light_renders_off_d, p->light_renders_d, part_gm,
-                                 part_light, part_render, at<float>(scratch, p->sc_glight), glparams, s));
+                                 part_light, part_render, at<float>(scratch, p->sc_glight),
+                                 at<unsigned>(scratch, p->sc_done), glparams, s));
     DSM_MARK(DSM_STAGE_COUNT);
     return DSM_OK;
 }

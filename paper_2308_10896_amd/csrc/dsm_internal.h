@@ -39,7 +39,7 @@ struct ViewConst {
     int antialias;
     long long map_off;  // light views: first texel of the 2-channel maps (plane stride S*S)
     int part_off;       // light views: first per-tile slot of the backward light-frame partials
-    int part_gm_off;    // light views: first per-vertex-block slot of the dL/dM partials
+    int part_gm_off;    // light views: first slot of the dL/dM partials (one per 64 vertices)
     int cube_face;      // cube-face lights: face 0..5 (+x, -x, +y, -y, +z, -z)
     float warp_c;       // light views: exponential maps store exp(c z), exp(2 c z); 0 = plain z, z^2
     float bleed;        // light views: light-bleeding reduction amount
@@ -151,7 +151,8 @@ struct DevCounters {
     unsigned int overflow_list_len;
     unsigned int large_len, item_len; // listed large triangles and their items (LargeLists)
     unsigned int bin_cursor;         // running total of the tile scan
-    unsigned int pad[4];
+    unsigned int medium_len;         // listed triangles of kOwnRows + 1 .. kBigBin pairs
+    unsigned int pad[3];
 };
 
 // Triangles of more than kBigBin tiles, and their pairs in items (triangle,
@@ -159,10 +160,14 @@ struct DevCounters {
 // can fit the bins; with more pairs than that the items may be incomplete.
 constexpr unsigned kBigBin = 32, kLargeChunk = 512;
 constexpr int kLargeBlocks = 512;      // workgroups that take the items
+// medium lists the triangles of more than kOwnRows pairs that are not large:
+// the backward sums their rows before its gathers.
+constexpr unsigned kOwnRows = 4;
 struct LargeLists {
     unsigned *list;
     uint2 *items;
     unsigned item_cap;
+    unsigned *medium;
 };
 
 // f(t, q0, n) for workgroup b's share of the items, n the triangle's pairs
@@ -331,9 +336,16 @@ bool valid_filter(int S, int filter, int k);
 struct CamStatic;
 // Jacobian of a light frame (M[16], pos[3], dir[3]) w.r.t. its three parameter components, [22][3].
 constexpr int kJac = 66;
-// Also clears bytes1 at z1 and bytes2 at z2 (multiples of 4) in the same launch.
+// Also clears bytes1 at z1 and bytes2 at z2 (multiples of 4) and, with rows, the
+// 96-byte rows of the listed triangles, in the same launch.
+struct ClearRows {
+    float *rows;                    // nullptr: none
+    const unsigned *list_a, *list_b;
+    const unsigned *len_a, *len_b;
+};
 hipError_t launch_light_frames(ViewConst *views, const CamStatic *cams, const float *params, int L, float *jac,
-                               float *zc_out, void *z1, size_t bytes1, void *z2, size_t bytes2, hipStream_t s);
+                               float *zc_out, void *z1, size_t bytes1, void *z2, size_t bytes2, const ClearRows &rows,
+                               hipStream_t s);
 hipError_t launch_setup(const ViewConst *views, const TriBlock *blocks, int nblocks, const int *faces,
                         const float *verts, const float *albedo, int C, TriVerts *tv, TriSetup *setup,
                         signed char *facing8, unsigned *pair_local, unsigned *block_total, const LargeLists &large,
@@ -384,18 +396,18 @@ hipError_t launch_light_backward(int tile, const ViewConst *views, int L, int ma
                                  const unsigned *tile_start, const unsigned *bins, const unsigned *bin_pair,
                                  unsigned char *pair_flag, float *pair_sums, float *gtri, float *part_light,
                                  const float *jac, const unsigned *pair_off, unsigned capacity, hipStream_t s);
-hipError_t launch_vertex_gradients(const ViewConst *views, int L, int B, int max_verts, int max_faces, int ntri,
-                                   unsigned capacity, const int *scene_vert_off, const int *scene_face_off,
+hipError_t launch_vertex_gradients(const ViewConst *views, int L, int B, int max_verts, int max_faces, int max_views,
+                                   int ntri, unsigned capacity, const TriSetup *setup, const LargeLists &large,
+                                   const DevCounters *counters, const int *scene_vert_off, const int *scene_face_off,
                                    const int *scene_views_off, const int *scene_views, const int *vc_off,
                                    const int *vc_list, const unsigned *pair_off, const unsigned char *pair_flag,
-                                   const float *pair_sums, float *gtri, const float *zero_rec,
-                                   unsigned *big_list, unsigned *big_count, const float *verts, const float4 *gclip,
-                                   float *gverts, float *part_gm, float *galbedo, int C, const float *jac, hipStream_t s);
-hipError_t launch_overflow_rows_zero(const unsigned *list, const DevCounters *counters, float *gtri, hipStream_t s);
+                                   const float *pair_sums, float *gtri, const float *zero_rec, const float *verts,
+                                   const float4 *gclip, float *gverts, float *part_gm, float *galbedo, int C,
+                                   const float *jac, hipStream_t s);
 hipError_t launch_glight_reduce(const ViewConst *views, int L, const RenderConst *renders,
                                 const int *light_renders_off, const int *light_renders, const float *part_gm,
-                                const float *part_light, const float *part_render, float *gl_part, float *gparams,
-                                hipStream_t s);
+                                const float *part_light, const float *part_render, float *gl_part, unsigned *done,
+                                float *gparams, hipStream_t s);
 hipError_t launch_pose(const int *scene_vert_off, const int *pose_counts, const float *pose_centers, int B,
                        int max_verts, const float *local, const float *poses, float *world, hipStream_t s);
 hipError_t launch_pose_backward(const int *scene_vert_off, const int *pose_counts, int B, int max_verts,

@@ -18,6 +18,8 @@
 //
 // Vertex-indexed gradients are reduced per (tile, triangle) before they reach
 // global memory (see "tile accumulation" below).
+#include <algorithm>
+
 #include "aa.h"
 #include "dsm_internal.h"
 #include "frames.h"
@@ -282,14 +284,20 @@ __global__ __launch_bounds__(64) void aa_camera_backward_kernel(
 // terms and the bilinear moment-map scatter use atomics.
 constexpr int kNV = 21;   // per pair: 9 world-position terms, 9 clip (x, y, w) terms, 3 albedo terms
 
-// Per-triangle gradient rows (gtri) hold the same 21 values as three 8-float
-// corner records, [world x y z | clip x y w | albedo term of channel c | 0]
-// for corner c, so that the per-vertex gather reads one aligned 32-byte
-// sector per incident corner.  gtri_slot maps value index i (the pair-row
-// order above) to its place in the row.
-constexpr int kGtriStride = 24;
-__host__ __device__ constexpr int gtri_slot(int i) {
+// The rows of pairs (and those of gtri, of triangles that overflowed the bins
+// or have many pairs) hold the 21 values as three 8-float corner records,
+// [world x y z | clip x y w | albedo term of channel c | pad] for corner c, so
+// that the per-vertex gather reads one aligned 32-byte sector per incident
+// corner.  row_slot maps value index i to its place in the row.  Rows of light
+// views have no albedo terms.
+constexpr int kRow = 24;
+__host__ __device__ constexpr int row_slot(int i) {
     return i < 9 ? (i / 3) * 8 + i % 3 : i < 18 ? ((i - 9) / 3) * 8 + 3 + (i - 9) % 3 : (i - 18) * 8 + 6;
+}
+// Value index at place p of a row (pads and, for N < 21, albedo terms repeat value 0).
+template <int N>
+__host__ __device__ constexpr int row_value(int p) {
+    return p % 8 < 3 ? (p / 8) * 3 + p % 8 : p % 8 < 6 ? 9 + (p / 8) * 3 + p % 8 - 3 : p % 8 == 6 && N > 18 ? 18 + p / 8 : 0;
 }
 
 template <int T>
@@ -450,14 +458,14 @@ __device__ __forceinline__ void tile_pair_sums(const ViewConst &v, const BinHead
 #pragma unroll 1
             for (int it0 = 0; it0 < iters; it0 += G) {
                 float pv[G];
-                unsigned dst[G];
+                size_t dst[G];
                 bool wr[G];
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
                     const int f = tid + (it0 + g) * TS::NT;
                     const int e = min(f / N, CH - 1), i = f - (f / N) * N;
                     wr[g] = f < n * N && hit[e] != 0;
-                    dst[g] = slot[e] * (unsigned)kNV + (unsigned)i;
+                    dst[g] = (size_t)slot[e] * kRow + (size_t)row_slot(i);
                     pv[g] = part[min(f, CH * N - 1)];
                 }
 #pragma unroll
@@ -479,7 +487,7 @@ __device__ __forceinline__ void overflow_rows(const ViewConst &v, const int (&ke
         const bool a = active[k] && !matched[k];
         if (__ballot(a))
             scatter_by_key(a, key[k], val[k],
-                           [&](int t, int i) { return gtri + (size_t)(v.setup_off + t) * kGtriStride + gtri_slot(i); });
+                           [&](int t, int i) { return gtri + (size_t)(v.setup_off + t) * kRow + row_slot(i); });
     }
 }
 
@@ -537,7 +545,7 @@ __device__ __forceinline__ void wave_pair_sums(const ViewConst &v, int tx, int t
         for (int i = 0; i < N; ++i) masked[i] = in ? val[i] : 0.f;
         const float t = wave_sum_multi(masked);          // lane 2i: the group's total of value i
         const unsigned sl = (unsigned)__builtin_amdgcn_readlane((int)slot, l);
-        if ((lane & 1) == 0 && (lane >> 1) < N) pair_sums[(size_t)sl * kNV + (lane >> 1)] = t;
+        if ((lane & 1) == 0 && (lane >> 1) < N) pair_sums[(size_t)sl * kRow + row_slot(lane >> 1)] = t;
         if (lane == l) pair_flag[sl] = 1;
         mine = mine && !in;
     }
@@ -554,8 +562,11 @@ __device__ __forceinline__ void wave_pair_sums(const ViewConst &v, int tx, int t
     }
     __syncthreads();
     if (lead) {
+        float4 *row = (float4 *)(pair_sums + (size_t)slot * kRow);
 #pragma unroll
-        for (int i = 0; i < N; ++i) pair_sums[(size_t)slot * kNV + i] = part[lane * N + i];
+        for (int q = 0; q < kRow / 4; ++q)
+            row[q] = make_float4(part[lane * N + row_value<N>(4 * q)], part[lane * N + row_value<N>(4 * q + 1)],
+                                 part[lane * N + row_value<N>(4 * q + 2)], part[lane * N + row_value<N>(4 * q + 3)]);
         pair_flag[slot] = 1;
     }
     __syncthreads();
@@ -1179,60 +1190,109 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void l
 
 // ----------------------------------------------------------------------------- gathers
 
-// Zero the gtri rows of triangles that overflowed the bins (their pixels are
-// added there with atomics) and reset the big-triangle list.
-__global__ void overflow_rows_zero_kernel(const unsigned *__restrict__ list, const DevCounters *counters,
-                                          float *__restrict__ gtri) {
-    const unsigned n = counters->overflow_list_len;
-    for (unsigned o = blockIdx.x; o < n; o += gridDim.x)
-        for (int i = threadIdx.x; i < kGtriStride; i += blockDim.x) gtri[(size_t)list[o] * kGtriStride + i] = 0.f;
+// A triangle's gradient is the sum of its flagged pair rows: up to kOwnRows of
+// them are read where it is needed; overflowed triangles and those with more
+// pairs have one row in gtri.
+struct TriRows {
+    const float *rows;       // first row
+    unsigned mask;           // rows that hold a sum
+};
+__device__ __forceinline__ unsigned flag_word(const unsigned char *p) {      // four flag bytes, any alignment
+    unsigned w;
+    __builtin_memcpy(&w, p, 4);
+    return w;
+}
+// Rows of triangle t with pairs [a, b); w: the flag bytes from a on.
+__device__ __forceinline__ TriRows tri_rows(unsigned t, unsigned a, unsigned b, unsigned w, unsigned capacity,
+                                            const float *__restrict__ pair_sums, const float *__restrict__ gtri) {
+    static_assert(kOwnRows == 4, "one word of flags");
+    const unsigned n = b - a;
+    if (n > kOwnRows || b > capacity) return TriRows{gtri + (size_t)t * kRow, n ? 1u : 0u};
+    const unsigned m = (w & 1u) | (w >> 7 & 2u) | (w >> 14 & 4u) | (w >> 21 & 8u);
+    return TriRows{pair_sums + (size_t)a * kRow, m & ((1u << n) - 1u)};
 }
 
-constexpr unsigned kBigPairs = 16;
-
-// gtri[i] = sum of triangle i's pair slots (triangles with many pairs are listed for the big pass).
-__global__ void pair_reduce_kernel(const unsigned *__restrict__ pair_off, int ntri, unsigned capacity,
-                                   const unsigned char *__restrict__ pair_flag,
-                                   const float *__restrict__ pair_sums, float *__restrict__ gtri,
-                                   unsigned *__restrict__ big_list, unsigned *__restrict__ big_count) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ntri) return;
-    const unsigned a = pair_off[i], b = pair_off[i + 1];
-    if (b > capacity && b > a) return;            // overflowed: rows filled by atomics
-    if (b - a > kBigPairs) {
-        big_list[atomicAdd(big_count, 1u)] = (unsigned)i;
-        return;
-    }
-    float acc[kNV];
+// Rows of the listed triangles.  Large ones: a workgroup per item sums its
+// pairs' rows; a triangle of one item gets its row stored, the items of a
+// larger one are added to its row, which the backward's setup cleared.  Those
+// of kOwnRows + 1 to kBigBin pairs: half a wave each, a value of the row a
+// lane, the flagged rows added in order (as single lanes of the gather read
+// them, 32 rows were 32 dependent rounds: tiny cube 17 -> 5 us).
+__global__ __launch_bounds__(256) void large_reduce_kernel(const ViewConst *__restrict__ views, int L,
+                                                           const TriSetup *__restrict__ setup, LargeLists large,
+                                                           const DevCounters *counters,
+                                                           const unsigned *__restrict__ pair_off, unsigned capacity,
+                                                           const unsigned char *__restrict__ pair_flag,
+                                                           const float *__restrict__ pair_sums,
+                                                           float *__restrict__ gtri) {
+    __shared__ float part[4][kNV];
+    for_large_items(large, counters, (int)blockIdx.x, kLargeBlocks,
+                    [&](unsigned t) { return pair_off[t + 1] - pair_off[t]; },
+                    [&](unsigned t, unsigned q0, unsigned n) {
+                        const unsigned a = pair_off[t];
+                        if (a + n > capacity) return;                       // overflowed: filled by atomics
+                        constexpr int PER = kLargeChunk / 256;
+                        bool on[PER];
 #pragma unroll
-    for (int q = 0; q < kNV; ++q) acc[q] = 0.f;
-    for (unsigned p = a; p < b; ++p)
-        if (pair_flag[p])
+                        for (int k = 0; k < PER; ++k) {
+                            const unsigned q = q0 + 256u * k + threadIdx.x;
+                            on[k] = q < n && pair_flag[a + q];
+                        }
+                        float4 acc[kRow / 4];
 #pragma unroll
-            for (int q = 0; q < kNV; ++q) acc[q] += pair_sums[(size_t)p * kNV + q];
+                        for (int i = 0; i < kRow / 4; ++i) acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int q = 0; q < kNV; ++q) gtri[(size_t)i * kGtriStride + gtri_slot(q)] = acc[q];
-}
-
-__global__ __launch_bounds__(256) void big_pair_reduce_kernel(const unsigned *__restrict__ pair_off,
-                                                              const unsigned char *__restrict__ pair_flag,
-                                                              const float *__restrict__ pair_sums,
-                                                              float *__restrict__ gtri,
-                                                              const unsigned *__restrict__ big_list,
-                                                              const unsigned *__restrict__ big_count) {
-    const unsigned n = *big_count;
-    for (unsigned o = blockIdx.x; o < n; o += gridDim.x) {
-        const unsigned i = big_list[o];
-        const unsigned a = pair_off[i], b = pair_off[i + 1];
-        float acc[kNV];
+                        for (int k = 0; k < PER; ++k) {
+                            if (!on[k]) continue;
+                            const float4 *row = (const float4 *)(pair_sums + (size_t)(a + q0 + 256u * k + threadIdx.x) * kRow);
 #pragma unroll
-        for (int q = 0; q < kNV; ++q) acc[q] = 0.f;
-        for (unsigned p = a + threadIdx.x; p < b; p += blockDim.x)
-            if (pair_flag[p])
+                            for (int i = 0; i < kRow / 4; ++i) {
+                                const float4 r = row[i];
+                                acc[i].x += r.x; acc[i].y += r.y; acc[i].z += r.z; acc[i].w += r.w;
+                            }
+                        }
+                        float v[kNV];
 #pragma unroll
-                for (int q = 0; q < kNV; ++q) acc[q] += pair_sums[(size_t)p * kNV + q];
-        block_sum_store<4>(acc, gtri + (size_t)i * kGtriStride, [](int q) { return gtri_slot(q); });
-        __syncthreads();
+                        for (int i = 0; i < kNV; ++i) {
+                            const float4 c = acc[row_slot(i) / 4];
+                            v[i] = row_slot(i) % 4 == 0 ? c.x : row_slot(i) % 4 == 1 ? c.y : row_slot(i) % 4 == 2 ? c.z : c.w;
+                        }
+                        const int lane = (int)(threadIdx.x & 63), i = lane >> 1;
+                        const float s = wave_sum_multi(v);
+                        __syncthreads();
+                        if ((lane & 1) == 0 && i < kNV) part[threadIdx.x >> 6][i] = s;
+                        __syncthreads();
+                        if (threadIdx.x < kNV) {
+                            const int q = (int)threadIdx.x;
+                            const float total = (part[0][q] + part[1][q]) + (part[2][q] + part[3][q]);
+                            float *dst = gtri + (size_t)t * kRow + row_slot(q);
+                            // light views' rows have no albedo terms
+                            if (q >= 18 && setup[t].pad2[0] < L) return;
+                            if (n <= kLargeChunk) *dst = total;
+                            else atomic_add_f32(dst, total);
+                        }
+                    });
+    const unsigned nmedium = counters->medium_len;
+    const int half = (int)(threadIdx.x & 63) >> 5, i = (int)(threadIdx.x & 31);
+    for (unsigned o = blockIdx.x * 8u + (threadIdx.x >> 5); __ballot(o < nmedium) != 0ull; o += kLargeBlocks * 8u) {
+        const unsigned t = o < nmedium ? large.medium[o] : 0u;
+        const unsigned a = pair_off[t], n = o < nmedium ? pair_off[t + 1] - a : 0u;
+        const bool live = n > 0 && a + n <= capacity;
+        const unsigned long long m2 = __ballot(live && (unsigned)i < n && pair_flag[a + (live ? i : 0)]);
+        unsigned m = (unsigned)(half ? m2 >> 32 : m2);
+        if (!live || i >= kRow) continue;
+        const float *rows = pair_sums + (size_t)a * kRow + i;
+        float acc = 0.f;
+        while (m) {
+            float v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                v[k] = m ? rows[(size_t)(__ffs((int)m) - 1) * kRow] : 0.f;
+                m &= m - 1;
+            }
+            acc += v[0]; acc += v[1]; acc += v[2]; acc += v[3];
+        }
+        gtri[(size_t)t * kRow + i] = acc;
     }
 }
 
@@ -1243,6 +1303,9 @@ __device__ __forceinline__ void albedo_gather_block(const ViewConst *__restrict_
                                                     const int *__restrict__ scene_face_off,
                                                     const int *__restrict__ scene_views_off,
                                                     const int *__restrict__ scene_views,
+                                                    const unsigned *__restrict__ pair_off, unsigned capacity,
+                                                    const unsigned char *__restrict__ pair_flag,
+                                                    const float *__restrict__ pair_sums,
                                                     const float *__restrict__ gtri, float *__restrict__ galbedo,
                                                     int C) {
     const int fl = bx * blockDim.x + threadIdx.x;
@@ -1251,31 +1314,100 @@ __device__ __forceinline__ void albedo_gather_block(const ViewConst *__restrict_
     for (int s = scene_views_off[b]; s < scene_views_off[b + 1]; ++s) {
         const int vi = scene_views[s];
         if (vi < L) continue;
-        const float *row = gtri + (size_t)(views[vi].setup_off + fl) * kGtriStride;
-        for (int c = 0; c < C; ++c) acc[c] += row[gtri_slot(18 + c)];
+        const unsigned t = (unsigned)(views[vi].setup_off + fl), p0 = pair_off[t], p1 = pair_off[t + 1];
+        TriRows r = tri_rows(t, p0, p1, flag_word(pair_flag + (p1 <= capacity ? p0 : 0u)), capacity, pair_sums, gtri);
+        while (r.mask) {
+            const int j = __ffs((int)r.mask) - 1;
+            r.mask &= r.mask - 1;
+            for (int c = 0; c < C; ++c) acc[c] += r.rows[(size_t)j * kRow + row_slot(18 + c)];
+        }
     }
     for (int c = 0; c < C; ++c) galbedo[(size_t)(scene_face_off[b] + fl) * C + c] = acc[c];
 }
 
+// Corners whose records a lane gathers together, and the number up to which it
+// does so itself: a vertex of a closed mesh has about six, the pole of a UV
+// sphere one per longitude, whose records past the first kOwnCorners are
+// gathered by the whole wave.  (8 or 4 at a time: 58 and 53 us against 52 on 64
+// scenes, registers against round trips.)
+constexpr int kCorners = 6, kOwnCorners = 24;
+
+// Six terms (world x y z, clip x y w) of up to kCorners triangle corners e[]
+// (triangle << 2 | corner, -1: none) of one view: the first row of every
+// corner in flight together, then every second one, and so on.  Corners with
+// no row left read an all-zero record (zero_rec), so that no load sits behind
+// a branch.  Uniform call.
+template <int N>
+__device__ __forceinline__ void gather_corners(const int (&e)[N], int soff, unsigned capacity,
+                                               const unsigned *__restrict__ pair_off,
+                                               const unsigned char *__restrict__ pair_flag,
+                                               const float *__restrict__ pair_sums, const float *__restrict__ gtri,
+                                               const float *__restrict__ zero_rec, float (&g)[6]) {
+    unsigned p0[N], p1[N], w[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const unsigned t = (unsigned)(soff + (max(e[k], 0) >> 2));
+        p0[k] = pair_off[t];
+        p1[k] = pair_off[t + 1];
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        if (e[k] < 0) p1[k] = p0[k];
+        w[k] = flag_word(pair_flag + (p1[k] <= capacity ? p0[k] : 0u));
+    }
+    TriRows r[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+        r[k] = tri_rows((unsigned)(soff + (max(e[k], 0) >> 2)), p0[k], p1[k], w[k], capacity, pair_sums, gtri);
+    for (;;) {
+        unsigned any = 0;
+#pragma unroll
+        for (int k = 0; k < N; ++k) any |= r[k].mask;
+        if (__ballot(any != 0) == 0ull) break;
+        float4 a[N];
+        float2 b[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const float *rec = r[k].mask ? r[k].rows + (size_t)(__ffs((int)r[k].mask) - 1) * kRow + (e[k] & 3) * 8 : zero_rec;
+            r[k].mask &= r[k].mask - 1;       // 0 stays 0
+            a[k] = *(const float4 *)rec;
+            b[k] = *(const float2 *)(rec + 4);
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            g[0] += a[k].x; g[1] += a[k].y; g[2] += a[k].z;
+            g[3] += a[k].w; g[4] += b[k].x; g[5] += b[k].y;
+        }
+    }
+}
+
 // Per vertex: sum its triangle corners' terms over every view of its scene,
 // add the silhouette clip terms, map clip terms through M^T; per light view
-// the workgroup's share of dL/dM is written for glight_reduce.
+// the wave's share of dL/dM is written for glight_reduce.  A workgroup takes
+// 64 vertices, a vertex a lane, and its waves share the views.  Bound by the
+// latency of the chain corner -> pair range -> flags -> rows.  With the rows of
+// up to four pairs read here, no pass writes a row per triangle: with the
+// reduction before it, 64 scenes 150 -> 76 us; 24 views of a 50k-vertex sphere
+// whose poles have 316 corners 744 -> 91.
 __global__ __launch_bounds__(256) void vertex_gather_kernel(
     const ViewConst *__restrict__ views, int L, const int *__restrict__ scene_vert_off,
     const int *__restrict__ scene_views_off, const int *__restrict__ scene_views, const int *__restrict__ vc_off,
-    const int *__restrict__ vc_list, const float *__restrict__ verts, const float *__restrict__ gtri,
-    const float *__restrict__ zero_rec, const float4 *__restrict__ gclip, float *__restrict__ gverts,
-    float *__restrict__ part_gm, const float *__restrict__ jac, int vx, const int *__restrict__ scene_face_off,
-    float *__restrict__ galbedo, int C) {
+    const int *__restrict__ vc_list, const float *__restrict__ verts, const unsigned *__restrict__ pair_off,
+    unsigned capacity, const unsigned char *__restrict__ pair_flag, const float *__restrict__ pair_sums,
+    const float *__restrict__ gtri, const float *__restrict__ zero_rec, const float4 *__restrict__ gclip,
+    float *__restrict__ gverts, float *__restrict__ part_gm, const float *__restrict__ jac, int vx,
+    const int *__restrict__ scene_face_off, float *__restrict__ galbedo, int C) {
     const int b = blockIdx.y;
     if ((int)blockIdx.x >= vx) {                               // the albedo gather's workgroups
-        albedo_gather_block(views, L, b, (int)blockIdx.x - vx, scene_face_off, scene_views_off, scene_views, gtri,
-                            galbedo, C);
+        albedo_gather_block(views, L, b, (int)blockIdx.x - vx, scene_face_off, scene_views_off, scene_views, pair_off,
+                            capacity, pair_flag, pair_sums, gtri, galbedo, C);
         return;
     }
     const int nv = scene_vert_off[b + 1] - scene_vert_off[b];
-    if ((int)(blockIdx.x * blockDim.x) >= nv) return;        // whole workgroup
-    const int vl = blockIdx.x * blockDim.x + threadIdx.x;
+    if ((int)blockIdx.x * 64 >= nv) return;                  // whole workgroup
+    __shared__ float sum[3][3][64];
+    const int lane = (int)(threadIdx.x & 63), wave = (int)(threadIdx.x >> 6), nwaves = (int)(blockDim.x >> 6);
+    const int vl = blockIdx.x * 64 + lane;
     const bool in = vl < nv;
     const int gv_idx = scene_vert_off[b] + (in ? vl : 0);
     float x[3] = {0, 0, 0};
@@ -1283,70 +1415,46 @@ __global__ __launch_bounds__(256) void vertex_gather_kernel(
         for (int k = 0; k < 3; ++k) x[k] = verts[3 * (size_t)gv_idx + k];
     float gv[3] = {0, 0, 0};
     const int c0 = in ? vc_off[gv_idx] : 0, c1 = in ? vc_off[gv_idx + 1] : 0;
-    // the first eight corners' indices, loaded once for every view (a vertex
-    // of a closed mesh has about six)
-    constexpr int kHeld = 8;
-    int eh[kHeld];
+    int held[kCorners];                        // loaded once for every view
 #pragma unroll
-    for (int k = 0; k < kHeld; ++k) eh[k] = c0 + k < c1 ? vc_list[c0 + k] : -1;
-    for (int s = scene_views_off[b]; s < scene_views_off[b + 1]; ++s) {
+    for (int k = 0; k < kCorners; ++k) held[k] = c0 + k < c1 ? vc_list[c0 + k] : -1;
+    const int own = min(c1, c0 + kOwnCorners);
+    const unsigned long long many = __ballot(c1 > own);
+    for (int s = scene_views_off[b] + wave; s < scene_views_off[b + 1]; s += nwaves) {
         const int vi = scene_views[s];
         const ViewConst &v = views[vi];
         const int soff = v.setup_off;
-        float gc[3] = {0, 0, 0};
-        // Every slot loads a record, absent corners an all-zero one
-        // (zero_rec), so that no load sits behind a branch and the sums add
-        // the same terms in the same order.  Corners past the held ones go
-        // sixteen at a time, the next sixteen indices loaded with the current
-        // records: a vertex of high valence (the pole of a UV sphere has one
-        // corner per longitude) waits for one load per sixteen corners.
-        constexpr int kChunk = 16;
         const float4 ga = gclip[v.clip_off + (in ? vl : 0)];     // silhouette terms, issued early
-        int e[kChunk];
+        float g[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        gather_corners(held, soff, capacity, pair_off, pair_flag, pair_sums, gtri, zero_rec, g);
+        for (int c = c0 + kCorners; __ballot(c < own) != 0ull; c += kCorners) {
+            int e[kCorners];
 #pragma unroll
-        for (int k = 0; k < kChunk; ++k) e[k] = c0 + kHeld + k < c1 ? vc_list[c0 + kHeld + k] : -1;
-        {
-            // the held corners' records: eight loads in flight
-            float4 a[kHeld];
-            float2 bb[kHeld];
-#pragma unroll
-            for (int k = 0; k < kHeld; ++k) {
-                // the corner's record: world x y z, clip x | clip y w
-                const float *rec =
-                    eh[k] >= 0 ? gtri + (size_t)(soff + (eh[k] >> 2)) * kGtriStride + (eh[k] & 3) * 8 : zero_rec;
-                a[k] = *(const float4 *)rec;
-                bb[k] = *(const float2 *)(rec + 4);
+            for (int k = 0; k < kCorners; ++k) e[k] = c + k < own ? vc_list[c + k] : -1;
+            gather_corners(e, soff, capacity, pair_off, pair_flag, pair_sums, gtri, zero_rec, g);
+        }
+        for (unsigned long long m = many; m; m &= m - 1) {
+            const int l = __ffsll(m) - 1;
+            const int q0 = __builtin_amdgcn_readlane(own, l), q1 = __builtin_amdgcn_readlane(c1, l);
+            float h[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            for (int q = q0; q < q1; q += 128) {
+                const int e[2] = {q + lane < q1 ? vc_list[q + lane] : -1, q + 64 + lane < q1 ? vc_list[q + 64 + lane] : -1};
+                gather_corners(e, soff, capacity, pair_off, pair_flag, pair_sums, gtri, zero_rec, h);
             }
+            const float t = wave_sum_multi(h);           // lane 2k: total of term k
 #pragma unroll
-            for (int k = 0; k < kHeld; ++k) {
-                gv[0] += a[k].x; gv[1] += a[k].y; gv[2] += a[k].z;
-                gc[0] += a[k].w; gc[1] += bb[k].x; gc[2] += bb[k].y;
+            for (int k = 0; k < 6; ++k) {
+                const float tk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), 2 * k));
+                if (lane == l) g[k] += tk;
             }
         }
-        for (int c = c0 + kHeld; c < c1; c += kChunk) {
-            float4 a[kChunk];
-            float2 b[kChunk];
-#pragma unroll
-            for (int k = 0; k < kChunk; ++k) {
-                const float *rec =
-                    e[k] >= 0 ? gtri + (size_t)(soff + (e[k] >> 2)) * kGtriStride + (e[k] & 3) * 8 : zero_rec;
-                a[k] = *(const float4 *)rec;
-                b[k] = *(const float2 *)(rec + 4);
-            }
-#pragma unroll
-            for (int k = 0; k < kChunk; ++k) e[k] = c + kChunk + k < c1 ? vc_list[c + kChunk + k] : -1;
-#pragma unroll
-            for (int k = 0; k < kChunk; ++k) {
-                gv[0] += a[k].x; gv[1] += a[k].y; gv[2] += a[k].z;
-                gc[0] += a[k].w; gc[1] += b[k].x; gc[2] += b[k].y;
-            }
-        }
+        float gc[3] = {g[3], g[4], g[5]};
         if (in) {
             gc[0] += ga.x; gc[1] += ga.y; gc[2] += ga.w;
         }
         const float *M = v.M;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) gv[k] += (M[k] * gc[0] + M[4 + k] * gc[1]) + M[12 + k] * gc[2];
+        for (int k = 0; k < 3; ++k) gv[k] += g[k] + ((M[k] * gc[0] + M[4 + k] * gc[1]) + M[12 + k] * gc[2]);
         if (vi < L) {
             // dL/dM = (gc_x, gc_y, 0, gc_w) outer [x, 1], pulled back to the light parameter
             const float xh[4] = {x[0], x[1], x[2], in ? 1.f : 0.f};
@@ -1360,31 +1468,42 @@ __global__ __launch_bounds__(256) void vertex_gather_kernel(
                     a += xh[k] * ((gc[0] * J[3 * k + j] + gc[1] * J[3 * (4 + k) + j]) + gc[2] * J[3 * (12 + k) + j]);
                 gp[j] = a;
             }
-            block_sum_store<4>(gp, part_gm + ((long long)v.part_gm_off + blockIdx.x) * 3);
+            const float t = wave_sum_multi(gp);
+            if ((lane & 1) == 0 && lane < 6) part_gm[((long long)v.part_gm_off + blockIdx.x) * 3 + (lane >> 1)] = t;
         }
+    }
+    if (nwaves > 1) {
+        if (wave > 0)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) sum[wave - 1][k][lane] = gv[k];
+        __syncthreads();
+        if (wave > 0) return;
+        for (int w = 1; w < nwaves; ++w)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) gv[k] += sum[w - 1][k][lane];
     }
     if (in)
         for (int k = 0; k < 3; ++k) gverts[3 * (size_t)gv_idx + k] = gv[k];
 }
 
 // glight[l] = sum of every partial written for light l (vertex blocks, light
-// tiles, and the tiles of each render that uses it), in two passes so that a
-// few lights with many partials still fill the GPU: kGlightBlocks workgroups
-// per light each sum a strided share, then one thread per light adds their
-// results in a fixed order (deterministic, no atomics).
-__global__ __launch_bounds__(256) void glight_partial_kernel(const ViewConst *__restrict__ views,
-                                                             const RenderConst *__restrict__ renders,
-                                                             const int *__restrict__ light_renders_off,
-                                                             const int *__restrict__ light_renders,
-                                                             const float *__restrict__ part_gm,
-                                                             const float *__restrict__ part_light,
-                                                             const float *__restrict__ part_render,
-                                                             float *__restrict__ gl_part) {
+// tiles, and the tiles of each render that uses it): kGlightBlocks workgroups
+// per light each sum a strided share, so that a few lights with many partials
+// still fill the GPU, and the last of them to finish (done[l], cleared by the
+// backward's setup) adds their results in a fixed order.
+__global__ __launch_bounds__(256) void glight_kernel(const ViewConst *__restrict__ views,
+                                                     const RenderConst *__restrict__ renders,
+                                                     const int *__restrict__ light_renders_off,
+                                                     const int *__restrict__ light_renders,
+                                                     const float *__restrict__ part_gm,
+                                                     const float *__restrict__ part_light,
+                                                     const float *__restrict__ part_render, float *gl_part,
+                                                     unsigned *done, float *__restrict__ gparams) {
     const int l = blockIdx.y;
     const ViewConst &v = views[l];
     const int first = blockIdx.x * blockDim.x + threadIdx.x, step = kGlightBlocks * blockDim.x;
     float acc[3] = {0.f, 0.f, 0.f};
-    const int nvb = (v.nverts + 255) / 256;
+    const int nvb = (v.nverts + 63) / 64;
     for (int q = first; q < nvb; q += step)
 #pragma unroll
         for (int k = 0; k < 3; ++k) acc[k] += part_gm[((long long)v.part_gm_off + q) * 3 + k];
@@ -1401,16 +1520,30 @@ __global__ __launch_bounds__(256) void glight_partial_kernel(const ViewConst *__
 #pragma unroll
             for (int k = 0; k < 3; ++k) acc[k] += part_render[R.part_off + ((long long)slot * nct + q) * 3 + k];
     }
-    block_sum_store<4>(acc, gl_part + ((long long)l * kGlightBlocks + blockIdx.x) * 3);
-}
-
-__global__ void glight_final_kernel(const float *__restrict__ gl_part, int L, float *__restrict__ gparams) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 3 * L) return;
-    const int l = t / 3, k = t % 3;
-    float a = 0.f;
-    for (int b = 0; b < kGlightBlocks; ++b) a += gl_part[((long long)l * kGlightBlocks + b) * 3 + k];
-    gparams[t] = a;
+    __shared__ float total[3];
+    block_sum_store<4>(acc, total);
+    // the three threads that publish the workgroup's sums are in one wave,
+    // whose first lane counts it as finished after them
+    float *mine = gl_part + ((long long)l * kGlightBlocks + blockIdx.x) * 3;
+    if (threadIdx.x >= 64) return;
+    wave_sync();
+    if (threadIdx.x < 3)
+        __hip_atomic_store(mine + threadIdx.x, total[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // The stores go through to where every XCD sees them; waiting for them is
+    // all the release there is to do (a fence would write back the whole L2:
+    // 36 us for 64 lights, 5 with the wait).
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    unsigned before = 0;
+    if (threadIdx.x == 0)
+        before = __hip_atomic_fetch_add(done + l, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane((int)before) != kGlightBlocks - 1) return;
+    if (threadIdx.x < 3) {
+        float a = 0.f;
+        for (int b = 0; b < kGlightBlocks; ++b)
+            a += __hip_atomic_load(gl_part + ((long long)l * kGlightBlocks + b) * 3 + threadIdx.x, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        gparams[3 * l + threadIdx.x] = a;
+    }
 }
 
 // ----------------------------------------------------------------------------- pose
@@ -1592,44 +1725,35 @@ hipError_t launch_light_backward(int tile, const ViewConst *views, int L, int ma
     return hipGetLastError();
 }
 
-hipError_t launch_vertex_gradients(const ViewConst *views, int L, int B, int max_verts, int max_faces, int ntri,
-                                   unsigned capacity, const int *scene_vert_off, const int *scene_face_off,
+hipError_t launch_vertex_gradients(const ViewConst *views, int L, int B, int max_verts, int max_faces, int max_views,
+                                   int ntri, unsigned capacity, const TriSetup *setup, const LargeLists &large,
+                                   const DevCounters *counters, const int *scene_vert_off, const int *scene_face_off,
                                    const int *scene_views_off, const int *scene_views, const int *vc_off,
                                    const int *vc_list, const unsigned *pair_off, const unsigned char *pair_flag,
-                                   const float *pair_sums, float *gtri, const float *zero_rec,
-                                   unsigned *big_list, unsigned *big_count, const float *verts, const float4 *gclip,
-                                   float *gverts, float *part_gm, float *galbedo, int C, const float *jac, hipStream_t s) {
-    if (ntri > 0) {
-        hipLaunchKernelGGL(pair_reduce_kernel, dim3((ntri + 255) / 256), dim3(256), 0, s, pair_off, ntri, capacity,
-                           pair_flag, pair_sums, gtri, big_list, big_count);
-        hipLaunchKernelGGL(big_pair_reduce_kernel, dim3(512), dim3(256), 0, s, pair_off, pair_flag, pair_sums, gtri,
-                           big_list,
-                           (const unsigned *)big_count);
-    }
-    // one launch: the vertex gather's workgroups, then the albedo gather's
-    const int vx = (max_verts + 255) / 256, fx = (galbedo && max_faces > 0) ? (max_faces + 255) / 256 : 0;
+                                   const float *pair_sums, float *gtri, const float *zero_rec, const float *verts,
+                                   const float4 *gclip, float *gverts, float *part_gm, float *galbedo, int C,
+                                   const float *jac, hipStream_t s) {
+    if (ntri > 0)
+        hipLaunchKernelGGL(large_reduce_kernel, dim3(kLargeBlocks), dim3(256), 0, s, views, L, setup, large, counters,
+                           pair_off, capacity, pair_flag, pair_sums, gtri);
+    // one launch: the vertex gather's workgroups, then the albedo gather's;
+    // a wave per view of the scene, up to four
+    const int nt = 64 * std::min(std::max(max_views, 1), 4);
+    const int vx = (max_verts + 63) / 64, fx = (galbedo && max_faces > 0) ? (max_faces + nt - 1) / nt : 0;
     if (B > 0 && vx + fx > 0)
-        hipLaunchKernelGGL(vertex_gather_kernel, dim3(vx + fx, B), dim3(256), 0, s, views, L, scene_vert_off,
-                           scene_views_off, scene_views, vc_off, vc_list, verts, gtri, zero_rec, gclip, gverts,
-                           part_gm, jac, vx, scene_face_off, galbedo, C);
-    return hipGetLastError();
-}
-
-hipError_t launch_overflow_rows_zero(const unsigned *list, const DevCounters *counters, float *gtri, hipStream_t s) {
-    hipLaunchKernelGGL(overflow_rows_zero_kernel, dim3(256), dim3(64), 0, s, list, counters, gtri);
+        hipLaunchKernelGGL(vertex_gather_kernel, dim3(vx + fx, B), dim3(nt), 0, s, views, L, scene_vert_off,
+                           scene_views_off, scene_views, vc_off, vc_list, verts, pair_off, capacity, pair_flag,
+                           pair_sums, gtri, zero_rec, gclip, gverts, part_gm, jac, vx, scene_face_off, galbedo, C);
     return hipGetLastError();
 }
 
 hipError_t launch_glight_reduce(const ViewConst *views, int L, const RenderConst *renders,
                                 const int *light_renders_off, const int *light_renders, const float *part_gm,
-                                const float *part_light, const float *part_render, float *gl_part, float *gparams,
-                                hipStream_t s) {
+                                const float *part_light, const float *part_render, float *gl_part, unsigned *done,
+                                float *gparams, hipStream_t s) {
     if (L == 0) return hipSuccess;
-    hipLaunchKernelGGL(glight_partial_kernel, dim3(kGlightBlocks, L), dim3(256), 0, s, views, renders,
-                       light_renders_off, light_renders, part_gm, part_light, part_render, gl_part);
-    const hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(glight_final_kernel, dim3((3 * L + 255) / 256), dim3(256), 0, s, gl_part, L, gparams);
+    hipLaunchKernelGGL(glight_kernel, dim3(kGlightBlocks, L), dim3(256), 0, s, views, renders, light_renders_off,
+                       light_renders, part_gm, part_light, part_render, gl_part, done, gparams);
     return hipGetLastError();
 }
 

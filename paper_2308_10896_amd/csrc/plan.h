@@ -22,7 +22,7 @@ struct dsm_plan {
     int blur_tiles = 0, blur_rmax = 0, max_pose_verts = 0;
     int max_light_tiles = 0, max_cam_tiles = 0, max_lights_per_render = 0;
     int max_cam_regions = 0, max_light_regions = 0, max_cam_renders = 0;   // smoothing regions; renders of one camera
-    int max_scene_verts = 0, max_scene_faces = 0;
+    int max_scene_verts = 0, max_scene_faces = 0, max_scene_views = 0;
 
     std::vector<dsm::ViewConst> views_h;
     std::vector<dsm::CamStatic> light_cams_h;
@@ -67,14 +67,14 @@ struct dsm_plan {
     // layout of the caller's saved buffer (byte offsets): everything the
     // forward writes and the backward reads, the binning state included
     size_t sv_counters = 0, sv_zero_end = 0, sv_keys = 0, sv_setup = 0, sv_sil = 0, sv_tv = 0, sv_F0 = 0,
-           sv_M = 0, sv_img0 = 0, sv_pair_off = 0, sv_tile_start = 0, sv_bins = 0, sv_bin_pair = 0, sv_overflow = 0, sv_large = 0, sv_items = 0, sv_zc = 0, sv_aa_flag = 0,
+           sv_M = 0, sv_img0 = 0, sv_pair_off = 0, sv_tile_start = 0, sv_bins = 0, sv_bin_pair = 0, sv_overflow = 0, sv_large = 0, sv_items = 0, sv_medium = 0, sv_zc = 0, sv_aa_flag = 0,
            saved_bytes = 0;
     // layout of the caller's scratch buffer (byte offsets): temporaries of
     // one call, nothing carried from a forward to its backward
     size_t sc_pair_local = 0, sc_block_total = 0, sc_tile_cnt = 0, sc_facing = 0,
            sc_pair_slot = 0, sc_pair_flag = 0, sc_F1 = 0, sc_fwd_end = 0, sc_gimg0 = 0, sc_gM = 0, sc_gF1 = 0,
-           sc_gclip = 0, sc_glight = 0, sc_zero_fwd_end = 0, sc_bigcount = 0, sc_zero_rec = 0, sc_zero_bwd_end = 0,
-           sc_pair_sums = 0, sc_gtri = 0, sc_biglist = 0, sc_part_light = 0, sc_part_gm = 0, sc_part_render = 0, sc_jac = 0,
+           sc_gclip = 0, sc_glight = 0, sc_zero_fwd_end = 0, sc_done = 0, sc_zero_rec = 0, sc_zero_bwd_end = 0,
+           sc_pair_sums = 0, sc_gtri = 0, sc_part_light = 0, sc_part_gm = 0, sc_part_render = 0, sc_jac = 0,
            scratch_bytes = 0;
 
     hipGraph_t graph = nullptr;

@@ -49,16 +49,24 @@ __device__ void light_jacobian(const CamStatic &cam, const float *param, float *
 // One thread per light: the light camera from its float32 parameter, in
 // float64, rounded to float32 for the rest of the pipeline; with jac, also
 // the frame's Jacobian.  Workgroups from nf on clear the words z1[0, n1) and
-// z2[0, n2) instead (the pass's counters and accumulators: one launch for
-// all of it).
+// z2[0, n2) instead, and those rows (the pass's counters and accumulators: one
+// launch for all of it).
 __global__ void light_frames_kernel(ViewConst *views, const CamStatic *cams, const float *params, int L,
                                     float *zc_out, float *jac, int nf, unsigned *z1, size_t n1, unsigned *z2,
-                                    size_t n2) {
+                                    size_t n2, ClearRows rows) {
     if ((int)blockIdx.x >= nf) {
         const size_t stride = (size_t)(gridDim.x - nf) * blockDim.x;
-        for (size_t i = (size_t)(blockIdx.x - nf) * blockDim.x + threadIdx.x; i < n1 + n2; i += stride) {
+        const size_t first = (size_t)(blockIdx.x - nf) * blockDim.x + threadIdx.x;
+        for (size_t i = first; i < n1 + n2; i += stride) {
             if (i < n1) z1[i] = 0u;
             else z2[i - n1] = 0u;
+        }
+        if (rows.rows) {
+            const size_t la = *rows.len_a, lb = *rows.len_b;
+            for (size_t i = first; i < 24 * (la + lb); i += stride) {
+                const size_t o = i / 24;
+                rows.rows[(size_t)(o < la ? rows.list_a[o] : rows.list_b[o - la]) * 24 + i % 24] = 0.f;
+            }
         }
         return;
     }
@@ -235,6 +243,7 @@ __global__ __launch_bounds__(kTriThreads) void setup_kernel(
         facing8[v.setup_off + t] = s.facing;
         npairs[0] = tile_box(i0, i1, j0, j1, shift).n;
         if (npairs[0] > kBigBin) list_large((unsigned)(v.setup_off + t), npairs[0], large, counters);
+        else if (npairs[0] > kOwnRows) large.medium[atomicAdd(&counters->medium_len, 1u)] = (unsigned)(v.setup_off + t);
         nculled += !ok && !bad ? 1u : 0u;
         nbad += bad ? 1u : 0u;
     }
@@ -925,13 +934,14 @@ __global__ __launch_bounds__(kRasterThreads) void raster_kernel(
 // ----------------------------------------------------------------------------- host launchers
 
 hipError_t launch_light_frames(ViewConst *views, const CamStatic *cams, const float *params, int L, float *jac,
-                               float *zc_out, void *z1, size_t bytes1, void *z2, size_t bytes2, hipStream_t s) {
+                               float *zc_out, void *z1, size_t bytes1, void *z2, size_t bytes2, const ClearRows &rows,
+                               hipStream_t s) {
     const int nf = (L + 63) / 64;
     const size_t n1 = bytes1 / 4, n2 = bytes2 / 4;
     const size_t nz = std::min<size_t>((n1 + n2 + 255) / 256, 16384);
     if (nf + nz == 0) return hipSuccess;
     hipLaunchKernelGGL(light_frames_kernel, dim3((unsigned)(nf + nz)), dim3(64), 0, s, views, cams, params, L, zc_out,
-                       jac, nf, (unsigned *)z1, n1, (unsigned *)z2, n2);
+                       jac, nf, (unsigned *)z1, n1, (unsigned *)z2, n2, rows);
     return hipGetLastError();
 }
 
