@@ -368,15 +368,15 @@ __device__ __forceinline__ unsigned aa_pairs_item(const AAPairs<NT> &l, unsigned
     return l.item[base + e];
 }
 
-// Renders of one camera share its keys, so a thread of the camera smoothing
-// (and of its adjoint) evaluates its sample's pairs once and applies them to
-// a chunk of the camera's renders.  The chunk is the whole list unless that
-// leaves the GPU under kAaFillBlocks workgroups, where a single camera with
-// many renders would be a serial loop on an idle chip.
-constexpr int kAaFillBlocks = 2048;
-inline int aa_render_chunk(int max_renders, long long blocks) {
+// Renders of one camera share its keys, so the lookup, the camera smoothing and
+// its adjoint do what depends on the keys alone once for a chunk of the
+// camera's renders.  The chunk is the whole list unless that leaves the GPU
+// under kFillBlocks workgroups, where a single camera with many renders would
+// be a serial loop on an idle chip.
+constexpr int kFillBlocks = 2048;
+inline int render_chunk(int max_renders, long long blocks) {
     int chunk = max_renders;
-    while (chunk > 1 && blocks * ((max_renders + chunk - 1) / chunk) < kAaFillBlocks) chunk = (chunk + 1) / 2;
+    while (chunk > 1 && blocks * ((max_renders + chunk - 1) / chunk) < kFillBlocks) chunk = (chunk + 1) / 2;
     return chunk;
 }
 

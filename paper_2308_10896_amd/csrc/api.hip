@@ -738,8 +738,8 @@ dsm_status enqueue_forward(dsm_plan *p, const float *verts, const float *lparams
     for (const auto &g : p->blur_groups)
         DSM_TRY(launch_blur(p->blur_jobs_d + g.first, g.n, g.tiles, F1, Mm, false, g.R, s));
     DSM_MARK(DSM_STAGE_LOOKUP);
-    DSM_TRY(launch_lookup(p->views_d, p->renders_d, p->R, p->max_cam_pix, p->render_lights_d, tv, albedo, keys, Mm,
-                          img0, p->C, s));
+    DSM_TRY(launch_lookup(p->views_d, p->L, p->Cm, p->max_cam_pix, p->max_cam_renders, p->renders_d,
+                          p->cam_renders_off_d, p->cam_renders_d, p->render_lights_d, tv, keys, Mm, img0, p->C, s));
     DSM_MARK(DSM_STAGE_CAMERA_AA);
     DSM_TRY(launch_aa_camera(p->views_d, p->L, p->Cm, p->max_cam_regions, p->max_cam_renders, p->renders_d,
                              p->cam_renders_off_d, p->cam_renders_d, setup, p->faces_d, silm, verts, keys, img0, images,
@@ -792,11 +792,10 @@ dsm_status enqueue_backward(dsm_plan *p, const float *verts, const float *lparam
                                       p->cam_renders_off_d, p->cam_renders_d, setup, p->faces_d, silm, verts, keys,
                                       aa_flag, img0, gimg, gimg0, gclip, p->C, s));
     DSM_MARK(DSM_STAGE_LOOKUP_ADJ);
-    DSM_TRY(launch_lookup_backward(p->tile, p->views_d, p->L, p->Cm, p->max_cam_tiles, p->max_lights_per_render,
-                                   p->renders_d, p->cam_renders_off_d, p->cam_renders_d, p->render_lights_d,
-                                   p->faces_d, verts, albedo, tv, keys, Mm, gimg0, gM, setup, tile_start, bins,
-                                   bin_pair, pair_flag, pair_sums, gtri, part_render, p->C, jac, pair_off,
-                                   p->capacity, s));
+    DSM_TRY(launch_lookup_backward(p->tile, p->views_d, p->L, p->Cm, p->max_cam_tiles, p->renders_d,
+                                   p->cam_renders_off_d, p->cam_renders_d, p->render_lights_d, tv, keys, Mm, gimg0, gM,
+                                   setup, tile_start, bins, bin_pair, pair_flag, pair_sums, gtri, part_render, p->C,
+                                   jac, pair_off, p->capacity, s));
     DSM_MARK(DSM_STAGE_FILTER_ADJ);
     for (const auto &g : p->blur_groups)
         DSM_TRY(launch_blur(p->blur_jobs_d + p->L + g.first, g.n, g.tiles, gM, gF1, true, g.R, s));

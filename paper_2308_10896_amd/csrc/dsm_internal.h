@@ -208,66 +208,93 @@ __device__ __forceinline__ float wave_sum(float v) {
     return (r0 + r1) + (r2 + r3);
 }
 
+// lo summed over lane ^ 32 in the lower half of the wave, hi in the upper half
+// (one swap of the halves instead of two selects and a permute through LDS);
+// likewise over lane ^ 16 in even and odd rows of 16.
+__device__ __forceinline__ float swap32_add(float lo, float hi) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap16_add(float lo, float hi) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Wave-wide sums of N <= 32 values at once by recursive halving: at each
 // butterfly step every lane keeps half of its remaining values and receives
-// its partner's copy of that half, so the 64 lanes end up each holding one
-// total.  Lane l returns the total of value (l >> 1) (0 for (l >> 1) >= N).
-// About 4 instructions per value instead of 11 for N separate wave_sum calls.
+// its partner's copy of that half, until one value is left; the lanes that
+// share it sum it.  Lane l returns the total of value l >> kSumShift<N>
+// (0 for values >= N).  About 3 instructions per value; 10 in all for N <= 4.
 // All 64 lanes must be active.
+template <int N>
+constexpr int kSumShift = N <= 4 ? 4 : N <= 8 ? 3 : N <= 16 ? 2 : 1;
+
 template <int N>
 __device__ __forceinline__ float wave_sum_multi(const float (&v)[N]) {
     static_assert(N >= 1 && N <= 32, "wave_sum_multi handles up to 32 values");
+    constexpr int W = 64 >> kSumShift<N>;
     const int lane = (int)(threadIdx.x & 63);
-    const bool b5 = lane & 32, b4 = lane & 16, b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
-    float a[16];
+    const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
+    float a[W / 2];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {            // partner lane ^ 32
-        const float lo = j < N ? v[j] : 0.f, hi = j + 16 < N ? v[j + 16] : 0.f;
-        a[j] = (b5 ? hi : lo) + __shfl_xor(b5 ? lo : hi, 32, 64);
+    for (int j = 0; j < W / 2; ++j) a[j] = swap32_add(j < N ? v[j] : 0.f, j + W / 2 < N ? v[j + W / 2] : 0.f);
+    float b[W / 4];
+#pragma unroll
+    for (int j = 0; j < W / 4; ++j) b[j] = swap16_add(a[j], a[j + W / 4]);
+    if constexpr (W == 4) {
+        float e = b[0];
+        e += dpp_mov<0x128>(e);       // row_ror:8
+        e += dpp_mov<0x124>(e);       // row_ror:4
+        e += dpp_mov<0x4E>(e);        // quad_perm [2,3,0,1]
+        return e + dpp_mov<0xB1>(e);  // quad_perm [1,0,3,2]
+    } else {
+        float c[W / 8];
+#pragma unroll
+        for (int j = 0; j < W / 8; ++j)           // partner lane ^ 8: row_ror:8 within 16-lane rows
+            c[j] = (b3 ? b[j + W / 8] : b[j]) + dpp_mov<0x128>(b3 ? b[j] : b[j + W / 8]);
+        if constexpr (W == 8) {
+            float e = c[0];
+            e += dpp_mov<0x141>(e);   // row_half_mirror: lane 7 - l of each 8
+            e += dpp_mov<0x4E>(e);
+            return e + dpp_mov<0xB1>(e);
+        } else {
+            float d[W / 16];
+#pragma unroll
+            for (int j = 0; j < W / 16; ++j) {    // partner lane ^ 4: from lane + 4 (row_ror:12) or lane - 4 (row_ror:4)
+                const float send = b2 ? c[j] : c[j + W / 16];
+                const float up = dpp_mov<0x12C>(send), down = dpp_mov<0x124>(send);
+                d[j] = (b2 ? c[j + W / 16] : c[j]) + (b2 ? down : up);
+            }
+            float e;
+            if constexpr (W == 16) e = d[0] + dpp_mov<0x4E>(d[0]);
+            else e = (b1 ? d[1] : d[0]) + dpp_mov<0x4E>(b1 ? d[0] : d[1]);   // partner lane ^ 2
+            return e + dpp_mov<0xB1>(e);                                     // partner lane ^ 1: plain sum
+        }
     }
-    float b[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j)               // partner lane ^ 16
-        b[j] = (b4 ? a[j + 8] : a[j]) + __shfl_xor(b4 ? a[j] : a[j + 8], 16, 64);
-    float c[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)               // partner lane ^ 8: row_ror:8 within 16-lane rows
-        c[j] = (b3 ? b[j + 4] : b[j]) + dpp_mov<0x128>(b3 ? b[j] : b[j + 4]);
-    float d[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {             // partner lane ^ 4: from lane + 4 (row_ror:12) or lane - 4 (row_ror:4)
-        const float send = b2 ? c[j] : c[j + 2];
-        const float up = dpp_mov<0x12C>(send), down = dpp_mov<0x124>(send);
-        d[j] = (b2 ? c[j + 2] : c[j]) + (b2 ? down : up);
-    }
-    float e = (b1 ? d[1] : d[0]) + dpp_mov<0x4E>(b1 ? d[0] : d[1]);   // partner lane ^ 2
-    e += dpp_mov<0xB1>(e);                                              // partner lane ^ 1: plain sum
-    return e;
 }
 
 template <int CTRL>
 __device__ __forceinline__ int dpp_movi(int v) {
     return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, false);
 }
-// Minimum over the 64 lanes of a wave, returned to every lane.  All lanes active.
-__device__ __forceinline__ int wave_min(int v) {
-    v = min(v, dpp_movi<0xB1>(v));
-    v = min(v, dpp_movi<0x4E>(v));
-    v = min(v, dpp_movi<0x124>(v));
-    v = min(v, dpp_movi<0x128>(v));
-    const int r0 = __builtin_amdgcn_readlane(v, 0), r1 = __builtin_amdgcn_readlane(v, 16);
-    const int r2 = __builtin_amdgcn_readlane(v, 32), r3 = __builtin_amdgcn_readlane(v, 48);
-    return min(min(r0, r1), min(r2, r3));
+// Minimum (maximum) over the 64 lanes of a wave of two unsigned 16-bit values
+// packed in a word, returned to every lane.  All lanes active.
+typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+template <bool MAX>
+__device__ __forceinline__ unsigned pk_best(unsigned a, unsigned b) {
+    const ushort2v x = __builtin_bit_cast(ushort2v, a), y = __builtin_bit_cast(ushort2v, b);
+    return __builtin_bit_cast(unsigned, MAX ? __builtin_elementwise_max(x, y) : __builtin_elementwise_min(x, y));
 }
-// Maximum over the 64 lanes of a wave, returned to every lane.  All lanes active.
-__device__ __forceinline__ int wave_max(int v) {
-    v = max(v, dpp_movi<0xB1>(v));
-    v = max(v, dpp_movi<0x4E>(v));
-    v = max(v, dpp_movi<0x124>(v));
-    v = max(v, dpp_movi<0x128>(v));
-    const int r0 = __builtin_amdgcn_readlane(v, 0), r1 = __builtin_amdgcn_readlane(v, 16);
-    const int r2 = __builtin_amdgcn_readlane(v, 32), r3 = __builtin_amdgcn_readlane(v, 48);
-    return max(max(r0, r1), max(r2, r3));
+template <bool MAX>
+__device__ __forceinline__ unsigned wave_pk_best(unsigned v) {
+    v = pk_best<MAX>(v, (unsigned)dpp_movi<0xB1>((int)v));
+    v = pk_best<MAX>(v, (unsigned)dpp_movi<0x4E>((int)v));
+    v = pk_best<MAX>(v, (unsigned)dpp_movi<0x124>((int)v));
+    v = pk_best<MAX>(v, (unsigned)dpp_movi<0x128>((int)v));
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = pk_best<MAX>(r[0], r[1]);
+    const auto q = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return (unsigned)__builtin_amdgcn_readfirstlane((int)pk_best<MAX>(q[0], q[1]));
 }
 
 // Order the LDS accesses of a wave's lanes before and after (the hardware
@@ -373,23 +400,23 @@ hipError_t launch_aa_camera(const ViewConst *views, int L, int Cm, int max_regio
                             const TriSetup *setup, const int *faces, const unsigned char *silm, const float *verts,
                             const unsigned long long *keys, const float *src, float *dst, int C,
                             unsigned char *aa_flag, hipStream_t s);
-hipError_t launch_lookup(const ViewConst *views, const RenderConst *renders, int R, int max_pix,
-                         const int *render_lights, const TriVerts *tv, const float *albedo,
-                         const unsigned long long *keys, const float *maps, float *img0, int C, hipStream_t s);
+hipError_t launch_lookup(const ViewConst *views, int L, int Cm, int max_pix, int max_renders,
+                         const RenderConst *renders, const int *cam_renders_off, const int *cam_renders,
+                         const int *render_lights, const TriVerts *tv, const unsigned long long *keys,
+                         const float *maps, float *img0, int C, hipStream_t s);
 // backward
 hipError_t launch_aa_camera_backward(const ViewConst *views, int L, int Cm, int max_regions, int max_renders,
                                      const RenderConst *renders, const int *cam_renders_off, const int *cam_renders,
                                      const TriSetup *setup, const int *faces, const unsigned char *silm, const float *verts,
                                      const unsigned long long *keys, const unsigned char *aa_flag, const float *img0,
                                      const float *gimg, float *gimg0, float4 *gclip, int C, hipStream_t s);
-hipError_t launch_lookup_backward(int tile, const ViewConst *views, int L, int Cm, int max_tiles, int max_lights,
+hipError_t launch_lookup_backward(int tile, const ViewConst *views, int L, int Cm, int max_tiles,
                                   const RenderConst *renders, const int *cam_renders_off, const int *cam_renders,
-                                  const int *render_lights, const int *faces, const float *verts, const float *albedo,
-                                  const TriVerts *tv, const unsigned long long *keys, const float *maps,
-                                  const float *gimg0, float *gmaps, const TriSetup *setup, const unsigned *tile_start,
-                                  const unsigned *bins, const unsigned *bin_pair, unsigned char *pair_flag,
-                                  float *pair_sums, float *gtri, float *part_render, int C, const float *jac,
-                                  const unsigned *pair_off, unsigned capacity, hipStream_t s);
+                                  const int *render_lights, const TriVerts *tv, const unsigned long long *keys,
+                                  const float *maps, const float *gimg0, float *gmaps, const TriSetup *setup,
+                                  const unsigned *tile_start, const unsigned *bins, const unsigned *bin_pair,
+                                  unsigned char *pair_flag, float *pair_sums, float *gtri, float *part_render, int C,
+                                  const float *jac, const unsigned *pair_off, unsigned capacity, hipStream_t s);
 hipError_t launch_light_backward(int tile, const ViewConst *views, int L, int max_tiles, const TriSetup *setup,
                                  const int *faces, const unsigned char *silm, const float *verts, const TriVerts *tv,
                                  const unsigned long long *keys, const unsigned char *aa_flag, const float *F0, const float *gF1, float4 *gclip,

@@ -138,9 +138,9 @@ __device__ __forceinline__ void edge_add(EdgeTerm &t, float4 *__restrict__ gclip
         float v[6];
 #pragma unroll
         for (int k = 0; k < 6; ++k) v[k] = mine ? t.g[k] : 0.f;
-        const float s = wave_sum_multi(v);               // lane 2k: the group's total of term k
-        const int k = lane >> 1;
-        if ((lane & 1) == 0 && k < 6) {
+        const float s = wave_sum_multi(v);               // lane 8k: the group's total of term k
+        const int k = lane >> kSumShift<6>;
+        if ((lane & 7) == 0 && k < 6) {
             float *p = (float *)(gclip + (k < 3 ? va : vb));
             const int c = k < 3 ? k : k - 3;
             atomic_add_f32(p + (c == 2 ? 3 : c), s);
@@ -319,13 +319,14 @@ __device__ __forceinline__ void block_sum_store(const float (&val)[N], float *ds
     __shared__ float part[NW][32];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     __syncthreads();
-    const float t = wave_sum_multi(val);      // lane 2i holds the wave's total of value i
-    const int i = lane >> 1;
+    const float t = wave_sum_multi(val);
+    const int i = lane >> kSumShift<N>;
+    const bool holds = (lane & ((1 << kSumShift<N>) - 1)) == 0 && i < N;
     if (NW == 1) {
-        if ((lane & 1) == 0 && i < N) dst[slot(i)] = t;
+        if (holds) dst[slot(i)] = t;
         return;
     }
-    if ((lane & 1) == 0 && i < N) part[w][i] = t;
+    if (holds) part[w][i] = t;
     __syncthreads();
     if (threadIdx.x < N) {
         float s = 0.f;
@@ -543,7 +544,7 @@ __device__ __forceinline__ void wave_pair_sums(const ViewConst &v, int tx, int t
         float masked[N];
 #pragma unroll
         for (int i = 0; i < N; ++i) masked[i] = in ? val[i] : 0.f;
-        const float t = wave_sum_multi(masked);          // lane 2i: the group's total of value i
+        const float t = wave_sum_multi(masked);          // lane 2i: the group's total of value i (17 <= N <= 32)
         const unsigned sl = (unsigned)__builtin_amdgcn_readlane((int)slot, l);
         if ((lane & 1) == 0 && (lane >> 1) < N) pair_sums[(size_t)sl * kRow + row_slot(lane >> 1)] = t;
         if (lane == l) pair_flag[sl] = 1;
@@ -574,9 +575,6 @@ __device__ __forceinline__ void wave_pair_sums(const ViewConst &v, int tx, int t
 
 // ----------------------------------------------------------------------------- lookup^T
 
-// Gradient contributions of one camera pixel: vertex terms (gv[9] for the
-// 3 corners' world positions, gc[9] for their clip (x, y, w)), albedo terms,
-// and per-light frame terms added into accl.
 // Where one pixel's gradient lands in a light's moment maps: the bilinear
 // taps around texel coordinate (ix + fx, iy + fy), weights for (gm1, gm2).
 struct MapHit {
@@ -584,229 +582,226 @@ struct MapHit {
     float fx, fy, gm1, gm2;
 };
 
-template <int MAXL, bool DIRECT>
-__device__ __forceinline__ void lookup_pixel_grad(const ViewConst &cv, const RenderConst &R,
-                                                  const ViewConst *__restrict__ views,
-                                                  const int *__restrict__ render_lights,
-                                                  const TriVerts *__restrict__ tv, const float *__restrict__ albedo,
-                                                  const float *__restrict__ maps,
-                                                  float *__restrict__ gmaps, int i, int j, int tri, const float g[3],
-                                                  int C, float (&vals)[21], float (&accl)[MAXL][3],
-                                                  MapHit (&hits)[MAXL], const float *__restrict__ jac) {
-    const TriVerts r = tv[cv.face_off + tri];
-    const float v0[3] = {r.a.x, r.a.y, r.a.z}, v1[3] = {r.a.w, r.b.x, r.b.y}, v2[3] = {r.b.z, r.b.w, r.c.x};
-    const float px = ndc_c(i, cv.W), py = -ndc_c(j, cv.H);
-    const float4 c0 = clip_of(cv.M, v0[0], v0[1], v0[2]), c1 = clip_of(cv.M, v1[0], v1[1], v1[2]),
-                 c2 = clip_of(cv.M, v2[0], v2[1], v2[2]);
-    const BaryFull b = bary_full(c0, c1, c2, px, py);
-    const float x = (b.b0 * v0[0] + b.b1 * v1[0]) + b.b2 * v2[0];
-    const float y = (b.b0 * v0[1] + b.b1 * v1[1]) + b.b2 * v2[1];
-    const float z = (b.b0 * v0[2] + b.b1 * v1[2]) + b.b2 * v2[2];
-    const float e1x = v1[0] - v0[0], e1y = v1[1] - v0[1], e1z = v1[2] - v0[2];
-    const float e2x = v2[0] - v0[0], e2y = v2[1] - v0[1], e2z = v2[2] - v0[2];
+// A camera pixel as its renders share it: the point and normal, recomputed as
+// the forward forms them, what the adjoint of those needs, and the gradients
+// that every light of every render adds to.  The adjoint from the point and
+// the normal to the corners is linear in them, so it runs once per pixel.
+struct PixelGeom {
+    BaryFull b;
+    float px, py;
+    float v0[3], v1[3], v2[3], rho[3];
+    float x, y, z, nx, ny, nz, rn;
+    float gx[3], gn[3];
+};
+
+__device__ __forceinline__ void pixel_geom(PixelGeom &g, const ViewConst &cv, const TriVerts &r, int i, int j) {
+    g.v0[0] = r.a.x; g.v0[1] = r.a.y; g.v0[2] = r.a.z;
+    g.v1[0] = r.a.w; g.v1[1] = r.b.x; g.v1[2] = r.b.y;
+    g.v2[0] = r.b.z; g.v2[1] = r.b.w; g.v2[2] = r.c.x;
+    g.rho[0] = r.c.y; g.rho[1] = r.c.z; g.rho[2] = r.c.w;          // from the face record
+    g.px = ndc_c(i, cv.W);
+    g.py = -ndc_c(j, cv.H);
+    const float4 c0 = clip_of(cv.M, g.v0[0], g.v0[1], g.v0[2]), c1 = clip_of(cv.M, g.v1[0], g.v1[1], g.v1[2]),
+                 c2 = clip_of(cv.M, g.v2[0], g.v2[1], g.v2[2]);
+    g.b = bary_full(c0, c1, c2, g.px, g.py);
+    g.x = (g.b.b0 * g.v0[0] + g.b.b1 * g.v1[0]) + g.b.b2 * g.v2[0];
+    g.y = (g.b.b0 * g.v0[1] + g.b.b1 * g.v1[1]) + g.b.b2 * g.v2[1];
+    g.z = (g.b.b0 * g.v0[2] + g.b.b1 * g.v1[2]) + g.b.b2 * g.v2[2];
+    const float e1x = g.v1[0] - g.v0[0], e1y = g.v1[1] - g.v0[1], e1z = g.v1[2] - g.v0[2];
+    const float e2x = g.v2[0] - g.v0[0], e2y = g.v2[1] - g.v0[1], e2z = g.v2[2] - g.v0[2];
     const float crx = e1y * e2z - e1z * e2y, cry = e1z * e2x - e1x * e2z, crz = e1x * e2y - e1y * e2x;
-    const float rn0 = __builtin_amdgcn_rsqf((crx * crx + cry * cry) + crz * crz);
-    const float nx = crx * rn0, ny = cry * rn0, nz = crz * rn0;
-    float rho[3] = {0.f, 0.f, 0.f};
-    for (int c = 0; c < C; ++c) rho[c] = c == 0 ? r.c.y : c == 1 ? r.c.z : r.c.w;   // from the face record
-    float srho = 0.f;
-    for (int c = 0; c < C; ++c) srho += g[c] * rho[c];
-    float gx[3] = {0, 0, 0}, gn[3] = {0, 0, 0};
-    float shade = 0.f;
+    g.rn = __builtin_amdgcn_rsqf((crx * crx + cry * cry) + crz * crz);
+    g.nx = crx * g.rn;
+    g.ny = cry * g.rn;
+    g.nz = crz * g.rn;
 #pragma unroll
-    for (int q = 0; q < MAXL; ++q) {
-        if (q >= R.light_count) break;
-        const ViewConst &l = views[render_lights[R.light_begin + q]];
-        const float *M = l.M;
-        const float cx = ((M[0] * x + M[1] * y) + M[2] * z) + M[3];
-        const float cy = ((M[4] * x + M[5] * y) + M[6] * z) + M[7];
-        const float cw = ((M[12] * x + M[13] * y) + M[14] * z) + M[15];
-        const float rcw = __builtin_amdgcn_rcpf(cw);
-        const float ux = cx * rcw, uy = cy * rcw;
-        const bool inside = cw > 0.f && fabsf(ux) <= 1.f && fabsf(uy) <= 1.f;
-        float vis = 1.f, visr = 1.f, zz = 0.f, zw = 0.f, floor_v = 0.f, m1 = 0.f, m2 = 0.f, var = 0.f, dd = 0.f,
-              fx = 0.f, fy = 0.f;
-        long long o00 = 0, o01 = 0, o10 = 0, o11 = 0;
-        int ixs = 0, iys = 0;
-        hits[q].gm1 = 0.f;
-        hits[q].gm2 = 0.f;
-        // outside its own directions a cube face adds nothing, nor any gradient
-        if (l.kind == kCubeFace && cube_face_of(x - l.pos[0], y - l.pos[1], z - l.pos[2]) != l.cube_face) continue;
-        const int S = l.W;
-        // filtered maps are stored with side Sp; cube faces keep P texels of
-        // their neighbours around the face, so taps may cross the seam
-        const int P = l.fpad, Sp = S + 2 * P;
-        // filtered maps hold (m1, m2) interleaved per texel
-        const float2 *mm = (const float2 *)(maps + l.fmap_off);
-        float2 t00 = make_float2(0.f, 0.f), t01 = t00, t10 = t00, t11 = t00;
-        if (inside) {
-            const float sx = (ux + 1.f) * (0.5f * S) - 0.5f;
-            const float sy = (1.f - uy) * (0.5f * S) - 0.5f;
-            const float fx0 = floorf(sx), fy0 = floorf(sy);
-            fx = sx - fx0;
-            fy = sy - fy0;
-            const int ix = (int)fx0 + P, iy = (int)fy0 + P;
-            ixs = ix;
-            iys = iy;
-            const int x0 = min(max(ix, 0), Sp - 1), x1 = min(max(ix + 1, 0), Sp - 1);
-            const int y0 = min(max(iy, 0), Sp - 1), y1 = min(max(iy + 1, 0), Sp - 1);
-            const float w00 = (1.f - fx) * (1.f - fy), w01 = fx * (1.f - fy), w10 = (1.f - fx) * fy, w11 = fx * fy;
-            o00 = (long long)y0 * Sp + x0; o01 = (long long)y0 * Sp + x1;
-            o10 = (long long)y1 * Sp + x0; o11 = (long long)y1 * Sp + x1;
-            t00 = mm[o00]; t01 = mm[o01]; t10 = mm[o10]; t11 = mm[o11];
-            m1 = ((w00 * t00.x + w01 * t01.x) + w10 * t10.x) + w11 * t11.x;
-            m2 = ((w00 * t00.y + w01 * t01.y) + w10 * t10.y) + w11 * t11.y;
-            float depth;
-            if (l.kind == kDirectional)
-                depth = ((x - l.pos[0]) * l.dir[0] + (y - l.pos[1]) * l.dir[1]) + (z - l.pos[2]) * l.dir[2];
-            else {
-                const float ddx = x - l.pos[0], ddy = y - l.pos[1], ddz = z - l.pos[2];
-                depth = sqrtf((ddx * ddx + ddy * ddy) + ddz * ddz);
-            }
-            zz = depth * grcp(l.zfar) - l.zc;
-            warp_receiver(l, zz, zw, floor_v);
-            var = fmaxf(m2 - m1 * m1, floor_v);
-            dd = zw - m1;
-            visr = (zw <= m1) ? 1.f : var * grcp(var + dd * dd);
-            vis = bleed_reduce(l, visr);
+    for (int k = 0; k < 3; ++k) g.gx[k] = g.gn[k] = 0.f;
+}
+
+// One light of one render: the shade it adds, its terms in gx and gn, this
+// pixel's gradient w.r.t. the light parameter (al) and its map gradient.
+__device__ __forceinline__ void light_terms(PixelGeom &g, const ViewConst &l, const float *__restrict__ J,
+                                            const float *__restrict__ maps, float srho, float &shade, float (&al)[3],
+                                            MapHit &hit) {
+    const float x = g.x, y = g.y, z = g.z, nx = g.nx, ny = g.ny, nz = g.nz;
+    const float *M = l.M;
+    // outside its own directions a cube face adds nothing, nor any gradient
+    if (l.kind == kCubeFace && cube_face_of(x - l.pos[0], y - l.pos[1], z - l.pos[2]) != l.cube_face) return;
+    const float cx = ((M[0] * x + M[1] * y) + M[2] * z) + M[3];
+    const float cy = ((M[4] * x + M[5] * y) + M[6] * z) + M[7];
+    const float cw = ((M[12] * x + M[13] * y) + M[14] * z) + M[15];
+    const float rcw = __builtin_amdgcn_rcpf(cw);
+    const float ux = cx * rcw, uy = cy * rcw;
+    const bool inside = cw > 0.f && fabsf(ux) <= 1.f && fabsf(uy) <= 1.f;
+    float vis = 1.f, visr = 1.f, zz = 0.f, zw = 0.f, floor_v = 0.f, m1 = 0.f, m2 = 0.f, var = 0.f, dd = 0.f, fx = 0.f,
+          fy = 0.f;
+    int ixs = 0, iys = 0;
+    const int S = l.W;
+    // filtered maps are stored with side Sp; cube faces keep P texels of
+    // their neighbours around the face, so taps may cross the seam
+    const int P = l.fpad, Sp = S + 2 * P;
+    // filtered maps hold (m1, m2) interleaved per texel
+    const float2 *mm = (const float2 *)(maps + l.fmap_off);
+    float2 t00 = make_float2(0.f, 0.f), t01 = t00, t10 = t00, t11 = t00;
+    if (inside) {
+        const float sx = (ux + 1.f) * (0.5f * S) - 0.5f;
+        const float sy = (1.f - uy) * (0.5f * S) - 0.5f;
+        const float fx0 = floorf(sx), fy0 = floorf(sy);
+        fx = sx - fx0;
+        fy = sy - fy0;
+        const int ix = (int)fx0 + P, iy = (int)fy0 + P;
+        ixs = ix;
+        iys = iy;
+        const int x0 = min(max(ix, 0), Sp - 1), x1 = min(max(ix + 1, 0), Sp - 1);
+        const int y0 = min(max(iy, 0), Sp - 1), y1 = min(max(iy + 1, 0), Sp - 1);
+        const float w00 = (1.f - fx) * (1.f - fy), w01 = fx * (1.f - fy), w10 = (1.f - fx) * fy, w11 = fx * fy;
+        t00 = mm[y0 * Sp + x0]; t01 = mm[y0 * Sp + x1]; t10 = mm[y1 * Sp + x0]; t11 = mm[y1 * Sp + x1];
+        m1 = ((w00 * t00.x + w01 * t01.x) + w10 * t10.x) + w11 * t11.x;
+        m2 = ((w00 * t00.y + w01 * t01.y) + w10 * t10.y) + w11 * t11.y;
+        float depth;
+        if (l.kind == kDirectional)
+            depth = ((x - l.pos[0]) * l.dir[0] + (y - l.pos[1]) * l.dir[1]) + (z - l.pos[2]) * l.dir[2];
+        else {
+            const float ddx = x - l.pos[0], ddy = y - l.pos[1], ddz = z - l.pos[2];
+            depth = sqrtf((ddx * ddx + ddy * ddy) + ddz * ddz);
         }
-        float ox, oy, oz, olen = 1.f;
-        if (l.kind == kDirectional) {
-            ox = -l.dir[0]; oy = -l.dir[1]; oz = -l.dir[2];
-        } else {
-            ox = l.pos[0] - x; oy = l.pos[1] - y; oz = l.pos[2] - z;
-            olen = sqrtf((ox * ox + oy * oy) + oz * oz);
-            const float rol = grcp(olen);
-            ox *= rol; oy *= rol; oz *= rol;
-        }
-        const float ndo = (nx * ox + ny * oy) + nz * oz;
-        const float lam = fmaxf(ndo, 0.f);
-        float cone = 1.f;
-        if (l.kind == kSpot) {
-            const float ca = -((ox * l.dir[0] + oy * l.dir[1]) + oz * l.dir[2]);
-            cone = ca >= l.cos_half ? 1.f : 0.f;
-        }
-        shade += lam * vis * l.intensity * cone;
-        const float gvis = srho * lam * l.intensity * cone;
-        const float glam = srho * vis * l.intensity * cone;
-        const float gndo = ndo > 0.f ? glam : 0.f;
-        // from here on only gradient terms are formed: fused multiply-adds
-        // (nothing below feeds a forward value or a decision)
-        gn[0] = fmaf(gndo, ox, gn[0]); gn[1] = fmaf(gndo, oy, gn[1]); gn[2] = fmaf(gndo, oz, gn[2]);
-        const float gox = gndo * nx, goy = gndo * ny, goz = gndo * nz;
-        // this pixel's gradient w.r.t. the light frame (M, pos, dir), pulled
-        // back to the light parameter through the frame's Jacobian at the end
-        float gpos[3] = {0.f, 0.f, 0.f}, gdir[3] = {0.f, 0.f, 0.f};
-        float gcx = 0.f, gcy = 0.f, gcw = 0.f;
-        if (l.kind == kDirectional) {
-            gdir[0] -= gox; gdir[1] -= goy; gdir[2] -= goz;
-        } else {
-            const float od = fmaf(oz, goz, fmaf(oy, goy, ox * gox));
-            const float rl = grcp(olen);
-            const float gpx = fmaf(-ox, od, gox) * rl, gpy = fmaf(-oy, od, goy) * rl, gpz = fmaf(-oz, od, goz) * rl;
-            gpos[0] += gpx; gpos[1] += gpy; gpos[2] += gpz;
-            gx[0] -= gpx; gx[1] -= gpy; gx[2] -= gpz;
-        }
-        // through the bleeding reduction: slope 1 / (1 - a) on [a, 1], else 0
-        const float gvr = l.bleed > 0.f ? (visr >= l.bleed ? gvis / (1.f - l.bleed) : 0.f) : gvis;
-        if (inside && gvr != 0.f && zw > m1) {
-            const float qd = var + dd * dd;
-            float dv_dmu, dv_dvar_raw;
-            if (l.warp_c > 0.f) {
-                // exponential maps: the squares of var and dd overflow float32
-                const float rq = grcp(qd);
-                const float tv = var * rq, td = dd * rq;
-                dv_dmu = 2.f * tv * td;
-                dv_dvar_raw = td * td;
-            } else {
-                const float rq2 = grcp(qd * qd);
-                dv_dmu = 2.f * var * dd * rq2;
-                dv_dvar_raw = dd * dd * rq2;
-            }
-            const bool clamped = m2 - m1 * m1 < floor_v;
-            const float dv_dvar = clamped ? 0.f : dv_dvar_raw;
-            const float gm1 = gvr * fmaf(-2.f * m1, dv_dvar, dv_dmu);
-            const float gm2 = gvr * dv_dvar;
-            // d v / d (receiver depth): through d - mu, through the floor when
-            // it binds and follows the warp, and through the warp itself
-            float dv_dzw = -dv_dmu;
-            if (l.warp_c > 0.f) {
-                if (clamped) dv_dzw = fmaf(dv_dvar_raw, 2.f * l.min_var * l.warp_c * l.warp_c * zw, dv_dzw);
-                dv_dzw *= l.warp_c * zw;
-            }
-            const float gdepth = gvr * dv_dzw * grcp(l.zfar);
-            if (l.kind == kDirectional) {
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    gx[k] = fmaf(gdepth, l.dir[k], gx[k]);
-                    gpos[k] = fmaf(-gdepth, l.dir[k], gpos[k]);
-                }
-                gdir[0] = fmaf(gdepth, x - l.pos[0], gdir[0]);
-                gdir[1] = fmaf(gdepth, y - l.pos[1], gdir[1]);
-                gdir[2] = fmaf(gdepth, z - l.pos[2], gdir[2]);
-            } else {
-                const float ddx = x - l.pos[0], ddy = y - l.pos[1], ddz = z - l.pos[2];
-                const float dl = sqrtf((ddx * ddx + ddy * ddy) + ddz * ddz);
-                const float rd = grcp(dl);
-                const float ux_ = ddx * rd, uy_ = ddy * rd, uz_ = ddz * rd;
-                gx[0] = fmaf(gdepth, ux_, gx[0]); gx[1] = fmaf(gdepth, uy_, gx[1]); gx[2] = fmaf(gdepth, uz_, gx[2]);
-                gpos[0] = fmaf(-gdepth, ux_, gpos[0]); gpos[1] = fmaf(-gdepth, uy_, gpos[1]);
-                gpos[2] = fmaf(-gdepth, uz_, gpos[2]);
-            }
-            // bilinear scatter to the moment maps
-            if (DIRECT) {
-                float *ga = gmaps + l.fmap_off, *gb = gmaps + l.fmap_off + 1;      // interleaved: texel o at 2 o
-                o00 *= 2; o01 *= 2; o10 *= 2; o11 *= 2;
-                const float w00 = (1.f - fx) * (1.f - fy), w01 = fx * (1.f - fy), w10 = (1.f - fx) * fy, w11 = fx * fy;
-                atomic_add_f32(ga + o00, gm1 * w00); atomic_add_f32(ga + o01, gm1 * w01);
-                atomic_add_f32(ga + o10, gm1 * w10); atomic_add_f32(ga + o11, gm1 * w11);
-                atomic_add_f32(gb + o00, gm2 * w00); atomic_add_f32(gb + o01, gm2 * w01);
-                atomic_add_f32(gb + o10, gm2 * w10); atomic_add_f32(gb + o11, gm2 * w11);
-            } else {
-                hits[q] = MapHit{ixs, iys, fx, fy, gm1, gm2};
-            }
-            // the map position moves with x and with the light camera
-            // d m / d(fx, fy): each a lerp of two texel differences
-            const float a1 = t01.x - t00.x, b1 = t11.x - t10.x, c1 = t10.x - t00.x, d1 = t11.x - t01.x;
-            const float a2 = t01.y - t00.y, b2 = t11.y - t10.y, c2 = t10.y - t00.y, d2 = t11.y - t01.y;
-            const float dm1fx = fmaf(fy, b1 - a1, a1), dm1fy = fmaf(fx, d1 - c1, c1);
-            const float dm2fx = fmaf(fy, b2 - a2, a2), dm2fy = fmaf(fx, d2 - c2, c2);
-            const float hs = 0.5f * S;
-            const float gsx = fmaf(gm2, dm2fx, gm1 * dm1fx) * hs;
-            const float gsy = fmaf(gm2, dm2fy, gm1 * dm1fy) * hs;
-            const float rw = grcp(cw);
-            gcx = gsx * rw;
-            gcy = -gsy * rw;
-            gcw = fmaf(-gsx, cx, gsy * cy) * (rw * rw);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) gx[k] = fmaf(M[12 + k], gcw, fmaf(M[4 + k], gcy, fmaf(M[k], gcx, gx[k])));
-        }
-        // dL/dM = (gcx, gcy, 0, gcw) outer [x, 1]; with dL/dpos, dL/ddir through J
-        const float *J = jac + (size_t)kJac * render_lights[R.light_begin + q];
-        const float xh[4] = {x, y, z, 1.f};
-        // per parameter j: sum over rows r in (x, y, w) of g_r (J_r(j) . [x, 1]),
-        // plus the position and direction terms
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            float u[3];
-#pragma unroll
-            for (int r = 0; r < 3; ++r) {
-                const int row = r == 0 ? 0 : r == 1 ? 4 : 12;
-                u[r] = fmaf(xh[2], J[3 * (row + 2) + j],
-                            fmaf(xh[1], J[3 * (row + 1) + j], fmaf(xh[0], J[3 * row + j], J[3 * (row + 3) + j])));
-            }
-            float a = fmaf(gcw, u[2], fmaf(gcy, u[1], fmaf(gcx, u[0], accl[q][j])));
-#pragma unroll
-            for (int i = 0; i < 3; ++i) a = fmaf(gdir[i], J[3 * (19 + i) + j], fmaf(gpos[i], J[3 * (16 + i) + j], a));
-            accl[q][j] = a;
-        }
+        zz = depth * grcp(l.zfar) - l.zc;
+        warp_receiver(l, zz, zw, floor_v);
+        var = fmaxf(m2 - m1 * m1, floor_v);
+        dd = zw - m1;
+        visr = (zw <= m1) ? 1.f : var * grcp(var + dd * dd);
+        vis = bleed_reduce(l, visr);
     }
-    // albedo
-    for (int c = 0; c < 3; ++c) vals[18 + c] = c < C ? g[c] * shade : 0.f;
+    float ox, oy, oz, olen = 1.f;
+    if (l.kind == kDirectional) {
+        ox = -l.dir[0]; oy = -l.dir[1]; oz = -l.dir[2];
+    } else {
+        ox = l.pos[0] - x; oy = l.pos[1] - y; oz = l.pos[2] - z;
+        olen = sqrtf((ox * ox + oy * oy) + oz * oz);
+        const float rol = grcp(olen);
+        ox *= rol; oy *= rol; oz *= rol;
+    }
+    const float ndo = (nx * ox + ny * oy) + nz * oz;
+    const float lam = fmaxf(ndo, 0.f);
+    float cone = 1.f;
+    if (l.kind == kSpot) {
+        const float ca = -((ox * l.dir[0] + oy * l.dir[1]) + oz * l.dir[2]);
+        cone = ca >= l.cos_half ? 1.f : 0.f;
+    }
+    shade += lam * vis * l.intensity * cone;
+    const float gvis = srho * lam * l.intensity * cone;
+    const float glam = srho * vis * l.intensity * cone;
+    const float gndo = ndo > 0.f ? glam : 0.f;
+    // from here on only gradient terms are formed: fused multiply-adds
+    // (nothing below feeds a forward value or a decision)
+    g.gn[0] = fmaf(gndo, ox, g.gn[0]); g.gn[1] = fmaf(gndo, oy, g.gn[1]); g.gn[2] = fmaf(gndo, oz, g.gn[2]);
+    const float gox = gndo * nx, goy = gndo * ny, goz = gndo * nz;
+    // this pixel's gradient w.r.t. the light frame (M, pos, dir), pulled
+    // back to the light parameter through the frame's Jacobian at the end
+    float gpos[3] = {0.f, 0.f, 0.f}, gdir[3] = {0.f, 0.f, 0.f};
+    float gcx = 0.f, gcy = 0.f, gcw = 0.f;
+    if (l.kind == kDirectional) {
+        gdir[0] -= gox; gdir[1] -= goy; gdir[2] -= goz;
+    } else {
+        const float od = fmaf(oz, goz, fmaf(oy, goy, ox * gox));
+        const float rl = grcp(olen);
+        const float gpx = fmaf(-ox, od, gox) * rl, gpy = fmaf(-oy, od, goy) * rl, gpz = fmaf(-oz, od, goz) * rl;
+        gpos[0] += gpx; gpos[1] += gpy; gpos[2] += gpz;
+        g.gx[0] -= gpx; g.gx[1] -= gpy; g.gx[2] -= gpz;
+    }
+    // through the bleeding reduction: slope 1 / (1 - a) on [a, 1], else 0
+    const float gvr = l.bleed > 0.f ? (visr >= l.bleed ? gvis / (1.f - l.bleed) : 0.f) : gvis;
+    if (inside && gvr != 0.f && zw > m1) {
+        const float qd = var + dd * dd;
+        float dv_dmu, dv_dvar_raw;
+        if (l.warp_c > 0.f) {
+            // exponential maps: the squares of var and dd overflow float32
+            const float rq = grcp(qd);
+            const float tv = var * rq, td = dd * rq;
+            dv_dmu = 2.f * tv * td;
+            dv_dvar_raw = td * td;
+        } else {
+            const float rq2 = grcp(qd * qd);
+            dv_dmu = 2.f * var * dd * rq2;
+            dv_dvar_raw = dd * dd * rq2;
+        }
+        const bool clamped = m2 - m1 * m1 < floor_v;
+        const float dv_dvar = clamped ? 0.f : dv_dvar_raw;
+        const float gm1 = gvr * fmaf(-2.f * m1, dv_dvar, dv_dmu);
+        const float gm2 = gvr * dv_dvar;
+        // d v / d (receiver depth): through d - mu, through the floor when
+        // it binds and follows the warp, and through the warp itself
+        float dv_dzw = -dv_dmu;
+        if (l.warp_c > 0.f) {
+            if (clamped) dv_dzw = fmaf(dv_dvar_raw, 2.f * l.min_var * l.warp_c * l.warp_c * zw, dv_dzw);
+            dv_dzw *= l.warp_c * zw;
+        }
+        const float gdepth = gvr * dv_dzw * grcp(l.zfar);
+        if (l.kind == kDirectional) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                g.gx[k] = fmaf(gdepth, l.dir[k], g.gx[k]);
+                gpos[k] = fmaf(-gdepth, l.dir[k], gpos[k]);
+            }
+            gdir[0] = fmaf(gdepth, x - l.pos[0], gdir[0]);
+            gdir[1] = fmaf(gdepth, y - l.pos[1], gdir[1]);
+            gdir[2] = fmaf(gdepth, z - l.pos[2], gdir[2]);
+        } else {
+            const float ddx = x - l.pos[0], ddy = y - l.pos[1], ddz = z - l.pos[2];
+            const float dl = sqrtf((ddx * ddx + ddy * ddy) + ddz * ddz);
+            const float rd = grcp(dl);
+            const float ux_ = ddx * rd, uy_ = ddy * rd, uz_ = ddz * rd;
+            g.gx[0] = fmaf(gdepth, ux_, g.gx[0]); g.gx[1] = fmaf(gdepth, uy_, g.gx[1]);
+            g.gx[2] = fmaf(gdepth, uz_, g.gx[2]);
+            gpos[0] = fmaf(-gdepth, ux_, gpos[0]); gpos[1] = fmaf(-gdepth, uy_, gpos[1]);
+            gpos[2] = fmaf(-gdepth, uz_, gpos[2]);
+        }
+        hit = MapHit{ixs, iys, fx, fy, gm1, gm2};        // bilinear scatter to the moment maps
+        // the map position moves with x and with the light camera
+        // d m / d(fx, fy): each a lerp of two texel differences
+        const float a1 = t01.x - t00.x, b1 = t11.x - t10.x, c1 = t10.x - t00.x, d1 = t11.x - t01.x;
+        const float a2 = t01.y - t00.y, b2 = t11.y - t10.y, c2 = t10.y - t00.y, d2 = t11.y - t01.y;
+        const float dm1fx = fmaf(fy, b1 - a1, a1), dm1fy = fmaf(fx, d1 - c1, c1);
+        const float dm2fx = fmaf(fy, b2 - a2, a2), dm2fy = fmaf(fx, d2 - c2, c2);
+        const float hs = 0.5f * S;
+        const float gsx = fmaf(gm2, dm2fx, gm1 * dm1fx) * hs;
+        const float gsy = fmaf(gm2, dm2fy, gm1 * dm1fy) * hs;
+        const float rw = grcp(cw);
+        gcx = gsx * rw;
+        gcy = -gsy * rw;
+        gcw = fmaf(-gsx, cx, gsy * cy) * (rw * rw);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) g.gx[k] = fmaf(M[12 + k], gcw, fmaf(M[4 + k], gcy, fmaf(M[k], gcx, g.gx[k])));
+    }
+    // dL/dM = (gcx, gcy, 0, gcw) outer [x, 1]; with dL/dpos, dL/ddir through J
+    const float xh[4] = {x, y, z, 1.f};
+    // per parameter j: sum over rows r in (x, y, w) of g_r (J_r(j) . [x, 1]),
+    // plus the position and direction terms
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        float u[3];
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const int row = r == 0 ? 0 : r == 1 ? 4 : 12;
+            u[r] = fmaf(xh[2], J[3 * (row + 2) + j],
+                        fmaf(xh[1], J[3 * (row + 1) + j], fmaf(xh[0], J[3 * row + j], J[3 * (row + 3) + j])));
+        }
+        float a = fmaf(gcw, u[2], fmaf(gcy, u[1], fmaf(gcx, u[0], al[j])));
+#pragma unroll
+        for (int i = 0; i < 3; ++i) a = fmaf(gdir[i], J[3 * (19 + i) + j], fmaf(gpos[i], J[3 * (16 + i) + j], a));
+        al[j] = a;
+    }
+}
+
+// From the point and the normal to the corners: vals[0..9) the corners' world
+// positions, vals[9..18) their clip (x, y, w).
+__device__ __forceinline__ void pixel_adjoint(const PixelGeom &g, float (&vals)[kNV]) {
+    const float e1x = g.v1[0] - g.v0[0], e1y = g.v1[1] - g.v0[1], e1z = g.v1[2] - g.v0[2];
+    const float e2x = g.v2[0] - g.v0[0], e2y = g.v2[1] - g.v0[1], e2z = g.v2[2] - g.v0[2];
     // normal: n = cr / |cr|, cr = e1 x e2
-    const float ndg = fmaf(nz, gn[2], fmaf(ny, gn[1], nx * gn[0]));
-    const float rn = rn0;
-    const float gcr[3] = {fmaf(-nx, ndg, gn[0]) * rn, fmaf(-ny, ndg, gn[1]) * rn, fmaf(-nz, ndg, gn[2]) * rn};
+    const float ndg = fmaf(g.nz, g.gn[2], fmaf(g.ny, g.gn[1], g.nx * g.gn[0]));
+    const float gcr[3] = {fmaf(-g.nx, ndg, g.gn[0]) * g.rn, fmaf(-g.ny, ndg, g.gn[1]) * g.rn,
+                          fmaf(-g.nz, ndg, g.gn[2]) * g.rn};
     const float ge1[3] = {fmaf(e2y, gcr[2], -e2z * gcr[1]), fmaf(e2z, gcr[0], -e2x * gcr[2]),
                           fmaf(e2x, gcr[1], -e2y * gcr[0])};
     const float ge2[3] = {fmaf(gcr[1], e1z, -gcr[2] * e1y), fmaf(gcr[2], e1x, -gcr[0] * e1z),
@@ -814,15 +809,15 @@ __device__ __forceinline__ void lookup_pixel_grad(const ViewConst &cv, const Ren
     // x = sum b_i v_i
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        vals[k] = fmaf(b.b0, gx[k], -ge1[k]) - ge2[k];
-        vals[3 + k] = fmaf(b.b1, gx[k], ge1[k]);
-        vals[6 + k] = fmaf(b.b2, gx[k], ge2[k]);
+        vals[k] = fmaf(g.b.b0, g.gx[k], -ge1[k]) - ge2[k];
+        vals[3 + k] = fmaf(g.b.b1, g.gx[k], ge1[k]);
+        vals[6 + k] = fmaf(g.b.b2, g.gx[k], ge2[k]);
     }
-    const float gb0 = fmaf(gx[2], v0[2], fmaf(gx[1], v0[1], gx[0] * v0[0]));
-    const float gb1 = fmaf(gx[2], v1[2], fmaf(gx[1], v1[1], gx[0] * v1[0]));
-    const float gb2 = fmaf(gx[2], v2[2], fmaf(gx[1], v2[1], gx[0] * v2[0]));
+    const float gb0 = fmaf(g.gx[2], g.v0[2], fmaf(g.gx[1], g.v0[1], g.gx[0] * g.v0[0]));
+    const float gb1 = fmaf(g.gx[2], g.v1[2], fmaf(g.gx[1], g.v1[1], g.gx[0] * g.v1[0]));
+    const float gb2 = fmaf(g.gx[2], g.v2[2], fmaf(g.gx[1], g.v2[1], g.gx[0] * g.v2[0]));
     float gc[9];
-    bary_backward(b, px, py, gb0, gb1, gb2, gc);
+    bary_backward(g.b, g.px, g.py, gb0, gb1, gb2, gc);
 #pragma unroll
     for (int k = 0; k < 9; ++k) vals[9 + k] = gc[k];
 }
@@ -836,29 +831,29 @@ __device__ __forceinline__ void lookup_pixel_grad(const ViewConst &cv, const Ren
 // global memory directly.  Uniform call.
 template <int NW, int PPT, int WIN>
 __device__ __forceinline__ void map_window_scatter(const MapHit (&hit)[PPT], int S, float *__restrict__ gmap) {
-    __shared__ float win[NW][2][WIN * WIN];
+    static_assert(WIN == 16 || WIN == 32, "the window's rows are walked in powers of two");
+    __shared__ float2 win[NW][WIN * WIN];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int mx = 0x7fffffff, my = 0x7fffffff, Mx = -1, My = -1;
+    // smallest and largest tap, (x, y) packed in 16 bits each (S is at most 8192 and its padding)
+    unsigned lo = 0xFFFFFFFFu, hi = 0u;
 #pragma unroll
     for (int k = 0; k < PPT; ++k)
         if (hit[k].gm1 != 0.f || hit[k].gm2 != 0.f) {
-            mx = min(mx, min(max(hit[k].ix, 0), S - 1));
-            my = min(my, min(max(hit[k].iy, 0), S - 1));
-            Mx = max(Mx, min(max(hit[k].ix + 1, 0), S - 1));
-            My = max(My, min(max(hit[k].iy + 1, 0), S - 1));
+            lo = pk_best<false>(lo, (unsigned)min(max(hit[k].ix, 0), S - 1) | (unsigned)min(max(hit[k].iy, 0), S - 1) << 16);
+            hi = pk_best<true>(hi, (unsigned)min(max(hit[k].ix + 1, 0), S - 1) |
+                                       (unsigned)min(max(hit[k].iy + 1, 0), S - 1) << 16);
         }
-    mx = wave_min(mx);
-    my = wave_min(my);
-    Mx = wave_max(Mx);
-    My = wave_max(My);
-    const bool any = mx != 0x7fffffff;
+    lo = wave_pk_best<false>(lo);
+    const bool any = lo != 0xFFFFFFFFu;
+    if (NW == 1 && !any) return;
+    hi = wave_pk_best<true>(hi);
+    const int mx = (int)(lo & 0xFFFFu), my = (int)(lo >> 16);
     // every tap that lands in the window lies in the bounding box
-    const int bw = any ? min(Mx - mx + 1, WIN) : 0, bh = any ? min(My - my + 1, WIN) : 0;
-    for (int e = lane; e < bw * bh; e += 64) {
-        const int o = (e / bw) * WIN + e % bw;
-        win[w][0][o] = 0.f;
-        win[w][1][o] = 0.f;
-    }
+    const int bw = any ? min((int)(hi & 0xFFFFu) - mx + 1, WIN) : 0, bh = any ? min((int)(hi >> 16) - my + 1, WIN) : 0;
+    // lanes over the box: 8 columns wide where that holds it
+    const int cs = bw <= 8 ? 3 : WIN == 16 ? 4 : 5, ex = lane & ((1 << cs) - 1), ey0 = lane >> cs, es = 64 >> cs;
+    if (ex < bw)
+        for (int ey = ey0; ey < bh; ey += es) win[w][ey * WIN + ex] = make_float2(0.f, 0.f);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
@@ -869,13 +864,12 @@ __device__ __forceinline__ void map_window_scatter(const MapHit (&hit)[PPT], int
         const float w00 = (1.f - h.fx) * (1.f - h.fy), w01 = h.fx * (1.f - h.fy);
         const float w10 = (1.f - h.fx) * h.fy, w11 = h.fx * h.fy;
         if (x1 - mx < WIN && y1 - my < WIN) {
-            float *a = win[w][0], *b = win[w][1];
-            const int o00 = (y0 - my) * WIN + (x0 - mx), o01 = (y0 - my) * WIN + (x1 - mx);
-            const int o10 = (y1 - my) * WIN + (x0 - mx), o11 = (y1 - my) * WIN + (x1 - mx);
-            atomicAdd(a + o00, h.gm1 * w00); atomicAdd(a + o01, h.gm1 * w01);
-            atomicAdd(a + o10, h.gm1 * w10); atomicAdd(a + o11, h.gm1 * w11);
-            atomicAdd(b + o00, h.gm2 * w00); atomicAdd(b + o01, h.gm2 * w01);
-            atomicAdd(b + o10, h.gm2 * w10); atomicAdd(b + o11, h.gm2 * w11);
+            float2 *o = win[w] + (y0 - my) * WIN + (x0 - mx);
+            const int dx = x1 - x0, dy = (y1 - y0) * WIN;
+            atomicAdd(&o[0].x, h.gm1 * w00); atomicAdd(&o[dx].x, h.gm1 * w01);
+            atomicAdd(&o[dy].x, h.gm1 * w10); atomicAdd(&o[dy + dx].x, h.gm1 * w11);
+            atomicAdd(&o[0].y, h.gm2 * w00); atomicAdd(&o[dx].y, h.gm2 * w01);
+            atomicAdd(&o[dy].y, h.gm2 * w10); atomicAdd(&o[dy + dx].y, h.gm2 * w11);
         } else {
             float *a = gmap, *b = gmap + 1;          // interleaved (m1, m2): texel o at 2 o
             const long long o00 = 2 * ((long long)y0 * S + x0), o01 = 2 * ((long long)y0 * S + x1);
@@ -887,28 +881,36 @@ __device__ __forceinline__ void map_window_scatter(const MapHit (&hit)[PPT], int
         }
     }
     __syncthreads();
-    if (any) {
-        for (int e = lane; e < bw * bh; e += 64) {
-            const int ex = e % bw, ey = e / bw;
-            const long long o = 2 * ((long long)(my + ey) * S + (mx + ex));
-            const float a = win[w][0][ey * WIN + ex], b = win[w][1][ey * WIN + ex];
-            if (a != 0.f) atomic_add_f32(gmap + o, a);
-            if (b != 0.f) atomic_add_f32(gmap + o + 1, b);
+    if (ex < bw)
+        for (int ey = ey0; ey < bh; ey += es) {
+            const float2 t = win[w][ey * WIN + ex];
+            float *o = gmap + 2 * ((long long)(my + ey) * S + (mx + ex));
+            if (t.x != 0.f) atomic_add_f32(o, t.x);
+            if (t.y != 0.f) atomic_add_f32(o + 1, t.y);
         }
-    }
     __syncthreads();
 }
 
-template <int T, int MAXL>
-__device__ __forceinline__ void lookup_backward_body(
+// Per camera tile, for every render of the camera and every light of the
+// render in turn: the light's terms of each pixel, their map gradient through
+// the LDS window, the tile's share of the light-parameter gradient; then once
+// per pixel the adjoint to the corners and the per-(triangle, tile) sums.
+// Nothing is kept per light, so the registers do not depend on how many there
+// are (arrays over 4 or 16 lights spilled, and 16 scattered with global
+// atomics), and a camera's renders share the point, the normal and their
+// adjoint.  Vector issue bounds it, then the latency of key -> record -> taps.
+// 64 renders with a light each 494 -> 399 us (5 waves per SIMD; 418 at 4), 16
+// cameras with 8 renders each 716 -> 483, a 1080p RGB render with 3 lights
+// 205 -> 117 (4 waves; 120 at 5).
+template <int T, int C>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 32 ? 2 : C == 1 ? 5 : 4))) void lookup_backward_kernel(
     const ViewConst *__restrict__ views, int L, const RenderConst *__restrict__ renders,
     const int *__restrict__ cam_renders_off, const int *__restrict__ cam_renders,
-    const int *__restrict__ render_lights, const int *__restrict__ faces, const float *__restrict__ verts,
-    const float *__restrict__ albedo, const TriVerts *__restrict__ tv, const unsigned long long *__restrict__ keys,
+    const int *__restrict__ render_lights, const TriVerts *__restrict__ tv, const unsigned long long *__restrict__ keys,
     const float *__restrict__ maps, const float *__restrict__ gimg0, float *__restrict__ gmaps,
     const TriSetup *__restrict__ setup, const unsigned *__restrict__ tile_start, const unsigned *__restrict__ bins,
     const unsigned *__restrict__ bin_pair, unsigned char *__restrict__ pair_flag, float *__restrict__ pair_sums,
-    float *__restrict__ gtri, float *__restrict__ part_render, int C, const float *__restrict__ jac,
+    float *__restrict__ gtri, float *__restrict__ part_render, const float *__restrict__ jac,
     const unsigned *__restrict__ pair_off, unsigned capacity) {
     using TS = TileShape<T>;
     // one wave per 8x8 tile: pair rows found from the setup records (wave_pair_sums)
@@ -923,65 +925,82 @@ __device__ __forceinline__ void lookup_backward_body(
     if (!kWavePairs) head = bin_head(gt, (int)threadIdx.x, tile_start, bins, bin_pair);
     const int tx = lt % cv.tiles_x, ty = lt / cv.tiles_x;
     const int tid = threadIdx.x;
-    int key[TS::PPT], pi[TS::PPT], pj[TS::PPT];
+    const int rr0 = cam_renders_off[cam], rr1 = cam_renders_off[cam + 1];
+    int key[TS::PPT], pp[TS::PPT];
     bool act[TS::PPT], matched[TS::PPT];
-    float val[TS::PPT][kNV];
+    PixelGeom geo[TS::PPT];
+    float galb[TS::PPT][3];
+    const float *gfirst = gimg0 + (rr0 < rr1 ? renders[cam_renders[rr0]].img_off : 0);
+    float g0[TS::PPT][C];        // upstream gradient in the first render, requested with the keys
 #pragma unroll
     for (int k = 0; k < TS::PPT; ++k) {
         const int l = tid + k * TS::NT;
-        pi[k] = tx * T + (l % T);
-        pj[k] = ty * T + (l / T);
-        const bool in = pi[k] < cv.W && pj[k] < cv.H;
-        const unsigned long long kk = in ? keys[cv.pix_off + (long long)pj[k] * cv.W + pi[k]] : kBgKey;
+        const int i = tx * T + (l % T), j = ty * T + (l / T);
+        const bool in = i < cv.W && j < cv.H;
+        pp[k] = in ? j * cv.W + i : 0;
+        const unsigned long long kk = in ? keys[cv.pix_off + pp[k]] : kBgKey;
         key[k] = kk == kBgKey ? -1 : (int)(unsigned)kk;
+#pragma unroll
+        for (int c = 0; c < C; ++c) g0[k][c] = rr0 < rr1 ? gfirst[(long long)pp[k] * C + c] : 0.f;
+    }
+#pragma unroll
+    for (int k = 0; k < TS::PPT; ++k) {
         act[k] = false;
         matched[k] = false;
-#pragma unroll
-        for (int i = 0; i < kNV; ++i) val[k][i] = 0.f;
+        galb[k][0] = galb[k][1] = galb[k][2] = 0.f;
+        if (key[k] >= 0) {
+            const int l = tid + k * TS::NT;
+            pixel_geom(geo[k], cv, tv[cv.face_off + key[k]], tx * T + (l % T), ty * T + (l / T));
+        }
     }
-    for (int rr = cam_renders_off[cam]; rr < cam_renders_off[cam + 1]; ++rr) {
-        const int r = cam_renders[rr];
-        const RenderConst &R = renders[r];
-        float accl[MAXL][3];
-#pragma unroll
-        for (int q = 0; q < MAXL; ++q)
-#pragma unroll
-            for (int i = 0; i < 3; ++i) accl[q][i] = 0.f;
-        constexpr bool kDirect = TS::PPT * MAXL > 4;     // register budget for deferred map taps
-        MapHit hits[TS::PPT][MAXL];
+    for (int rr = rr0; rr < rr1; ++rr) {
+        const RenderConst &R = renders[cam_renders[rr]];
+        float g[TS::PPT][C], srho[TS::PPT], shade[TS::PPT];
+        bool on[TS::PPT];
 #pragma unroll
         for (int k = 0; k < TS::PPT; ++k) {
+            on[k] = false;
+            srho[k] = shade[k] = 0.f;
 #pragma unroll
-            for (int q = 0; q < MAXL; ++q) hits[k][q] = MapHit{0, 0, 0.f, 0.f, 0.f, 0.f};
-            if (key[k] < 0) continue;
-            const long long p = (long long)pj[k] * cv.W + pi[k];
-            float g[3] = {0.f, 0.f, 0.f};
-            for (int c = 0; c < C; ++c) g[c] = gimg0[R.img_off + p * C + c];
-            if (g[0] == 0.f && g[1] == 0.f && g[2] == 0.f) continue;
-            float tmp[kNV];
-            lookup_pixel_grad<MAXL, kDirect>(cv, R, views, render_lights, tv, albedo, maps, gmaps,
-                                             pi[k], pj[k], key[k], g, C, tmp, accl, hits[k], jac);
-            act[k] = true;
-#pragma unroll
-            for (int i = 0; i < kNV; ++i) val[k][i] += tmp[i];
-        }
-        if (!kDirect) {
-#pragma unroll
-            for (int q = 0; q < MAXL; ++q) {
-                if (q >= R.light_count) break;
-                const ViewConst &l = views[render_lights[R.light_begin + q]];
-                MapHit hq[TS::PPT];
-#pragma unroll
-                for (int k = 0; k < TS::PPT; ++k) hq[k] = hits[k][q];
-                map_window_scatter<TS::NW, TS::PPT, (T == 32 ? 32 : 16)>(hq, l.W + 2 * l.fpad, gmaps + l.fmap_off);
+            for (int c = 0; c < C; ++c) {
+                g[k][c] = rr == rr0 ? g0[k][c] : gimg0[R.img_off + (long long)pp[k] * C + c];
+                on[k] = on[k] || g[k][c] != 0.f;
             }
+            on[k] = on[k] && key[k] >= 0;
+            act[k] = act[k] || on[k];
+            if (on[k])
+#pragma unroll
+                for (int c = 0; c < C; ++c) srho[k] += g[k][c] * geo[k].rho[c];
         }
         const int ntiles = cv.tiles_x * cv.tiles_y;
+        for (int q = 0; q < R.light_count; ++q) {
+            const int li = render_lights[R.light_begin + q];
+            const ViewConst &l = views[li];
+            float al[3] = {0.f, 0.f, 0.f};
+            MapHit hits[TS::PPT];
 #pragma unroll
-        for (int q = 0; q < MAXL; ++q) {
-            if (q >= R.light_count) break;
-            block_sum_store<TS::NW>(accl[q], part_render + R.part_off + ((long long)q * ntiles + lt) * 3);
+            for (int k = 0; k < TS::PPT; ++k) {
+                hits[k] = MapHit{0, 0, 0.f, 0.f, 0.f, 0.f};
+                if (on[k]) light_terms(geo[k], l, jac + (size_t)kJac * li, maps, srho[k], shade[k], al, hits[k]);
+            }
+            map_window_scatter<TS::NW, TS::PPT, (T == 32 ? 32 : 16)>(hits, l.W + 2 * l.fpad, gmaps + l.fmap_off);
+            block_sum_store<TS::NW>(al, part_render + R.part_off + ((long long)q * ntiles + lt) * 3);
         }
+#pragma unroll
+        for (int k = 0; k < TS::PPT; ++k)
+            if (on[k])
+#pragma unroll
+                for (int c = 0; c < C; ++c) galb[k][c] += g[k][c] * shade[k];
+    }
+    float val[TS::PPT][kNV];
+#pragma unroll
+    for (int k = 0; k < TS::PPT; ++k) {
+#pragma unroll
+        for (int i = 0; i < kNV; ++i) val[k][i] = 0.f;
+        if (!act[k]) continue;
+        pixel_adjoint(geo[k], val[k]);
+#pragma unroll
+        for (int c = 0; c < C; ++c) val[k][18 + c] = galb[k][c];
     }
     if constexpr (kWavePairs)
         wave_pair_sums<T, kNV>(cv, tx, ty, key[0], val[0], act[0], matched[0], setup, pair_off, capacity, pair_flag,
@@ -989,36 +1008,6 @@ __device__ __forceinline__ void lookup_backward_body(
     else
         tile_pair_sums<T, kNV>(cv, head, bins, bin_pair, key, val, act, matched, pair_flag, pair_sums);
     overflow_rows(cv, key, val, act, matched, gtri);
-}
-
-template <int T, int MAXL>
-__global__ __launch_bounds__(256) void lookup_backward_kernel(
-    const ViewConst *__restrict__ views, int L, const RenderConst *__restrict__ renders,
-    const int *__restrict__ cam_renders_off, const int *__restrict__ cam_renders,
-    const int *__restrict__ render_lights, const int *__restrict__ faces, const float *__restrict__ verts,
-    const float *__restrict__ albedo, const TriVerts *__restrict__ tv, const unsigned long long *__restrict__ keys,
-    const float *__restrict__ maps, const float *__restrict__ gimg0, float *__restrict__ gmaps,
-    const TriSetup *__restrict__ setup, const unsigned *__restrict__ tile_start, const unsigned *__restrict__ bins,
-    const unsigned *__restrict__ bin_pair, unsigned char *__restrict__ pair_flag, float *__restrict__ pair_sums,
-    float *__restrict__ gtri, float *__restrict__ part_render, int C, const float *__restrict__ jac,
-    const unsigned *__restrict__ pair_off, unsigned capacity) {
-    lookup_backward_body<T, MAXL>(views, L, renders, cam_renders_off, cam_renders, render_lights, faces, verts, albedo, tv, keys, maps, gimg0, gmaps, setup, tile_start, bins, bin_pair, pair_flag, pair_sums, gtri, part_render, C, jac, pair_off, capacity);
-}
-
-// One light per render at 8x8 or 16x16 tiles: capped at 128 VGPRs (4 waves
-// per SIMD instead of 3) at the cost of a few spilled dwords.
-template <int T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void lookup_backward_kernel_1l(
-    const ViewConst *__restrict__ views, int L, const RenderConst *__restrict__ renders,
-    const int *__restrict__ cam_renders_off, const int *__restrict__ cam_renders,
-    const int *__restrict__ render_lights, const int *__restrict__ faces, const float *__restrict__ verts,
-    const float *__restrict__ albedo, const TriVerts *__restrict__ tv, const unsigned long long *__restrict__ keys,
-    const float *__restrict__ maps, const float *__restrict__ gimg0, float *__restrict__ gmaps,
-    const TriSetup *__restrict__ setup, const unsigned *__restrict__ tile_start, const unsigned *__restrict__ bins,
-    const unsigned *__restrict__ bin_pair, unsigned char *__restrict__ pair_flag, float *__restrict__ pair_sums,
-    float *__restrict__ gtri, float *__restrict__ part_render, int C, const float *__restrict__ jac,
-    const unsigned *__restrict__ pair_off, unsigned capacity) {
-    lookup_backward_body<T, 1>(views, L, renders, cam_renders_off, cam_renders, render_lights, faces, verts, albedo, tv, keys, maps, gimg0, gmaps, setup, tile_start, bins, bin_pair, pair_flag, pair_sums, gtri, part_render, C, jac, pair_off, capacity);
 }
 
 // ----------------------------------------------------------------------------- light smoothing^T + resolve^T
@@ -1441,10 +1430,10 @@ __global__ __launch_bounds__(256) void vertex_gather_kernel(
                 const int e[2] = {q + lane < q1 ? vc_list[q + lane] : -1, q + 64 + lane < q1 ? vc_list[q + 64 + lane] : -1};
                 gather_corners(e, soff, capacity, pair_off, pair_flag, pair_sums, gtri, zero_rec, h);
             }
-            const float t = wave_sum_multi(h);           // lane 2k: total of term k
+            const float t = wave_sum_multi(h);           // lane 8k: total of term k
 #pragma unroll
             for (int k = 0; k < 6; ++k) {
-                const float tk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), 2 * k));
+                const float tk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), k << kSumShift<6>));
                 if (lane == l) g[k] += tk;
             }
         }
@@ -1469,7 +1458,7 @@ __global__ __launch_bounds__(256) void vertex_gather_kernel(
                 gp[j] = a;
             }
             const float t = wave_sum_multi(gp);
-            if ((lane & 1) == 0 && lane < 6) part_gm[((long long)v.part_gm_off + blockIdx.x) * 3 + (lane >> 1)] = t;
+            if ((lane & 15) == 0 && lane < 48) part_gm[((long long)v.part_gm_off + blockIdx.x) * 3 + (lane >> 4)] = t;
         }
     }
     if (nwaves > 1) {
@@ -1660,7 +1649,7 @@ hipError_t launch_aa_camera_backward(const ViewConst *views, int L, int Cm, int 
                                      const unsigned long long *keys, const unsigned char *aa_flag, const float *img0,
                                      const float *gimg, float *gimg0, float4 *gclip, int C, hipStream_t s) {
     if (Cm == 0 || max_renders == 0) return hipSuccess;
-    const int chunk = aa_render_chunk(max_renders, (long long)max_regions * Cm);
+    const int chunk = render_chunk(max_renders, (long long)max_regions * Cm);
     const dim3 grid(max_regions, Cm, (max_renders + chunk - 1) / chunk);
 #define DSM_AACB(CC)                                                                                                 \
     hipLaunchKernelGGL(aa_camera_backward_kernel<CC>, grid, dim3(64), 0, s, views, L, renders, cam_renders_off,     \
@@ -1671,37 +1660,27 @@ hipError_t launch_aa_camera_backward(const ViewConst *views, int L, int Cm, int 
     return hipGetLastError();
 }
 
-hipError_t launch_lookup_backward(int tile, const ViewConst *views, int L, int Cm, int max_tiles, int max_lights,
+hipError_t launch_lookup_backward(int tile, const ViewConst *views, int L, int Cm, int max_tiles,
                                   const RenderConst *renders, const int *cam_renders_off, const int *cam_renders,
-                                  const int *render_lights, const int *faces, const float *verts, const float *albedo,
-                                  const TriVerts *tv, const unsigned long long *keys, const float *maps,
-                                  const float *gimg0, float *gmaps, const TriSetup *setup, const unsigned *tile_start,
-                                  const unsigned *bins, const unsigned *bin_pair, unsigned char *pair_flag,
-                                  float *pair_sums, float *gtri, float *part_render, int C, const float *jac,
-                                  const unsigned *pair_off, unsigned capacity, hipStream_t s) {
+                                  const int *render_lights, const TriVerts *tv, const unsigned long long *keys,
+                                  const float *maps, const float *gimg0, float *gmaps, const TriSetup *setup,
+                                  const unsigned *tile_start, const unsigned *bins, const unsigned *bin_pair,
+                                  unsigned char *pair_flag, float *pair_sums, float *gtri, float *part_render, int C,
+                                  const float *jac, const unsigned *pair_off, unsigned capacity, hipStream_t s) {
     if (Cm == 0 || max_tiles == 0) return hipSuccess;
     const dim3 grid(max_tiles, Cm);
-#define DSM_LB1(TT)                                                                                                 \
-    hipLaunchKernelGGL((lookup_backward_kernel_1l<TT>), grid, dim3(TileShape<TT>::NT), 0, s, views, L, renders,     \
-                       cam_renders_off, cam_renders, render_lights, faces, verts, albedo, tv, keys, maps, gimg0,     \
-                       gmaps, setup, tile_start, bins, bin_pair, pair_flag, pair_sums, gtri, part_render, C, jac, \
-                       pair_off, capacity)
-#define DSM_LB(TT, ML)                                                                                              \
-    hipLaunchKernelGGL((lookup_backward_kernel<TT, ML>), grid, dim3(TileShape<TT>::NT), 0, s, views, L, renders,   \
-                       cam_renders_off, cam_renders, render_lights, faces, verts, albedo, tv, keys, maps, gimg0,     \
-                       gmaps, setup, tile_start, bins, bin_pair, pair_flag, pair_sums, gtri, part_render, C, jac, \
-                       pair_off, capacity)
-#define DSM_LB_T(TT)                                                  \
-    if (max_lights <= 1 && TT <= 16) DSM_LB1(TT);                     \
-    else if (max_lights <= 1) DSM_LB(TT, 1);                          \
-    else if (max_lights <= 4) DSM_LB(TT, 4);                          \
-    else DSM_LB(TT, DSM_MAX_LIGHTS_PER_RENDER)
-    if (tile == 8) { DSM_LB_T(8); }
-    else if (tile == 16) { DSM_LB_T(16); }
-    else { DSM_LB_T(32); }
-#undef DSM_LB_T
+#define DSM_LB(TT, CC)                                                                                             \
+    hipLaunchKernelGGL((lookup_backward_kernel<TT, CC>), grid, dim3(TileShape<TT>::NT), 0, s, views, L, renders,  \
+                       cam_renders_off, cam_renders, render_lights, tv, keys, maps, gimg0, gmaps, setup,          \
+                       tile_start, bins, bin_pair, pair_flag, pair_sums, gtri, part_render, jac, pair_off, capacity)
+#define DSM_LB_C(TT)          \
+    if (C == 1) DSM_LB(TT, 1); \
+    else DSM_LB(TT, 3)
+    if (tile == 8) { DSM_LB_C(8); }
+    else if (tile == 16) { DSM_LB_C(16); }
+    else { DSM_LB_C(32); }
+#undef DSM_LB_C
 #undef DSM_LB
-#undef DSM_LB1
     return hipGetLastError();
 }
 

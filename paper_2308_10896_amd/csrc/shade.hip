@@ -268,16 +268,22 @@ __global__ __launch_bounds__(64) void aa_camera_forward_kernel(
 // three dependent gathers of a pixel (its depth|id key, its triangle's
 // record, its map taps) are issued for all PPT pixels before any of them is
 // used, so a thread waits for three round trips per PPT pixels instead of
-// three per pixel.  Each pixel's arithmetic is the one-pixel form, unchanged.
+// three per pixel.  The pixels' points and normals are formed once for a chunk
+// of the camera's renders.  Each pixel's arithmetic is the one-pixel form,
+// unchanged.
 template <int PPT>
-__global__ __launch_bounds__(256) void lookup_kernel(const ViewConst *__restrict__ views,
+__global__ __launch_bounds__(256) void lookup_kernel(const ViewConst *__restrict__ views, int L,
                                                      const RenderConst *__restrict__ renders,
+                                                     const int *__restrict__ cam_renders_off,
+                                                     const int *__restrict__ cam_renders, int chunk,
                                                      const int *__restrict__ render_lights,
-                                                     const TriVerts *__restrict__ tv, const float *__restrict__ albedo,
+                                                     const TriVerts *__restrict__ tv,
                                                      const unsigned long long *__restrict__ keys,
                                                      const float *__restrict__ maps, float *__restrict__ img0, int C) {
-    const RenderConst &R = renders[blockIdx.y];
-    const ViewConst &cv = views[R.camera_view];
+    const int r0 = cam_renders_off[blockIdx.y] + (int)blockIdx.z * chunk,
+              r1 = min(r0 + chunk, cam_renders_off[blockIdx.y + 1]);
+    if (r0 >= r1) return;
+    const ViewConst &cv = views[L + blockIdx.y];
     const int W = cv.W, H = cv.H, P = W * H;
     const int p0 = blockIdx.x * (256 * PPT) + (int)threadIdx.x;
     if (p0 >= P) return;
@@ -291,10 +297,9 @@ __global__ __launch_bounds__(256) void lookup_kernel(const ViewConst *__restrict
 #pragma unroll
     for (int k = 0; k < PPT; ++k)
         if (key[k] != kBgKey) r[k] = tv[cv.face_off + (int)(unsigned)key[k]];
-    float x[PPT], y[PPT], z[PPT], nx[PPT], ny[PPT], nz[PPT], shade[PPT];
+    float x[PPT], y[PPT], z[PPT], nx[PPT], ny[PPT], nz[PPT];
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
-        shade[k] = 0.f;
         x[k] = y[k] = z[k] = nx[k] = ny[k] = nz[k] = 0.f;
         if (key[k] == kBgKey) continue;
         const float v0[3] = {r[k].a.x, r[k].a.y, r[k].a.z}, v1[3] = {r[k].a.w, r[k].b.x, r[k].b.y},
@@ -316,98 +321,103 @@ __global__ __launch_bounds__(256) void lookup_kernel(const ViewConst *__restrict
         ny[k] = cy * rn;
         nz[k] = cz * rn;
     }
-    for (int q = 0; q < R.light_count; ++q) {
-        const ViewConst &l = views[render_lights[R.light_begin + q]];
-        const int S = l.W, Sp = S + 2 * l.fpad;
-        const float2 *mm = (const float2 *)(maps + l.fmap_off);     // (m1, m2) interleaved per texel
-        bool inside[PPT];
-        float fx[PPT], fy[PPT];
-        int o00[PPT], o01[PPT], o10[PPT], o11[PPT];
+    for (int rr = r0; rr < r1; ++rr) {
+        const RenderConst &R = renders[cam_renders[rr]];
+        float shade[PPT];
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) shade[k] = 0.f;
+        for (int q = 0; q < R.light_count; ++q) {
+            const ViewConst &l = views[render_lights[R.light_begin + q]];
+            const int S = l.W, Sp = S + 2 * l.fpad;
+            const float2 *mm = (const float2 *)(maps + l.fmap_off);     // (m1, m2) interleaved per texel
+            bool inside[PPT];
+            float fx[PPT], fy[PPT];
+            int o00[PPT], o01[PPT], o10[PPT], o11[PPT];
+#pragma unroll
+            for (int k = 0; k < PPT; ++k) {
+                inside[k] = false;
+                fx[k] = fy[k] = 0.f;
+                o00[k] = o01[k] = o10[k] = o11[k] = 0;
+                if (key[k] == kBgKey) continue;
+                // a cube face lights only the directions it owns: no fetch elsewhere
+                if (l.kind == kCubeFace &&
+                    cube_face_of(x[k] - l.pos[0], y[k] - l.pos[1], z[k] - l.pos[2]) != l.cube_face)
+                    continue;
+                const float *M = l.M;
+                const float cx = ((M[0] * x[k] + M[1] * y[k]) + M[2] * z[k]) + M[3];
+                const float cy = ((M[4] * x[k] + M[5] * y[k]) + M[6] * z[k]) + M[7];
+                const float cw = ((M[12] * x[k] + M[13] * y[k]) + M[14] * z[k]) + M[15];
+                const float rcw = __builtin_amdgcn_rcpf(cw);
+                const float ux = cx * rcw, uy = cy * rcw;
+                inside[k] = cw > 0.f && fabsf(ux) <= 1.f && fabsf(uy) <= 1.f;
+                if (!inside[k]) continue;
+                const float sx = (ux + 1.f) * (0.5f * S) - 0.5f;
+                const float sy = (1.f - uy) * (0.5f * S) - 0.5f;
+                const float fx0 = floorf(sx), fy0 = floorf(sy);
+                fx[k] = sx - fx0;
+                fy[k] = sy - fy0;
+                const int ix = (int)fx0 + l.fpad, iy = (int)fy0 + l.fpad;
+                const int x0 = min(max(ix, 0), Sp - 1), x1 = min(max(ix + 1, 0), Sp - 1);
+                const int y0 = min(max(iy, 0), Sp - 1), y1 = min(max(iy + 1, 0), Sp - 1);
+                o00[k] = y0 * Sp + x0; o01[k] = y0 * Sp + x1;
+                o10[k] = y1 * Sp + x0; o11[k] = y1 * Sp + x1;
+            }
+            float2 t00[PPT], t01[PPT], t10[PPT], t11[PPT];
+#pragma unroll
+            for (int k = 0; k < PPT; ++k) {
+                // offsets of pixels without a fetch are 0, a texel of this map
+                t00[k] = mm[o00[k]]; t01[k] = mm[o01[k]]; t10[k] = mm[o10[k]]; t11[k] = mm[o11[k]];
+            }
+#pragma unroll
+            for (int k = 0; k < PPT; ++k) {
+                if (key[k] == kBgKey) continue;
+                if (l.kind == kCubeFace &&
+                    cube_face_of(x[k] - l.pos[0], y[k] - l.pos[1], z[k] - l.pos[2]) != l.cube_face)
+                    continue;
+                float vis = 1.f;
+                if (inside[k]) {
+                    const float w00 = (1.f - fx[k]) * (1.f - fy[k]), w01 = fx[k] * (1.f - fy[k]);
+                    const float w10 = (1.f - fx[k]) * fy[k], w11 = fx[k] * fy[k];
+                    const float m1 = ((w00 * t00[k].x + w01 * t01[k].x) + w10 * t10[k].x) + w11 * t11[k].x;
+                    const float m2 = ((w00 * t00[k].y + w01 * t01[k].y) + w10 * t10[k].y) + w11 * t11[k].y;
+                    float zw, floor_v;
+                    warp_receiver(l, light_depth(l, x[k], y[k], z[k]), zw, floor_v);
+                    const float var = fmaxf(m2 - m1 * m1, floor_v);
+                    const float dd = zw - m1;
+                    vis = bleed_reduce(l, (zw <= m1) ? 1.f : var * __builtin_amdgcn_rcpf(var + dd * dd));
+                }
+                float ox, oy, oz;
+                if (l.kind == kDirectional) {
+                    ox = -l.dir[0];
+                    oy = -l.dir[1];
+                    oz = -l.dir[2];
+                } else {
+                    ox = l.pos[0] - x[k];
+                    oy = l.pos[1] - y[k];
+                    oz = l.pos[2] - z[k];
+                    const float ron = __builtin_amdgcn_rsqf((ox * ox + oy * oy) + oz * oz);
+                    ox *= ron;
+                    oy *= ron;
+                    oz *= ron;
+                }
+                const float lam = fmaxf((nx[k] * ox + ny[k] * oy) + nz[k] * oz, 0.f);
+                float cone = 1.f;
+                if (l.kind == kSpot) {
+                    // cos of the angle between x - p and the axis: (-omega) . axis
+                    const float ca = -((ox * l.dir[0] + oy * l.dir[1]) + oz * l.dir[2]);
+                    cone = ca >= l.cos_half ? 1.f : 0.f;
+                }
+                shade[k] += lam * vis * l.intensity * cone;
+            }
+        }
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
-            inside[k] = false;
-            fx[k] = fy[k] = 0.f;
-            o00[k] = o01[k] = o10[k] = o11[k] = 0;
-            if (key[k] == kBgKey) continue;
-            // a cube face lights only the directions it owns: no fetch elsewhere
-            if (l.kind == kCubeFace &&
-                cube_face_of(x[k] - l.pos[0], y[k] - l.pos[1], z[k] - l.pos[2]) != l.cube_face)
-                continue;
-            const float *M = l.M;
-            const float cx = ((M[0] * x[k] + M[1] * y[k]) + M[2] * z[k]) + M[3];
-            const float cy = ((M[4] * x[k] + M[5] * y[k]) + M[6] * z[k]) + M[7];
-            const float cw = ((M[12] * x[k] + M[13] * y[k]) + M[14] * z[k]) + M[15];
-            const float rcw = __builtin_amdgcn_rcpf(cw);
-            const float ux = cx * rcw, uy = cy * rcw;
-            inside[k] = cw > 0.f && fabsf(ux) <= 1.f && fabsf(uy) <= 1.f;
-            if (!inside[k]) continue;
-            const float sx = (ux + 1.f) * (0.5f * S) - 0.5f;
-            const float sy = (1.f - uy) * (0.5f * S) - 0.5f;
-            const float fx0 = floorf(sx), fy0 = floorf(sy);
-            fx[k] = sx - fx0;
-            fy[k] = sy - fy0;
-            const int ix = (int)fx0 + l.fpad, iy = (int)fy0 + l.fpad;
-            const int x0 = min(max(ix, 0), Sp - 1), x1 = min(max(ix + 1, 0), Sp - 1);
-            const int y0 = min(max(iy, 0), Sp - 1), y1 = min(max(iy + 1, 0), Sp - 1);
-            o00[k] = y0 * Sp + x0; o01[k] = y0 * Sp + x1;
-            o10[k] = y1 * Sp + x0; o11[k] = y1 * Sp + x1;
-        }
-        float2 t00[PPT], t01[PPT], t10[PPT], t11[PPT];
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            // offsets of pixels without a fetch are 0, a texel of this map
-            t00[k] = mm[o00[k]]; t01[k] = mm[o01[k]]; t10[k] = mm[o10[k]]; t11[k] = mm[o11[k]];
-        }
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            if (key[k] == kBgKey) continue;
-            if (l.kind == kCubeFace &&
-                cube_face_of(x[k] - l.pos[0], y[k] - l.pos[1], z[k] - l.pos[2]) != l.cube_face)
-                continue;
-            float vis = 1.f;
-            if (inside[k]) {
-                const float w00 = (1.f - fx[k]) * (1.f - fy[k]), w01 = fx[k] * (1.f - fy[k]);
-                const float w10 = (1.f - fx[k]) * fy[k], w11 = fx[k] * fy[k];
-                const float m1 = ((w00 * t00[k].x + w01 * t01[k].x) + w10 * t10[k].x) + w11 * t11[k].x;
-                const float m2 = ((w00 * t00[k].y + w01 * t01[k].y) + w10 * t10[k].y) + w11 * t11[k].y;
-                float zw, floor_v;
-                warp_receiver(l, light_depth(l, x[k], y[k], z[k]), zw, floor_v);
-                const float var = fmaxf(m2 - m1 * m1, floor_v);
-                const float dd = zw - m1;
-                vis = bleed_reduce(l, (zw <= m1) ? 1.f : var * __builtin_amdgcn_rcpf(var + dd * dd));
-            }
-            float ox, oy, oz;
-            if (l.kind == kDirectional) {
-                ox = -l.dir[0];
-                oy = -l.dir[1];
-                oz = -l.dir[2];
-            } else {
-                ox = l.pos[0] - x[k];
-                oy = l.pos[1] - y[k];
-                oz = l.pos[2] - z[k];
-                const float ron = __builtin_amdgcn_rsqf((ox * ox + oy * oy) + oz * oz);
-                ox *= ron;
-                oy *= ron;
-                oz *= ron;
-            }
-            const float lam = fmaxf((nx[k] * ox + ny[k] * oy) + nz[k] * oz, 0.f);
-            float cone = 1.f;
-            if (l.kind == kSpot) {
-                // cos of the angle between x - p and the axis: (-omega) . axis
-                const float ca = -((ox * l.dir[0] + oy * l.dir[1]) + oz * l.dir[2]);
-                cone = ca >= l.cos_half ? 1.f : 0.f;
-            }
-            shade[k] += lam * vis * l.intensity * cone;
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        const int p = p0 + 256 * k;
-        if (p >= P) continue;
-        float *out = img0 + R.img_off + (long long)p * C;
-        const float rho[3] = {r[k].c.y, r[k].c.z, r[k].c.w};    // albedo, carried in the face record
-        for (int c = 0; c < C; ++c) out[c] = key[k] == kBgKey ? 0.f : rho[c] * shade[k];
-    }
+            const int p = p0 + 256 * k;
+            if (p >= P) continue;
+            float *out = img0 + R.img_off + (long long)p * C;
+            const float rho[3] = {r[k].c.y, r[k].c.z, r[k].c.w};    // albedo, carried in the face record
+            for (int c = 0; c < C; ++c) out[c] = key[k] == kBgKey ? 0.f : rho[c] * shade[k];
+        }    }
 }
 
 // ----------------------------------------------------------------------------- launchers
@@ -428,7 +438,7 @@ hipError_t launch_aa_camera(const ViewConst *views, int L, int Cm, int max_regio
                             const unsigned long long *keys, const float *src, float *dst, int C,
                             unsigned char *aa_flag, hipStream_t s) {
     if (Cm == 0 || max_renders == 0) return hipSuccess;
-    const int chunk = aa_render_chunk(max_renders, (long long)max_regions * Cm);
+    const int chunk = render_chunk(max_renders, (long long)max_regions * Cm);
     const dim3 grid(max_regions, Cm, (max_renders + chunk - 1) / chunk);
 #define DSM_AAC(CC)                                                                                                 \
     hipLaunchKernelGGL(aa_camera_forward_kernel<CC>, grid, dim3(64), 0, s, views, L, renders, cam_renders_off,     \
@@ -439,13 +449,16 @@ hipError_t launch_aa_camera(const ViewConst *views, int L, int Cm, int max_regio
     return hipGetLastError();
 }
 
-hipError_t launch_lookup(const ViewConst *views, const RenderConst *renders, int R, int max_pix,
-                         const int *render_lights, const TriVerts *tv, const float *albedo,
-                         const unsigned long long *keys, const float *maps, float *img0, int C, hipStream_t s) {
-    if (R == 0) return hipSuccess;
+hipError_t launch_lookup(const ViewConst *views, int L, int Cm, int max_pix, int max_renders,
+                         const RenderConst *renders, const int *cam_renders_off, const int *cam_renders,
+                         const int *render_lights, const TriVerts *tv, const unsigned long long *keys,
+                         const float *maps, float *img0, int C, hipStream_t s) {
+    if (Cm == 0 || max_renders == 0) return hipSuccess;
     constexpr int PPT = kLookupPixelsPerThread;
-    hipLaunchKernelGGL(lookup_kernel<PPT>, dim3((max_pix + 256 * PPT - 1) / (256 * PPT), R), dim3(256), 0, s, views,
-                       renders, render_lights, tv, albedo, keys, maps, img0, C);
+    const int bx = (max_pix + 256 * PPT - 1) / (256 * PPT);
+    const int chunk = render_chunk(max_renders, (long long)bx * Cm);
+    hipLaunchKernelGGL(lookup_kernel<PPT>, dim3(bx, Cm, (max_renders + chunk - 1) / chunk), dim3(256), 0, s, views, L,
+                       renders, cam_renders_off, cam_renders, chunk, render_lights, tv, keys, maps, img0, C);
     return hipGetLastError();
 }
 
