@@ -460,8 +460,12 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
             const int l = order[q];
             const dsm_light_desc &x = d->lights[l];
             const int R = (x.k - 1) / 2;
-            if (p->blur_groups.empty() || p->blur_groups.back().R != R)
-                p->blur_groups.push_back(dsm_plan::BlurGroup{R, q, 0, 0});
+            if (p->blur_groups.empty() || p->blur_groups.back().R != R) {
+                long long tall = 0;
+                for (int u = q; u < L && (d->lights[order[u]].k - 1) / 2 == R; ++u)
+                    tall += blur_tall_tiles(p->views_h[order[u]].W + 2 * p->views_h[order[u]].fpad, R);
+                p->blur_groups.push_back(dsm_plan::BlurGroup{R, q, 0, 0, blur_tile_height(R, tall)});
+            }
             dsm_plan::BlurGroup &g = p->blur_groups.back();
             // forward: smoothed maps (cube faces: their padded copies) -> filtered maps
             const ViewConst &v = p->views_h[l];
@@ -475,7 +479,7 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
             j.tile_off = g.tiles;
             j.tiles_x = blur_tiles_x(sp);
             filter_taps_host(x.filter, x.k, x.sigma, j.w);
-            g.tiles += blur_tiles(sp, R);
+            g.tiles += blur_tiles(sp, g.ty);
             g.n += 1;
             p->blur_jobs_h.push_back(j);
         }
@@ -736,7 +740,7 @@ dsm_status enqueue_forward(dsm_plan *p, const float *verts, const float *lparams
     DSM_MARK(DSM_STAGE_FILTER);
     if (p->has_cube) DSM_TRY(launch_cube_pad(p->views_d, p->L, p->max_cube_padded, p->cube_taps_d, F1, s));
     for (const auto &g : p->blur_groups)
-        DSM_TRY(launch_blur(p->blur_jobs_d + g.first, g.n, g.tiles, F1, Mm, false, g.R, s));
+        DSM_TRY(launch_blur(p->blur_jobs_d + g.first, g.n, g.tiles, F1, Mm, false, g.R, g.ty, s));
     DSM_MARK(DSM_STAGE_LOOKUP);
     DSM_TRY(launch_lookup(p->views_d, p->L, p->Cm, p->max_cam_pix, p->max_cam_renders, p->renders_d,
                           p->cam_renders_off_d, p->cam_renders_d, p->render_lights_d, tv, keys, Mm, img0, p->C, s));
@@ -798,7 +802,7 @@ dsm_status enqueue_backward(dsm_plan *p, const float *verts, const float *lparam
                                    jac, pair_off, p->capacity, s));
     DSM_MARK(DSM_STAGE_FILTER_ADJ);
     for (const auto &g : p->blur_groups)
-        DSM_TRY(launch_blur(p->blur_jobs_d + p->L + g.first, g.n, g.tiles, gM, gF1, true, g.R, s));
+        DSM_TRY(launch_blur(p->blur_jobs_d + p->L + g.first, g.n, g.tiles, gM, gF1, true, g.R, g.ty, s));
     if (p->has_cube)
         DSM_TRY(launch_cube_pad_transpose(p->views_d, p->L, p->max_cube_texels, p->max_cube_ring, p->cube_taps_d,
                                           gF1, s));

@@ -8,7 +8,12 @@
 // rows: it forms the horizontal filter of that column for every staged row
 // (the k taps are neighbouring LDS words) and pushes the results through a
 // register ring of the last k rows, from which each output row is one
-// k-tap dot product.  Each input texel is read from HBM once (halo re-reads
+// k-tap dot product.  The taps are fused multiply-adds (from k = 9 on the
+// filter is bound by them, below by HBM): three 1000^2 maps at k = 11, transpose
+// 25.6 -> 21.8 us.  The pipeline's forward filter alone keeps the rounded
+// product: its maps are what the lookup takes every decision from, and at the
+// variance floor the Chebyshev quotient shows their last bits in the image.
+// Each input texel is read from HBM once (halo re-reads
 // of neighbouring tiles are served by L2) and each output texel written
 // once: 16 bytes of algorithmic traffic per texel.
 //
@@ -26,13 +31,20 @@ namespace dsm {
 constexpr int kBlurTX = 64;                          // tile width: one column per lane
 constexpr int kBlurThreads = 256;
 
-// Tile height for radius R.  The staged tile carries 2R halo rows, so short
+// Tile heights for radius R.  The staged tile carries 2R halo rows, so short
 // tiles pay relatively more for wide filters, and tall tiles keep fewer
-// workgroups resident.  Measured on this GPU (stand-alone filter and
-// transpose, 64 x 512^2, 8 x 1024^2 and 3 x 2048^2 maps): 32 rows is
+// workgroups resident.  Measured on this GPU with the chip full (stand-alone
+// filter and transpose, 64 x 512^2, 8 x 1024^2 and 3 x 2048^2 maps): 32 rows is
 // fastest for R <= 4 (k <= 9), 64 rows from R = 5 (k >= 11) on; 16 rows is
-// slower everywhere and 128 slower at R = 2.
-__host__ __device__ constexpr int blur_ty(int R) { return R <= 4 ? 32 : 64; }
+// slower everywhere and 128 slower at R = 2.  From R = 5 on, where the 64-row
+// tiles would not give every CU one, a tile's own rows are the launch's time
+// and 16-row tiles win (k = 15, one 512^2 map, 64 tiles: 13.4 / 19.3 us filter /
+// transpose against 10.0 / 11.0; at 256 tiles 15.1 / 20.7 against 15.3 / 19.4,
+// at 384 17.1 / 22.2 against 20.4 / 25.7).
+constexpr int kBlurFewTiles = 256;
+__host__ __device__ constexpr int blur_tall(int R) { return R <= 4 ? 32 : 64; }
+__host__ __device__ constexpr int blur_short(int R) { return R <= 4 ? 32 : 16; }
+int blur_tile_height(int R, long long tall_tiles) { return tall_tiles < kBlurFewTiles ? blur_short(R) : blur_tall(R); }
 
 __device__ __forceinline__ int find_job(const BlurJob *jobs, int njobs, int tile) {
     int lo = 0, hi = njobs - 1;
@@ -46,12 +58,12 @@ __device__ __forceinline__ int find_job(const BlurJob *jobs, int njobs, int tile
 // Staged tile geometry for radius R.  LDS row layout: [pad | halo R | 64
 // interior | halo R | pad] with the interior at column H4 = 4 ceil(R / 4), so
 // that it is written with 128-bit stores.
-template <int R>
+template <int R, int TY_>
 struct BlurGeom {
     static constexpr int K = 2 * R + 1;
     static constexpr int H4 = (R + 3) & ~3;
     static constexpr int RWP = kBlurTX + 2 * H4;                    // LDS row stride (floats)
-    static constexpr int TY = blur_ty(R);                           // tile height
+    static constexpr int TY = TY_;                                  // tile height
     static constexpr int WR = TY / (kBlurThreads / kBlurTX);        // output rows per lane
     static constexpr int RH = TY + 2 * R;                           // staged rows
     static constexpr int NQ = RH * (kBlurTX / 4);                   // interior quads per channel
@@ -66,11 +78,11 @@ struct BlurGeom {
 // IL: the filtered side (the output of the forward pass, the input of the
 // transpose) holds (m1, m2) interleaved per texel, so that a bilinear tap of
 // the lookup is one 8-byte load; the smoothed side stays channel-planar.
-template <bool ADJ, int R, bool IL>
+template <bool ADJ, int R, bool IL, int TY>
 __global__ __launch_bounds__(kBlurThreads) void blur_kernel(const BlurJob *__restrict__ jobs, int njobs,
                                                             BlurJob single, int per_map,
                                                             const float *__restrict__ in, float *__restrict__ out) {
-    using G = BlurGeom<R>;
+    using G = BlurGeom<R, TY>;
     constexpr int K = G::K, H4 = G::H4, RWP = G::RWP, RH = G::RH;
     __shared__ __align__(16) float tile_s[2][RH][RWP];
     const int item = xcd_remap((int)blockIdx.x, (int)gridDim.x);
@@ -249,6 +261,7 @@ __global__ __launch_bounds__(kBlurThreads) void blur_kernel(const BlurJob *__res
             }
         }
     }
+    auto tap = [](float a, float b, float c) { return IL && !ADJ ? c + a * b : fmaf(a, b, c); };
     const int lane = tid & (kBlurTX - 1);
     const int x = x0 + lane;
     const int lr0 = (tid / kBlurTX) * G::WR;                  // first output row of this wave (tile-local)
@@ -259,21 +272,21 @@ __global__ __launch_bounds__(kBlurThreads) void blur_kernel(const BlurJob *__res
         hb = 0.f;
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            ha += w[j] * pa[j];
-            hb += w[j] * pb[j];
+            ha = tap(w[j], pa[j], ha);
+            hb = tap(w[j], pb[j], hb);
         }
         if (ADJ && R > 0) {
             if (x == 0)               // taps clamped onto column 0: column i at element H4 + i
 #pragma unroll
                 for (int i = 0; i < R; ++i) {
-                    ha += cum[R - 1 - i] * tile_s[0][l][H4 + i];
-                    hb += cum[R - 1 - i] * tile_s[1][l][H4 + i];
+                    ha = tap(cum[R - 1 - i], tile_s[0][l][H4 + i], ha);
+                    hb = tap(cum[R - 1 - i], tile_s[1][l][H4 + i], hb);
                 }
             if (x == S - 1)           // column S-1-i at element H4 + lane - i
 #pragma unroll
                 for (int i = 0; i < R; ++i) {
-                    ha += cum[R - 1 - i] * tile_s[0][l][H4 + lane - i];
-                    hb += cum[R - 1 - i] * tile_s[1][l][H4 + lane - i];
+                    ha = tap(cum[R - 1 - i], tile_s[0][l][H4 + lane - i], ha);
+                    hb = tap(cum[R - 1 - i], tile_s[1][l][H4 + lane - i], hb);
                 }
         }
     };
@@ -290,22 +303,22 @@ __global__ __launch_bounds__(kBlurThreads) void blur_kernel(const BlurJob *__res
         float va = 0.f, vb = 0.f;
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            va += w[j] * ra[j];
-            vb += w[j] * rb[j];
+            va = tap(w[j], ra[j], va);
+            vb = tap(w[j], rb[j], vb);
         }
         if (ADJ && R > 0) {
             if (yy == 0) {             // taps clamped onto row 0: rows 0..R-1 sit at ring R..2R-1
 #pragma unroll
                 for (int k = 0; k < R; ++k) {
-                    va += cum[R - 1 - k] * ra[R + k];
-                    vb += cum[R - 1 - k] * rb[R + k];
+                    va = tap(cum[R - 1 - k], ra[R + k], va);
+                    vb = tap(cum[R - 1 - k], rb[R + k], vb);
                 }
             }
             if (yy == S - 1) {         // rows S-1-k sit at ring R-k
 #pragma unroll
                 for (int k = 0; k < R; ++k) {
-                    va += cum[R - 1 - k] * ra[R - k];
-                    vb += cum[R - 1 - k] * rb[R - k];
+                    va = tap(cum[R - 1 - k], ra[R - k], va);
+                    vb = tap(cum[R - 1 - k], rb[R - k], vb);
                 }
             }
         }
@@ -330,12 +343,15 @@ __global__ __launch_bounds__(kBlurThreads) void blur_kernel(const BlurJob *__res
 }
 
 template <bool ADJ, bool IL>
-static hipError_t launch_r(int R, dim3 grid, const BlurJob *jobs, int njobs, const BlurJob &single, int per_map,
+static hipError_t launch_r(int R, int ty, dim3 grid, const BlurJob *jobs, int njobs, const BlurJob &single, int per_map,
                            const float *in, float *out, hipStream_t s) {
-#define DSM_BR(RR)                                                                                                    \
-    case RR:                                                                                                         \
-        hipLaunchKernelGGL((blur_kernel<ADJ, RR, IL>), grid, dim3(kBlurThreads), 0, s, jobs, njobs, single, per_map, \
-                           in, out);                                                                                  \
+#define DSM_BRT(RR, TT)                                                                                           \
+    hipLaunchKernelGGL((blur_kernel<ADJ, RR, IL, TT>), grid, dim3(kBlurThreads), 0, s, jobs, njobs, single, per_map, \
+                       in, out)
+#define DSM_BR(RR)                                       \
+    case RR:                                            \
+        if (ty == blur_tall(RR)) DSM_BRT(RR, blur_tall(RR)); \
+        else DSM_BRT(RR, blur_short(RR));               \
         break;
     switch (R) {
         DSM_BR(0) DSM_BR(1) DSM_BR(2) DSM_BR(3) DSM_BR(4) DSM_BR(5) DSM_BR(6) DSM_BR(7)
@@ -343,20 +359,21 @@ static hipError_t launch_r(int R, dim3 grid, const BlurJob *jobs, int njobs, con
         default: return hipErrorInvalidValue;
     }
 #undef DSM_BR
+#undef DSM_BRT
     return hipGetLastError();
 }
 
 int blur_tiles_x(int S) { return (S + kBlurTX - 1) / kBlurTX; }
-int blur_tiles(int S, int R) { return blur_tiles_x(S) * ((S + blur_ty(R) - 1) / blur_ty(R)); }
-int blur_tile_height(int R) { return blur_ty(R); }
+int blur_tiles(int S, int ty) { return blur_tiles_x(S) * ((S + ty - 1) / ty); }
+int blur_tall_tiles(int S, int R) { return blur_tiles(S, blur_tall(R)); }
 
-// jobs_dev: njobs jobs of one radius R (job.k == 2R + 1), tile offsets from 0.
+// jobs_dev: njobs jobs of one radius R (job.k == 2R + 1) and tile height ty, tile offsets from 0.
 hipError_t launch_blur(const BlurJob *jobs_dev, int njobs, int total_tiles, const float *in, float *out,
-                       bool adjoint, int R, hipStream_t s) {
+                       bool adjoint, int R, int ty, hipStream_t s) {
     if (total_tiles == 0 || njobs == 0) return hipSuccess;
     BlurJob none{};
-    if (adjoint) return launch_r<true, true>(R, dim3(total_tiles), jobs_dev, njobs, none, 1, in, out, s);
-    return launch_r<false, true>(R, dim3(total_tiles), jobs_dev, njobs, none, 1, in, out, s);
+    if (adjoint) return launch_r<true, true>(R, ty, dim3(total_tiles), jobs_dev, njobs, none, 1, in, out, s);
+    return launch_r<false, true>(R, ty, dim3(total_tiles), jobs_dev, njobs, none, 1, in, out, s);
 }
 
 hipError_t launch_blur_uniform(const BlurJob &job, int n_maps, const float *in, float *out, bool adjoint,
@@ -365,12 +382,13 @@ hipError_t launch_blur_uniform(const BlurJob &job, int n_maps, const float *in, 
     BlurJob j = job;
     j.tile_off = 0;
     j.tiles_x = blur_tiles_x(job.S);
-    const int per_map = blur_tiles(job.S, R);
+    const int ty = blur_tile_height(R, (long long)blur_tall_tiles(job.S, R) * n_maps);
+    const int per_map = blur_tiles(job.S, ty);
     const long long total = (long long)per_map * n_maps;
     if (total >= (1LL << 31)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)total);
-    if (adjoint) return launch_r<true, false>(R, grid, nullptr, 0, j, per_map, in, out, s);
-    return launch_r<false, false>(R, grid, nullptr, 0, j, per_map, in, out, s);
+    if (adjoint) return launch_r<true, false>(R, ty, grid, nullptr, 0, j, per_map, in, out, s);
+    return launch_r<false, false>(R, ty, grid, nullptr, 0, j, per_map, in, out, s);
 }
 
 void filter_taps_host(int filter, int k, float sigma, float *w) {

@@ -352,11 +352,13 @@ __device__ __forceinline__ void atomic_add_f32(float *p, float v) {
 // Host-side launchers implemented per translation unit.
 namespace dsm {
 hipError_t launch_blur(const BlurJob *jobs_dev, int njobs, int total_tiles, const float *in, float *out,
-                       bool adjoint, int rmax, hipStream_t s);
-int blur_tile_height(int rmax);
+                       bool adjoint, int R, int ty, hipStream_t s);
+// Tile height for radius R where blur_tall_tiles would sum to tall_tiles.
+int blur_tile_height(int R, long long tall_tiles);
+int blur_tall_tiles(int S, int R);
 hipError_t launch_blur_uniform(const BlurJob &job, int n_maps, const float *in, float *out, bool adjoint,
                                hipStream_t s);
-int blur_tiles(int S, int rmax);
+int blur_tiles(int S, int ty);
 int blur_tiles_x(int S);
 bool valid_filter(int S, int filter, int k);
 

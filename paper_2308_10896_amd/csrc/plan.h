@@ -35,7 +35,7 @@ struct dsm_plan {
     int max_cube_padded = 0, max_cube_texels = 0, max_cube_ring = 0;
     std::vector<dsm::CubeTap> cube_taps_h;
     struct BlurGroup {
-        int R, first, n, tiles;
+        int R, first, n, tiles, ty;
     };
     std::vector<BlurGroup> blur_groups;
 
