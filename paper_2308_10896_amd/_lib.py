@@ -6,10 +6,12 @@ or fails to load, every call raises.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, 'libdsm.so')
+EXT_PATH = os.path.join(HERE, '_dsm_torch.so')
 
 DSM_OK = 0
 STATUS = {0: 'ok', 1: 'invalid argument', 2: 'out of memory', 3: 'workspace too small', 4: 'unsupported',
@@ -113,6 +115,24 @@ def lib():
             fn.argtypes = args
         _lib = h
     return _lib
+
+
+_ext = None
+
+
+def ext():
+    """The autograd nodes' module (raises if it is not built)."""
+    global _ext
+    if _ext is None:
+        if not os.path.exists(EXT_PATH):
+            raise RuntimeError(f'{EXT_PATH} is missing: build it with `python -m paper_2308_10896_amd.build`')
+        import torch  # noqa: F401  (its libraries first)
+        lib()
+        spec = importlib.util.spec_from_file_location('_dsm_torch', EXT_PATH)
+        m = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(m)
+        _ext = m
+    return _ext
 
 
 def check(fn, status):

@@ -1,7 +1,9 @@
 """Build the HIP library in-tree with hipcc for gfx950.
 
 Usage: python -m paper_2308_10896_amd.build  (or call build()).
-The shared library lands next to this file as libdsm.so.
+The shared library lands next to this file as libdsm.so, the autograd nodes
+over it (csrc/binding.cpp, compiled against the installed torch) as
+_dsm_torch.so.
 """
 from __future__ import annotations
 
@@ -17,6 +19,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, 'csrc')
 INCLUDE = os.path.join(ROOT, 'include')
 LIB = os.path.join(HERE, 'libdsm.so')
+EXT = os.path.join(HERE, '_dsm_torch.so')
 
 # -ffp-contract=off: no fused multiply-add anywhere, so the float32
 #   transform / snapping / depth arithmetic that decides coverage is exactly
@@ -42,12 +45,39 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, '*.hip')))
 
 
+def binding_command(obj):
+    """g++ line that compiles csrc/binding.cpp."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    inc = [sysconfig.get_path('include'), INCLUDE] + cpp_extension.include_paths('cuda')
+    return ['g++', '-O2', '-std=c++17', '-fPIC', '-fvisibility=hidden', '-c', os.path.join(CSRC, 'binding.cpp'), '-o', obj,
+            '-D__HIP_PLATFORM_AMD__=1', '-DUSE_ROCM=1', '-DTORCH_EXTENSION_NAME=_dsm_torch',
+            f'-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}'] + [f'-I{d}' for d in inc]
+
+
+def link_binding(obj):
+    from torch.utils import cpp_extension
+    tmp = EXT + '.tmp'
+    cmd = ['g++', '-shared', '-o', tmp, obj, f'-L{HERE}', '-ldsm', '-Wl,-rpath,$ORIGIN']
+    cmd += [f'-L{d}' for d in cpp_extension.library_paths('cuda')]
+    cmd += ['-lc10', '-lc10_hip', '-ltorch', '-ltorch_cpu', '-ltorch_hip', '-ltorch_python']
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f'link failed:\n{r.stdout}\n{r.stderr}')
+    os.replace(tmp, EXT)
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every HIP source into libdsm.so (always recompiles)."""
+    """Compile every source into libdsm.so and _dsm_torch.so (always recompiles)."""
     srcs = sources()
     with tempfile.TemporaryDirectory() as tmp:
         objs = []
         procs = []
+        bind = os.path.join(tmp, 'binding.o')
+        procs.append(('binding.cpp', subprocess.Popen(binding_command(bind), stdout=subprocess.PIPE,
+                                                      stderr=subprocess.STDOUT)))
         for s in srcs:
             o = os.path.join(tmp, os.path.basename(s) + '.o')
             cmd = [hipcc()] + [f for f in FLAGS if f not in ('-shared',)] + ['-c', '-I', INCLUDE, '-I', CSRC, s, '-o', o]
@@ -60,7 +90,7 @@ def build(verbose: bool = False) -> str:
             text = out.decode(errors='replace')
             text = '\n'.join(l for l in text.splitlines() if 'packed-fp32-ops' not in l and l.strip())
             if p.returncode != 0:
-                raise RuntimeError(f'hipcc failed on {s}:\n{text}')
+                raise RuntimeError(f'compiling {s} failed:\n{text}')
             if verbose and text:
                 print(text)
         tmp_lib = LIB + '.tmp'
@@ -69,6 +99,7 @@ def build(verbose: bool = False) -> str:
         if r.returncode != 0:
             raise RuntimeError(f'link failed:\n{r.stdout}\n{r.stderr}')
         os.replace(tmp_lib, LIB)
+        link_binding(bind)
     return LIB
 
 

@@ -2,7 +2,8 @@
 
 Every step of the render and of its gradient runs in the HIP library; torch
 only provides device memory and the current stream.  The functions mirror the
-ABI names without the ``dsm_`` prefix.
+ABI names without the ``dsm_`` prefix; ``render`` and ``pose`` are autograd
+nodes in C++ (csrc/binding.cpp).
 """
 from __future__ import annotations
 
@@ -158,6 +159,7 @@ class Plan:
         h = C.c_void_p()
         L.call('dsm_plan_create', C.byref(desc), int(tile_size), int(bin_capacity_scale), C.byref(h))
         self.handle = h
+        self._nodes = L.ext().PlanHandle(self, h.value)
         info = L.PlanInfo()
         L.call('dsm_plan_info_get', h, C.byref(info))
         self.info = info
@@ -311,46 +313,15 @@ def autotune(batch, verts, light_params, albedo, grad_images, reps: int = 3, cac
     return int(tile.value), int(scale.value), float(ms.value)
 
 
-class _Render(torch.autograd.Function):
-    @staticmethod
-    def forward(ctx, plan, verts, light_params, albedo):
-        saved = torch.empty(int(plan.info.saved_bytes), dtype=torch.uint8, device=verts.device)
-        images = plan.forward(verts, light_params, albedo, saved, plan.scratch(verts.device))
-        ctx.plan = plan
-        ctx.save_for_backward(verts, light_params, albedo, saved)
-        return images
-
-    @staticmethod
-    def backward(ctx, grad_images):
-        verts, light_params, albedo, saved = ctx.saved_tensors
-        gv, gl, ga = ctx.plan.backward(verts, light_params, albedo, saved, ctx.plan.scratch(verts.device),
-                                       grad_images.contiguous(),
-                                       want_albedo=ctx.needs_input_grad[3])
-        return None, gv, gl, ga
-
-
-class _Pose(torch.autograd.Function):
-    @staticmethod
-    def forward(ctx, plan, local, poses):
-        ctx.plan = plan
-        ctx.save_for_backward(local, poses)
-        return plan.pose_forward(local, poses)
-
-    @staticmethod
-    def backward(ctx, grad_world):
-        local, poses = ctx.saved_tensors
-        return None, None, ctx.plan.pose_backward(local, poses, grad_world.contiguous())
-
-
 def render(plan: Plan, verts, light_params, albedo):
     """Differentiable render of every image of the plan (flat float32 tensor;
     ``plan.split_images`` gives per-render [H, W, C] views)."""
-    return _Render.apply(plan, verts, light_params, albedo)
+    return _lib.ext().render(plan._nodes, verts, light_params, albedo, plan.scratch(verts.device))
 
 
 def pose(plan: Plan, local, poses):
     """Differentiable rigid pose of each scene's posed vertex prefix."""
-    return _Pose.apply(plan, local, poses)
+    return _lib.ext().pose(plan._nodes, local, poses)
 
 
 def batch_inputs(batch, device='cuda'):
