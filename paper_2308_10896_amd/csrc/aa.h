@@ -103,19 +103,21 @@ __device__ __forceinline__ bool aa_eval(const ViewConst &v, const TriSetup *__re
         out.w = (float)(0.5 - alpha);
     }
     if (WANT_GRAD) {
-        const double dF = -eO / (D * D), dO = eF / (D * D);    // d alpha / d eF, d alpha / d eO
+        // gradient terms only: one reciprocal each of D^2 and of the two w
+        const double rD = 1.0 / (D * D), ra = 1.0 / ca[3], rb = 1.0 / cb[3];
+        const double dF = -eO * rD, dO = eF * rD;    // d alpha / d eF, d alpha / d eO
         // d E(p) / d (xa, ya, xb, yb)
-        const double gxa = dF * (yb - pfy) + dO * (yb - poy);
-        const double gya = dF * (pfx - xb) + dO * (pox - xb);
-        const double gxb = dF * (pfy - ya) + dO * (poy - ya);
-        const double gyb = -dF * (pfx - xa) - dO * (pox - xa);
+        const double gxa = (dF * (yb - pfy) + dO * (yb - poy)) * hw;
+        const double gya = (dF * (pfx - xb) + dO * (pox - xb)) * hh;
+        const double gxb = (dF * (pfy - ya) + dO * (poy - ya)) * hw;
+        const double gyb = (-dF * (pfx - xa) - dO * (pox - xa)) * hh;
         // screen coordinates to clip (x, y, w)
-        out.dax = gxa * hw / ca[3];
-        out.day = -gya * hh / ca[3];
-        out.daw = -gxa * hw * ca[0] / (ca[3] * ca[3]) + gya * hh * ca[1] / (ca[3] * ca[3]);
-        out.dbx = gxb * hw / cb[3];
-        out.dby = -gyb * hh / cb[3];
-        out.dbw = -gxb * hw * cb[0] / (cb[3] * cb[3]) + gyb * hh * cb[1] / (cb[3] * cb[3]);
+        out.dax = gxa * ra;
+        out.day = -gya * ra;
+        out.daw = (gya * ca[1] - gxa * ca[0]) * (ra * ra);
+        out.dbx = gxb * rb;
+        out.dby = -gyb * rb;
+        out.dbw = (gyb * cb[1] - gxb * cb[0]) * (rb * rb);
     }
     return true;
 }

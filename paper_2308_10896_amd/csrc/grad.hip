@@ -163,11 +163,12 @@ __device__ __forceinline__ void edge_add(EdgeTerm &t, float4 *__restrict__ gclip
 // A wave per 64 x 4 region for a chunk of the camera's renders: as in the
 // forward, the pairs are evaluated once, a pair a lane.  A pair across a
 // region's border is evaluated in both; the region of its receiving sample
-// adds the edge's terms.  64 512^2 images 188 -> 120 us; a 1920 x 1080 image
-// with long outlines 260 -> 32 and a 256^2 one 46 -> 10, where the atomics of
-// all samples of an outline met on its two vertices.
+// adds the edge's terms.  64 512^2 images 188 -> 101 us; a 1920 x 1080 image
+// with long outlines 260 -> 30 and a 256^2 one 46 -> 10, where the atomics of
+// all samples of an outline met on its two vertices.  One channel at 6 waves
+// per SIMD (4: 117 us), three at 4.
 template <int C>
-__global__ __launch_bounds__(64) void aa_camera_backward_kernel(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(C == 1 ? 6 : 4))) void aa_camera_backward_kernel(
     const ViewConst *__restrict__ views, int L, const RenderConst *__restrict__ renders,
     const int *__restrict__ cam_renders_off, const int *__restrict__ cam_renders, int chunk,
     const TriSetup *__restrict__ setup, const int *__restrict__ faces, const unsigned char *__restrict__ silm,

@@ -768,11 +768,12 @@ __device__ __forceinline__ void overflow_raster(const ViewConst *__restrict__ vi
 // wave-wide test alone uses 64 lanes on the four samples of a 2 x 2 box), a
 // crowded tile is shared by four waves, and a group of nearly empty tiles
 // waits for one chain of loads instead of one per tile.  Against one wave per
-// tile testing its bin an entry at a time: 64 scenes at 512^2 388 -> 266 us,
-// 8 x 1024^2 maps and 16 views of a 99k-triangle sphere 432 -> 136, four
-// scenes at 200^2 (hundreds of entries a tile) 133 -> 23.  Groups of 4 or 16
-// tiles: 338 and 313 us on the 64 scenes.
+// tile testing its bin an entry at a time: 64 scenes at 512^2 388 -> 259 us,
+// 8 x 1024^2 maps and 16 views of a 99k-triangle sphere 432 -> 142, four
+// scenes at 200^2 (hundreds of entries a tile) 133 -> 24.  Groups of 4 or 16
+// tiles: 338 and 313 us on the 64 scenes; 6 waves per SIMD 271, 8 (spills) 403.
 constexpr int kRasterThreads = 256;
+constexpr int kWide = 128;      // records of the shared list; a chunk with more takes another round
 
 template <int T>
 struct RasterShape {
@@ -781,7 +782,7 @@ struct RasterShape {
 };
 
 template <int T>
-__global__ __launch_bounds__(kRasterThreads) void raster_kernel(
+__global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(T == 8 ? 7 : 4))) void raster_kernel(
     const ViewConst *__restrict__ views, const int *__restrict__ tile_view, int ntiles,
     const TriSetup *__restrict__ setup, const unsigned *__restrict__ tile_start, const unsigned *__restrict__ bins,
     unsigned long long *__restrict__ keys, const unsigned *__restrict__ overflow_list, DevCounters *counters,
@@ -799,7 +800,7 @@ __global__ __launch_bounds__(kRasterThreads) void raster_kernel(
     };
     __shared__ unsigned long long best[RS::kPix];
     __shared__ TileInfo info[G];
-    __shared__ __align__(16) RasterTri wide[kRasterThreads];
+    __shared__ __align__(16) RasterTri wide[kWide];
     __shared__ unsigned nwide;
     const int g0 = xcd_remap((int)blockIdx.x, ngroups) * G;
     const int ng = min(G, ntiles - g0);
@@ -853,11 +854,13 @@ __global__ __launch_bounds__(kRasterThreads) void raster_kernel(
         const int most = n16 - n64 > 48 ? 64 : n16 - n32 > 16 ? 32 : n0 - n16 > 8 ? 16 : 0;
         const bool own = area > 0 && area <= most, shared = area > most;
         const unsigned long long m = __ballot(shared);
+        unsigned at = ~0u;                    // this lane's place in the list
         if (m) {
-            unsigned at = 0;
-            if (lane == 0) at = atomicAdd(&nwide, (unsigned)__popcll(m));
-            at = (unsigned)__builtin_amdgcn_readfirstlane((int)at);
-            if (shared) wide[at + __popcll(m & ((1ull << lane) - 1ull))] = r;
+            unsigned first = 0;
+            if (lane == 0) first = atomicAdd(&nwide, (unsigned)__popcll(m));
+            first = (unsigned)__builtin_amdgcn_readfirstlane((int)first);
+            if (shared) at = first + (unsigned)__popcll(m & ((1ull << lane) - 1ull));
+            if (at < kWide) wide[at] = r;
         }
         if (own) {
             unsigned long long *row = best + k * (T * T) + y0 * T;
@@ -885,26 +888,33 @@ __global__ __launch_bounds__(kRasterThreads) void raster_kernel(
         }
         __syncthreads();
         const int n = (int)nwide;
-        for (int j = tid >> 6; j < n; j += kRasterThreads / 64) {
-            const RasterTri w = wide[j];
-            const int wx0 = w.box & 31, wx1 = (w.box >> 5) & 31, wy0 = (w.box >> 10) & 31, wy1 = (w.box >> 15) & 31;
-            unsigned long long *tb = best + ((w.box >> 20) & 15) * (T * T);
-            // the tile's 8 x 8 blocks that the bounding box touches
-            if constexpr (T == 8) {
-                const int lx = lane & 7, ly = lane >> 3;
-                if (lx >= wx0 && lx <= wx1 && ly >= wy0 && ly <= wy1) {
-                    const unsigned long long key = pixel_key(w, sample_pos(lx), sample_pos(ly));
-                    if (key != kBgKey) atomicMin(&tb[lane], key);
-                }
-                continue;
+        for (int base = 0; base < n; base += kWide) {                   // uniform
+            if (base > 0) {
+                __syncthreads();
+                if (at != ~0u && at >= (unsigned)base && at < (unsigned)(base + kWide)) wide[at - base] = r;
+                __syncthreads();
             }
-            for (int by = wy0 >> 3; by <= wy1 >> 3; ++by)
-                for (int bx = wx0 >> 3; bx <= wx1 >> 3; ++bx) {
-                    const int lx = bx * 8 + (lane & 7), ly = by * 8 + (lane >> 3);
-                    if (lx < wx0 || lx > wx1 || ly < wy0 || ly > wy1) continue;
-                    const unsigned long long key = pixel_key(w, sample_pos(lx), sample_pos(ly));
-                    if (key != kBgKey) atomicMin(&tb[ly * T + lx], key);
+            for (int j = tid >> 6; j < min(n - base, kWide); j += kRasterThreads / 64) {
+                const RasterTri w = wide[j];
+                const int wx0 = w.box & 31, wx1 = (w.box >> 5) & 31, wy0 = (w.box >> 10) & 31, wy1 = (w.box >> 15) & 31;
+                unsigned long long *tb = best + ((w.box >> 20) & 15) * (T * T);
+                // the tile's 8 x 8 blocks that the bounding box touches
+                if constexpr (T == 8) {
+                    const int lx = lane & 7, ly = lane >> 3;
+                    if (lx >= wx0 && lx <= wx1 && ly >= wy0 && ly <= wy1) {
+                        const unsigned long long key = pixel_key(w, sample_pos(lx), sample_pos(ly));
+                        if (key != kBgKey) atomicMin(&tb[lane], key);
+                    }
+                    continue;
                 }
+                for (int by = wy0 >> 3; by <= wy1 >> 3; ++by)
+                    for (int bx = wx0 >> 3; bx <= wx1 >> 3; ++bx) {
+                        const int lx = bx * 8 + (lane & 7), ly = by * 8 + (lane >> 3);
+                        if (lx < wx0 || lx > wx1 || ly < wy0 || ly > wy1) continue;
+                        const unsigned long long key = pixel_key(w, sample_pos(lx), sample_pos(ly));
+                        if (key != kBgKey) atomicMin(&tb[ly * T + lx], key);
+                    }
+            }
         }
         __syncthreads();
         if (c + kRasterThreads < ts[G]) {

@@ -92,9 +92,10 @@ __device__ __forceinline__ float texel_moment(const ViewConst &l, const TriVerts
 // smoothed (f, f^2).  A pair's giving sample outside the region is resolved
 // again from its key.  Bytes a texel: 8 (key) + 4 (F0) + 8 (F1) + 1 (flag),
 // where a resolve, a copying pass and a list pass moved 41; 64 512^2 maps
-// 212 -> 134 us (vector issue and the record gathers; the bytes take 70),
-// three 2048^2 maps 177 -> 106.
-__global__ __launch_bounds__(64) void light_moments_kernel(const ViewConst *__restrict__ views,
+// 212 -> 127 us (vector issue and the record gathers; the bytes take 70),
+// three 2048^2 maps 177 -> 100.  At 6 waves per SIMD (5: 134 and 106; 8 spills:
+// 203 and 169).
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) void light_moments_kernel(const ViewConst *__restrict__ views,
                                                            const TriVerts *__restrict__ tv,
                                                            const TriSetup *__restrict__ setup,
                                                            const int *__restrict__ faces,
@@ -183,10 +184,11 @@ __global__ __launch_bounds__(64) void light_moments_kernel(const ViewConst *__re
 // Edge smoothing of the camera images, a wave per 64 x 4 region, for a chunk
 // of the camera's renders: the pairs depend on the keys alone, so they are
 // evaluated once for all of them.  Latency of the pairs' loads bounds it; 64
-// 512^2 images 121 -> 79 us against four pair tests per thread in place, 16
-// cameras with 8 renders each 211 -> 96.
+// 512^2 images 121 -> 73 us against four pair tests per thread in place, 16
+// cameras with 8 renders each 211 -> 95.  One channel at 8 waves per SIMD (6:
+// 77 us), three at 5 (8 spills: 22 -> 29 us on a 1080p image).
 template <int C>
-__global__ __launch_bounds__(64) void aa_camera_forward_kernel(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(C == 1 ? 8 : 5))) void aa_camera_forward_kernel(
     const ViewConst *__restrict__ views, int L, const RenderConst *__restrict__ renders,
     const int *__restrict__ cam_renders_off, const int *__restrict__ cam_renders, int chunk,
     const TriSetup *__restrict__ setup, const int *__restrict__ faces, const unsigned char *__restrict__ silm,

@@ -82,8 +82,28 @@ def _crowded():
     return b
 
 
+def _stacked():
+    """600 triangles at random heights, each over most of a small view, and four
+    small ones after each: some hundred boxes of more samples than a lane
+    tests alone in every chunk of a tile's entries, more than the shared list
+    holds at once."""
+    rng = np.random.default_rng(23)
+    parts = []
+    for y in rng.uniform(0.0, 1.0, 600):
+        parts.append(np.array([[-5, y, -3], [0, y + rng.uniform(-.2, .2), 2.8], [5, y, -3]]))
+        for x, z in rng.uniform(-1.5, 1.5, (4, 2)):
+            parts.append(np.array([[x, y, z], [x, y, z + .5], [x + .5, y, z]]))
+    v = np.concatenate(parts)
+    f = np.arange(len(v), dtype=np.int32).reshape(-1, 3)
+    b = sg.config0()
+    b.scenes = [sg.Scene(verts=v, faces=f, albedo=np.full((len(f), 1), 0.8, np.float32))]
+    b.lights[0].resolution, b.lights[0].k = 9, 1
+    b.cameras[0].width, b.cameras[0].height = 21, 13
+    return b
+
+
 CASES = {'soup': lambda: _soup(250, 190, 200), 'soup_narrow': lambda: _soup(67, 9, 33), 'one_pixel': lambda: _soup(1, 1, 1),
-         'crowded': _crowded}
+         'crowded': _crowded, 'stacked': _stacked}
 
 
 @pytest.mark.gpu
