@@ -467,8 +467,21 @@ __global__ __launch_bounds__(kTriThreads) void block_prefix_kernel(unsigned *__r
 // Count pass.  A triangle's first pair is its offset in its workgroup plus the
 // totals of the workgroups before, which every workgroup sums itself (or finds
 // scanned, past kMaxTriBlocks of them).  The silhouette masks ride along: they need every
-// facing byte, as this pass needs every total.  Bound by the latency of the
-// tile counters' atomics.
+// facing byte, as this pass needs every total.
+//
+// Bound by the latency of the tile counters' atomics, so a workgroup counts
+// its own pairs first: where the tiles its triangles touch lie in a box of at
+// most kTileTable tiles (the triangles of a mesh are neighbours), a table in
+// LDS holds a counter for each of them, one global atomic per tile that has
+// pairs fetches the tile's first slot, and a second walk over the pairs hands
+// out the slots from the table.  Wider boxes (a strip across a large view,
+// triangles in no order) aggregate a wave's equal tiles with ballots
+// (wave_slot), which took the place of the table before: 64 scenes at 512^2
+// 57 -> 32 us, three 2048^2 maps and a 1080p view 43 -> 30, a 10k-triangle
+// sphere at 512^2 20 -> 7 (no aggregation at all: 167, 159 and 9).  4096
+// counters are 16 KB, so that eight workgroups share a CU, and all tiles of a
+// 512^2 view.
+constexpr int kTileTable = 4096;
 __global__ __launch_bounds__(kTriThreads) void bin_count_kernel(
     const ViewConst *__restrict__ views, const TriBlock *__restrict__ blocks, int nblocks,
     const TriSetup *__restrict__ setup, const int *__restrict__ adj, const signed char *__restrict__ facing8,
@@ -477,12 +490,17 @@ __global__ __launch_bounds__(kTriThreads) void bin_count_kernel(
     int ntri,
     unsigned *__restrict__ tile_count, unsigned *__restrict__ pair_slot, LargeLists large,
     unsigned *__restrict__ overflow_list, DevCounters *counters) {
-    __shared__ BinWave wave[kTriThreads / 64];
+    // the tile table, a wave's triangles, or the prefix of the totals
+    __shared__ union {
+        unsigned table[kTileTable];
+        BinWave wave[kTriThreads / 64];
+        unsigned prefix[kMaxTriBlocks];
+    } sh;
     const int tid = (int)threadIdx.x;
     if ((int)blockIdx.x >= nblocks) {
         if (counters->large_len == 0) return;
         // the workgroup's own prefix of all totals, one entry per TriBlock
-        __shared__ unsigned prefix[kMaxTriBlocks];
+        unsigned *prefix = sh.prefix;
         __shared__ unsigned carry;
         if (tid == 0) carry = 0;
         for (int c = 0; c < nblocks && !scanned; c += kTriThreads) {
@@ -505,39 +523,103 @@ __global__ __launch_bounds__(kTriThreads) void bin_count_kernel(
     }
     const TriBlock blk = blocks[blockIdx.x];
     const ViewConst &v = views[blk.view];
+    const int t = blk.first + tid;
+    const bool mine = t < v.nfaces;
+    TileBox b{0, 0, 1, 0u};
+    unsigned local = 0;
+    if (mine) {
+        b = tile_box(setup[v.setup_off + t], shift);
+        local = pair_local[v.setup_off + t];
+    }
+    const int nty = (int)small_div(b.n, b.ntx);
     __shared__ unsigned part[kTriThreads / 64];
+    __shared__ int boxes[kTriThreads / 64][4];        // the waves' tiles: first x, first y, last x, last y
     unsigned sum = 0;
     if (!scanned)
         for (int k = tid; k < (int)blockIdx.x; k += kTriThreads) sum += block_total[k];
+    const bool small = b.n > 0 && b.n <= kBigBin;
+    int lo_x = small ? b.tx0 : 65536, lo_y = small ? b.ty0 : 65536;
+    int hi_x = small ? b.tx0 + b.ntx - 1 : -1, hi_y = small ? b.ty0 + nty - 1 : -1;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-    if ((tid & 63) == 0) part[tid >> 6] = sum;
+    for (int o = 32; o > 0; o >>= 1) {
+        sum += __shfl_xor(sum, o, 64);
+        lo_x = min(lo_x, __shfl_xor(lo_x, o, 64));
+        lo_y = min(lo_y, __shfl_xor(lo_y, o, 64));
+        hi_x = max(hi_x, __shfl_xor(hi_x, o, 64));
+        hi_y = max(hi_y, __shfl_xor(hi_y, o, 64));
+    }
+    if ((tid & 63) == 0) {
+        int *q = boxes[tid >> 6];
+        part[tid >> 6] = sum;
+        q[0] = lo_x;
+        q[1] = lo_y;
+        q[2] = hi_x;
+        q[3] = hi_y;
+    }
     __syncthreads();
     const unsigned base = scanned ? block_total[blockIdx.x] : (part[0] + part[1]) + (part[2] + part[3]);
+#pragma unroll
+    for (int k = 0; k < kTriThreads / 64; ++k) {
+        lo_x = min(lo_x, boxes[k][0]);
+        lo_y = min(lo_y, boxes[k][1]);
+        hi_x = max(hi_x, boxes[k][2]);
+        hi_y = max(hi_y, boxes[k][3]);
+    }
+    const int bw = hi_x - lo_x + 1, nbox = hi_x < 0 ? 0 : bw * (hi_y - lo_y + 1);
+    const bool table = nbox <= kTileTable;            // the same in every lane
+    if (table)
+        for (int k = tid; k < nbox; k += kTriThreads) sh.table[k] = 0u;
     if ((int)blockIdx.x == nblocks - 1 && tid == 0) {
         const unsigned total = scanned ? block_total[nblocks] : base + block_total[blockIdx.x];
         pair_off[ntri] = total;
         counters->pairs = total;       // for the plan's statistics
     }
-    const int t = blk.first + tid;
     unsigned cnt = 0;
     BinItem it{};
-    if (t < v.nfaces) {
+    it.a = local + base;
+    it.ntx = b.ntx;
+    it.tile0 = v.tile_off + b.ty0 * v.tiles_x + b.tx0;
+    if (mine) {
         const int si = v.setup_off + t;
-        const TileBox b = tile_box(setup[si], shift);
-        it.a = pair_local[si] + base;
-        it.ntx = b.ntx;
-        it.tile0 = v.tile_off + b.ty0 * v.tiles_x + b.tx0;
         pair_off[si] = it.a;
         const unsigned end = it.a + b.n;
         if (end > capacity) {                                // overflow path
             if (b.n) overflow_list[atomicAdd(&counters->overflow_list_len, 1u)] = (unsigned)si;
-        } else if (b.n <= kBigBin) {
+        } else if (small) {
             cnt = b.n;
         }
         silm[si] = silhouette_mask(adj, facing8 + v.setup_off, t, (size_t)(v.face_off + t));
     }
-    for_wave_pairs(wave[tid >> 6], cnt, it,
+    if (table) {
+        if (nbox == 0) return;
+        unsigned *first = sh.table + (b.ty0 - lo_y) * bw + (b.tx0 - lo_x);
+        __syncthreads();
+        if (cnt)
+            for (int y = 0; y < nty; ++y)
+                for (int x = 0; x < b.ntx; ++x) atomicAdd(first + y * bw + x, 1u);
+        __syncthreads();
+        const int tile0 = v.tile_off + lo_y * v.tiles_x + lo_x;
+        for (int c = tid; c < nbox; c += kTriThreads * kPairSteps) {
+            unsigned n[kPairSteps];
+#pragma unroll
+            for (int u = 0; u < kPairSteps; ++u) {
+                const int k = c + u * kTriThreads;
+                n[u] = k < nbox ? sh.table[k] : 0u;
+                if (n[u]) n[u] = atomicAdd(&tile_count[tile0 + (k / bw) * v.tiles_x + k % bw], n[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < kPairSteps; ++u)
+                if (c + u * kTriThreads < nbox) sh.table[c + u * kTriThreads] = n[u];
+        }
+        __syncthreads();
+        if (cnt) {
+            unsigned *slot = pair_slot + it.a;
+            for (int y = 0; y < nty; ++y)
+                for (int x = 0; x < b.ntx; ++x) *slot++ = atomicAdd(first + y * bw + x, 1u);
+        }
+        return;
+    }
+    for_wave_pairs(sh.wave[tid >> 6], cnt, it,
                    [&](int n, const BinItem (&b)[kPairSteps], const unsigned (&q)[kPairSteps],
                        const bool (&has)[kPairSteps], const int (&starts)[kPairSteps]) {
                        WaveSlot s[kPairSteps];

@@ -62,3 +62,32 @@ def test_more_workgroups_than_totals_summed_directly():
         assert np.array_equal(m['keys'][i], a['keys'][0]) and np.array_equal(m['keys'][600 + i], a['keys'][1])
         assert np.array_equal(m['images'][i], a['images'][0])
     assert m['stats']['pairs'] == 600 * a['stats']['pairs']
+
+
+@pytest.mark.parametrize('w,h,res', [(512, 512, 504), (520, 512, 513), (1024, 8, 1)])
+def test_tiles_of_a_workgroup_around_the_table(w, h, res):
+    """Triangles in no order, so that the tiles of every 256 of them span the
+    view: 64 x 64 tiles (as many as the count pass has counters for), one
+    column more, and a strip; then the same in two scenes, so that a view's
+    tiles start away from zero."""
+    rng = np.random.default_rng([9, w])
+    n = 900
+    c = np.stack([rng.uniform(-2.5, 2.5, n), rng.uniform(0.0, 0.6, n), rng.uniform(-2.5, 2.5, n)], 1)
+    size = np.where(rng.random(n) < 0.1, 0.4, 0.06)
+    v = (c[:, None, :] + size[:, None, None] * rng.uniform(-0.5, 0.5, (n, 3, 3))).reshape(-1, 3)
+    b = sg.config0()
+    b.scenes = [sg.Scene(verts=v, faces=np.arange(3 * n, dtype=np.int32).reshape(n, 3),
+                         albedo=np.full((n, 1), 0.8, np.float32))]
+    b.lights[0].resolution, b.lights[0].k = res, 1
+    b.cameras[0].width, b.cameras[0].height = w, h
+    o = oracle_run(b)
+    _keys_equal(gpu_run(b), o)
+    two = sg.Batch('two', b.scenes * 2, [], [], [], channels=1)
+    for i in range(2):
+        two.lights.append(sg.Light(**{**b.lights[0].__dict__, 'scene': i}))
+        two.cameras.append(sg.Camera(**{**b.cameras[0].__dict__, 'scene': i}))
+        two.renders.append(sg.Render(i, [i]))
+    g = gpu_run(two)
+    for i in range(2):
+        for k, kg in enumerate((g['keys'][i], g['keys'][2 + i])):
+            assert np.array_equal(kg, o['keys'][k]), f'scene {i} view {k}'
