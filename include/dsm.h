@@ -353,8 +353,8 @@ typedef enum {
     DSM_STAGE_LOOKUP_ADJ,       /* lookup + shading^T, map-gradient scatter, per-(triangle, tile) sums */
     DSM_STAGE_FILTER_ADJ,       /* G^T */
     DSM_STAGE_LIGHT_ADJ,        /* light-view smoothing^T + resolve^T */
-    DSM_STAGE_VERTEX_GRAD,      /* per-triangle reduction, vertex and albedo gathers */
-    DSM_STAGE_LIGHT_GRAD,       /* light partial reduction and light-parameter chain */
+    DSM_STAGE_VERTEX_GRAD,      /* large triangles' rows and light partials; vertex, light and albedo sums */
+    DSM_STAGE_LIGHT_GRAD,       /* no work of its own (the last vertex workgroups or a launch of theirs finish the lights) */
     DSM_STAGE_COUNT
 } dsm_stage;
 #define DSM_MAX_TIMING_REPS 1000

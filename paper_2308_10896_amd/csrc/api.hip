@@ -527,7 +527,7 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
     p->sc_fwd_end = o;                 // the forward touches nothing past this
     p->sc_pair_flag = o; o = align_up(o + (size_t)p->capacity + 4);      // read four bytes at a time
     p->sc_gimg0 = o; o = align_up(o + 4 * (size_t)img);
-    p->sc_done = o; o = align_up(o + 4 * (size_t)std::max(L, 1));       // the light-gradient sum's finished workgroups
+    p->sc_done = o; o = align_up(o + 4 * (size_t)std::max(B, 1));       // vertex workgroups of a scene that finished
     p->sc_zero_rec = o; o = align_up(o + 32);          // an all-zero corner record for the vertex gather
     p->sc_gM = o; o = align_up(o + 4 * (size_t)fmaps);
     p->sc_gclip = o; o = align_up(o + 16 * (size_t)clip);
@@ -811,15 +811,14 @@ dsm_status enqueue_backward(dsm_plan *p, const float *verts, const float *lparam
                                   tv, keys, aa_flag, F0, gF1, gclip, tile_start, bins, bin_pair, pair_flag, pair_sums,
                                   gtri, part_light, jac, pair_off, p->capacity, s));
     DSM_MARK(DSM_STAGE_VERTEX_GRAD);
+    const LightSum lights{p->renders_d, p->light_renders_off_d, p->light_renders_d, part_light, part_render,
+                          at<float>(scratch, p->sc_glight), at<unsigned>(scratch, p->sc_done), glparams};
     DSM_TRY(launch_vertex_gradients(p->views_d, p->L, p->B, p->max_scene_verts, p->max_scene_faces, p->max_scene_views,
                                     p->ntri, p->capacity, setup, large, cnt, p->scene_vert_off_d, p->scene_face_off_d,
                                     p->scene_views_off_d, p->scene_views_d, p->vc_off_d, p->vc_list_d, pair_off,
                                     pair_flag, pair_sums, gtri, at<float>(scratch, p->sc_zero_rec), verts, gclip, gverts,
-                                    part_gm, galbedo, p->C, jac, s));
-    DSM_MARK(DSM_STAGE_LIGHT_GRAD);
-    DSM_TRY(launch_glight_reduce(p->views_d, p->L, p->renders_d, p->light_renders_off_d, p->light_renders_d, part_gm,
-                                 part_light, part_render, at<float>(scratch, p->sc_glight),
-                                 at<unsigned>(scratch, p->sc_done), glparams, s));
+                                    part_gm, galbedo, p->C, jac, lights, s));
+    DSM_MARK(DSM_STAGE_LIGHT_GRAD);     // runs with the vertex gradients
     DSM_MARK(DSM_STAGE_COUNT);
     return DSM_OK;
 }

@@ -115,6 +115,18 @@ struct RenderConst {
     long long pix_off;  // camera view's first sample (keys)
 };
 
+// The light gradient's inputs and outputs: the partials of light tiles and of
+// render tiles, where light_partials leaves its kGlightBlocks sums per light,
+// the scenes' counters of finished workgroups, and the gradient [L][3].
+struct LightSum {
+    const RenderConst *renders;
+    const int *light_renders_off, *light_renders;
+    const float *part_light, *part_render;
+    float *gl_part;
+    unsigned *done;
+    float *gparams;
+};
+
 // Per (view, triangle) fixed-point setup, written by the setup kernel.
 struct TriSetup {
     long long A;                 // doubled area, > 0 when valid
@@ -432,11 +444,7 @@ hipError_t launch_vertex_gradients(const ViewConst *views, int L, int B, int max
                                    const int *vc_list, const unsigned *pair_off, const unsigned char *pair_flag,
                                    const float *pair_sums, float *gtri, const float *zero_rec, const float *verts,
                                    const float4 *gclip, float *gverts, float *part_gm, float *galbedo, int C,
-                                   const float *jac, hipStream_t s);
-hipError_t launch_glight_reduce(const ViewConst *views, int L, const RenderConst *renders,
-                                const int *light_renders_off, const int *light_renders, const float *part_gm,
-                                const float *part_light, const float *part_render, float *gl_part, unsigned *done,
-                                float *gparams, hipStream_t s);
+                                   const float *jac, const LightSum &ls, hipStream_t s);
 hipError_t launch_pose(const int *scene_vert_off, const int *pose_counts, const float *pose_centers, int B,
                        int max_verts, const float *local, const float *poses, float *world, hipStream_t s);
 hipError_t launch_pose_backward(const int *scene_vert_off, const int *pose_counts, int B, int max_verts,

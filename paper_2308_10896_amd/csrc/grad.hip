@@ -1202,6 +1202,36 @@ __device__ __forceinline__ TriRows tri_rows(unsigned t, unsigned a, unsigned b, 
     return TriRows{pair_sums + (size_t)a * kRow, m & ((1u << n) - 1u)};
 }
 
+// Share blk of kGlightBlocks of the partials that light l's tiles and the tiles of
+// each render that uses it left; a few lights with many of them still fill the
+// GPU.  A render's tiles are cut only as far as that takes: the way to them
+// (render, camera) is a chain of loads, and 16 renders one after the other
+// took 20 us.
+__device__ __forceinline__ void light_partials(int l, int blk, const ViewConst *__restrict__ views,
+                                               const LightSum &ls) {
+    const ViewConst &v = views[l];
+    float acc[3] = {0.f, 0.f, 0.f};
+    const int nlt = v.tiles_x * v.tiles_y;
+#pragma unroll 4
+    for (int q = blk * 256 + (int)threadIdx.x; q < nlt; q += kGlightBlocks * 256)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) acc[k] += ls.part_light[((long long)v.part_off + q) * 3 + k];
+    const int e0 = ls.light_renders_off[l], n = ls.light_renders_off[l + 1] - e0;
+    const int cut = n > 0 ? (kGlightBlocks + n - 1) / n : 1;
+    for (int u = blk; u < n * cut; u += kGlightBlocks) {
+        const int e = ls.light_renders[e0 + u / cut], r = e >> 5, slot = e & 31;
+        const RenderConst &R = ls.renders[r];
+        const ViewConst &cv = views[R.camera_view];
+        const int nct = cv.tiles_x * cv.tiles_y;
+        const float *part = ls.part_render + R.part_off + (long long)slot * nct * 3;
+#pragma unroll 4
+        for (int q = u % cut * 256 + (int)threadIdx.x; q < nct; q += cut * 256)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) acc[k] += part[3 * q + k];
+    }
+    block_sum_store<4>(acc, ls.gl_part + ((long long)l * kGlightBlocks + blk) * 3);
+}
+
 // Rows of the listed triangles.  Large ones: a workgroup per item sums its
 // pairs' rows; a triangle of one item gets its row stored, the items of a
 // larger one are added to its row, which the backward's setup cleared.  Those
@@ -1214,7 +1244,12 @@ __global__ __launch_bounds__(256) void large_reduce_kernel(const ViewConst *__re
                                                            const unsigned *__restrict__ pair_off, unsigned capacity,
                                                            const unsigned char *__restrict__ pair_flag,
                                                            const float *__restrict__ pair_sums,
-                                                           float *__restrict__ gtri) {
+                                                           float *__restrict__ gtri, LightSum ls) {
+    if ((int)blockIdx.x >= kLargeBlocks) {
+        const int q = (int)blockIdx.x - kLargeBlocks;
+        light_partials(q / kGlightBlocks, q % kGlightBlocks, views, ls);
+        return;
+    }
     __shared__ float part[4][kNV];
     for_large_items(large, counters, (int)blockIdx.x, kLargeBlocks,
                     [&](unsigned t) { return pair_off[t + 1] - pair_off[t]; },
@@ -1371,22 +1406,47 @@ __device__ __forceinline__ void gather_corners(const int (&e)[N], int soff, unsi
     }
 }
 
+// The gradient of light l by a wave: the vertex workgroups' shares and
+// light_partials' sums in a fixed order.  AGENT: the shares come from the same
+// launch.
+template <bool AGENT>
+__device__ __forceinline__ void finish_light(const ViewConst &v, int l, const float *part_gm, const LightSum &ls) {
+    const int lane = (int)(threadIdx.x & 63), nblk = (v.nverts + 63) / 64;
+    float acc[3] = {0.f, 0.f, 0.f};
+    const float *part = part_gm + (long long)v.part_gm_off * 3;
+    static_assert(kGlightBlocks <= 64, "a lane each");
+    if (lane < kGlightBlocks)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) acc[k] = ls.gl_part[((long long)l * kGlightBlocks + lane) * 3 + k];
+#pragma unroll 4
+    for (int q = lane; q < nblk; q += 64)
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            acc[k] += AGENT ? __hip_atomic_load(part + 3 * q + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                            : part[3 * q + k];
+    const float t = wave_sum_multi(acc);
+    if ((lane & 15) == 0 && lane < 48) ls.gparams[3 * l + (lane >> 4)] = t;
+}
+
 // Per vertex: sum its triangle corners' terms over every view of its scene,
 // add the silhouette clip terms, map clip terms through M^T; per light view
-// the wave's share of dL/dM is written for glight_reduce.  A workgroup takes
+// the wave's share of dL/dM is written to part_gm.  With LIGHTS the scene's
+// last workgroup to finish (done, cleared by the backward's setup) adds those of
+// each light to light_partials' sums, else light_sum_kernel does.  A workgroup takes
 // 64 vertices, a vertex a lane, and its waves share the views.  Bound by the
 // latency of the chain corner -> pair range -> flags -> rows.  With the rows of
 // up to four pairs read here, no pass writes a row per triangle: with the
 // reduction before it, 64 scenes 150 -> 76 us; 24 views of a 50k-vertex sphere
 // whose poles have 316 corners 744 -> 91.
+template <bool LIGHTS>
 __global__ __launch_bounds__(256) void vertex_gather_kernel(
     const ViewConst *__restrict__ views, int L, const int *__restrict__ scene_vert_off,
     const int *__restrict__ scene_views_off, const int *__restrict__ scene_views, const int *__restrict__ vc_off,
     const int *__restrict__ vc_list, const float *__restrict__ verts, const unsigned *__restrict__ pair_off,
     unsigned capacity, const unsigned char *__restrict__ pair_flag, const float *__restrict__ pair_sums,
     const float *__restrict__ gtri, const float *__restrict__ zero_rec, const float4 *__restrict__ gclip,
-    float *__restrict__ gverts, float *__restrict__ part_gm, const float *__restrict__ jac, int vx,
-    const int *__restrict__ scene_face_off, float *__restrict__ galbedo, int C) {
+    float *__restrict__ gverts, float *part_gm, const float *__restrict__ jac, int vx,
+    const int *__restrict__ scene_face_off, float *__restrict__ galbedo, int C, LightSum ls) {
     const int b = blockIdx.y;
     if ((int)blockIdx.x >= vx) {                               // the albedo gather's workgroups
         albedo_gather_block(views, L, b, (int)blockIdx.x - vx, scene_face_off, scene_views_off, scene_views, pair_off,
@@ -1394,7 +1454,8 @@ __global__ __launch_bounds__(256) void vertex_gather_kernel(
         return;
     }
     const int nv = scene_vert_off[b + 1] - scene_vert_off[b];
-    if ((int)blockIdx.x * 64 >= nv) return;                  // whole workgroup
+    const int nblk = max((nv + 63) / 64, 1);                 // a scene without vertices still finishes its lights
+    if ((int)blockIdx.x >= nblk) return;                     // whole workgroup
     __shared__ float sum[3][3][64];
     const int lane = (int)(threadIdx.x & 63), wave = (int)(threadIdx.x >> 6), nwaves = (int)(blockDim.x >> 6);
     const int vl = blockIdx.x * 64 + lane;
@@ -1410,7 +1471,8 @@ __global__ __launch_bounds__(256) void vertex_gather_kernel(
     for (int k = 0; k < kCorners; ++k) held[k] = c0 + k < c1 ? vc_list[c0 + k] : -1;
     const int own = min(c1, c0 + kOwnCorners);
     const unsigned long long many = __ballot(c1 > own);
-    for (int s = scene_views_off[b] + wave; s < scene_views_off[b + 1]; s += nwaves) {
+    const int views_end = scene_views_off[b + (nv > 0 ? 1 : 0)];
+    for (int s = scene_views_off[b] + wave; s < views_end; s += nwaves) {
         const int vi = scene_views[s];
         const ViewConst &v = views[vi];
         const int soff = v.setup_off;
@@ -1459,81 +1521,47 @@ __global__ __launch_bounds__(256) void vertex_gather_kernel(
                 gp[j] = a;
             }
             const float t = wave_sum_multi(gp);
-            if ((lane & 15) == 0 && lane < 48) part_gm[((long long)v.part_gm_off + blockIdx.x) * 3 + (lane >> 4)] = t;
+            float *share = part_gm + ((long long)v.part_gm_off + blockIdx.x) * 3 + (lane >> 4);
+            if ((lane & 15) == 0 && lane < 48) {
+                if constexpr (LIGHTS) __hip_atomic_store(share, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                else *share = t;
+            }
         }
     }
-    if (nwaves > 1) {
-        if (wave > 0)
+    if (wave > 0)
 #pragma unroll
-            for (int k = 0; k < 3; ++k) sum[wave - 1][k][lane] = gv[k];
-        __syncthreads();
-        if (wave > 0) return;
+        for (int k = 0; k < 3; ++k) sum[wave - 1][k][lane] = gv[k];
+    __shared__ unsigned before;
+    if constexpr (LIGHTS) {
+        // The shares go through to where every XCD sees them; waiting for them is
+        // all the release there is to do (a fence would write back the whole L2).
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    if (LIGHTS || nwaves > 1) __syncthreads();
+    if constexpr (LIGHTS)
+        if (threadIdx.x == 0)
+            before = __hip_atomic_fetch_add(ls.done + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (wave == 0) {
         for (int w = 1; w < nwaves; ++w)
 #pragma unroll
             for (int k = 0; k < 3; ++k) gv[k] += sum[w - 1][k][lane];
+        if (in)
+            for (int k = 0; k < 3; ++k) gverts[3 * (size_t)gv_idx + k] = gv[k];
     }
-    if (in)
-        for (int k = 0; k < 3; ++k) gverts[3 * (size_t)gv_idx + k] = gv[k];
+    if constexpr (LIGHTS) {
+        __syncthreads();
+        if (before != (unsigned)nblk - 1u) return;
+        for (int s = scene_views_off[b] + wave; s < scene_views_off[b + 1]; s += nwaves) {
+            const int vi = scene_views[s];
+            if (vi < L) finish_light<true>(views[vi], vi, part_gm, ls);
+        }
+    }
 }
 
-// glight[l] = sum of every partial written for light l (vertex blocks, light
-// tiles, and the tiles of each render that uses it): kGlightBlocks workgroups
-// per light each sum a strided share, so that a few lights with many partials
-// still fill the GPU, and the last of them to finish (done[l], cleared by the
-// backward's setup) adds their results in a fixed order.
-__global__ __launch_bounds__(256) void glight_kernel(const ViewConst *__restrict__ views,
-                                                     const RenderConst *__restrict__ renders,
-                                                     const int *__restrict__ light_renders_off,
-                                                     const int *__restrict__ light_renders,
-                                                     const float *__restrict__ part_gm,
-                                                     const float *__restrict__ part_light,
-                                                     const float *__restrict__ part_render, float *gl_part,
-                                                     unsigned *done, float *__restrict__ gparams) {
-    const int l = blockIdx.y;
-    const ViewConst &v = views[l];
-    const int first = blockIdx.x * blockDim.x + threadIdx.x, step = kGlightBlocks * blockDim.x;
-    float acc[3] = {0.f, 0.f, 0.f};
-    const int nvb = (v.nverts + 63) / 64;
-    for (int q = first; q < nvb; q += step)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) acc[k] += part_gm[((long long)v.part_gm_off + q) * 3 + k];
-    const int nlt = v.tiles_x * v.tiles_y;
-    for (int q = first; q < nlt; q += step)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) acc[k] += part_light[((long long)v.part_off + q) * 3 + k];
-    for (int e = light_renders_off[l]; e < light_renders_off[l + 1]; ++e) {
-        const int r = light_renders[e] >> 5, slot = light_renders[e] & 31;
-        const RenderConst &R = renders[r];
-        const ViewConst &cv = views[R.camera_view];
-        const int nct = cv.tiles_x * cv.tiles_y;
-        for (int q = first; q < nct; q += step)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) acc[k] += part_render[R.part_off + ((long long)slot * nct + q) * 3 + k];
-    }
-    __shared__ float total[3];
-    block_sum_store<4>(acc, total);
-    // the three threads that publish the workgroup's sums are in one wave,
-    // whose first lane counts it as finished after them
-    float *mine = gl_part + ((long long)l * kGlightBlocks + blockIdx.x) * 3;
-    if (threadIdx.x >= 64) return;
-    wave_sync();
-    if (threadIdx.x < 3)
-        __hip_atomic_store(mine + threadIdx.x, total[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // The stores go through to where every XCD sees them; waiting for them is
-    // all the release there is to do (a fence would write back the whole L2:
-    // 36 us for 64 lights, 5 with the wait).
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    unsigned before = 0;
-    if (threadIdx.x == 0)
-        before = __hip_atomic_fetch_add(done + l, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (__builtin_amdgcn_readfirstlane((int)before) != kGlightBlocks - 1) return;
-    if (threadIdx.x < 3) {
-        float a = 0.f;
-        for (int b = 0; b < kGlightBlocks; ++b)
-            a += __hip_atomic_load(gl_part + ((long long)l * kGlightBlocks + b) * 3 + threadIdx.x, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-        gparams[3 * l + threadIdx.x] = a;
-    }
+// The lights' gradients where the gather does not finish them, a wave each.
+__global__ __launch_bounds__(64) void light_sum_kernel(const ViewConst *__restrict__ views, const float *part_gm,
+                                                       LightSum ls) {
+    finish_light<false>(views[blockIdx.x], (int)blockIdx.x, part_gm, ls);
 }
 
 // ----------------------------------------------------------------------------- pose
@@ -1712,28 +1740,30 @@ hipError_t launch_vertex_gradients(const ViewConst *views, int L, int B, int max
                                    const int *vc_list, const unsigned *pair_off, const unsigned char *pair_flag,
                                    const float *pair_sums, float *gtri, const float *zero_rec, const float *verts,
                                    const float4 *gclip, float *gverts, float *part_gm, float *galbedo, int C,
-                                   const float *jac, hipStream_t s) {
-    if (ntri > 0)
-        hipLaunchKernelGGL(large_reduce_kernel, dim3(kLargeBlocks), dim3(256), 0, s, views, L, setup, large, counters,
-                           pair_off, capacity, pair_flag, pair_sums, gtri);
+                                   const float *jac, const LightSum &ls, hipStream_t s) {
+    if (ntri > 0 || L > 0)
+        hipLaunchKernelGGL(large_reduce_kernel, dim3(kLargeBlocks + kGlightBlocks * L), dim3(256), 0, s, views, L, setup,
+                           large, counters, pair_off, capacity, pair_flag, pair_sums, gtri, ls);
     // one launch: the vertex gather's workgroups, then the albedo gather's;
     // a wave per view of the scene, up to four
     const int nt = 64 * std::min(std::max(max_views, 1), 4);
-    const int vx = (max_verts + 63) / 64, fx = (galbedo && max_faces > 0) ? (max_faces + nt - 1) / nt : 0;
-    if (B > 0 && vx + fx > 0)
-        hipLaunchKernelGGL(vertex_gather_kernel, dim3(vx + fx, B), dim3(nt), 0, s, views, L, scene_vert_off,
-                           scene_views_off, scene_views, vc_off, vc_list, verts, pair_off, capacity, pair_flag,
-                           pair_sums, gtri, zero_rec, gclip, gverts, part_gm, jac, vx, scene_face_off, galbedo, C);
-    return hipGetLastError();
-}
-
-hipError_t launch_glight_reduce(const ViewConst *views, int L, const RenderConst *renders,
-                                const int *light_renders_off, const int *light_renders, const float *part_gm,
-                                const float *part_light, const float *part_render, float *gl_part, unsigned *done,
-                                float *gparams, hipStream_t s) {
-    if (L == 0) return hipSuccess;
-    hipLaunchKernelGGL(glight_kernel, dim3(kGlightBlocks, L), dim3(256), 0, s, views, renders, light_renders_off,
-                       light_renders, part_gm, part_light, part_render, gl_part, done, gparams);
+    const int vx = std::max((max_verts + 63) / 64, 1), fx = (galbedo && max_faces > 0) ? (max_faces + nt - 1) / nt : 0;
+    if (B == 0) return hipGetLastError();
+#define DSM_GATHER(LIGHTS)                                                                                          \
+    hipLaunchKernelGGL(vertex_gather_kernel<LIGHTS>, dim3(vx + fx, B), dim3(nt), 0, s, views, L, scene_vert_off,   \
+                       scene_views_off, scene_views, vc_off, vc_list, verts, pair_off, capacity, pair_flag,        \
+                       pair_sums, gtri, zero_rec, gclip, gverts, part_gm, jac, vx, scene_face_off, galbedo, C, ls)
+    // Up to a workgroup or so per CU, finishing the lights in the gather costs its
+    // last workgroup 2 us and saves a launch of 4 us with its gap; with more, the wait for
+    // the shares keeps every workgroup's place (64 scenes: 51 -> 69 us against a
+    // launch of 4).
+    constexpr long long kFinishBlocks = 256;
+    if (L > 0 && (long long)vx * B <= kFinishBlocks) DSM_GATHER(true);
+    else {
+        DSM_GATHER(false);
+        if (L > 0) hipLaunchKernelGGL(light_sum_kernel, dim3(L), dim3(64), 0, s, views, part_gm, ls);
+    }
+#undef DSM_GATHER
     return hipGetLastError();
 }
 
