@@ -501,7 +501,13 @@ __device__ __forceinline__ void overflow_rows(const ViewConst &v, const int (&ke
 // triangle in the wave); a group of 16 or more lanes (a large ground
 // polygon) is summed with one multi-value wave reduction, the others with
 // LDS atomics into the row of their leader (the group's lowest lane), which
-// then stores the row and flags the pair.  Pair flags start at zero (the
+// then stores the row and flags the pair.  The atomics of a group meet on one
+// address each, and where the groups are several samples wide that is what
+// bounds the sums: horizontal neighbours of one triangle are added first
+// (three 2048^2 maps 205 -> 174 us, the lookup's adjoint at 1080p 120 -> 110),
+// unless few lanes have one (meshes with a sample or two a triangle and tile:
+// 187 -> 191 with it).  The test for zero per value is worth its instructions
+// (64 scenes 388 us, 465 without it): unlit samples are zero in most values.  Pair flags start at zero (the
 // backward clears them), so pairs without a pixel keep flag 0.  Pixels of
 // triangles that overflowed the bins stay unmatched for overflow_rows.
 // Uniform call (all 64 lanes).
@@ -514,7 +520,13 @@ __device__ __forceinline__ void wave_pair_sums(const ViewConst &v, int tx, int t
     const int lane = (int)(threadIdx.x & 63);
     unsigned slot = 0;
     bool mine = false;
-    if (act && key >= 0) {
+    // a pixel turned away from its lights has no terms: no sum, and no row for
+    // triangles that hold only such pixels (the gather of 64 scenes 51 -> 47 us);
+    // light texels that get here have some
+    bool some = N <= 18;
+#pragma unroll
+    for (int i = 0; i < N; ++i) some = some || val[i] != 0.f;
+    if (act && some && key >= 0) {
         const int si = v.setup_off + key;
         const unsigned a = pair_off[si], b = pair_off[si + 1];
         if (!(b > capacity && b > a)) {                  // else: the overflow path
@@ -524,7 +536,7 @@ __device__ __forceinline__ void wave_pair_sums(const ViewConst &v, int tx, int t
             mine = true;
         }
     }
-    matched = mine;
+    matched = mine || !some;
     // leader of every lane's group; groups of 16 or more lanes go to the wave reduction
     int leader = lane;
     unsigned long long pending = __ballot(mine), big = 0ull;
@@ -552,15 +564,27 @@ __device__ __forceinline__ void wave_pair_sums(const ViewConst &v, int tx, int t
         mine = mine && !in;
     }
     const bool lead = mine && leader == lane;
+    float sum[N];
+    bool own = mine;
+    const int beside = dpp_movi<0xB1>(mine ? leader : -1);          // of lane ^ 1, read with every lane active
+    const bool same = mine && beside == leader;
+    if (__popcll(__ballot(same)) >= 16) {                // uniform
+#pragma unroll
+        for (int i = 0; i < N; ++i) sum[i] = val[i] + dpp_mov<0xB1>(same ? val[i] : 0.f);
+        own = own && !(same && (lane & 1));
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) sum[i] = val[i];
+    }
     if (lead) {
 #pragma unroll
-        for (int i = 0; i < N; ++i) part[lane * N + i] = val[i];
+        for (int i = 0; i < N; ++i) part[lane * N + i] = sum[i];
     }
     __syncthreads();
-    if (mine && !lead) {
+    if (own && !lead) {
 #pragma unroll
         for (int i = 0; i < N; ++i)
-            if (val[i] != 0.f) atomicAdd(part + leader * N + i, val[i]);
+            if (sum[i] != 0.f) atomicAdd(part + leader * N + i, sum[i]);
     }
     __syncthreads();
     if (lead) {
@@ -637,6 +661,18 @@ __device__ __forceinline__ void light_terms(PixelGeom &g, const ViewConst &l, co
     float vis = 1.f, visr = 1.f, zz = 0.f, zw = 0.f, floor_v = 0.f, m1 = 0.f, m2 = 0.f, var = 0.f, dd = 0.f, fx = 0.f,
           fy = 0.f;
     int ixs = 0, iys = 0;
+    // the direction to the light, with one distance for the receiver depth, the
+    // shading and their adjoints (the correctly rounded root is 16 instructions)
+    const bool directional = l.kind == kDirectional;
+    float ox, oy, oz, olen = 1.f, rol = 1.f;
+    if (directional) {
+        ox = -l.dir[0]; oy = -l.dir[1]; oz = -l.dir[2];
+    } else {
+        ox = l.pos[0] - x; oy = l.pos[1] - y; oz = l.pos[2] - z;
+        olen = sqrtf((ox * ox + oy * oy) + oz * oz);
+        rol = grcp(olen);
+        ox *= rol; oy *= rol; oz *= rol;
+    }
     const int S = l.W;
     // filtered maps are stored with side Sp; cube faces keep P texels of
     // their neighbours around the face, so taps may cross the seam
@@ -659,28 +695,14 @@ __device__ __forceinline__ void light_terms(PixelGeom &g, const ViewConst &l, co
         t00 = mm[y0 * Sp + x0]; t01 = mm[y0 * Sp + x1]; t10 = mm[y1 * Sp + x0]; t11 = mm[y1 * Sp + x1];
         m1 = ((w00 * t00.x + w01 * t01.x) + w10 * t10.x) + w11 * t11.x;
         m2 = ((w00 * t00.y + w01 * t01.y) + w10 * t10.y) + w11 * t11.y;
-        float depth;
-        if (l.kind == kDirectional)
-            depth = ((x - l.pos[0]) * l.dir[0] + (y - l.pos[1]) * l.dir[1]) + (z - l.pos[2]) * l.dir[2];
-        else {
-            const float ddx = x - l.pos[0], ddy = y - l.pos[1], ddz = z - l.pos[2];
-            depth = sqrtf((ddx * ddx + ddy * ddy) + ddz * ddz);
-        }
+        const float depth =
+            directional ? ((x - l.pos[0]) * l.dir[0] + (y - l.pos[1]) * l.dir[1]) + (z - l.pos[2]) * l.dir[2] : olen;
         zz = depth * grcp(l.zfar) - l.zc;
         warp_receiver(l, zz, zw, floor_v);
         var = fmaxf(m2 - m1 * m1, floor_v);
         dd = zw - m1;
         visr = (zw <= m1) ? 1.f : var * grcp(var + dd * dd);
         vis = bleed_reduce(l, visr);
-    }
-    float ox, oy, oz, olen = 1.f;
-    if (l.kind == kDirectional) {
-        ox = -l.dir[0]; oy = -l.dir[1]; oz = -l.dir[2];
-    } else {
-        ox = l.pos[0] - x; oy = l.pos[1] - y; oz = l.pos[2] - z;
-        olen = sqrtf((ox * ox + oy * oy) + oz * oz);
-        const float rol = grcp(olen);
-        ox *= rol; oy *= rol; oz *= rol;
     }
     const float ndo = (nx * ox + ny * oy) + nz * oz;
     const float lam = fmaxf(ndo, 0.f);
@@ -705,8 +727,7 @@ __device__ __forceinline__ void light_terms(PixelGeom &g, const ViewConst &l, co
         gdir[0] -= gox; gdir[1] -= goy; gdir[2] -= goz;
     } else {
         const float od = fmaf(oz, goz, fmaf(oy, goy, ox * gox));
-        const float rl = grcp(olen);
-        const float gpx = fmaf(-ox, od, gox) * rl, gpy = fmaf(-oy, od, goy) * rl, gpz = fmaf(-oz, od, goz) * rl;
+        const float gpx = fmaf(-ox, od, gox) * rol, gpy = fmaf(-oy, od, goy) * rol, gpz = fmaf(-oz, od, goz) * rol;
         gpos[0] += gpx; gpos[1] += gpy; gpos[2] += gpz;
         g.gx[0] -= gpx; g.gx[1] -= gpy; g.gx[2] -= gpz;
     }
@@ -748,14 +769,10 @@ __device__ __forceinline__ void light_terms(PixelGeom &g, const ViewConst &l, co
             gdir[1] = fmaf(gdepth, y - l.pos[1], gdir[1]);
             gdir[2] = fmaf(gdepth, z - l.pos[2], gdir[2]);
         } else {
-            const float ddx = x - l.pos[0], ddy = y - l.pos[1], ddz = z - l.pos[2];
-            const float dl = sqrtf((ddx * ddx + ddy * ddy) + ddz * ddz);
-            const float rd = grcp(dl);
-            const float ux_ = ddx * rd, uy_ = ddy * rd, uz_ = ddz * rd;
-            g.gx[0] = fmaf(gdepth, ux_, g.gx[0]); g.gx[1] = fmaf(gdepth, uy_, g.gx[1]);
-            g.gx[2] = fmaf(gdepth, uz_, g.gx[2]);
-            gpos[0] = fmaf(-gdepth, ux_, gpos[0]); gpos[1] = fmaf(-gdepth, uy_, gpos[1]);
-            gpos[2] = fmaf(-gdepth, uz_, gpos[2]);
+            g.gx[0] = fmaf(-gdepth, ox, g.gx[0]); g.gx[1] = fmaf(-gdepth, oy, g.gx[1]);
+            g.gx[2] = fmaf(-gdepth, oz, g.gx[2]);
+            gpos[0] = fmaf(gdepth, ox, gpos[0]); gpos[1] = fmaf(gdepth, oy, gpos[1]);
+            gpos[2] = fmaf(gdepth, oz, gpos[2]);
         }
         hit = MapHit{ixs, iys, fx, fy, gm1, gm2};        // bilinear scatter to the moment maps
         // the map position moves with x and with the light camera
@@ -767,10 +784,9 @@ __device__ __forceinline__ void light_terms(PixelGeom &g, const ViewConst &l, co
         const float hs = 0.5f * S;
         const float gsx = fmaf(gm2, dm2fx, gm1 * dm1fx) * hs;
         const float gsy = fmaf(gm2, dm2fy, gm1 * dm1fy) * hs;
-        const float rw = grcp(cw);
-        gcx = gsx * rw;
-        gcy = -gsy * rw;
-        gcw = fmaf(-gsx, cx, gsy * cy) * (rw * rw);
+        gcx = gsx * rcw;
+        gcy = -gsy * rcw;
+        gcw = fmaf(-gsx, cx, gsy * cy) * (rcw * rcw);
 #pragma unroll
         for (int k = 0; k < 3; ++k) g.gx[k] = fmaf(M[12 + k], gcw, fmaf(M[4 + k], gcy, fmaf(M[k], gcx, g.gx[k])));
     }
@@ -789,7 +805,10 @@ __device__ __forceinline__ void light_terms(PixelGeom &g, const ViewConst &l, co
         }
         float a = fmaf(gcw, u[2], fmaf(gcy, u[1], fmaf(gcx, u[0], al[j])));
 #pragma unroll
-        for (int i = 0; i < 3; ++i) a = fmaf(gdir[i], J[3 * (19 + i) + j], fmaf(gpos[i], J[3 * (16 + i) + j], a));
+        for (int i = 0; i < 3; ++i) a = fmaf(gpos[i], J[3 * (16 + i) + j], a);
+        if (directional)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) a = fmaf(gdir[i], J[3 * (19 + i) + j], a);
         al[j] = a;
     }
 }
@@ -900,9 +919,9 @@ __device__ __forceinline__ void map_window_scatter(const MapHit (&hit)[PPT], int
 // are (arrays over 4 or 16 lights spilled, and 16 scattered with global
 // atomics), and a camera's renders share the point, the normal and their
 // adjoint.  Vector issue bounds it, then the latency of key -> record -> taps.
-// 64 renders with a light each 494 -> 399 us (5 waves per SIMD; 418 at 4), 16
-// cameras with 8 renders each 716 -> 483, a 1080p RGB render with 3 lights
-// 205 -> 117 (4 waves; 120 at 5).
+// 64 renders with a light each 494 -> 388 us (5 waves per SIMD; 4: 5% more), 16
+// cameras with 8 renders each 716 -> 477, a 1080p RGB render with 3 lights
+// 205 -> 110 (4 waves; 5: 3% more).
 template <int T, int C>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 32 ? 2 : C == 1 ? 5 : 4))) void lookup_backward_kernel(
     const ViewConst *__restrict__ views, int L, const RenderConst *__restrict__ renders,
