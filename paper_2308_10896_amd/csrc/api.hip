@@ -518,6 +518,8 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
     // scratch layout
     o = 0;
     p->sc_tile_cnt = o; o = align_up(o + 4 * ((size_t)tiles + 1));
+    p->sc_group_total = o;
+    o = align_up(o + 4 * kGroupStride * (((size_t)tri / kTriRun + (size_t)p->nviews) / kTriGroup + 1));
     p->sc_zero_fwd_end = o;
     p->sc_pair_local = o; o = align_up(o + 4 * ((size_t)tri + 1));
     p->sc_block_total = o; o = align_up(o + 4 * ((size_t)tri / kTriRun + (size_t)p->nviews + 2));
@@ -702,6 +704,7 @@ dsm_status enqueue_forward(dsm_plan *p, const float *verts, const float *lparams
     unsigned *pair_slot = at<unsigned>(scratch, p->sc_pair_slot);
     unsigned *pair_local = at<unsigned>(scratch, p->sc_pair_local);
     unsigned *block_total = at<unsigned>(scratch, p->sc_block_total);
+    unsigned *group_total = at<unsigned>(scratch, p->sc_group_total);
     unsigned *pair_off = at<unsigned>(saved, p->sv_pair_off);
     const LargeLists large{at<unsigned>(saved, p->sv_large), at<uint2>(saved, p->sv_items), p->item_cap,
                            at<unsigned>(saved, p->sv_medium)};
@@ -720,15 +723,16 @@ dsm_status enqueue_forward(dsm_plan *p, const float *verts, const float *lparams
     float *img0 = at<float>(saved, p->sv_img0);
 
     DSM_MARK(DSM_STAGE_SETUP);
-    // with the light frames, the counters (saved) and the tile counts (scratch) are cleared
+    // with the light frames, the counters (saved) and the tile counts and group totals (scratch) are cleared
     DSM_TRY(launch_light_frames(p->views_d, p->light_cams_d, lparams, p->L, nullptr, at<float>(saved, p->sv_zc), saved,
                                 p->sv_zero_end, scratch, p->sc_zero_fwd_end, ClearRows{}, s));
     signed char *facing8 = at<signed char>(scratch, p->sc_facing);
     DSM_TRY(launch_setup(p->views_d, p->tri_blocks_d, p->tri_blocks, p->faces_d, verts, albedo, p->C,
-                         tv, setup, facing8, pair_local, block_total, large, p->tile, cnt, s));
+                         tv, setup, facing8, pair_local, block_total, group_total, large, p->tile, cnt, s));
     DSM_MARK(DSM_STAGE_BIN);
     DSM_TRY(launch_binning(p->views_d, p->tri_blocks_d, p->tri_blocks, setup, p->adj_d, facing8, silm,
-                           pair_local, block_total, pair_off, p->ntri, p->capacity, p->tile, tile_cnt, tile_start,
+                           pair_local, block_total, group_total, pair_off, p->ntri, p->capacity, p->tile, tile_cnt,
+                           tile_start,
                            pair_slot, p->ntiles, bins, bin_pair, overflow, large, cnt, keys, p->key_count, s));
     DSM_MARK(DSM_STAGE_RASTER);
     DSM_TRY(launch_raster(p->views_d, p->tile_view_d, p->ntiles, p->tile, setup, tile_start, bins, overflow, cnt, keys,

@@ -164,7 +164,8 @@ __global__ __launch_bounds__(kTriThreads) void setup_kernel(
     const ViewConst *__restrict__ views, const TriBlock *__restrict__ blocks, const int *__restrict__ faces,
     const float *__restrict__ verts, const float *__restrict__ albedo, int C, TriVerts *__restrict__ tv,
     TriSetup *__restrict__ setup, signed char *__restrict__ facing8, unsigned *__restrict__ pair_local,
-    unsigned *__restrict__ block_total, LargeLists large, int shift, DevCounters *counters) {
+    unsigned *__restrict__ block_total, unsigned *__restrict__ group_total, LargeLists large, int shift,
+    DevCounters *counters) {
     const TriBlock blk = blocks[blockIdx.x];
     const ViewConst &v = views[blk.view];
     const float hw = 0.5f * (float)v.W, hh = 0.5f * (float)v.H;
@@ -250,7 +251,10 @@ __global__ __launch_bounds__(kTriThreads) void setup_kernel(
     unsigned off[1], total;
     tri_block_scan(npairs, off, &total);
     if (t < v.nfaces) pair_local[v.setup_off + t] = off[0];
-    if (threadIdx.x == 0) block_total[blockIdx.x] = total;
+    if (threadIdx.x == 0) {
+        block_total[blockIdx.x] = total;
+        if (total) atomicAdd(&group_total[blockIdx.x / kTriGroup * kGroupStride], total);
+    }
     if (__ballot(nculled + nbad != 0)) {
         if (nculled) atomicAdd(&counters->culled, (unsigned long long)nculled);
         if (nbad) atomicAdd(&counters->bad_indices, (unsigned long long)nbad);
@@ -441,7 +445,7 @@ __device__ __forceinline__ unsigned char silhouette_mask(const int *__restrict__
 }
 
 // Totals of the triangle passes' workgroups scanned in place by one workgroup,
-// for plans with more than kMaxTriBlocks of them.
+// for plans with more than kMaxTriGroups groups of them.
 __global__ __launch_bounds__(kTriThreads) void block_prefix_kernel(unsigned *__restrict__ total, int n) {
     __shared__ unsigned carry;
     const int tid = (int)threadIdx.x;
@@ -465,8 +469,10 @@ __global__ __launch_bounds__(kTriThreads) void block_prefix_kernel(unsigned *__r
 }
 
 // Count pass.  A triangle's first pair is its offset in its workgroup plus the
-// totals of the workgroups before, which every workgroup sums itself (or finds
-// scanned, past kMaxTriBlocks of them).  The silhouette masks ride along: they need every
+// totals of the workgroups before, which every workgroup sums itself: the
+// setup added them up by groups of kTriGroup, so that is a load or two a lane
+// (a scan in a launch of its own before: 16 us for 24 views of 99k triangles).
+// Past kMaxTriGroups groups it finds the totals scanned.  The silhouette masks ride along: they need every
 // facing byte, as this pass needs every total.
 //
 // Bound by the latency of the tile counters' atomics, so a workgroup counts
@@ -477,7 +483,8 @@ __global__ __launch_bounds__(kTriThreads) void block_prefix_kernel(unsigned *__r
 // out the slots from the table.  Wider boxes (a strip across a large view,
 // triangles in no order) aggregate a wave's equal tiles with ballots
 // (wave_slot), which took the place of the table before: 64 scenes at 512^2
-// 57 -> 32 us, three 2048^2 maps and a 1080p view 43 -> 30, a 10k-triangle
+// 57 -> 32 us (36 with the group totals, but without a scan of 11), three
+// 2048^2 maps and a 1080p view 43 -> 30, a 10k-triangle
 // sphere at 512^2 20 -> 7 (no aggregation at all: 167, 159 and 9).  4096
 // counters are 16 KB, so that eight workgroups share a CU, and all tiles of a
 // 512^2 view.
@@ -486,30 +493,32 @@ __global__ __launch_bounds__(kTriThreads) void bin_count_kernel(
     const ViewConst *__restrict__ views, const TriBlock *__restrict__ blocks, int nblocks,
     const TriSetup *__restrict__ setup, const int *__restrict__ adj, const signed char *__restrict__ facing8,
     unsigned char *__restrict__ silm, const unsigned *__restrict__ pair_local,
-    const unsigned *__restrict__ block_total, bool scanned, unsigned *__restrict__ pair_off, unsigned capacity, int shift,
+    const unsigned *__restrict__ block_total, const unsigned *__restrict__ group_total, bool scanned,
+    unsigned *__restrict__ pair_off, unsigned capacity, int shift,
     int ntri,
     unsigned *__restrict__ tile_count, unsigned *__restrict__ pair_slot, LargeLists large,
     unsigned *__restrict__ overflow_list, DevCounters *counters) {
-    // the tile table, a wave's triangles, or the prefix of the totals
+    // the tile table, a wave's triangles, or the prefix of the groups' totals
     __shared__ union {
         unsigned table[kTileTable];
         BinWave wave[kTriThreads / 64];
-        unsigned prefix[kMaxTriBlocks];
+        unsigned prefix[kMaxTriGroups];
     } sh;
     const int tid = (int)threadIdx.x;
     if ((int)blockIdx.x >= nblocks) {
         if (counters->large_len == 0) return;
-        // the workgroup's own prefix of all totals, one entry per TriBlock
+        // the workgroup's own prefix of the groups' totals
         unsigned *prefix = sh.prefix;
         __shared__ unsigned carry;
         if (tid == 0) carry = 0;
-        for (int c = 0; c < nblocks && !scanned; c += kTriThreads) {
-            const unsigned v[1] = {c + tid < nblocks ? block_total[c + tid] : 0u};
+        const int ngroups = (nblocks + kTriGroup - 1) / kTriGroup;
+        for (int c = 0; c < ngroups && !scanned; c += kTriThreads) {
+            const unsigned v[1] = {c + tid < ngroups ? group_total[(c + tid) * kGroupStride] : 0u};
             unsigned o[1], total;
             tri_block_scan(v, o, &total);
             const unsigned base = carry;
             __syncthreads();
-            if (c + tid < nblocks) prefix[c + tid] = base + o[0];
+            if (c + tid < ngroups) prefix[c + tid] = base + o[0];
             if (tid == 0) carry = base + total;
             __syncthreads();
         }
@@ -517,7 +526,13 @@ __global__ __launch_bounds__(kTriThreads) void bin_count_kernel(
                          nullptr, nullptr, large, counters, [&](unsigned t) {
                              const ViewConst &v = views[setup[t].pad2[0]];
                              const int k = v.tri_block + (int)(t - v.setup_off) / kTriRun;
-                             return pair_local[t] + (scanned ? block_total[k] : prefix[k]);
+                             if (scanned) return pair_local[t] + block_total[k];
+                             // in its group by each wave alone
+                             unsigned before = 0;
+                             for (int q = (k & ~(kTriGroup - 1)) + (tid & 63); q < k; q += 64) before += block_total[q];
+#pragma unroll
+                             for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+                             return pair_local[t] + prefix[k / kTriGroup] + before;
                          });
         return;
     }
@@ -535,8 +550,12 @@ __global__ __launch_bounds__(kTriThreads) void bin_count_kernel(
     __shared__ unsigned part[kTriThreads / 64];
     __shared__ int boxes[kTriThreads / 64][4];        // the waves' tiles: first x, first y, last x, last y
     unsigned sum = 0;
-    if (!scanned)
-        for (int k = tid; k < (int)blockIdx.x; k += kTriThreads) sum += block_total[k];
+    if (!scanned) {
+        static_assert(kTriGroup <= kTriThreads, "a lane each");
+        const int g = (int)blockIdx.x / kTriGroup;
+        for (int k = tid; k < g; k += kTriThreads) sum += group_total[k * kGroupStride];
+        if (g * kTriGroup + tid < (int)blockIdx.x) sum += block_total[g * kTriGroup + tid];
+    }
     const bool small = b.n > 0 && b.n <= kBigBin;
     int lo_x = small ? b.tx0 : 65536, lo_y = small ? b.ty0 : 65536;
     int hi_x = small ? b.tx0 + b.ntx - 1 : -1, hi_y = small ? b.ty0 + nty - 1 : -1;
@@ -1039,29 +1058,30 @@ hipError_t launch_light_frames(ViewConst *views, const CamStatic *cams, const fl
 
 hipError_t launch_setup(const ViewConst *views, const TriBlock *blocks, int nblocks, const int *faces,
                         const float *verts, const float *albedo, int C, TriVerts *tv, TriSetup *setup,
-                        signed char *facing8, unsigned *pair_local, unsigned *block_total, const LargeLists &large,
-                        int tile, DevCounters *counters, hipStream_t s) {
+                        signed char *facing8, unsigned *pair_local, unsigned *block_total, unsigned *group_total,
+                        const LargeLists &large, int tile, DevCounters *counters, hipStream_t s) {
     if (nblocks == 0) return hipSuccess;
     hipLaunchKernelGGL(setup_kernel, dim3(nblocks), dim3(kTriThreads), 0, s, views, blocks, faces, verts, albedo, C, tv,
-                       setup, facing8, pair_local, block_total, large, __builtin_ctz(tile), counters);
+                       setup, facing8, pair_local, block_total, group_total, large, __builtin_ctz(tile), counters);
     return hipGetLastError();
 }
 
 hipError_t launch_binning(const ViewConst *views, const TriBlock *blocks, int nblocks, const TriSetup *setup,
                           const int *adj, const signed char *facing8, unsigned char *silm, const unsigned *pair_local,
-                          unsigned *block_total, unsigned *pair_off, int ntri, unsigned capacity, int tile,
+                          unsigned *block_total, const unsigned *group_total, unsigned *pair_off, int ntri,
+                          unsigned capacity, int tile,
                           unsigned *tile_count, unsigned *tile_start, unsigned *pair_slot, int ntiles, unsigned *bins,
                           unsigned *bin_pair, unsigned *overflow_list, const LargeLists &large,
                           DevCounters *counters, unsigned long long *keys, long long nkeys,
                           hipStream_t s) {
     if (ntri > kScanBlock * kScanBlock || ntiles > kScanBlock * kScanBlock) return hipErrorInvalidValue;
-    const bool scanned = nblocks > kMaxTriBlocks;
+    const bool scanned = nblocks > kTriGroup * kMaxTriGroups;
     if (scanned) hipLaunchKernelGGL(block_prefix_kernel, dim3(1), dim3(kTriThreads), 0, s, block_total, nblocks);
     const dim3 grid(nblocks + kLargeBlocks);
     const int shift = __builtin_ctz(tile);
     if (nblocks > 0)
         hipLaunchKernelGGL(bin_count_kernel, grid, dim3(kTriThreads), 0, s, views, blocks, nblocks, setup, adj, facing8,
-                           silm, pair_local, block_total, scanned, pair_off, capacity, shift, ntri, tile_count,
+                           silm, pair_local, block_total, group_total, scanned, pair_off, capacity, shift, ntri, tile_count,
                            pair_slot, large, overflow_list, counters);
     if (ntiles > 0)
         hipLaunchKernelGGL(tile_scan_kernel, dim3((ntiles + kScanBlock - 1) / kScanBlock), dim3(kTriThreads), 0, s,

@@ -91,3 +91,30 @@ def test_tiles_of_a_workgroup_around_the_table(w, h, res):
     for i in range(2):
         for k, kg in enumerate((g['keys'][i], g['keys'][2 + i])):
             assert np.array_equal(kg, o['keys'][k]), f'scene {i} view {k}'
+
+
+@pytest.mark.parametrize('n', [1100, 33000])
+def test_totals_by_groups_and_scanned(n):
+    """n lights and n cameras of one small view each, a triangle workgroup
+    each: their totals summed by groups, and scanned past 65,536 of them.  The
+    quads' tiles in every view follow from the totals before it."""
+    import torch
+    from paper_2308_10896_amd import dsm
+    b = sg.config0()
+    b.scenes = [sg.Scene(verts=v, faces=f, albedo=np.full((len(f), 1), 0.8, np.float32))
+                for v, f in [sg.merge([sg.quad(2.0), sg.cube((0.1, 0.5, 0.0), 0.5)])]]
+    b.lights[0].resolution, b.lights[0].k = 5, 1
+    b.cameras[0].width = b.cameras[0].height = 6
+    ref = gpu_run(b)
+    lights, cams = [b.lights[0]] * n, [b.cameras[0]] * n
+    many = sg.Batch('many', b.scenes, lights, cams, [sg.Render(i, [i]) for i in range(n)], channels=1)
+    plan = dsm.Plan(many)
+    verts, lp, alb, _ = dsm.batch_inputs(many)
+    saved, scratch = plan.workspace()
+    images = plan.forward(verts, lp, alb, saved, scratch)
+    flat = images.reshape(n, -1).cpu().numpy()
+    assert np.array_equal(flat, np.broadcast_to(ref['images'][0].reshape(1, -1), flat.shape))
+    for v in (0, 1, 63, 64, n - 1, n, n + 65, 2 * n - 1):
+        k = plan.view_keys(saved, v).cpu().numpy().view(np.uint64)
+        assert np.array_equal(k, ref['keys'][0 if v < n else 1]), f'view {v}'
+    assert plan.stats(saved)['pairs'] == n * ref['stats']['pairs']
