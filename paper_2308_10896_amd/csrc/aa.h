@@ -9,7 +9,7 @@
 // float32 ratio E(F) / (E(F) - E(O)), lower edge index on ties) is taken.
 // The pair is smoothed only if that edge is a silhouette in the view
 // (boundary, non-manifold, or neighbour of opposite facing; precomputed per
-// triangle as TriSetup::sil) and, so that
+// triangle as a byte per view, silhouette_mask) and, so that
 // each edge is handled in one direction only, |dY| > |dX| for horizontal
 // pairs and |dY| <= |dX| for vertical ones.  The continuous crossing
 // alpha = E(F) / (E(F) - E(O)) is computed from the unsnapped vertex

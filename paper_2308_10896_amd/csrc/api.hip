@@ -318,7 +318,6 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
         pix += (long long)W * H;
         tiles += (long long)v.tiles_x * v.tiles_y;
         p->max_verts = std::max(p->max_verts, v.nverts);
-        p->max_faces = std::max(p->max_faces, v.nfaces);
     };
     p->views_h.resize(p->nviews);
     p->light_cams_h.resize(L);
@@ -366,7 +365,6 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
         v.part_gm_off = (int)part_gm;
         part_gm += (v.nverts + 63) / 64;
         p->max_light_regions = std::max(p->max_light_regions, aa_regions(x.resolution, x.resolution));
-        p->max_light_texels = std::max(p->max_light_texels, x.resolution * x.resolution);
         p->max_light_tiles = std::max(p->max_light_tiles, v.tiles_x * v.tiles_y);
         p->views_h[l] = v;
         CamStatic &cs = p->light_cams_h[l];
