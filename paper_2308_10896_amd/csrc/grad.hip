@@ -176,7 +176,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(C == 1 ? 6 :
     const unsigned char *__restrict__ aa_flag, const float *__restrict__ img0, const float *__restrict__ gimg,
     float *__restrict__ gimg0, float4 *__restrict__ gclip) {
     __shared__ AARegion g;
-    const Blk blk = xcd_block2();
+    const Blk blk = xcd_block2<16, 8192>();
     const ViewConst &v = views[L + blk.y];
     const int W = v.W, H = v.H;
     if (blk.x >= aa_regions(W, H)) return;
@@ -504,7 +504,8 @@ __device__ __forceinline__ void overflow_rows(const ViewConst &v, const int (&ke
 // then stores the row and flags the pair.  The atomics of a group meet on one
 // address each, and where the groups are several samples wide that is what
 // bounds the sums: horizontal neighbours of one triangle are added first
-// (three 2048^2 maps 205 -> 174 us, the lookup's adjoint at 1080p 120 -> 110),
+// (three 2048^2 maps 205 -> 174 us, then 153 with the XCDs in turns; the
+// lookup's adjoint at 1080p 120 -> 110, then 81),
 // unless few lanes have one (meshes with a sample or two a triangle and tile:
 // 187 -> 191 with it).  The test for zero per value is worth its instructions
 // (64 scenes 388 us, 465 without it): unlit samples are zero in most values.  Pair flags start at zero (the
@@ -921,7 +922,7 @@ __device__ __forceinline__ void map_window_scatter(const MapHit (&hit)[PPT], int
 // adjoint.  Vector issue bounds it, then the latency of key -> record -> taps.
 // 64 renders with a light each 494 -> 388 us (5 waves per SIMD; 4: 5% more), 16
 // cameras with 8 renders each 716 -> 477, a 1080p RGB render with 3 lights
-// 205 -> 110 (4 waves; 5: 3% more).
+// 205 -> 81 (4 waves; 5: 3% more).
 template <int T, int C>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 32 ? 2 : C == 1 ? 5 : 4))) void lookup_backward_kernel(
     const ViewConst *__restrict__ views, int L, const RenderConst *__restrict__ renders,
@@ -935,7 +936,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 32 ? 2
     using TS = TileShape<T>;
     // one wave per 8x8 tile: pair rows found from the setup records (wave_pair_sums)
     constexpr bool kWavePairs = T == 8;
-    const Blk blk = xcd_block2();
+    const Blk blk = xcd_block2<128, 4096>();
     const int cam = blk.y;
     const ViewConst &cv = views[L + cam];
     const int lt = blk.x;
@@ -1044,7 +1045,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void l
     using TS = TileShape<T>;
     // one wave per 8x8 tile: pair rows found from the setup records (wave_pair_sums)
     constexpr bool kWavePairs = T == 8;
-    const Blk blk = xcd_block2();
+    const Blk blk = xcd_block2<128, 4096>();
     const int lidx = blk.y;
     const ViewConst &l = views[lidx];
     const int S = l.W;

@@ -869,11 +869,21 @@ __device__ __forceinline__ void overflow_raster(const ViewConst *__restrict__ vi
 // wave-wide test alone uses 64 lanes on the four samples of a 2 x 2 box), a
 // crowded tile is shared by four waves, and a group of nearly empty tiles
 // waits for one chain of loads instead of one per tile.  Against one wave per
-// tile testing its bin an entry at a time: 64 scenes at 512^2 388 -> 259 us,
-// 8 x 1024^2 maps and 16 views of a 99k-triangle sphere 432 -> 142, four
+// tile testing its bin an entry at a time: 64 scenes at 512^2 388 -> 211 us,
+// 8 x 1024^2 maps and 16 views of a 99k-triangle sphere 432 -> 102, four
 // scenes at 200^2 (hundreds of entries a tile) 133 -> 24.  Groups of 4 or 16
-// tiles: 338 and 313 us on the 64 scenes; 6 waves per SIMD 271, 8 (spills) 403.
+// tiles: 338 and 313 us on the 64 scenes where 8 took 259; 6 waves per SIMD 271,
+// 8 (spills) 403.
 constexpr int kRasterThreads = 256;
+// Groups are cheap over sky and dear over a mesh, so the XCDs take turns of
+// kGroupRun of them (an odd number, so that a turn does not repeat with the rows
+// of a view) instead of a range each: 64 scenes 259 -> 211 us (16: 231, 5: 238,
+// 128: 303), 24 views of 99k triangles 142 -> 102, 28,600 groups of a 1080p view
+// and its maps 163 -> 140.  Up to kRangeGroups, four rounds of resident
+// workgroups, there is less to even out and the ranges stay for the records
+// that neighbours share: 7,200 groups of a 960 x 540 view and its maps 52 us, in
+// turns 58.
+constexpr int kGroupRun = 23, kRangeGroups = 8192;
 constexpr int kWide = 128;      // records of the shared list; a chunk with more takes another round
 
 template <int T>
@@ -903,7 +913,8 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
     __shared__ TileInfo info[G];
     __shared__ __align__(16) RasterTri wide[kWide];
     __shared__ unsigned nwide;
-    const int g0 = xcd_remap((int)blockIdx.x, ngroups) * G;
+    const int gb = (int)blockIdx.x;
+    const int g0 = (ngroups > kRangeGroups ? xcd_turns<kGroupRun>(gb, ngroups) : xcd_remap(gb, ngroups)) * G;
     const int ng = min(G, ntiles - g0);
     const int tid = (int)threadIdx.x, lane = tid & 63;
     unsigned ts[G + 1];

@@ -92,9 +92,10 @@ __device__ __forceinline__ float texel_moment(const ViewConst &l, const TriVerts
 // smoothed (f, f^2).  A pair's giving sample outside the region is resolved
 // again from its key.  Bytes a texel: 8 (key) + 4 (F0) + 8 (F1) + 1 (flag),
 // where a resolve, a copying pass and a list pass moved 41; 64 512^2 maps
-// 212 -> 127 us (vector issue and the record gathers; the bytes take 70),
-// three 2048^2 maps 177 -> 100.  At 6 waves per SIMD (5: 134 and 106; 8 spills:
-// 203 and 169).
+// 212 -> 119 us (vector issue and the record gathers; the bytes take 70),
+// three 2048^2 maps 177 -> 88.  At 6 waves per SIMD (5 and 8, which spills, were
+// 6 and 60 % slower), the XCDs in turns of 16 regions (127 and 100 with a range
+// each).
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) void light_moments_kernel(const ViewConst *__restrict__ views,
                                                            const TriVerts *__restrict__ tv,
                                                            const TriSetup *__restrict__ setup,
@@ -107,7 +108,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) void li
     constexpr int ZW = kAaW + 2;
     __shared__ AARegion g;
     __shared__ float zs[(kAaH + 2) * ZW];       // f of the region and, where a pair needs it, of its border
-    const Blk blk = xcd_block2();
+    const Blk blk = xcd_block2<16, 8192, true>();
     const ViewConst &l = views[blk.y];
     const int S = l.W;
     if (blk.x >= aa_regions(S, S)) return;
@@ -195,7 +196,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(C == 1 ? 8 :
     const float *__restrict__ verts, const unsigned long long *__restrict__ keys, const float *__restrict__ src,
     float *__restrict__ dst, unsigned char *__restrict__ flag) {
     __shared__ AARegion g;
-    const Blk blk = xcd_block2();
+    const Blk blk = xcd_block2<16, 8192>();
     const ViewConst &v = views[L + blk.y];
     const int W = v.W, H = v.H;
     if (blk.x >= aa_regions(W, H)) return;
