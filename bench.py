@@ -50,10 +50,10 @@ HBM_PEAK_GBS = 8000.0
 # had when the counters were taken (and at tile side 8, where they were).
 PMC_COPY = dict(fetch_kib=65547.6, write_kib=131072.0, moved_kib=131072.0)
 PMC = {
-    'filter': dict(kernel='blur_kernel<false, 2, true, 32>', fetch_kib=65777.9, write_kib=131072.0, rd_bytes=134649907, wr_bytes=134217728, waves=32768, valu_per_wave=716.2, valu_busy=0.562, occupancy=19.4, sources=('blur.h', 'blur.hip', 'dsm_internal.h'), sha1='8a90f23c2c33b292'),
-    'filter_adj': dict(kernel='blur_kernel<true, 2, true, 32>', fetch_kib=65616.2, write_kib=131072.0, rd_bytes=134302976, wr_bytes=134217728, waves=32768, valu_per_wave=641.1, valu_busy=0.553, occupancy=19.9, sources=('blur.h', 'blur_transpose.hip', 'dsm_internal.h'), sha1='c7b6b74d387b0f45'),
-    'lookup': dict(kernel='lookup_kernel<2>', fetch_kib=200698.0, write_kib=65536.0, rd_bytes=410712614, wr_bytes=67108864, waves=131072, valu_per_wave=468.0, valu_busy=0.926, occupancy=26.2, sources=('shade.hip', 'dsm_internal.h'), sha1='a4363f5348160d51'),
-    'lookup_adj': dict(kernel='lookup_backward_kernel<8, 1>', fetch_kib=126899.9, write_kib=122144.6, rd_bytes=259533529, wr_bytes=125081849, waves=262144, valu_per_wave=729.2, valu_busy=0.840, occupancy=18.3, sources=('grad.hip', 'dsm_internal.h'), sha1='bc101b5a40d85219'),
+    'filter': dict(kernel='blur_kernel<false, 2, true, 32>', fetch_kib=65702.5, write_kib=131072.0, rd_bytes=134524492, wr_bytes=134217728, waves=32768, valu_per_wave=716.2, valu_busy=0.557, occupancy=18.0, sources=('blur.h', 'blur.hip', 'dsm_internal.h'), sha1='1ac4978480ccb948'),
+    'filter_adj': dict(kernel='blur_kernel<true, 2, true, 32>', fetch_kib=65615.9, write_kib=131072.0, rd_bytes=134303257, wr_bytes=134217728, waves=32768, valu_per_wave=641.1, valu_busy=0.553, occupancy=20.2, sources=('blur.h', 'blur_transpose.hip', 'dsm_internal.h'), sha1='158042a326373fe5'),
+    'lookup': dict(kernel='lookup_kernel<2>', fetch_kib=200697.9, write_kib=65536.0, rd_bytes=410712435, wr_bytes=67108864, waves=131072, valu_per_wave=468.0, valu_busy=0.919, occupancy=26.5, sources=('shade.hip', 'dsm_internal.h'), sha1='6f917b872bf2569b'),
+    'lookup_adj': dict(kernel='lookup_backward_kernel<8, 1>', fetch_kib=126895.5, write_kib=122201.4, rd_bytes=259537382, wr_bytes=125111417, waves=262144, valu_per_wave=729.2, valu_busy=0.837, occupancy=18.4, sources=('grad.hip', 'dsm_internal.h'), sha1='ab3329d092a1bf46'),
 }
 
 # Issue peak of the vector ALUs: 256 CUs x 4 SIMDs x 2.4 GHz / 4 cycles per
