@@ -6,12 +6,11 @@
 #include <stdint.h>
 
 #include "dsm.h"
+#include "raster_tri.h"
 
 namespace dsm {
 
-constexpr int kSub = 256;              // 8 sub-pixel bits of the fixed-point grid
 constexpr float kGuard = 32768.0f;     // |screen coordinate| limit in pixels
-constexpr uint64_t kBgKey = ~0ull;     // background key (no triangle)
 constexpr int kMaxTaps = 32;
 
 enum ViewKind { kDirectional = 0, kPoint = 1, kSpot = 2, kCamera = 3, kCubeFace = 4 };
@@ -130,20 +129,6 @@ struct LightSum {
     unsigned *done;
     float *gparams;
 };
-
-// Per (view, triangle) fixed-point setup, written by the setup kernel.
-struct TriSetup {
-    long long A;                 // doubled area, > 0 when valid
-    int X[3], Y[3];              // oriented fixed-point screen coordinates
-    float z[3];                  // oriented z01
-    unsigned short bx0, by0, bx1, by1;  // inclusive pixel bbox, clipped to the view
-    signed char facing;          // +1 / -1 orientation before re-orienting, 0 if not rasterized
-    unsigned char swapped;       // 2nd and 3rd vertex exchanged
-    unsigned char sil;           // unused (the silhouette mask lives in its own byte array)
-    unsigned char pad1;
-    int pad2[2];
-};
-static_assert(sizeof(TriSetup) == 64, "TriSetup must stay 64 bytes");
 
 // Workgroups per light in the first pass of the light-gradient reduction.
 constexpr int kGlightBlocks = 16;
