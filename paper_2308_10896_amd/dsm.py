@@ -313,14 +313,58 @@ def autotune(batch, verts, light_params, albedo, grad_images, reps: int = 3, cac
     return int(tile.value), int(scale.value), float(ms.value)
 
 
+class _RecordedRender(torch.autograd.Function):
+    """render for the calls of _in_python, over the raw calls."""
+
+    @staticmethod
+    def forward(ctx, plan, verts, light_params, albedo):
+        saved = torch.empty(int(plan.info.saved_bytes), dtype=torch.uint8, device=verts.device)
+        images = plan.forward(verts, light_params, albedo, saved, plan.scratch(verts.device))
+        ctx.plan = plan
+        ctx.save_for_backward(verts, light_params, albedo, saved)
+        return images
+
+    @staticmethod
+    def backward(ctx, grad_images):
+        verts, light_params, albedo, saved = ctx.saved_tensors
+        return None, *ctx.plan.backward(verts, light_params, albedo, saved, ctx.plan.scratch(verts.device),
+                                        grad_images.contiguous(), want_albedo=ctx.needs_input_grad[3])
+
+
+class _RecordedPose(torch.autograd.Function):
+    @staticmethod
+    def forward(ctx, plan, local, poses):
+        ctx.plan = plan
+        ctx.save_for_backward(local, poses)
+        return plan.pose_forward(local, poses)
+
+    @staticmethod
+    def backward(ctx, grad_world):
+        local, poses = ctx.saved_tensors
+        return None, None, ctx.plan.pose_backward(local, poses, grad_world.contiguous())
+
+
+def _in_python(*tensors):
+    """The calls that go through Python functions instead of the C++ nodes:
+    under torch.jit.trace, which records a Python autograd function as one
+    operation but of a C++ node only the allocation of its outputs, and with
+    tensor subclasses, whose class the results take."""
+    return torch.jit.is_tracing() or any(type(t) is not torch.Tensor and type(t) is not torch.nn.Parameter
+                                         for t in tensors)
+
+
 def render(plan: Plan, verts, light_params, albedo):
     """Differentiable render of every image of the plan (flat float32 tensor;
     ``plan.split_images`` gives per-render [H, W, C] views)."""
+    if _in_python(verts, light_params, albedo):
+        return _RecordedRender.apply(plan, verts, light_params, albedo)
     return _lib.ext().render(plan._nodes, verts, light_params, albedo, plan.scratch(verts.device))
 
 
 def pose(plan: Plan, local, poses):
     """Differentiable rigid pose of each scene's posed vertex prefix."""
+    if _in_python(local, poses):
+        return _RecordedPose.apply(plan, local, poses)
     return _lib.ext().pose(plan._nodes, local, poses)
 
 
