@@ -1,7 +1,7 @@
 // Autograd nodes of the binding: render and pose as C++ functions over the C
 // ABI.  A pass of a small scene is a few dozen microseconds of kernels, as long
 // as a Python autograd function takes to marshal its arguments, so the nodes
-// run without the interpreter (their backward without its lock).  Memory,
+// run without the interpreter and without its lock.  Memory,
 // streams and error classes are the Python binding's: the caller's tensors are
 // checked and used as they are, outputs come from torch's allocator, work goes
 // to the current stream.
@@ -138,15 +138,21 @@ struct PlanHandle {
     c10::intrusive_ptr<PlanRef> ref() const { return c10::make_intrusive<PlanRef>(owner, plan); }
 };
 
+// The call without the interpreter's lock, as the raw calls run: launching can
+// take as long as a full queue takes to drain, and other threads go on meanwhile.
+template <class Node, class... Args>
+Tensor call(const PlanHandle &p, const Args &...args) {
+    const c10::intrusive_ptr<PlanRef> ref = p.ref();
+    const pybind11::gil_scoped_release unlocked;
+    return Node::apply(ref, args...);
+}
+
 }  // namespace
 
 PYBIND11_MODULE(_dsm_torch, m) {
     pybind11::class_<PlanHandle>(m, "PlanHandle").def(pybind11::init([](pybind11::handle owner, uintptr_t plan) {
         return PlanHandle{owner.ptr(), reinterpret_cast<dsm_plan *>(plan)};
     }));
-    m.def("render", [](const PlanHandle &p, const Tensor &verts, const Tensor &light_params, const Tensor &albedo,
-                       const Tensor &scratch) { return Render::apply(p.ref(), verts, light_params, albedo, scratch); });
-    m.def("pose", [](const PlanHandle &p, const Tensor &local, const Tensor &poses) {
-        return Pose::apply(p.ref(), local, poses);
-    });
+    m.def("render", &call<Render, Tensor, Tensor, Tensor, Tensor>);     // verts, light_params, albedo, scratch
+    m.def("pose", &call<Pose, Tensor, Tensor>);                         // local, poses
 }
