@@ -8,6 +8,7 @@ nodes in C++ (csrc/binding.cpp).
 from __future__ import annotations
 
 import ctypes as C
+import functools
 
 import numpy as np
 import torch
@@ -159,7 +160,6 @@ class Plan:
         h = C.c_void_p()
         L.call('dsm_plan_create', C.byref(desc), int(tile_size), int(bin_capacity_scale), C.byref(h))
         self.handle = h
-        self._nodes = L.ext().PlanHandle(self, h.value)
         info = L.PlanInfo()
         L.call('dsm_plan_info_get', h, C.byref(info))
         self.info = info
@@ -179,6 +179,12 @@ class Plan:
             except Exception:
                 pass
             self.handle = None
+
+    @functools.cached_property
+    def _nodes(self):
+        """The plan as the autograd nodes take it.  Their module is loaded when a
+        call first needs it: the raw calls work with the library alone."""
+        return _lib.ext().PlanHandle(self, self.handle.value)
 
     # --- memory
     def workspace(self, device='cuda'):
