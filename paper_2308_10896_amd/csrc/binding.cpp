@@ -23,9 +23,10 @@ using torch::autograd::AutogradContext;
 using torch::autograd::Variable;
 using torch::autograd::variable_list;
 
-// The plan as the nodes hold it: a reference to the Python Plan that owns the
-// library's plan, released under the interpreter's lock (a graph may be freed
-// on any thread).
+// The plan as the nodes hold it: a reference to the Python object that owns the
+// library's plan (and refers to nothing: Python's collector does not see this
+// reference), released under the interpreter's lock (a graph may be freed on any
+// thread).
 struct PlanRef : torch::CustomClassHolder {
     PyObject *owner;
     dsm_plan *plan;
@@ -130,8 +131,9 @@ struct Pose : torch::autograd::Function<Pose> {
     }
 };
 
-// What Plan keeps for the calls below.  It refers to the Plan without owning
-// it (the Plan owns this); each node takes a reference of its own.
+// What Plan keeps for the calls below.  It refers to the owner of the library's
+// plan without owning it (the Plan owns both); each node takes a reference of
+// its own.
 struct PlanHandle {
     PyObject *owner;
     dsm_plan *plan;

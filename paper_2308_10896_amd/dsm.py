@@ -138,6 +138,21 @@ class _BatchDesc:
         self.desc = desc
 
 
+class _LibraryPlan:
+    """The library's plan, destroyed with its last reference.  A Plan holds one,
+    and every autograd graph of its calls: it refers to nothing, so a Plan that
+    keeps its own images is no cycle through memory that Python cannot see."""
+
+    def __init__(self, handle):
+        self.handle = handle
+
+    def __del__(self):
+        try:
+            _lib.lib().dsm_plan_destroy(self.handle)
+        except Exception:
+            pass
+
+
 class Plan:
     """A batch of scenes / lights / cameras / renders bound to the HIP library.
 
@@ -160,6 +175,7 @@ class Plan:
         h = C.c_void_p()
         L.call('dsm_plan_create', C.byref(desc), int(tile_size), int(bin_capacity_scale), C.byref(h))
         self.handle = h
+        self._library = _LibraryPlan(h)
         info = L.PlanInfo()
         L.call('dsm_plan_info_get', h, C.byref(info))
         self.info = info
@@ -171,20 +187,11 @@ class Plan:
         self.light_res = [l.resolution for l in batch.lights]
         self._scratch = {}
 
-    def __del__(self):
-        h = getattr(self, 'handle', None)
-        if h is not None and h.value:
-            try:
-                _lib.lib().dsm_plan_destroy(h)
-            except Exception:
-                pass
-            self.handle = None
-
     @functools.cached_property
     def _nodes(self):
         """The plan as the autograd nodes take it.  Their module is loaded when a
         call first needs it: the raw calls work with the library alone."""
-        return _lib.ext().PlanHandle(self, self.handle.value)
+        return _lib.ext().PlanHandle(self._library, self.handle.value)
 
     # --- memory
     def workspace(self, device='cuda'):
