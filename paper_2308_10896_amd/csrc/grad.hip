@@ -1427,9 +1427,7 @@ __device__ __forceinline__ void gather_corners(const int (&e)[N], int soff, unsi
 }
 
 // The gradient of light l by a wave: the vertex workgroups' shares and
-// light_partials' sums in a fixed order.  AGENT: the shares come from the same
-// launch.
-template <bool AGENT>
+// light_partials' sums in a fixed order.
 __device__ __forceinline__ void finish_light(const ViewConst &v, int l, const float *part_gm, const LightSum &ls) {
     const int lane = (int)(threadIdx.x & 63), nblk = (v.nverts + 63) / 64;
     float acc[3] = {0.f, 0.f, 0.f};
@@ -1441,9 +1439,7 @@ __device__ __forceinline__ void finish_light(const ViewConst &v, int l, const fl
 #pragma unroll 4
     for (int q = lane; q < nblk; q += 64)
 #pragma unroll
-        for (int k = 0; k < 3; ++k)
-            acc[k] += AGENT ? __hip_atomic_load(part + 3 * q + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                            : part[3 * q + k];
+        for (int k = 0; k < 3; ++k) acc[k] += part[3 * q + k];
     const float t = wave_sum_multi(acc);
     if ((lane & 15) == 0 && lane < 48) ls.gparams[3 * l + (lane >> 4)] = t;
 }
@@ -1541,26 +1537,19 @@ __global__ __launch_bounds__(256) void vertex_gather_kernel(
                 gp[j] = a;
             }
             const float t = wave_sum_multi(gp);
-            float *share = part_gm + ((long long)v.part_gm_off + blockIdx.x) * 3 + (lane >> 4);
-            if ((lane & 15) == 0 && lane < 48) {
-                if constexpr (LIGHTS) __hip_atomic_store(share, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                else *share = t;
-            }
+            if ((lane & 15) == 0 && lane < 48) part_gm[((long long)v.part_gm_off + blockIdx.x) * 3 + (lane >> 4)] = t;
         }
     }
     if (wave > 0)
 #pragma unroll
         for (int k = 0; k < 3; ++k) sum[wave - 1][k][lane] = gv[k];
     __shared__ unsigned before;
-    if constexpr (LIGHTS) {
-        // The shares go through to where every XCD sees them; waiting for them is
-        // all the release there is to do (a fence would write back the whole L2).
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    }
     if (LIGHTS || nwaves > 1) __syncthreads();
+    // releases the workgroup's shares (stored before the barrier) and, in the last
+    // one, acquires the others'
     if constexpr (LIGHTS)
         if (threadIdx.x == 0)
-            before = __hip_atomic_fetch_add(ls.done + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            before = __hip_atomic_fetch_add(ls.done + b, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
     if (wave == 0) {
         for (int w = 1; w < nwaves; ++w)
 #pragma unroll
@@ -1573,7 +1562,7 @@ __global__ __launch_bounds__(256) void vertex_gather_kernel(
         if (before != (unsigned)nblk - 1u) return;
         for (int s = scene_views_off[b] + wave; s < scene_views_off[b + 1]; s += nwaves) {
             const int vi = scene_views[s];
-            if (vi < L) finish_light<true>(views[vi], vi, part_gm, ls);
+            if (vi < L) finish_light(views[vi], vi, part_gm, ls);
         }
     }
 }
@@ -1581,7 +1570,7 @@ __global__ __launch_bounds__(256) void vertex_gather_kernel(
 // The lights' gradients where the gather does not finish them, a wave each.
 __global__ __launch_bounds__(64) void light_sum_kernel(const ViewConst *__restrict__ views, const float *part_gm,
                                                        LightSum ls) {
-    finish_light<false>(views[blockIdx.x], (int)blockIdx.x, part_gm, ls);
+    finish_light(views[blockIdx.x], (int)blockIdx.x, part_gm, ls);
 }
 
 // ----------------------------------------------------------------------------- pose
@@ -1773,11 +1762,12 @@ hipError_t launch_vertex_gradients(const ViewConst *views, int L, int B, int max
     hipLaunchKernelGGL(vertex_gather_kernel<LIGHTS>, dim3(vx + fx, B), dim3(nt), 0, s, views, L, scene_vert_off,   \
                        scene_views_off, scene_views, vc_off, vc_list, verts, pair_off, capacity, pair_flag,        \
                        pair_sums, gtri, zero_rec, gclip, gverts, part_gm, jac, vx, scene_face_off, galbedo, C, ls)
-    // Up to a workgroup or so per CU, finishing the lights in the gather costs its
-    // last workgroup 2 us and saves a launch of 4 us with its gap; with more, the wait for
-    // the shares keeps every workgroup's place (64 scenes: 51 -> 69 us against a
-    // launch of 4).
-    constexpr long long kFinishBlocks = 256;
+    // On few workgroups finishing the lights in the gather saves a launch: tiny cube
+    // 118.3 -> 116.4 us, icosphere 156.7 -> 155.8.  With more, the release of each
+    // (a write-back of its XCD's L2) keeps the workgroup's place: four lights and
+    // views, 111 workgroups 233.0 us a pass against 231.6 with the launch; one of
+    // each, 160: 144.7 against 143.1, 240: 146.4 against 144.2.
+    constexpr long long kFinishBlocks = 64;
     if (L > 0 && (long long)vx * B <= kFinishBlocks) DSM_GATHER(true);
     else {
         DSM_GATHER(false);
