@@ -7,6 +7,7 @@
 
 #include "dsm.h"
 #include "raster_tri.h"
+#include "xcd_order.h"
 
 namespace dsm {
 
@@ -306,45 +307,14 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Workgroups are dispatched to the 8 XCDs round-robin by linear id, and each
-// XCD has its own L2.  These renumber a grid so that each XCD takes a
-// contiguous range of work items: neighbouring tiles and rows, which share
-// cache lines and halos, then share an L2.  Both are bijections, so any
-// dispatch order stays correct.
-__device__ __forceinline__ int xcd_remap(int b, int n) {
-    constexpr int kXcd = 8;
-    const int xcd = b % kXcd, idx = b / kXcd;
-    const int per = n / kXcd, rem = n % kXcd;
-    return xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
-}
-
-// The same with the XCDs taking turns of `run` consecutive items, which evens
-// out ranges that cost more than others; the last items, too few for a turn, are
-// split as above.
-template <int RUN>
-__device__ __forceinline__ int xcd_turns(int b, int n) {
-    constexpr int kTurn = 8 * RUN;
-    const int whole = n / kTurn * kTurn;
-    return b < whole ? b / kTurn * kTurn + b % 8 * RUN + b / 8 % RUN : whole + xcd_remap(b - whole, n - whole);
-}
-
-// (x, y) of a grid of views y.  Where every XCD gets whole views (or nearly, of
-// 32 and more) a contiguous range is even, and a view's maps stay in one L2;
-// otherwise one XCD's range is sky and another's the object, and they take
-// turns: a 1080p camera's lookup adjoint 110 -> 81 us, three 2048^2 maps' light
-// adjoint 174 -> 153 (turns with 64 views instead: 388 -> 434 and 187 -> 188).
-// SPREAD: turns with many views too, for kernels that read little but their own
-// region.  Grids under FROM workgroups keep the ranges (a cube light's six small
-// maps 170 us a pass, 172 in turns); of 4,096 tiles on, turns pay (a 512^2 view's
-// lookup adjoint 19 -> 13 us).
+// (x, y) of this workgroup's item in a grid of views y (xcd_item).
 struct Blk {
     int x, y;
 };
 template <int RUN, int FROM, bool SPREAD = false>
 __device__ __forceinline__ Blk xcd_block2() {
-    const int gx = (int)gridDim.x, gy = (int)gridDim.y, b = (int)blockIdx.x + (int)blockIdx.y * gx, n = gx * gy;
-    const bool range = n < FROM || (!SPREAD && (gy % 8 == 0 || gy >= 32));
-    const int lin = range ? xcd_remap(b, n) : xcd_turns<RUN>(b, n);
+    const int gx = (int)gridDim.x;
+    const int lin = xcd_item<RUN, FROM, SPREAD>((int)blockIdx.x + (int)blockIdx.y * gx, gx, (int)gridDim.y);
     return Blk{lin % gx, lin / gx};
 }
 
