@@ -122,48 +122,40 @@ __device__ __forceinline__ bool aa_eval(const ViewConst &v, const TriSetup *__re
     return true;
 }
 
-// The four neighbours of sample (i, j) (order -x, +x, -y, +y) and which of
-// the pairs can be smoothed at all: different triangles and a front
-// triangle with a silhouette edge in this view.  All neighbour keys are
-// loaded together, then all silhouette bytes, so a sample waits for two
-// dependent loads instead of two per neighbour (one when no lane of its
-// wave has a differing neighbour).  The view must have faces.
-struct AANeighbours {
+// Which of sample (i, j)'s pairs with its four neighbours (order -x, +x, -y, +y)
+// can be smoothed at all: different triangles and a front triangle with a
+// silhouette edge in this view.  All neighbour keys are loaded together, then
+// all silhouette bytes, so a sample waits for two dependent loads instead of
+// two per neighbour (one when no lane of its wave has a differing neighbour).
+// The view must have faces.
+__device__ __forceinline__ void aa_candidates(const ViewConst &v, const unsigned long long *__restrict__ kv,
+                                              const unsigned char *__restrict__ silm, unsigned long long ks, int i,
+                                              int j, bool (&cand)[4]) {
     unsigned long long kn[4];
-    int q[4];
-    bool cand[4];
-};
-
-__device__ __forceinline__ AANeighbours aa_neighbours(const ViewConst &v, const unsigned long long *__restrict__ kv,
-                                                      const unsigned char *__restrict__ silm, unsigned long long ks,
-                                                      int i, int j) {
-    AANeighbours n;
     bool inb[4];
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
         const int in_ = i + (d == 0 ? -1 : d == 1 ? 1 : 0), jn = j + (d == 2 ? -1 : d == 3 ? 1 : 0);
         inb[d] = in_ >= 0 && in_ < v.W && jn >= 0 && jn < v.H;
-        n.q[d] = inb[d] ? jn * v.W + in_ : j * v.W + i;
-        n.kn[d] = kv[n.q[d]];
+        kn[d] = kv[inb[d] ? jn * v.W + in_ : j * v.W + i];
     }
     bool differ[4], any = false;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-        differ[d] = inb[d] && (unsigned)n.kn[d] != (unsigned)ks;
+        differ[d] = inb[d] && (unsigned)kn[d] != (unsigned)ks;
         any = any || differ[d];
-        n.cand[d] = false;
+        cand[d] = false;
     }
     // a wave inside one triangle (most of a ground plane) waits for no
     // silhouette byte at all
     if (__ballot(any) != 0ull) {
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
-            const unsigned front = ks < n.kn[d] ? (unsigned)ks : (unsigned)n.kn[d];
+            const unsigned front = ks < kn[d] ? (unsigned)ks : (unsigned)kn[d];
             const unsigned char sil = differ[d] ? silm[v.setup_off + front] : (unsigned char)0;
-            n.cand[d] = differ[d] && sil != 0;
+            cand[d] = differ[d] && sil != 0;
         }
     }
-    return n;
 }
 
 // Smoothing of a region of kAaW x kAaH samples by one wave: a lane owns a

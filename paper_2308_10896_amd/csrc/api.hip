@@ -421,7 +421,6 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
         rc.camera_view = L + x.camera;
         rc.light_begin = x.light_begin;
         rc.light_count = x.light_count;
-        p->max_lights_per_render = std::max(p->max_lights_per_render, x.light_count);
         rc.W = d->cameras[x.camera].width;
         rc.H = d->cameras[x.camera].height;
         rc.img_off = img;
@@ -432,7 +431,6 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
         p->renders_h[r] = rc;
     }
     p->render_lights_h.assign(d->render_light_list, d->render_light_list + list_len);
-    p->nclip = (int)clip;
     p->ntri = (int)tri;
     p->ntiles = (int)tiles;
     p->key_count = pix;

@@ -1,21 +1,21 @@
 // Separable moment filter, forward (m = G f~, Eq. moment1 / moment2) and
 // transpose (the gradient G^T of Sec. 4: the filter applied to the Jacobian).
 //
-// One workgroup (4 waves) filters a 64 x 64 tile of one 2-channel map.  The
-// tile plus an r-texel halo is staged in LDS in one phase: every thread
-// issues all of its loads before the first wait, so a workgroup keeps its
-// whole footprint in flight.  Each lane then owns one column of 16 output
-// rows: it forms the horizontal filter of that column for every staged row
-// (the k taps are neighbouring LDS words) and pushes the results through a
-// register ring of the last k rows, from which each output row is one
-// k-tap dot product.  The taps are fused multiply-adds (from k = 9 on the
+// One workgroup (4 waves) filters a tile of 64 columns and 16, 32 or 64 rows of
+// one 2-channel map (blur_tall, blur_short).  The tile plus an r-texel halo is
+// staged in LDS in one phase: every thread issues all of its loads before the
+// first wait, so a workgroup keeps its whole footprint in flight.  Each lane
+// then owns one column of a quarter of the rows: it forms the horizontal filter
+// of that column for every staged row (the k taps are neighbouring LDS words)
+// and pushes the results through a register ring of the last k rows, from which
+// each output row is one k-tap dot product.  The taps are fused multiply-adds (from k = 9 on the
 // filter is bound by them, below by HBM): three 1000^2 maps at k = 11, transpose
-// 25.6 -> 21.8 us.  The pipeline's forward filter alone keeps the rounded
+// 23.6 -> 20.9 us a call.  The pipeline's forward filter alone keeps the rounded
 // product: its maps are what the lookup takes every decision from, and at the
 // variance floor the Chebyshev quotient shows their last bits in the image.
-// Each input texel is read from HBM once (halo re-reads
-// of neighbouring tiles are served by L2) and each output texel written
-// once: 16 bytes of algorithmic traffic per texel.
+// Each input texel is read from HBM once (halo re-reads of neighbouring tiles
+// are served by L2) and each output texel written once: 16 bytes of algorithmic
+// traffic per texel.
 //
 // Boundary: clamp-to-edge in the forward pass.  Its transpose is
 // zero-padded correlation (the taps are symmetric) plus, on the first and

@@ -1083,11 +1083,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void l
             const int tid = (int)threadIdx.x;
             unsigned n = 0;
             if (TS::NW > 1 || __ballot(flagged) != 0ull) {
-                if (flagged) {
-                    const AANeighbours nb = aa_neighbours(l, kv, silm, ks, i, j);
-#pragma unroll
-                    for (int d = 0; d < 4; ++d) cand[d] = nb.cand[d];
-                }
+                if (flagged) aa_candidates(l, kv, silm, ks, i, j, cand);
                 if (k > 0) __syncthreads();
                 aa_pairs_list(pairs, tid, cand);
                 __syncthreads();

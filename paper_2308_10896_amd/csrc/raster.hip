@@ -16,7 +16,8 @@
 //    directed edge a -> b; a sample on an edge belongs to the triangle only
 //    for top (dy == 0, dx > 0) or left (dy < 0) edges;
 //  * z01 = 0.5 z/w + 0.5 per vertex, interpolated (z0 + b1 (z1-z0)) + b2 (z2-z0)
-//    with b_e = f32(E_e) / f32(A); samples with z01 outside [0,1] are dropped;
+//    with b_e = f32(E_e) rA, rA the correctly rounded float32 1 / A; samples with
+//    z01 outside [0,1] are dropped;
 //  * key = bits(z01) << 32 | local triangle index, minimum wins.
 #include "dsm_internal.h"
 #include "frames.h"
@@ -221,8 +222,7 @@ __global__ __launch_bounds__(kTriThreads) void setup_kernel(
         for (int k = 0; k < 3; ++k) { s.X[k] = X[k]; s.Y[k] = Y[k]; s.z[k] = z[k]; }
         s.facing = valid ? (swapped ? -1 : 1) : 0;
         s.swapped = swapped ? 1 : 0;
-        s.sil = 0;
-        s.pad1 = 0;
+        s.pad1[0] = s.pad1[1] = 0;
         s.pad2[0] = blk.view;
         s.pad2[1] = 0;
         int i0 = 1, i1 = 0, j0 = 1, j1 = 0;
@@ -793,10 +793,11 @@ constexpr int kRasterThreads = 256;
 // kGroupRun of them (an odd number, so that a turn does not repeat with the rows
 // of a view) instead of a range each: 64 scenes 259 -> 211 us (16: 231, 5: 238,
 // 128: 303), 24 views of 99k triangles 142 -> 102, 28,600 groups of a 1080p view
-// and its maps 163 -> 140.  Up to kRangeGroups, four rounds of resident
-// workgroups, there is less to even out and the ranges stay for the records
-// that neighbours share: 7,200 groups of a 960 x 540 view and its maps 52 us, in
-// turns 58.
+// and its maps 163 -> 140.  In a few rounds of resident workgroups (1,792 at a
+// time) there is less to even out, and the ranges stay for the records that
+// neighbours share: 7,164 groups of a 960 x 540 view and its maps 52 us, in turns
+// 58.  The line lies between that and the smallest grid measured faster in turns
+// (24,576 groups).
 constexpr int kGroupRun = 23, kRangeGroups = 8192;
 constexpr int kWide = 128;      // records of the shared list; a chunk with more takes another round
 

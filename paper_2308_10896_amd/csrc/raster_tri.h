@@ -20,9 +20,8 @@ struct TriSetup {
     unsigned short bx0, by0, bx1, by1;  // inclusive pixel bbox, clipped to the view
     signed char facing;          // +1 / -1 orientation before re-orienting, 0 if not rasterized
     unsigned char swapped;       // 2nd and 3rd vertex exchanged
-    unsigned char sil;           // unused (the silhouette mask lives in its own byte array)
-    unsigned char pad1;
-    int pad2[2];
+    unsigned char pad1[2];
+    int pad2[2];                 // view, 0
 };
 static_assert(sizeof(TriSetup) == 64, "TriSetup must stay 64 bytes");
 
