@@ -317,7 +317,6 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
         tri += v.nfaces;
         pix += (long long)W * H;
         tiles += (long long)v.tiles_x * v.tiles_y;
-        p->max_verts = std::max(p->max_verts, v.nverts);
     };
     p->views_h.resize(p->nviews);
     p->light_cams_h.resize(L);
@@ -918,7 +917,7 @@ extern "C" dsm_status dsm_pose_forward(dsm_plan *p, const float *local, const fl
     if (!p || (p->V_total > 0 && (!local || !world)) || !poses) return DSM_ERR_INVALID_ARG;
     if (local == world) return DSM_ERR_INVALID_ARG;
     DSM_TRY(launch_pose(p->scene_vert_off_d, p->pose_counts_d, p->pose_centers_d, p->B,
-                        std::max(p->max_verts, 1), local, poses, world, (hipStream_t)stream));
+                        std::max(p->max_scene_verts, 1), local, poses, world, (hipStream_t)stream));
     return DSM_OK;
 }
 

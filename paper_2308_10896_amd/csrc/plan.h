@@ -17,7 +17,7 @@ struct dsm_plan {
     int bin_scale = 8;
     unsigned capacity = 0, item_cap = 0;
     int ntri = 0, ntiles = 0;
-    int max_verts = 0, max_cam_pix = 0, max_pose_verts = 0;
+    int max_cam_pix = 0, max_pose_verts = 0;
     long long key_count = 0, map_floats = 0, image_floats = 0;
     int max_light_tiles = 0, max_cam_tiles = 0;
     int max_cam_regions = 0, max_light_regions = 0, max_cam_renders = 0;   // smoothing regions; renders of one camera
