@@ -514,7 +514,7 @@ extern "C" dsm_status dsm_plan_create(const dsm_batch_desc *d, int32_t tile_size
     o = 0;
     p->sc_tile_cnt = o; o = align_up(o + 4 * ((size_t)tiles + 1));
     p->sc_group_total = o;
-    o = align_up(o + 4 * kGroupStride * (((size_t)tri / kTriRun + (size_t)p->nviews) / kTriGroup + 1));
+    o = align_up(o + 8 * kGroupStride * (((size_t)tri / kTriRun + (size_t)p->nviews) / kTriGroup + 1));
     p->sc_zero_fwd_end = o;
     p->sc_pair_local = o; o = align_up(o + 4 * ((size_t)tri + 1));
     p->sc_block_total = o; o = align_up(o + 4 * ((size_t)tri / kTriRun + (size_t)p->nviews + 2));
@@ -699,7 +699,7 @@ dsm_status enqueue_forward(dsm_plan *p, const float *verts, const float *lparams
     unsigned *pair_slot = at<unsigned>(scratch, p->sc_pair_slot);
     unsigned *pair_local = at<unsigned>(scratch, p->sc_pair_local);
     unsigned *block_total = at<unsigned>(scratch, p->sc_block_total);
-    unsigned *group_total = at<unsigned>(scratch, p->sc_group_total);
+    unsigned long long *group_total = at<unsigned long long>(scratch, p->sc_group_total);
     unsigned *pair_off = at<unsigned>(saved, p->sv_pair_off);
     const LargeLists large{at<unsigned>(saved, p->sv_large), at<uint2>(saved, p->sv_items), p->item_cap,
                            at<unsigned>(saved, p->sv_medium)};
@@ -786,7 +786,8 @@ dsm_status enqueue_backward(dsm_plan *p, const float *verts, const float *lparam
     const LargeLists large{at<unsigned>(const_cast<void *>(saved), p->sv_large),
                            at<uint2>(const_cast<void *>(saved), p->sv_items), p->item_cap,
                            at<unsigned>(const_cast<void *>(saved), p->sv_medium)};
-    const ClearRows rows{gtri, overflow, large.list, &cnt->overflow_list_len, &cnt->large_len};
+    const ClearRows rows{gtri, overflow, large.list, &cnt->overflow_list_len, &cnt->large_len,
+                         p->tri_blocks ? pair_off + p->ntri : nullptr, (unsigned)p->ntri};
     DSM_TRY(launch_light_frames(p->views_d, p->light_cams_d, lparams, p->L, jac, nullptr, at<void>(scratch, p->sc_done),
                                 p->sc_zero_bwd_end - p->sc_done, pair_flag, ((size_t)p->capacity + 3) & ~(size_t)3,
                                 rows, s));

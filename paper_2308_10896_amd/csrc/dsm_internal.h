@@ -64,7 +64,14 @@ struct TriBlock {
 constexpr int kTriRun = 256, kTriGroup = 64, kMaxTriGroups = 1024;
 // Group totals lie a cache line apart: their atomics meet only within a group
 // (side by side the setup of 99k triangles in 24 views took 79 us, not 66).
-constexpr int kGroupStride = 32;
+constexpr int kGroupStride = 16;      // of 8 bytes
+// Pairs are numbered in 32 bits, and the bins hold fewer than 2^28, but many
+// triangles over whole large views (an optimization that diverged) have more
+// than 2^32 of them: the number stays at kPairEnd from there on, so that every
+// triangle past the bins stays past them.
+constexpr unsigned kPairEnd = 0x7fffffffu;
+__device__ __forceinline__ unsigned add_sat(unsigned a, unsigned b) { return __builtin_elementwise_add_sat(a, b); }
+__device__ __forceinline__ unsigned word_sat(unsigned long long x) { return x >> 32 ? ~0u : (unsigned)x; }
 // Tiles per workgroup of the tile scan.
 constexpr int kScanShift = 11, kScanBlock = 1 << kScanShift;
 
@@ -150,12 +157,14 @@ struct DevCounters {
     unsigned long long pairs;
     unsigned long long overflow;
     unsigned long long bad_indices;
+    unsigned long long item_len;     // items of the large triangles (LargeLists)
     unsigned int overflow_list_len;
-    unsigned int large_len, item_len; // listed large triangles and their items (LargeLists)
+    unsigned int large_len;          // listed large triangles
     unsigned int bin_cursor;         // running total of the tile scan
     unsigned int medium_len;         // listed triangles of kOwnRows + 1 .. kBigBin pairs
-    unsigned int pad[3];
+    unsigned int pad[2];
 };
+static_assert(sizeof(DevCounters) == 64, "DevCounters is a cache line");
 
 // Triangles of more than kBigBin tiles, and their pairs in items (triangle,
 // first pair within it) of kLargeChunk.  item_cap holds every item whose pairs
@@ -178,9 +187,10 @@ struct LargeLists {
 template <class Count, class F>
 __device__ __forceinline__ void for_large_items(const LargeLists &l, const DevCounters *counters, int b, int nb,
                                                 Count count, F f) {
-    const unsigned nitems = counters->item_len, nlist = counters->large_len;
+    const unsigned long long nitems = counters->item_len;
+    const unsigned nlist = counters->large_len;
     if (nitems <= l.item_cap) {
-        for (unsigned o = (unsigned)b; o < nitems; o += (unsigned)nb) f(l.items[o].x, l.items[o].y, count(l.items[o].x));
+        for (unsigned o = (unsigned)b; o < (unsigned)nitems; o += (unsigned)nb) f(l.items[o].x, l.items[o].y, count(l.items[o].x));
         return;
     }
     for (unsigned o = 0; o < nlist; ++o) {
@@ -358,24 +368,27 @@ struct CamStatic;
 // Jacobian of a light frame (M[16], pos[3], dir[3]) w.r.t. its three parameter components, [22][3].
 constexpr int kJac = 66;
 // Also clears bytes1 at z1 and bytes2 at z2 (multiples of 4) and, with rows, the
-// 96-byte rows of the listed triangles, in the same launch.
+// 96-byte rows of the listed triangles, in the same launch; with *pairs at
+// kPairEnd, where a triangle's pair numbers do not say whether it has any, the
+// rows of all ntri triangles.
 struct ClearRows {
     float *rows;                    // nullptr: none
     const unsigned *list_a, *list_b;
     const unsigned *len_a, *len_b;
+    const unsigned *pairs;
+    unsigned ntri;
 };
 hipError_t launch_light_frames(ViewConst *views, const CamStatic *cams, const float *params, int L, float *jac,
                                float *zc_out, void *z1, size_t bytes1, void *z2, size_t bytes2, const ClearRows &rows,
                                hipStream_t s);
 hipError_t launch_setup(const ViewConst *views, const TriBlock *blocks, int nblocks, const int *faces,
                         const float *verts, const float *albedo, int C, TriVerts *tv, TriSetup *setup,
-                        signed char *facing8, unsigned *pair_local, unsigned *block_total, unsigned *group_total,
-                        const LargeLists &large,
-                        int tile, DevCounters *counters, hipStream_t s);
+                        signed char *facing8, unsigned *pair_local, unsigned *block_total,
+                        unsigned long long *group_total, const LargeLists &large, int tile, DevCounters *counters, hipStream_t s);
 hipError_t launch_binning(const ViewConst *views, const TriBlock *blocks, int nblocks, const TriSetup *setup,
                           const int *adj, const signed char *facing8, unsigned char *silm, const unsigned *pair_local,
-                          unsigned *block_total, const unsigned *group_total, unsigned *pair_off, int ntri,
-                          unsigned capacity, int tile,
+                          unsigned *block_total, const unsigned long long *group_total, unsigned *pair_off,
+                          int ntri, unsigned capacity, int tile,
                           unsigned *tile_count, unsigned *tile_start, unsigned *pair_slot, int ntiles, unsigned *bins,
                           unsigned *bin_pair, unsigned *overflow_list, const LargeLists &large,
                           DevCounters *counters, unsigned long long *keys, long long nkeys,

@@ -530,7 +530,7 @@ __device__ __forceinline__ void wave_pair_sums(const ViewConst &v, int tx, int t
     if (act && some && key >= 0) {
         const int si = v.setup_off + key;
         const unsigned a = pair_off[si], b = pair_off[si + 1];
-        if (!(b > capacity && b > a)) {                  // else: the overflow path
+        if (b <= capacity) {                             // else: the overflow path
             const TriSetup &st = setup[si];
             const int tx0 = st.bx0 / T, ty0 = st.by0 / T, ntx = st.bx1 / T - tx0 + 1;
             slot = a + (unsigned)((ty - ty0) * ntx + (tx - tx0));
@@ -1213,7 +1213,8 @@ __device__ __forceinline__ TriRows tri_rows(unsigned t, unsigned a, unsigned b, 
                                             const float *__restrict__ pair_sums, const float *__restrict__ gtri) {
     static_assert(kOwnRows == 4, "one word of flags");
     const unsigned n = b - a;
-    if (n > kOwnRows || b > capacity) return TriRows{gtri + (size_t)t * kRow, n ? 1u : 0u};
+    // with both ends at kPairEnd it may have pairs or none, and its row is cleared in any case
+    if (n > kOwnRows || b > capacity) return TriRows{gtri + (size_t)t * kRow, n || a == kPairEnd ? 1u : 0u};
     const unsigned m = (w & 1u) | (w >> 7 & 2u) | (w >> 14 & 4u) | (w >> 21 & 8u);
     return TriRows{pair_sums + (size_t)a * kRow, m & ((1u << n) - 1u)};
 }
@@ -1393,7 +1394,7 @@ __device__ __forceinline__ void gather_corners(const int (&e)[N], int soff, unsi
     }
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-        if (e[k] < 0) p1[k] = p0[k];
+        if (e[k] < 0) p0[k] = p1[k] = 0u;
         w[k] = flag_word(pair_flag + (p1[k] <= capacity ? p0[k] : 0u));
     }
     TriRows r[N];

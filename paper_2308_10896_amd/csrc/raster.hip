@@ -63,6 +63,10 @@ __global__ void light_frames_kernel(ViewConst *views, const CamStatic *cams, con
             else z2[i - n1] = 0u;
         }
         if (rows.rows) {
+            if (rows.pairs && *rows.pairs == kPairEnd) {
+                for (size_t i = first; i < 24 * (size_t)rows.ntri; i += stride) rows.rows[i] = 0.f;
+                return;
+            }
             const size_t la = *rows.len_a, lb = *rows.len_b;
             for (size_t i = first; i < 24 * (la + lb); i += stride) {
                 const size_t o = i / 24;
@@ -97,8 +101,9 @@ __device__ __forceinline__ int floor_div256(int a) { return a >= 0 ? (a >> 8) : 
 constexpr int kTriThreads = kTriRun;
 
 // Exclusive scan over the workgroup's PPT * 256 values, value k of thread tid
-// at position k * 256 + tid; *total: their sum.  Uniform call.
-template <int PPT>
+// at position k * 256 + tid; *total: their sum.  SAT: every sum stays at the
+// largest value once it passes it.  Uniform call.
+template <int PPT, bool SAT = false>
 __device__ __forceinline__ void tri_block_scan(const unsigned (&v)[PPT], unsigned (&out)[PPT], unsigned *total) {
     constexpr int NW = kTriThreads / 64;
     __shared__ unsigned sum[PPT][NW];
@@ -109,10 +114,15 @@ __device__ __forceinline__ void tri_block_scan(const unsigned (&v)[PPT], unsigne
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
             const unsigned y = __shfl_up(x, o, 64);
-            if (lane >= o) x += y;
+            if (lane >= o) x = SAT ? add_sat(x, y) : x + y;
         }
         if (lane == 63) sum[k][wid] = x;
-        out[k] = x - v[k];
+        if (SAT) {
+            const unsigned before = __shfl_up(x, 1, 64);
+            out[k] = lane > 0 ? before : 0u;
+        } else {
+            out[k] = x - v[k];
+        }
     }
     __syncthreads();
     unsigned all = 0;
@@ -120,8 +130,8 @@ __device__ __forceinline__ void tri_block_scan(const unsigned (&v)[PPT], unsigne
     for (int k = 0; k < PPT; ++k)
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            if (w == wid) out[k] += all;
-            all += sum[k][w];
+            if (w == wid) out[k] = SAT ? add_sat(out[k], all) : out[k] + all;
+            all = SAT ? add_sat(all, sum[k][w]) : all + sum[k][w];
         }
     *total = all;
 }
@@ -151,7 +161,7 @@ __device__ __forceinline__ TileBox tile_box(const TriSetup &s, int shift) {
 __device__ __forceinline__ void list_large(unsigned t, unsigned n, const LargeLists &l, DevCounters *counters) {
     l.list[atomicAdd(&counters->large_len, 1u)] = t;
     const unsigned k = (n + kLargeChunk - 1) / kLargeChunk;
-    const unsigned at = atomicAdd(&counters->item_len, k);
+    const unsigned long long at = atomicAdd(&counters->item_len, (unsigned long long)k);
     for (unsigned q = 0; q < k && at + q < l.item_cap; ++q) l.items[at + q] = make_uint2(t, q * kLargeChunk);
 }
 
@@ -165,7 +175,7 @@ __global__ __launch_bounds__(kTriThreads) void setup_kernel(
     const ViewConst *__restrict__ views, const TriBlock *__restrict__ blocks, const int *__restrict__ faces,
     const float *__restrict__ verts, const float *__restrict__ albedo, int C, TriVerts *__restrict__ tv,
     TriSetup *__restrict__ setup, signed char *__restrict__ facing8, unsigned *__restrict__ pair_local,
-    unsigned *__restrict__ block_total, unsigned *__restrict__ group_total, LargeLists large, int shift,
+    unsigned *__restrict__ block_total, unsigned long long *__restrict__ group_total, LargeLists large, int shift,
     DevCounters *counters) {
     const TriBlock blk = blocks[blockIdx.x];
     const ViewConst &v = views[blk.view];
@@ -253,7 +263,7 @@ __global__ __launch_bounds__(kTriThreads) void setup_kernel(
     if (t < v.nfaces) pair_local[v.setup_off + t] = off[0];
     if (threadIdx.x == 0) {
         block_total[blockIdx.x] = total;
-        if (total) atomicAdd(&group_total[blockIdx.x / kTriGroup * kGroupStride], total);
+        if (total) atomicAdd(&group_total[blockIdx.x / kTriGroup * kGroupStride], (unsigned long long)total);
     }
     if (__ballot(nculled + nbad != 0)) {
         if (nculled) atomicAdd(&counters->culled, (unsigned long long)nculled);
@@ -416,7 +426,7 @@ __device__ __forceinline__ void bin_large(const ViewConst *__restrict__ views, c
     for_large_items(large, counters, b, kLargeBlocks, [&](unsigned t) { return tile_box(setup[t], shift).n; },
                     [&](unsigned t, unsigned q0, unsigned n) {
                         const unsigned a = off(t);
-                        if (a + n > capacity || a + n < a) return;          // overflow path
+                        if (a + n > capacity) return;                       // overflow path
                         const TriSetup &s = setup[t];
                         bin_range<FILL>(views[s.pad2[0]], s, t, a, q0, min(q0 + kLargeChunk, n), shift, tile_count,
                                         pair_slot, tile_start, bins, bin_pair);
@@ -454,15 +464,15 @@ __global__ __launch_bounds__(kTriThreads) void block_prefix_kernel(unsigned *__r
         unsigned v[16], o[16], sum;
 #pragma unroll
         for (int k = 0; k < 16; ++k) v[k] = c + k * kTriThreads + tid < n ? total[c + k * kTriThreads + tid] : 0u;
-        tri_block_scan(v, o, &sum);
+        tri_block_scan<16, true>(v, o, &sum);
         const unsigned base = carry;
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 16; ++k)
-            if (c + k * kTriThreads + tid < n) total[c + k * kTriThreads + tid] = base + o[k];
+            if (c + k * kTriThreads + tid < n) total[c + k * kTriThreads + tid] = add_sat(base, o[k]);
         if (tid == 0) {
-            carry = base + sum;
-            if (c + 16 * kTriThreads >= n) total[n] = base + sum;
+            carry = add_sat(base, sum);
+            if (c + 16 * kTriThreads >= n) total[n] = add_sat(base, sum);
         }
         __syncthreads();
     }
@@ -493,7 +503,7 @@ __global__ __launch_bounds__(kTriThreads) void bin_count_kernel(
     const ViewConst *__restrict__ views, const TriBlock *__restrict__ blocks, int nblocks,
     const TriSetup *__restrict__ setup, const int *__restrict__ adj, const signed char *__restrict__ facing8,
     unsigned char *__restrict__ silm, const unsigned *__restrict__ pair_local,
-    const unsigned *__restrict__ block_total, const unsigned *__restrict__ group_total, bool scanned,
+    const unsigned *__restrict__ block_total, const unsigned long long *__restrict__ group_total, bool scanned,
     unsigned *__restrict__ pair_off, unsigned capacity, int shift,
     int ntri,
     unsigned *__restrict__ tile_count, unsigned *__restrict__ pair_slot, LargeLists large,
@@ -513,26 +523,26 @@ __global__ __launch_bounds__(kTriThreads) void bin_count_kernel(
         if (tid == 0) carry = 0;
         const int ngroups = (nblocks + kTriGroup - 1) / kTriGroup;
         for (int c = 0; c < ngroups && !scanned; c += kTriThreads) {
-            const unsigned v[1] = {c + tid < ngroups ? group_total[(c + tid) * kGroupStride] : 0u};
+            const unsigned v[1] = {c + tid < ngroups ? word_sat(group_total[(c + tid) * kGroupStride]) : 0u};
             unsigned o[1], total;
-            tri_block_scan(v, o, &total);
+            tri_block_scan<1, true>(v, o, &total);
             const unsigned base = carry;
             __syncthreads();
-            if (c + tid < ngroups) prefix[c + tid] = base + o[0];
-            if (tid == 0) carry = base + total;
+            if (c + tid < ngroups) prefix[c + tid] = add_sat(base, o[0]);
+            if (tid == 0) carry = add_sat(base, total);
             __syncthreads();
         }
         bin_large<false>(views, setup, capacity, shift, (int)blockIdx.x - nblocks, tile_count, pair_slot, nullptr,
                          nullptr, nullptr, large, counters, [&](unsigned t) {
                              const ViewConst &v = views[setup[t].pad2[0]];
                              const int k = v.tri_block + (int)(t - v.setup_off) / kTriRun;
-                             if (scanned) return pair_local[t] + block_total[k];
+                             if (scanned) return min(add_sat(pair_local[t], block_total[k]), kPairEnd);
                              // in its group by each wave alone
                              unsigned before = 0;
-                             for (int q = (k & ~(kTriGroup - 1)) + (tid & 63); q < k; q += 64) before += block_total[q];
+                             for (int q = (k & ~(kTriGroup - 1)) + (tid & 63); q < k; q += 64) before = add_sat(before, block_total[q]);
 #pragma unroll
-                             for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
-                             return pair_local[t] + prefix[k / kTriGroup] + before;
+                             for (int o = 32; o > 0; o >>= 1) before = add_sat(before, __shfl_xor(before, o, 64));
+                             return min(add_sat(pair_local[t], add_sat(prefix[k / kTriGroup], before)), kPairEnd);
                          });
         return;
     }
@@ -553,15 +563,15 @@ __global__ __launch_bounds__(kTriThreads) void bin_count_kernel(
     if (!scanned) {
         static_assert(kTriGroup <= kTriThreads, "a lane each");
         const int g = (int)blockIdx.x / kTriGroup;
-        for (int k = tid; k < g; k += kTriThreads) sum += group_total[k * kGroupStride];
-        if (g * kTriGroup + tid < (int)blockIdx.x) sum += block_total[g * kTriGroup + tid];
+        for (int k = tid; k < g; k += kTriThreads) sum = add_sat(sum, word_sat(group_total[k * kGroupStride]));
+        if (g * kTriGroup + tid < (int)blockIdx.x) sum = add_sat(sum, block_total[g * kTriGroup + tid]);
     }
     const bool small = b.n > 0 && b.n <= kBigBin;
     int lo_x = small ? b.tx0 : 65536, lo_y = small ? b.ty0 : 65536;
     int hi_x = small ? b.tx0 + b.ntx - 1 : -1, hi_y = small ? b.ty0 + nty - 1 : -1;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
-        sum += __shfl_xor(sum, o, 64);
+        sum = add_sat(sum, __shfl_xor(sum, o, 64));
         lo_x = min(lo_x, __shfl_xor(lo_x, o, 64));
         lo_y = min(lo_y, __shfl_xor(lo_y, o, 64));
         hi_x = max(hi_x, __shfl_xor(hi_x, o, 64));
@@ -576,7 +586,8 @@ __global__ __launch_bounds__(kTriThreads) void bin_count_kernel(
         q[3] = hi_y;
     }
     __syncthreads();
-    const unsigned base = scanned ? block_total[blockIdx.x] : (part[0] + part[1]) + (part[2] + part[3]);
+    const unsigned base =
+        scanned ? block_total[blockIdx.x] : add_sat(add_sat(part[0], part[1]), add_sat(part[2], part[3]));
 #pragma unroll
     for (int k = 0; k < kTriThreads / 64; ++k) {
         lo_x = min(lo_x, boxes[k][0]);
@@ -589,19 +600,24 @@ __global__ __launch_bounds__(kTriThreads) void bin_count_kernel(
     if (table)
         for (int k = tid; k < nbox; k += kTriThreads) sh.table[k] = 0u;
     if ((int)blockIdx.x == nblocks - 1 && tid == 0) {
-        const unsigned total = scanned ? block_total[nblocks] : base + block_total[blockIdx.x];
+        const unsigned total = min(scanned ? block_total[nblocks] : add_sat(base, block_total[blockIdx.x]), kPairEnd);
         pair_off[ntri] = total;
-        counters->pairs = total;       // for the plan's statistics
+        unsigned long long all = total;                      // for the plan's statistics
+        if (total == kPairEnd) {
+            all = 0;
+            for (int g = 0; g < nblocks; g += kTriGroup) all += group_total[g / kTriGroup * kGroupStride];
+        }
+        counters->pairs = all;
     }
     unsigned cnt = 0;
     BinItem it{};
-    it.a = local + base;
+    it.a = min(add_sat(local, base), kPairEnd);
     it.ntx = b.ntx;
     it.tile0 = v.tile_off + b.ty0 * v.tiles_x + b.tx0;
     if (mine) {
         const int si = v.setup_off + t;
         pair_off[si] = it.a;
-        const unsigned end = it.a + b.n;
+        const unsigned end = it.a + b.n;                     // at most kPairEnd and a view's tiles: no wrap
         if (end > capacity) {                                // overflow path
             if (b.n) overflow_list[atomicAdd(&counters->overflow_list_len, 1u)] = (unsigned)si;
         } else if (small) {
@@ -963,8 +979,9 @@ hipError_t launch_light_frames(ViewConst *views, const CamStatic *cams, const fl
 
 hipError_t launch_setup(const ViewConst *views, const TriBlock *blocks, int nblocks, const int *faces,
                         const float *verts, const float *albedo, int C, TriVerts *tv, TriSetup *setup,
-                        signed char *facing8, unsigned *pair_local, unsigned *block_total, unsigned *group_total,
-                        const LargeLists &large, int tile, DevCounters *counters, hipStream_t s) {
+                        signed char *facing8, unsigned *pair_local, unsigned *block_total,
+                        unsigned long long *group_total, const LargeLists &large, int tile, DevCounters *counters,
+                        hipStream_t s) {
     if (nblocks == 0) return hipSuccess;
     hipLaunchKernelGGL(setup_kernel, dim3(nblocks), dim3(kTriThreads), 0, s, views, blocks, faces, verts, albedo, C, tv,
                        setup, facing8, pair_local, block_total, group_total, large, __builtin_ctz(tile), counters);
@@ -973,8 +990,8 @@ hipError_t launch_setup(const ViewConst *views, const TriBlock *blocks, int nblo
 
 hipError_t launch_binning(const ViewConst *views, const TriBlock *blocks, int nblocks, const TriSetup *setup,
                           const int *adj, const signed char *facing8, unsigned char *silm, const unsigned *pair_local,
-                          unsigned *block_total, const unsigned *group_total, unsigned *pair_off, int ntri,
-                          unsigned capacity, int tile,
+                          unsigned *block_total, const unsigned long long *group_total, unsigned *pair_off,
+                          int ntri, unsigned capacity, int tile,
                           unsigned *tile_count, unsigned *tile_start, unsigned *pair_slot, int ntiles, unsigned *bins,
                           unsigned *bin_pair, unsigned *overflow_list, const LargeLists &large,
                           DevCounters *counters, unsigned long long *keys, long long nkeys,
