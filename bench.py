@@ -50,10 +50,10 @@ HBM_PEAK_GBS = 8000.0
 # had when the counters were taken (and at tile side 8, where they were).
 PMC_COPY = dict(fetch_kib=65547.6, write_kib=131072.0, moved_kib=131072.0)
 PMC = {
-    'filter': dict(kernel='blur_kernel<false, 2, true, 32>', fetch_kib=65702.5, write_kib=131072.0, rd_bytes=134524492, wr_bytes=134217728, waves=32768, valu_per_wave=716.2, valu_busy=0.557, occupancy=18.0, sources=('blur.h', 'blur.hip', 'dsm_internal.h'), sha1='1ac4978480ccb948'),
-    'filter_adj': dict(kernel='blur_kernel<true, 2, true, 32>', fetch_kib=65615.9, write_kib=131072.0, rd_bytes=134303257, wr_bytes=134217728, waves=32768, valu_per_wave=641.1, valu_busy=0.553, occupancy=20.2, sources=('blur.h', 'blur_transpose.hip', 'dsm_internal.h'), sha1='158042a326373fe5'),
-    'lookup': dict(kernel='lookup_kernel<2>', fetch_kib=200697.9, write_kib=65536.0, rd_bytes=410712435, wr_bytes=67108864, waves=131072, valu_per_wave=468.0, valu_busy=0.919, occupancy=26.5, sources=('shade.hip', 'dsm_internal.h'), sha1='6f917b872bf2569b'),
-    'lookup_adj': dict(kernel='lookup_backward_kernel<8, 1>', fetch_kib=126895.5, write_kib=122201.4, rd_bytes=259537382, wr_bytes=125111417, waves=262144, valu_per_wave=729.2, valu_busy=0.837, occupancy=18.4, sources=('grad.hip', 'dsm_internal.h'), sha1='ab3329d092a1bf46'),
+    'filter': dict(kernel='blur_kernel<false, 2, true, 32>', fetch_kib=65701.6, write_kib=131072.0, rd_bytes=134494988, wr_bytes=134217728, waves=32768, valu_per_wave=716.2, valu_busy=0.557, occupancy=18.0, sources=('blur.h', 'blur.hip', 'dsm_internal.h', 'raster_tri.h', 'xcd_order.h'), sha1='90442fca3f717cf6'),
+    'filter_adj': dict(kernel='blur_kernel<true, 2, true, 32>', fetch_kib=65616.1, write_kib=131072.0, rd_bytes=134304243, wr_bytes=134217728, waves=32768, valu_per_wave=641.1, valu_busy=0.554, occupancy=20.1, sources=('blur.h', 'blur_transpose.hip', 'dsm_internal.h', 'raster_tri.h', 'xcd_order.h'), sha1='4d3485d087985988'),
+    'lookup': dict(kernel='lookup_kernel<2>', fetch_kib=200697.8, write_kib=65536.0, rd_bytes=410712204, wr_bytes=67108864, waves=131072, valu_per_wave=468.0, valu_busy=0.921, occupancy=26.4, sources=('shade.hip', 'dsm_internal.h', 'raster_tri.h', 'xcd_order.h'), sha1='78e92aee087aa01a'),
+    'lookup_adj': dict(kernel='lookup_backward_kernel<8, 1>', fetch_kib=126895.1, write_kib=122253.7, rd_bytes=259539916, wr_bytes=125172531, waves=262144, valu_per_wave=728.6, valu_busy=0.840, occupancy=18.4, sources=('grad.hip', 'dsm_internal.h', 'raster_tri.h', 'xcd_order.h'), sha1='f20603ad7609ebb6'),
 }
 
 # Issue peak of the vector ALUs: 256 CUs x 4 SIMDs x 2.4 GHz / 4 cycles per

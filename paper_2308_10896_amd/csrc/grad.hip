@@ -281,8 +281,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(C == 1 ? 6 :
 // tile) pair a unique index).  Later gathers sum those slots per triangle,
 // then per vertex (through the vertex -> triangle-corner lists), with plain
 // stores.  Per-light terms are written per tile and summed per light the
-// same way.  Only triangles that overflowed the bins, the sparse silhouette
-// terms and the bilinear moment-map scatter use atomics.
+// same way.  Only triangles that overflowed the bins, the 512-pair items of
+// larger triangles, the sparse silhouette terms and the bilinear moment-map
+// scatter use atomics, so their sums have no fixed order.
 constexpr int kNV = 21;   // per pair: 9 world-position terms, 9 clip (x, y, w) terms, 3 albedo terms
 
 // The rows of pairs (and those of gtri, of triangles that overflowed the bins
@@ -1251,7 +1252,8 @@ __device__ __forceinline__ void light_partials(int l, int blk, const ViewConst *
 
 // Rows of the listed triangles.  Large ones: a workgroup per item sums its
 // pairs' rows; a triangle of one item gets its row stored, the items of a
-// larger one are added to its row, which the backward's setup cleared.  Those
+// larger one are added to its row, which the backward's setup cleared, as they
+// finish (a workgroup per triangle, in order, took 126 us at 1080p).  Those
 // of kOwnRows + 1 to kBigBin pairs: half a wave each, a value of the row a
 // lane, the flagged rows added in order (as single lanes of the gather read
 // them, 32 rows were 32 dependent rounds: tiny cube 17 -> 5 us).
